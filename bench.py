@@ -231,7 +231,7 @@ def run_resident(workload, steps, warmup, fp16=False, grad_sets=3, layout="dense
     adamw_bytes = adamw_per_elem * N_pad
     achieved = adamw_bytes / (mean(adamw_ms) * 1e-3) / 1e9
     value = step_bytes / (ms_step * 1e-3) / 1e9
-    kname = "k_adamw<%s, unroll 4, non-temporal%s%s%s>" % ("fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "",
+    kname = "k_adamw<%s, one wave per workgroup, non-temporal%s%s%s>" % ("fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "",
                                                           ", fp32 gradients" if A else "", ", zeroing gradients" if zero_grads else "")
     out = {
         "workload": f"{workload}: {N} elements in {C} chunks of {S}, {layout_note}; arenas spread over physical memory, all "

@@ -138,8 +138,9 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
 
 /* Options (host state only, take effect at the next call).  Launch shape - none of these
  * changes a result bit:
- *   "adamw_grid"    workgroups of the update kernel; 0 = the library's default
- *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 = the library chooses by launch size (default)
+ *   "adamw_grid"    workgroups of the update kernel; 0 = one per tile (default)
+ *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 (default).  With neither this nor adamw_unroll
+ *                   set the library takes its own shape: workgroups of one wave, few of them per compute unit
  *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4 or 8
  *   "adamw_nt"      non-temporal hints on the update's loads and stores: 1 = always, 0 = never, 2 = the library
  *                   chooses by launch size (default): none while the launch's state fits the 256 MB Infinity Cache

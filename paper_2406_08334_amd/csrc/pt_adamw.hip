@@ -5,19 +5,19 @@
 // p16); 16 read with fp32 gradient chunks, and 2 or 4 more written when the gradients are
 // zeroed on the way out.  Work unit = 4 consecutive elements per lane: one 16-byte access per fp32
 // array and one 8-byte access per 16-bit array, so that every wave instruction
-// touches one contiguous 1 KiB (fp32) or 512 B (16-bit) span.  UNROLL units per
-// lane are loaded before the first is used, to keep enough bytes in flight.
+// touches one contiguous 1 KiB (fp32) or 512 B (16-bit) span.  The launch shape keeps the set of
+// DRAM rows in use small (see k_adamw).
 // Arithmetic: the fp32 operation sequence below with correctly rounded *, fma,
 // sqrt and / (this file is compiled with contraction off and without fast-math).
 #include "pt_common.h"
 
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 namespace {
-
-// workgroup size of the update kernel: 512 (default; measured 0.6-1.4 % faster than 256 on MI355X) or 256
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -53,9 +53,10 @@ __device__ __forceinline__ float decode16(uint32_t w16) {
 template <int DT>
 __device__ __forceinline__ uint32_t encode16(float x) {
   if (DT == PT_BF16) {
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x0040u;  // NaN stays NaN
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;                    // round to nearest, ties to even
+    const uint32_t u = __float_as_uint(x);
+    const uint32_t nan = (u >> 16) | 0x0040u;                          // NaN stays NaN
+    const uint32_t rne = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;       // round to nearest, ties to even
+    return (u & 0x7fffffffu) > 0x7f800000u ? nan : rne;                // a select: a branch per element was compiled before
   } else {
     // The recast rounds the STORED fp32 master weight.  Without this barrier the compiler
     // folds the producing fma and the conversion into one mixed-precision fma that rounds
@@ -111,12 +112,25 @@ __device__ __forceinline__ void update_unit(const Consts& k, const float (&dk)[4
   p2.y = pw[2] | (pw[3] << 16);
 }
 
-// One flat index space of tiles (256 x UNROLL units of 4 elements) over all chunks of
-// the launch: tile T belongs to chunk T / tiles_per_chunk.  Block b takes tiles
-// b, b + gridDim.x, ...  With the default grid (a third of the tiles) a block's two or three
-// tiles lie a third of the launch apart, in different chunks, so the five base pointers are
-// re-read from the table for nearly every tile (five uniform loads against 28 KiB or more of
-// traffic per tile); a small grid keeps consecutive tiles in one chunk and skips the re-read.
+// blockIdx.y is the chunk (table column first_col + blockIdx.y), blockIdx.x the tile of TH x UNROLL units inside
+// it; workgroups are dispatched in this order, so the traffic of a moment is one narrow window that slides over each
+// array.  A grid smaller than the tiles (option adamw_grid, or a dimension beyond its limit) walks on from there.
+//
+// What bounds the launch is DRAM row locality.  HBM is three regions of 96 GiB; four read and four write streams that
+// all fall into one of them - what plain allocation gives a state of up to about 100 GB - run out of open rows long
+// before they run out of bandwidth.  What helps is few bytes in flight, in address order: workgroups of ONE wave, one
+// unit per lane, and only 11 of them per compute unit (PT_ADAMW_LDS of unused LDS each; about 7 MB in flight chip-wide)
+// instead of 24 waves with four units each.  Moving the same bytes without the arithmetic over 2^28 elements: all
+// arrays in one region 5.4 -> 6.5 TB/s, spread over the regions 6.39 -> 6.55 TB/s.  The whole step of the GPT-2-XL
+// shape (plain allocations): 9.35 -> 7.8 ms; 9 or 13 waves per unit 8.1 and 8.0 ms, 128 lanes 8.1, two units per lane
+// 8.2, no limit on the waves 8.6 ms.
+//
+// Tiles start on a 128-byte line of the master array (the first one up to 7 units early, with those lanes idle), so
+// that chunks whose size is no multiple of a line do not split every wave's lines between two workgroups
+// (14 chunks of 5 000 200 elements: 428 -> 362 us a step).
+//
+// The loads are issued before the step's scalars are looked at: a skipped step reads in vain, every other one has its
+// traffic under way while the scalars arrive.
 //
 // MASKED: some element ranges of some chunks are kept out of the weight decay (sorted,
 // disjoint ranges per chunk: nd_begin[c] .. nd_begin[c+1] index pairs (lo, hi) in nd_ranges).
@@ -125,138 +139,115 @@ __device__ __forceinline__ void update_unit(const Consts& k, const float (&dk)[4
 //
 // GF32: the gradient chunks hold fp32 (accumulated micro-batches) instead of 16-bit words.
 // zero_grads: every gradient element is overwritten with zero once it has been read (for
-// callers whose backward pass adds into the chunk); a skipped step zeroes them as well (store-only
-// pass), so that the non-finite value that caused the skip does not stay in the sums.
-template <int AW_THREADS, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
-__global__ void __launch_bounds__(AW_THREADS)
-k_adamw(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_col, uint32_t n_cols,
-        uint64_t S, uint32_t tiles_per_chunk, const PtDevState* __restrict__ st, int recast_on_skip,
-        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges, uint32_t mask_chunk0,
-        int zero_grads) {
+// callers whose backward pass adds into the chunk); a skipped step zeroes them as well, so that the non-finite
+// value that caused the skip does not stay in the sums.
+// recast_on_skip: a chunk buffer of the streamed path is offloaded in full after a skipped step and its param16
+// array was never uploaded, so it is refilled from the untouched master weights (param16 == RNE(master) is the
+// invariant of every update).
+constexpr uint32_t LINE_UNITS = 8;     // units of a 128-byte line of an fp32 array
+
+template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
+__global__ void __launch_bounds__(TH)
+k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, uint32_t table_cols, uint32_t first_col,
+        uint32_t n_cols, uint32_t mask_chunk0, uint64_t units, uint64_t tiles, int recast_on_skip, int zero_grads,
+        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges) {
   typedef typename GradUnit<GF32>::vec gvec;
   typedef PT_GLOBAL gvec* g_ptr;
-  constexpr uint32_t TILE_UNITS = AW_THREADS * UNROLL;
+  constexpr uint32_t TILE_UNITS = TH * UNROLL;
   const gvec gzero = {};
-  const uint64_t units = S / 4;
-  const uint32_t total_tiles = tiles_per_chunk * n_cols;
-  if (st->skip) {
-    // Skipped step: nothing changes.  A chunk buffer of the streamed path is offloaded in
-    // full afterwards and its param16 array was never uploaded, so it is refilled from the
-    // untouched master weights (param16 == RNE(master) is the invariant of every update).
-    if (recast_on_skip) {
-      for (uint32_t T = blockIdx.x; T < total_tiles; T += gridDim.x) {
-        const uint32_t ci = T / tiles_per_chunk, tile = T - ci * tiles_per_chunk;
-        cgf32x4_ptr wq = (cgf32x4_ptr)(table[size_t(ROW_MASTER) * table_cols + first_col + ci]);
-        gu32x2_ptr pq = (gu32x2_ptr)(table[size_t(ROW_P16) * table_cols + first_col + ci]);
-        const uint64_t u_end = min(units, (uint64_t(tile) + 1) * TILE_UNITS);
-        for (uint64_t u = uint64_t(tile) * TILE_UNITS + threadIdx.x; u < u_end; u += AW_THREADS) {
-          f32x4 w = wq[u];
-          u32x2 p;
-          p.x = encode16<DT>(w[0]) | (encode16<DT>(w[1]) << 16);
-          p.y = encode16<DT>(w[2]) | (encode16<DT>(w[3]) << 16);
-          pq[u] = p;
-        }
-      }
-    }
-    // The gradients are zeroed on a skipped step too: a caller whose backward pass ADDS into the
-    // chunks would otherwise carry the inf/NaN that caused the skip into every later sum.
-    if (zero_grads) {
-      for (uint32_t T = blockIdx.x; T < total_tiles; T += gridDim.x) {
-        const uint32_t ci = T / tiles_per_chunk, tile = T - ci * tiles_per_chunk;
-        g_ptr gq = (g_ptr)(table[size_t(ROW_GRAD) * table_cols + first_col + ci]);
-        const uint64_t u_end = min(units, (uint64_t(tile) + 1) * TILE_UNITS);
-        for (uint64_t u = uint64_t(tile) * TILE_UNITS + threadIdx.x; u < u_end; u += AW_THREADS)
-          st_stream<NT>(gzero, gq + u);
-      }
-    }
-    return;
-  }
+  const int32_t skip = st->skip;
   Consts k;
   k.b1 = st->c[0]; k.b2 = st->c[1]; k.omb1 = st->c[2]; k.omb2 = st->c[3]; k.decay = st->c[4];
   k.step_size = st->c[5]; k.rsb2 = st->c[6]; k.eps = st->c[7]; k.gm = st->c[8];
-
-  uint32_t cur = 0xffffffffu;
-  g_ptr gp = nullptr;
-  gf32x4_ptr wp = nullptr, mp = nullptr, vp = nullptr;
-  gu32x2_ptr pp = nullptr;
-  for (uint32_t T = blockIdx.x; T < total_tiles; T += gridDim.x) {
-    const uint32_t ci = T / tiles_per_chunk, tile = T - ci * tiles_per_chunk;
-    if (ci != cur) {
-      cur = ci;
-      const uint32_t col = first_col + ci;
-      gp = (g_ptr)(table[size_t(ROW_GRAD) * table_cols + col]);
-      wp = (gf32x4_ptr)(table[size_t(ROW_MASTER) * table_cols + col]);
-      mp = (gf32x4_ptr)(table[size_t(ROW_M) * table_cols + col]);
-      vp = (gf32x4_ptr)(table[size_t(ROW_V) * table_cols + col]);
-      pp = (gu32x2_ptr)(table[size_t(ROW_P16) * table_cols + col]);
-    }
-    const uint64_t u0 = uint64_t(tile) * TILE_UNITS + threadIdx.x;
-    float dtile = k.decay;            // decay factor of the whole tile, when it has one
-    bool cut = false;                 // a range edge falls inside this tile
-    uint32_t r0 = 0, r1 = 0;          // ranges of this chunk from the first one that ends after the tile start
-    if (MASKED) {
-      const uint32_t c = mask_chunk0 + ci;
-      r1 = nd_begin[c + 1];
-      uint32_t lo = nd_begin[c], hi = r1;
-      const uint64_t e0 = uint64_t(tile) * TILE_UNITS * 4, e1 = e0 + uint64_t(TILE_UNITS) * 4;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (nd_ranges[2 * size_t(mid) + 1] <= e0) lo = mid + 1; else hi = mid;
-      }
-      r0 = lo;
-      if (r0 < r1 && nd_ranges[2 * size_t(r0)] < e1) {
-        if (nd_ranges[2 * size_t(r0)] <= e0 && nd_ranges[2 * size_t(r0) + 1] >= e1) dtile = 1.0f;
-        else cut = true;
-      }
-    }
-    if (MASKED && cut) {
-      // element-wise decay factors; also covers a ragged last tile
-      const uint64_t u_end = min(units, (uint64_t(tile) + 1) * TILE_UNITS);
-      for (uint64_t u = u0; u < u_end; u += AW_THREADS) {
-        float dk[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint64_t e = 4 * u + j;
-          float d = k.decay;
-          for (uint32_t r = r0; r < r1 && nd_ranges[2 * size_t(r)] <= e; ++r)
-            if (e < nd_ranges[2 * size_t(r) + 1]) d = 1.0f;
-          dk[j] = d;
-        }
-        gvec g = gp[u]; f32x4 w = wp[u], m = mp[u], v = vp[u]; u32x2 p;
-        update_unit<DT, GF32>(k, dk, g, w, m, v, p);
-        wp[u] = w; mp[u] = m; vp[u] = v; pp[u] = p;
-        if (zero_grads) gp[u] = gzero;
-      }
-      continue;
-    }
-    const float dk[4] = {dtile, dtile, dtile, dtile};
-    if ((uint64_t(tile) + 1) * TILE_UNITS <= units) {
+  for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
+    const uint32_t col = first_col + ci;
+    const uint64_t wa = table[size_t(ROW_MASTER) * table_cols + col];
+    const g_ptr gp = (g_ptr)(table[size_t(ROW_GRAD) * table_cols + col]);
+    const gf32x4_ptr wp = (gf32x4_ptr)wa;
+    const gf32x4_ptr mp = (gf32x4_ptr)(table[size_t(ROW_M) * table_cols + col]);
+    const gf32x4_ptr vp = (gf32x4_ptr)(table[size_t(ROW_V) * table_cols + col]);
+    const gu32x2_ptr pp = (gu32x2_ptr)(table[size_t(ROW_P16) * table_cols + col]);
+    const uint32_t back = uint32_t(wa >> 4) & (LINE_UNITS - 1);   // units from the line's start to the chunk's
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+      // first unit of the tile; "negative" (wrapped around, above `units`) for the idle lanes of the first tile
+      const uint64_t ub = tile * TILE_UNITS - back;
+      const bool full = ub < units && units - ub >= TILE_UNITS;
       gvec g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
+      if (full) {
 #pragma unroll
-      for (int r = 0; r < UNROLL; ++r) {
-        const uint64_t u = u0 + uint64_t(r) * AW_THREADS;
-        g[r] = ld_stream<NT>(gp + u);
-        w[r] = ld_stream<NT>(wp + u);
-        m[r] = ld_stream<NT>(mp + u);
-        v[r] = ld_stream<NT>(vp + u);
+        for (int r = 0; r < UNROLL; ++r) {
+          const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+          g[r] = ld_stream<NT>(gp + ub + o);
+          w[r] = ld_stream<NT>(wp + ub + o);
+          m[r] = ld_stream<NT>(mp + ub + o);
+          v[r] = ld_stream<NT>(vp + ub + o);
+        }
       }
+      asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind the branch
+      if (skip) {
+        for (int r = 0; r < UNROLL; ++r) {
+          const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
+          if (u >= units) continue;
+          if (recast_on_skip) {
+            const f32x4 x = wp[u];
+            u32x2 p;
+            p.x = encode16<DT>(x[0]) | (encode16<DT>(x[1]) << 16);
+            p.y = encode16<DT>(x[2]) | (encode16<DT>(x[3]) << 16);
+            pp[u] = p;
+          }
+          if (zero_grads) st_stream<NT>(gzero, gp + u);
+        }
+        continue;
+      }
+      float dtile = k.decay;            // decay factor of the whole tile, when it has one
+      bool cut = false;                 // a range edge falls inside this tile
+      uint32_t r0 = 0, r1 = 0;          // ranges of this chunk from the first one that ends after the tile start
+      if (MASKED) {
+        const uint32_t c = mask_chunk0 + ci;
+        r1 = nd_begin[c + 1];
+        uint32_t lo = nd_begin[c], hi = r1;
+        const uint64_t e0 = ub < units ? ub * 4 : 0, e1 = (ub + TILE_UNITS) * 4;
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (nd_ranges[2 * size_t(mid) + 1] <= e0) lo = mid + 1; else hi = mid;
+        }
+        r0 = lo;
+        if (r0 < r1 && nd_ranges[2 * size_t(r0)] < e1) {
+          if (nd_ranges[2 * size_t(r0)] <= e0 && nd_ranges[2 * size_t(r0) + 1] >= e1) dtile = 1.0f;
+          else cut = true;
+        }
+      }
+      if (full && !(MASKED && cut)) {
+        const float dk[4] = {dtile, dtile, dtile, dtile};
 #pragma unroll
-      for (int r = 0; r < UNROLL; ++r) {
-        const uint64_t u = u0 + uint64_t(r) * AW_THREADS;
-        u32x2 p;
-        update_unit<DT, GF32>(k, dk, g[r], w[r], m[r], v[r], p);
-        st_stream<NT>(w[r], wp + u);
-        st_stream<NT>(m[r], mp + u);
-        st_stream<NT>(v[r], vp + u);
-        st_stream<NT>(p, pp + u);
-        if (zero_grads) st_stream<NT>(gzero, gp + u);
+        for (int r = 0; r < UNROLL; ++r) {
+          const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+          u32x2 p;
+          update_unit<DT, GF32>(k, dk, g[r], w[r], m[r], v[r], p);
+          st_stream<NT>(w[r], wp + ub + o);
+          st_stream<NT>(m[r], mp + ub + o);
+          st_stream<NT>(v[r], vp + ub + o);
+          st_stream<NT>(p, pp + ub + o);
+          if (zero_grads) st_stream<NT>(gzero, gp + ub + o);
+        }
+        continue;
       }
-    } else {
-      // ragged last tile of a chunk
-      for (uint64_t u = u0; u < units; u += AW_THREADS) {
-        gvec g = gp[u]; f32x4 w = wp[u], m = mp[u], v = vp[u]; u32x2 p;
-        update_unit<DT, GF32>(k, dk, g, w, m, v, p);
-        wp[u] = w; mp[u] = m; vp[u] = v; pp[u] = p;
+      // the first and the last tile of a chunk, and tiles with a range edge inside: unit by unit
+      for (int r = 0; r < UNROLL; ++r) {
+        const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
+        if (u >= units) continue;
+        float dk[4] = {dtile, dtile, dtile, dtile};
+        if (MASKED && cut) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint64_t e = 4 * u + j;
+            for (uint32_t q = r0; q < r1 && nd_ranges[2 * size_t(q)] <= e; ++q)
+              if (e < nd_ranges[2 * size_t(q) + 1]) dk[j] = 1.0f;
+          }
+        }
+        gvec g1 = gp[u]; f32x4 w1 = wp[u], m1 = mp[u], v1 = vp[u]; u32x2 p;
+        update_unit<DT, GF32>(k, dk, g1, w1, m1, v1, p);
+        wp[u] = w1; mp[u] = m1; vp[u] = v1; pp[u] = p;
         if (zero_grads) gp[u] = gzero;
       }
     }
@@ -268,116 +259,127 @@ k_adamw(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_
 // momentum and variance are stored back as loaded and param16 is re-derived from the master weight
 // (which is what it holds already), so the state does not change.  What this kernel attains is what the
 // memory system gives this mix of streams on this placement; the update itself cannot be faster.
-template <int AW_THREADS, int DT, int UNROLL, bool NT>
-__global__ void __launch_bounds__(AW_THREADS)
+template <int TH, int DT, int UNROLL, bool NT>
+__global__ void __launch_bounds__(TH)
 k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_col, uint32_t n_cols,
-                uint64_t S, uint32_t tiles_per_chunk, uint32_t* __restrict__ sink) {
-  constexpr uint32_t TILE_UNITS = AW_THREADS * UNROLL;
-  const uint64_t units = S / 4;
-  const uint32_t total_tiles = tiles_per_chunk * n_cols;
+                uint64_t units, uint64_t tiles, uint32_t* __restrict__ sink) {
+  constexpr uint32_t TILE_UNITS = TH * UNROLL;
   uint32_t keep = 0;
-  for (uint32_t T = blockIdx.x; T < total_tiles; T += gridDim.x) {
-    const uint32_t ci = T / tiles_per_chunk, tile = T - ci * tiles_per_chunk;
+  for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
     const uint32_t col = first_col + ci;
+    const uint64_t wa = table[size_t(ROW_MASTER) * table_cols + col];
     cgu32x2_ptr gp = (cgu32x2_ptr)(table[size_t(ROW_GRAD) * table_cols + col]);
-    gf32x4_ptr wp = (gf32x4_ptr)(table[size_t(ROW_MASTER) * table_cols + col]);
+    gf32x4_ptr wp = (gf32x4_ptr)wa;
     gf32x4_ptr mp = (gf32x4_ptr)(table[size_t(ROW_M) * table_cols + col]);
     gf32x4_ptr vp = (gf32x4_ptr)(table[size_t(ROW_V) * table_cols + col]);
     gu32x2_ptr pp = (gu32x2_ptr)(table[size_t(ROW_P16) * table_cols + col]);
-    const uint64_t u0 = uint64_t(tile) * TILE_UNITS + threadIdx.x;
-    if ((uint64_t(tile) + 1) * TILE_UNITS > units) continue;      // ragged last tiles are left out (a few KiB per chunk)
-    u32x2 g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
+    const uint32_t back = uint32_t(wa >> 4) & (LINE_UNITS - 1);
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+      const uint64_t ub = tile * TILE_UNITS - back;
+      if (!(ub < units && units - ub >= TILE_UNITS)) continue;      // first and last tiles are left out (a few KiB per chunk)
+      u32x2 g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
 #pragma unroll
-    for (int r = 0; r < UNROLL; ++r) {
-      const uint64_t u = u0 + uint64_t(r) * AW_THREADS;
-      g[r] = ld_stream<NT>(gp + u);
-      w[r] = ld_stream<NT>(wp + u);
-      m[r] = ld_stream<NT>(mp + u);
-      v[r] = ld_stream<NT>(vp + u);
-    }
+      for (int r = 0; r < UNROLL; ++r) {
+        const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+        g[r] = ld_stream<NT>(gp + ub + o);
+        w[r] = ld_stream<NT>(wp + ub + o);
+        m[r] = ld_stream<NT>(mp + ub + o);
+        v[r] = ld_stream<NT>(vp + ub + o);
+      }
 #pragma unroll
-    for (int r = 0; r < UNROLL; ++r) {
-      const uint64_t u = u0 + uint64_t(r) * AW_THREADS;
-      // opaque to the optimiser, so that the stores of unchanged values are not dropped
-      asm volatile("" : "+v"(w[r]), "+v"(m[r]), "+v"(v[r]));
-      u32x2 p;
-      p.x = encode16<DT>(w[r][0]) | (encode16<DT>(w[r][1]) << 16);
-      p.y = encode16<DT>(w[r][2]) | (encode16<DT>(w[r][3]) << 16);
-      keep ^= g[r].x ^ g[r].y;
-      st_stream<NT>(w[r], wp + u);
-      st_stream<NT>(m[r], mp + u);
-      st_stream<NT>(v[r], vp + u);
-      st_stream<NT>(p, pp + u);
+      for (int r = 0; r < UNROLL; ++r) {
+        const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+        // opaque to the optimiser, so that the stores of unchanged values are not dropped
+        asm volatile("" : "+v"(w[r]), "+v"(m[r]), "+v"(v[r]));
+        u32x2 p;
+        p.x = encode16<DT>(w[r][0]) | (encode16<DT>(w[r][1]) << 16);
+        p.y = encode16<DT>(w[r][2]) | (encode16<DT>(w[r][3]) << 16);
+        keep ^= g[r].x ^ g[r].y;
+        st_stream<NT>(w[r], wp + ub + o);
+        st_stream<NT>(m[r], mp + ub + o);
+        st_stream<NT>(v[r], vp + ub + o);
+        st_stream<NT>(p, pp + ub + o);
+      }
     }
   }
   if (keep == 0x9e3779b9u && sink) *sink = keep;      // keeps the gradient loads alive; practically never taken
 }
 
-typedef void (*adamw_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint32_t,
-                               const PtDevState*, int, const uint32_t*, const uint64_t*, uint32_t, int);
+typedef void (*adamw_kernel_t)(const uint64_t*, const PtDevState*, uint32_t, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t,
+                               int, int, const uint32_t*, const uint64_t*);
+typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*);
 
-template <int TH, int DT, bool MASKED, bool GF32>
-adamw_kernel_t pick_unroll(uint32_t unroll, bool nt) {
-  switch (unroll) {
-    case 1: return nt ? k_adamw<TH, DT, 1, true, MASKED, GF32> : k_adamw<TH, DT, 1, false, MASKED, GF32>;
-    case 2: return nt ? k_adamw<TH, DT, 2, true, MASKED, GF32> : k_adamw<TH, DT, 2, false, MASKED, GF32>;
-    case 8: return nt ? k_adamw<TH, DT, 8, true, MASKED, GF32> : k_adamw<TH, DT, 8, false, MASKED, GF32>;
-    default: return nt ? k_adamw<TH, DT, 4, true, MASKED, GF32> : k_adamw<TH, DT, 4, false, MASKED, GF32>;
+// The instantiation for a launch shape: `K<threads, unroll>::adamw / ::pattern` for the shapes there are (the default
+// one, and what the options adamw_threads and adamw_unroll ask for).
+template <int DT, bool NT, bool MASKED, bool GF32>
+struct Kernels {
+  template <int TH, int U> static adamw_kernel_t adamw() { return k_adamw<TH, DT, U, NT, MASKED, GF32>; }
+  template <int TH> static adamw_kernel_t by_unroll(uint32_t u) {
+    return u == 1 ? adamw<TH, 1>() : u == 2 ? adamw<TH, 2>() : u == 8 ? adamw<TH, 8>() : adamw<TH, 4>();
   }
-}
+  static adamw_kernel_t pick(const PtAdamwShape& s) {
+    return s.threads == 64 ? adamw<64, 1>() : s.threads == 256 ? by_unroll<256>(s.unroll) : by_unroll<512>(s.unroll);
+  }
+};
 
-template <int TH, int DT>
-adamw_kernel_t pick_flags(uint32_t unroll, bool nt, bool masked, bool gf32) {
-  if (masked) return gf32 ? pick_unroll<TH, DT, true, true>(unroll, nt) : pick_unroll<TH, DT, true, false>(unroll, nt);
-  return gf32 ? pick_unroll<TH, DT, false, true>(unroll, nt) : pick_unroll<TH, DT, false, false>(unroll, nt);
+template <int DT, bool NT>
+adamw_kernel_t pick_flags(const PtAdamwShape& s, bool masked, bool gf32) {
+  if (masked) return gf32 ? Kernels<DT, NT, true, true>::pick(s) : Kernels<DT, NT, true, false>::pick(s);
+  return gf32 ? Kernels<DT, NT, false, true>::pick(s) : Kernels<DT, NT, false, false>::pick(s);
 }
 
 template <int DT>
-adamw_kernel_t pick_kernel(uint32_t threads, uint32_t unroll, bool nt, bool masked, bool gf32) {
-  return threads == 256 ? pick_flags<256, DT>(unroll, nt, masked, gf32) : pick_flags<512, DT>(unroll, nt, masked, gf32);
+adamw_kernel_t pick_kernel(const PtAdamwShape& s, bool nt, bool masked, bool gf32) {
+  return nt ? pick_flags<DT, true>(s, masked, gf32) : pick_flags<DT, false>(s, masked, gf32);
 }
 
-typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint32_t, uint32_t*);
+template <int TH, int DT, bool NT>
+pattern_kernel_t pattern_by_unroll(uint32_t u) {
+  return u == 1 ? k_adamw_pattern<TH, DT, 1, NT> : u == 2 ? k_adamw_pattern<TH, DT, 2, NT>
+       : u == 8 ? k_adamw_pattern<TH, DT, 8, NT> : k_adamw_pattern<TH, DT, 4, NT>;
+}
 
-template <int TH, int DT>
-pattern_kernel_t pick_pattern_unroll(uint32_t unroll, bool nt) {
-  switch (unroll) {
-    case 1: return nt ? k_adamw_pattern<TH, DT, 1, true> : k_adamw_pattern<TH, DT, 1, false>;
-    case 2: return nt ? k_adamw_pattern<TH, DT, 2, true> : k_adamw_pattern<TH, DT, 2, false>;
-    case 8: return nt ? k_adamw_pattern<TH, DT, 8, true> : k_adamw_pattern<TH, DT, 8, false>;
-    default: return nt ? k_adamw_pattern<TH, DT, 4, true> : k_adamw_pattern<TH, DT, 4, false>;
+template <int DT, bool NT>
+pattern_kernel_t pick_pattern(const PtAdamwShape& s) {
+  return s.threads == 64 ? k_adamw_pattern<64, DT, 1, NT>
+                         : s.threads == 256 ? pattern_by_unroll<256, DT, NT>(s.unroll) : pattern_by_unroll<512, DT, NT>(s.unroll);
+}
+
+// Tiles per chunk and grid of an update launch over n_cols chunks.
+struct Geometry { uint64_t tiles; dim3 grid; };
+
+Geometry geometry(const pt_ctx* ctx, const PtAdamwShape& s, uint32_t n_cols) {
+  const uint64_t tile_units = uint64_t(s.threads) * s.unroll;
+  Geometry g;
+  g.tiles = (ctx->S / 4 + (LINE_UNITS - 1) + tile_units - 1) / tile_units;   // a chunk may start up to 7 units into its first tile
+  uint64_t x = g.tiles, y = n_cols;
+  if (ctx->opt_adamw_grid) {
+    x = std::min<uint64_t>(x, ctx->opt_adamw_grid);
+    y = std::min<uint64_t>(y, std::max<uint64_t>(1, ctx->opt_adamw_grid / x));
   }
+  x = std::min<uint64_t>(x, 0xffffffffull / s.threads);       // a grid dimension holds fewer than 2^32 work items
+  g.grid = dim3(uint32_t(x), uint32_t(std::min<uint64_t>(y, 65535)));
+  return g;
 }
 
-template <int DT>
-pattern_kernel_t pick_pattern(uint32_t threads, uint32_t unroll, bool nt) {
-  return threads == 256 ? pick_pattern_unroll<256, DT>(unroll, nt) : pick_pattern_unroll<512, DT>(unroll, nt);
-}
+// Launches of more than 2^31 tiles of 8192 elements are refused (no memory holds them).
+bool too_many_tiles(const pt_ctx* ctx, uint32_t n_cols) { return (ctx->S / 8192 + 1) * n_cols > 0x7fffffffull; }
 
 }  // namespace
 
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
                     uint32_t mask_chunk0, bool zero_grads) {
   if (n_cols == 0) return PT_OK;
-  const uint32_t unroll = ctx->opt_adamw_unroll;
-  const uint64_t units = ctx->S / 4;
-  const uint32_t threads = pt_adamw_threads(ctx, n_cols);
-  const uint64_t tile_units = uint64_t(threads) * unroll;
-  const uint64_t tpc = (units + tile_units - 1) / tile_units;
-  if (tpc * n_cols > 0x7fffffffull)
+  if (too_many_tiles(ctx, n_cols))
     return pt_fail(ctx, PT_ERR_UNSUPPORTED, "update launch of %u chunks exceeds 2^31 tiles", n_cols);
-  const uint32_t total = uint32_t(tpc) * n_cols;
-  // Grid: measured on MI355X, many short-lived workgroups (about three tiles each) keep the
-  // memory system a few percent busier than a grid sized to what stays resident.
-  uint32_t want = ctx->opt_adamw_grid > 0 ? ctx->opt_adamw_grid : (total + 2) / 3;
-  if (ctx->opt_adamw_grid == 0 && want < PT_ADAMW_MIN_GRID) want = PT_ADAMW_MIN_GRID;
-  dim3 grid(want < total ? want : total);
+  const PtAdamwShape shape = pt_adamw_shape(ctx, n_cols);
+  const Geometry geo = geometry(ctx, shape, n_cols);
   const bool nt = pt_adamw_nt(ctx, n_cols), masked = ctx->d_nd_begin != nullptr;
-  adamw_kernel_t kern = ctx->dtype == PT_BF16 ? pick_kernel<PT_BF16>(threads, unroll, nt, masked, ctx->grad_f32)
-                                              : pick_kernel<PT_FP16>(threads, unroll, nt, masked, ctx->grad_f32);
-  hipLaunchKernelGGL(kern, grid, dim3(threads), 0, stream, ctx->d_table, ctx->table_cols, first_col, n_cols,
-                     ctx->S, uint32_t(tpc), ctx->d_state, recast_on_skip ? 1 : 0, ctx->d_nd_begin, ctx->d_nd_ranges,
-                     mask_chunk0, zero_grads ? 1 : 0);
+  adamw_kernel_t kern = ctx->dtype == PT_BF16 ? pick_kernel<PT_BF16>(shape, nt, masked, ctx->grad_f32)
+                                              : pick_kernel<PT_FP16>(shape, nt, masked, ctx->grad_f32);
+  hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, ctx->d_table, ctx->d_state, ctx->table_cols,
+                     first_col, n_cols, mask_chunk0, ctx->S / 4, geo.tiles, recast_on_skip ? 1 : 0, zero_grads ? 1 : 0,
+                     ctx->d_nd_begin, ctx->d_nd_ranges);
   PT_LAUNCH_CHECK(ctx, "k_adamw");
   return PT_OK;
 }
@@ -420,20 +422,14 @@ extern "C" int pt_calib_adamw_pattern(pt_ctx* ctx, uint32_t first_chunk, uint32_
         return pt_fail(ctx, PT_ERR_STATE, "pt_calib_adamw_pattern: chunk %u has not been through pt_chunk_adamw_step yet "
                        "(its pointers are not in the context's table)", c);
   if (n_chunks == 0) return PT_OK;
-  const uint32_t unroll = ctx->opt_adamw_unroll;
-  const uint32_t threads = pt_adamw_threads(ctx, n_chunks);
-  const uint64_t units = ctx->S / 4, tile_units = uint64_t(threads) * unroll;
-  const uint64_t tpc = (units + tile_units - 1) / tile_units;
-  if (tpc * n_chunks > 0x7fffffffull) return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_calib_adamw_pattern: more than 2^31 tiles");
-  const uint32_t total = uint32_t(tpc) * n_chunks;
-  uint32_t want = ctx->opt_adamw_grid > 0 ? ctx->opt_adamw_grid : (total + 2) / 3;      // as pt_launch_adamw
-  if (ctx->opt_adamw_grid == 0 && want < PT_ADAMW_MIN_GRID) want = PT_ADAMW_MIN_GRID;
-  dim3 grid(want < total ? want : total);
+  if (too_many_tiles(ctx, n_chunks)) return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_calib_adamw_pattern: more than 2^31 tiles");
+  const PtAdamwShape shape = pt_adamw_shape(ctx, n_chunks);
+  const Geometry geo = geometry(ctx, shape, n_chunks);
   const bool nt = pt_adamw_nt(ctx, n_chunks);
-  pattern_kernel_t kern = ctx->dtype == PT_BF16 ? pick_pattern<PT_BF16>(threads, unroll, nt)
-                                                : pick_pattern<PT_FP16>(threads, unroll, nt);
-  hipLaunchKernelGGL(kern, grid, dim3(threads), 0, (hipStream_t)stream, ctx->d_table, ctx->table_cols, first_chunk,
-                     n_chunks, ctx->S, uint32_t(tpc), (uint32_t*)nullptr);
+  pattern_kernel_t kern = ctx->dtype == PT_BF16 ? (nt ? pick_pattern<PT_BF16, true>(shape) : pick_pattern<PT_BF16, false>(shape))
+                                                : (nt ? pick_pattern<PT_FP16, true>(shape) : pick_pattern<PT_FP16, false>(shape));
+  hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, (hipStream_t)stream, ctx->d_table, ctx->table_cols,
+                     first_chunk, n_chunks, ctx->S / 4, geo.tiles, (uint32_t*)nullptr);
   PT_LAUNCH_CHECK(ctx, "k_adamw_pattern");
   return PT_OK;
 }

@@ -55,8 +55,7 @@ enum PtRow : int {
 };
 
 constexpr uint32_t PT_MAX_SLOTS = 8;
-constexpr uint32_t PT_ADAMW_MIN_GRID = 16384;      // default grid of the update kernel: max(this, tiles / 3)
-constexpr uint32_t PT_ADAMW_DEFAULT_UNROLL = 4;
+constexpr uint32_t PT_ADAMW_LDS = 14848;           // unused LDS of an update workgroup: 11 workgroups fit a unit's 160 KiB
 constexpr uint32_t PT_NORM_BLOCK_ELEMS = 32768;  // elements one block of the norm kernel reduces
 constexpr uint32_t PT_PACK_TILE_ELEMS = 8192;    // chunk-space tile of the pack kernel (one 4-vector batch per lane)
 
@@ -100,9 +99,9 @@ struct pt_ctx {
   uint32_t norm_blocks = 0;  // blocks per chunk of the norm kernel
   uint32_t table_cols = 0;   // C + PT_MAX_SLOTS
   // launch-shape options (pt_ctx_set_option)
-  uint32_t opt_adamw_grid = 0;      // workgroups of the update kernel; 0 = max(PT_ADAMW_MIN_GRID, tiles / 3)
-  uint32_t opt_adamw_unroll = PT_ADAMW_DEFAULT_UNROLL;  // 4-element units per lane per tile: 1, 2, 4 or 8
-  uint32_t opt_adamw_threads = 0;   // workgroup size of the update kernel: 256, 512, or 0 = by launch size (pt_adamw_threads)
+  uint32_t opt_adamw_grid = 0;      // workgroups of the update kernel; 0 = one per tile
+  uint32_t opt_adamw_unroll = 0;    // 4-element units per lane per tile: 1, 2, 4 or 8; 0 = the library's shape (pt_adamw_shape)
+  uint32_t opt_adamw_threads = 0;   // workgroup size of the update kernel: 256, 512, or 0 = the library's shape
   uint32_t opt_adamw_nt = 2;        // non-temporal hints on the update's loads and stores: 0 no, 1 yes, 2 = by launch size (pt_adamw_nt)
   uint32_t opt_pack_tile_elems = PT_PACK_TILE_ELEMS;  // read when a pack plan is created
   bool scaler = false;
@@ -239,12 +238,15 @@ inline const uint64_t* pt_row(const pt_ctx* ctx, int row) {
 // recast_on_skip: on a skipped step rewrite param16 = RNE(master) instead of doing nothing.
 // mask_chunk0: chunk index (for the no-decay ranges) of table column first_col.
 // zero_grads: overwrite the gradient chunks with zeros once read (resident chunks only).
-// Workgroup size for an update launch over n_cols chunks: the option if set, else 512 for launches of 2^28
-// elements or more (measured equal or up to 1 % faster there) and 256 for small ones (launch-bound: more, smaller
-// workgroups start sooner).
-inline uint32_t pt_adamw_threads(const pt_ctx* ctx, uint32_t n_cols) {
-  if (ctx->opt_adamw_threads) return ctx->opt_adamw_threads;
-  return ctx->S * uint64_t(n_cols) >= (uint64_t(1) << 28) ? 512u : 256u;
+// Launch shape of an update over n_cols chunks.  Left to itself: one wave per workgroup, one unit per lane, 11 workgroups per
+// compute unit - the best of the shapes at every size measured, 0.8 M to 6.8e9 elements (figures at k_adamw).  With
+// adamw_threads or adamw_unroll set: that shape without a limit, the other of the two by the size of the launch (512 threads
+// from 2^28 elements on) or four units.
+struct PtAdamwShape { uint32_t threads, unroll, lds; };
+inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
+  if (!ctx->opt_adamw_threads && !ctx->opt_adamw_unroll) return {64, 1, PT_ADAMW_LDS};
+  const uint32_t by_size = ctx->S * uint64_t(n_cols) >= (uint64_t(1) << 28) ? 512u : 256u;
+  return {ctx->opt_adamw_threads ? ctx->opt_adamw_threads : by_size, ctx->opt_adamw_unroll ? ctx->opt_adamw_unroll : 4u, 0};
 }
 // Non-temporal hints for an update launch over n_cols chunks: the option if set, else by the state the launch
 // touches (16 bytes per element).  A state that fits the 256 MB Infinity Cache is re-read from it step after
