@@ -340,7 +340,10 @@ int pt_stream_status(const pt_ctx* ctx, int32_t* duplex_tested, int32_t* duplex_
 /* Update of host-resident ("non-persistent") chunks through the chunk buffers
  * (paper: non-persistent chunks are offloaded to CPU memory and moved over the
  * CPU-GPU link, "Hierarchical Chunk Management for Model States"; upload/offload
- * terms of Appendix A.1).  For chunk i of the range, slot = i mod n_slots:
+ * terms of Appendix A.1).  If every array of the range is pinned memory the device can address (hipHostMalloc on
+ * the context's device; fp32 arrays 16-byte, 16-bit arrays 8-byte aligned, fp32 gradients 16), one kernel on a side
+ * stream updates them in place over the link and the chunk buffers stay unused; h_grad[i] and h_param16[i] may then
+ * be one array.  Otherwise, for chunk i of the range, slot = i mod n_slots:
  *     upload stream : wait slot free; H2D grad(2B) + master, m, v (12B) per element
  *     compute stream: wait upload;    the same update kernel on the slot
  *     offload stream: wait kernel;    D2H master, m, v (12B) + param16 (2B); slot free
@@ -355,7 +358,7 @@ int pt_stream_status(const pt_ctx* ctx, int32_t* duplex_tested, int32_t* duplex_
  * this library or initialised from the master weights.
  * h_*: host arrays of n_chunks PINNED pointers (entry i is chunk first_chunk+i).
  * Requires pt_stream_reserve and a finalized norm in this step.
- * The upload and offload streams want hardware queues of their own: in a process that holds many other
+ * Through the chunk buffers the upload and offload streams want hardware queues of their own: in a process that holds many other
  * streams (HIP maps streams onto GPU_MAX_HW_QUEUES hardware queues, 4 by default) the two directions can
  * end up behind each other, and the link then carries one direction at a time.  pt_stream_reserve checks
  * single copies for that; and each call here first reads two timed events that bracketed the previous

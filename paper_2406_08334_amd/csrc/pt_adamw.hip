@@ -146,111 +146,180 @@ __device__ __forceinline__ void update_unit(const Consts& k, const float (&dk)[4
 // invariant of every update).
 constexpr uint32_t LINE_UNITS = 8;     // units of a 128-byte line of an fp32 array
 
+// The five arrays of a chunk.  `back`: units from the start of the master array's 128-byte line to the chunk's start.
+template <bool GF32>
+struct ChunkPtrs {
+  PT_GLOBAL typename GradUnit<GF32>::vec* g;
+  gf32x4_ptr w, m, v;
+  gu32x2_ptr p;
+  uint32_t back;
+};
+
+template <bool GF32>
+__device__ __forceinline__ ChunkPtrs<GF32> chunk_ptrs(uint64_t g, uint64_t w, uint64_t m, uint64_t v, uint64_t p) {
+  return {(PT_GLOBAL typename GradUnit<GF32>::vec*)g, (gf32x4_ptr)w, (gf32x4_ptr)m, (gf32x4_ptr)v, (gu32x2_ptr)p,
+          uint32_t(w >> 4) & (LINE_UNITS - 1)};
+}
+
+// Tile `tile` of a chunk.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
+__device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
+                                            uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
+                                            const uint64_t* __restrict__ nd_ranges) {
+  typedef typename GradUnit<GF32>::vec gvec;
+  constexpr uint32_t TILE_UNITS = TH * UNROLL;
+  const gvec gzero = {};
+  // first unit of the tile; "negative" (wrapped around, above `units`) for the idle lanes of the first tile
+  const uint64_t ub = tile * TILE_UNITS - x.back;
+  const bool full = ub < units && units - ub >= TILE_UNITS;
+  gvec g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
+  if (full) {
+#pragma unroll
+    for (int r = 0; r < UNROLL; ++r) {
+      const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+      g[r] = ld_stream<NT>(x.g + ub + o);
+      w[r] = ld_stream<NT>(x.w + ub + o);
+      m[r] = ld_stream<NT>(x.m + ub + o);
+      v[r] = ld_stream<NT>(x.v + ub + o);
+    }
+  }
+  asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind the branch
+  if (skip) {
+    for (int r = 0; r < UNROLL; ++r) {
+      const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
+      if (u >= units) continue;
+      if (recast_on_skip) {
+        const f32x4 y = x.w[u];
+        u32x2 p;
+        p.x = encode16<DT>(y[0]) | (encode16<DT>(y[1]) << 16);
+        p.y = encode16<DT>(y[2]) | (encode16<DT>(y[3]) << 16);
+        x.p[u] = p;
+      }
+      if (zero_grads) st_stream<NT>(gzero, x.g + u);
+    }
+    return;
+  }
+  float dtile = k.decay;            // decay factor of the whole tile, when it has one
+  bool cut = false;                 // a range edge falls inside this tile
+  uint32_t r0 = 0, r1 = 0;          // ranges of this chunk from the first one that ends after the tile start
+  if (MASKED) {
+    r1 = nd_begin[c + 1];
+    uint32_t lo = nd_begin[c], hi = r1;
+    const uint64_t e0 = ub < units ? ub * 4 : 0, e1 = (ub + TILE_UNITS) * 4;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (nd_ranges[2 * size_t(mid) + 1] <= e0) lo = mid + 1; else hi = mid;
+    }
+    r0 = lo;
+    if (r0 < r1 && nd_ranges[2 * size_t(r0)] < e1) {
+      if (nd_ranges[2 * size_t(r0)] <= e0 && nd_ranges[2 * size_t(r0) + 1] >= e1) dtile = 1.0f;
+      else cut = true;
+    }
+  }
+  if (full && !(MASKED && cut)) {
+    const float dk[4] = {dtile, dtile, dtile, dtile};
+#pragma unroll
+    for (int r = 0; r < UNROLL; ++r) {
+      const uint32_t o = threadIdx.x + uint32_t(r) * TH;
+      u32x2 p;
+      update_unit<DT, GF32>(k, dk, g[r], w[r], m[r], v[r], p);
+      st_stream<NT>(w[r], x.w + ub + o);
+      st_stream<NT>(m[r], x.m + ub + o);
+      st_stream<NT>(v[r], x.v + ub + o);
+      st_stream<NT>(p, x.p + ub + o);
+      if (zero_grads) st_stream<NT>(gzero, x.g + ub + o);
+    }
+    return;
+  }
+  // the first and the last tile of a chunk, and tiles with a range edge inside: unit by unit
+  for (int r = 0; r < UNROLL; ++r) {
+    const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
+    if (u >= units) continue;
+    float dk[4] = {dtile, dtile, dtile, dtile};
+    if (MASKED && cut) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint64_t e = 4 * u + j;
+        for (uint32_t q = r0; q < r1 && nd_ranges[2 * size_t(q)] <= e; ++q)
+          if (e < nd_ranges[2 * size_t(q) + 1]) dk[j] = 1.0f;
+      }
+    }
+    gvec g1 = x.g[u]; f32x4 w1 = x.w[u], m1 = x.m[u], v1 = x.v[u]; u32x2 p;
+    update_unit<DT, GF32>(k, dk, g1, w1, m1, v1, p);
+    x.w[u] = w1; x.m[u] = m1; x.v[u] = v1; x.p[u] = p;
+    if (zero_grads) x.g[u] = gzero;
+  }
+}
+
+__device__ __forceinline__ Consts load_consts(const PtDevState* __restrict__ st) {
+  Consts k;
+  k.b1 = st->c[0]; k.b2 = st->c[1]; k.omb1 = st->c[2]; k.omb2 = st->c[3]; k.decay = st->c[4];
+  k.step_size = st->c[5]; k.rsb2 = st->c[6]; k.eps = st->c[7]; k.gm = st->c[8];
+  return k;
+}
+
 template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
 __global__ void __launch_bounds__(TH)
 k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, uint32_t table_cols, uint32_t first_col,
         uint32_t n_cols, uint32_t mask_chunk0, uint64_t units, uint64_t tiles, int recast_on_skip, int zero_grads,
         const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges) {
-  typedef typename GradUnit<GF32>::vec gvec;
-  typedef PT_GLOBAL gvec* g_ptr;
-  constexpr uint32_t TILE_UNITS = TH * UNROLL;
-  const gvec gzero = {};
   const int32_t skip = st->skip;
-  Consts k;
-  k.b1 = st->c[0]; k.b2 = st->c[1]; k.omb1 = st->c[2]; k.omb2 = st->c[3]; k.decay = st->c[4];
-  k.step_size = st->c[5]; k.rsb2 = st->c[6]; k.eps = st->c[7]; k.gm = st->c[8];
+  const Consts k = load_consts(st);
   for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
-    const uint32_t col = first_col + ci;
-    const uint64_t wa = table[size_t(ROW_MASTER) * table_cols + col];
-    const g_ptr gp = (g_ptr)(table[size_t(ROW_GRAD) * table_cols + col]);
-    const gf32x4_ptr wp = (gf32x4_ptr)wa;
-    const gf32x4_ptr mp = (gf32x4_ptr)(table[size_t(ROW_M) * table_cols + col]);
-    const gf32x4_ptr vp = (gf32x4_ptr)(table[size_t(ROW_V) * table_cols + col]);
-    const gu32x2_ptr pp = (gu32x2_ptr)(table[size_t(ROW_P16) * table_cols + col]);
-    const uint32_t back = uint32_t(wa >> 4) & (LINE_UNITS - 1);   // units from the line's start to the chunk's
-    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-      // first unit of the tile; "negative" (wrapped around, above `units`) for the idle lanes of the first tile
-      const uint64_t ub = tile * TILE_UNITS - back;
-      const bool full = ub < units && units - ub >= TILE_UNITS;
-      gvec g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
-      if (full) {
-#pragma unroll
-        for (int r = 0; r < UNROLL; ++r) {
-          const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-          g[r] = ld_stream<NT>(gp + ub + o);
-          w[r] = ld_stream<NT>(wp + ub + o);
-          m[r] = ld_stream<NT>(mp + ub + o);
-          v[r] = ld_stream<NT>(vp + ub + o);
-        }
-      }
-      asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind the branch
-      if (skip) {
-        for (int r = 0; r < UNROLL; ++r) {
-          const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
-          if (u >= units) continue;
-          if (recast_on_skip) {
-            const f32x4 x = wp[u];
-            u32x2 p;
-            p.x = encode16<DT>(x[0]) | (encode16<DT>(x[1]) << 16);
-            p.y = encode16<DT>(x[2]) | (encode16<DT>(x[3]) << 16);
-            pp[u] = p;
-          }
-          if (zero_grads) st_stream<NT>(gzero, gp + u);
-        }
+    const uint64_t* t = table + first_col + ci;
+    const ChunkPtrs<GF32> x = chunk_ptrs<GF32>(t[size_t(ROW_GRAD) * table_cols], t[size_t(ROW_MASTER) * table_cols],
+                                               t[size_t(ROW_M) * table_cols], t[size_t(ROW_V) * table_cols],
+                                               t[size_t(ROW_P16) * table_cols]);
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
+      update_tile<TH, DT, UNROLL, NT, MASKED, GF32>(k, skip, x, tile, units, mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin,
+                                                    nd_ranges);
+  }
+}
+
+// The update of chunks in pinned host memory, in place over the link: the kernel itself reads gradient, master, momentum
+// and variance from the host's arrays and writes master, momentum, variance and param16 back.
+//
+// What bounds it is the link with both directions busy (14 bytes per element each way).  Both directions share it from the
+// first microsecond to the last: no first upload and no last offload that run alone, and no event between streams that
+// could share a hardware queue.  Requests in flight are kept to what covers the link's latency (64 waves with one unit per
+// lane) because more of them queue up in front of everybody's HBM traffic, writes above all; and they all come from ONE
+// XCD (workgroups are dealt round robin over the eight: only every eighth works), so that the queues of the other seven
+// stay free.  If the dispatch order were another one, only that advantage would be lost.  Half of a 12-block model's chunks
+// (seven of 2^23 elements): 8 workgroups 21.4 ms a step, 12: 17.0, 16: 16.7 (49 GB/s per direction), 20: 17.0.  The
+// resident update of 6.4e8 elements beside it runs at 5.1 TB/s (beside the copy engines: 5.25, and those move 48 GB/s).
+// Moving the bytes without the arithmetic, with a copy in HBM (6.6 TB/s by itself) beside it: 32 waves on one XCD 49.9 GB/s
+// and 5.3 TB/s, 32 waves over all XCDs 49.4 and 3.7, 128 waves over all XCDs 49.2 and 0.95.
+constexpr uint32_t HOST_TH = 256, HOST_GROUPS = 16, N_XCD = 8;
+
+struct HostChunks { uint64_t at[PT_DIRECT_CHUNKS][5]; };     // g, master, m, v, param16 as the device addresses them
+
+template <int DT, bool MASKED, bool GF32>
+__global__ void __launch_bounds__(HOST_TH)
+k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_t n_chunks, uint32_t mask_chunk0, uint64_t units,
+             uint64_t tiles, const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges) {
+  if (blockIdx.x % N_XCD) return;
+  const uint32_t groups = gridDim.x / N_XCD;
+  const int32_t skip = st->skip;
+  const Consts k = load_consts(st);
+  uint64_t tile = blockIdx.x / N_XCD;          // the tiles of all chunks are dealt out as one sequence
+  for (uint32_t ci = 0; ci < n_chunks; ++ci) {
+    const uint64_t* a = chunks.at[ci];
+    const ChunkPtrs<GF32> x = chunk_ptrs<GF32>(a[0], a[1], a[2], a[3], a[4]);
+    for (; tile < tiles; tile += groups) {
+      if (!skip) {
+        update_tile<HOST_TH, DT, 1, true, MASKED, GF32>(k, 0, x, tile, units, mask_chunk0 + ci, 0, 0, nd_begin, nd_ranges);
         continue;
       }
-      float dtile = k.decay;            // decay factor of the whole tile, when it has one
-      bool cut = false;                 // a range edge falls inside this tile
-      uint32_t r0 = 0, r1 = 0;          // ranges of this chunk from the first one that ends after the tile start
-      if (MASKED) {
-        const uint32_t c = mask_chunk0 + ci;
-        r1 = nd_begin[c + 1];
-        uint32_t lo = nd_begin[c], hi = r1;
-        const uint64_t e0 = ub < units ? ub * 4 : 0, e1 = (ub + TILE_UNITS) * 4;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (nd_ranges[2 * size_t(mid) + 1] <= e0) lo = mid + 1; else hi = mid;
-        }
-        r0 = lo;
-        if (r0 < r1 && nd_ranges[2 * size_t(r0)] < e1) {
-          if (nd_ranges[2 * size_t(r0)] <= e0 && nd_ranges[2 * size_t(r0) + 1] >= e1) dtile = 1.0f;
-          else cut = true;
-        }
-      }
-      if (full && !(MASKED && cut)) {
-        const float dk[4] = {dtile, dtile, dtile, dtile};
-#pragma unroll
-        for (int r = 0; r < UNROLL; ++r) {
-          const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-          u32x2 p;
-          update_unit<DT, GF32>(k, dk, g[r], w[r], m[r], v[r], p);
-          st_stream<NT>(w[r], wp + ub + o);
-          st_stream<NT>(m[r], mp + ub + o);
-          st_stream<NT>(v[r], vp + ub + o);
-          st_stream<NT>(p, pp + ub + o);
-          if (zero_grads) st_stream<NT>(gzero, gp + ub + o);
-        }
-        continue;
-      }
-      // the first and the last tile of a chunk, and tiles with a range edge inside: unit by unit
-      for (int r = 0; r < UNROLL; ++r) {
-        const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
-        if (u >= units) continue;
-        float dk[4] = {dtile, dtile, dtile, dtile};
-        if (MASKED && cut) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint64_t e = 4 * u + j;
-            for (uint32_t q = r0; q < r1 && nd_ranges[2 * size_t(q)] <= e; ++q)
-              if (e < nd_ranges[2 * size_t(q) + 1]) dk[j] = 1.0f;
-          }
-        }
-        gvec g1 = gp[u]; f32x4 w1 = wp[u], m1 = mp[u], v1 = vp[u]; u32x2 p;
-        update_unit<DT, GF32>(k, dk, g1, w1, m1, v1, p);
-        wp[u] = w1; mp[u] = m1; vp[u] = v1; pp[u] = p;
-        if (zero_grads) gp[u] = gzero;
-      }
+      // a skipped step leaves param16 as the recast of the master weights, as the chunk buffers do
+      const uint64_t u = tile * HOST_TH - x.back + threadIdx.x;
+      if (u >= units) continue;
+      const f32x4 y = x.w[u];
+      u32x2 p;
+      p.x = encode16<DT>(y[0]) | (encode16<DT>(y[1]) << 16);
+      p.y = encode16<DT>(y[2]) | (encode16<DT>(y[3]) << 16);
+      x.p[u] = p;
     }
+    tile -= tiles;
   }
 }
 
@@ -381,6 +450,25 @@ int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_
                      first_col, n_cols, mask_chunk0, ctx->S / 4, geo.tiles, recast_on_skip ? 1 : 0, zero_grads ? 1 : 0,
                      ctx->d_nd_begin, ctx->d_nd_ranges);
   PT_LAUNCH_CHECK(ctx, "k_adamw");
+  return PT_OK;
+}
+
+int pt_launch_adamw_host(pt_ctx* ctx, const uint64_t (*at)[5], uint32_t n, hipStream_t stream, uint32_t mask_chunk0) {
+  const bool masked = ctx->d_nd_begin != nullptr, gf32 = ctx->grad_f32;
+  const uint64_t units = ctx->S / 4, tiles = (units + (LINE_UNITS - 1) + HOST_TH - 1) / HOST_TH;
+  for (uint32_t i = 0; i < n; i += PT_DIRECT_CHUNKS) {
+    HostChunks c{};
+    const uint32_t k = std::min(n - i, PT_DIRECT_CHUNKS);
+    std::memcpy(c.at, at + i, k * sizeof c.at[0]);
+    auto kern = ctx->dtype == PT_BF16
+        ? (masked ? (gf32 ? k_adamw_host<PT_BF16, true, true> : k_adamw_host<PT_BF16, true, false>)
+                  : (gf32 ? k_adamw_host<PT_BF16, false, true> : k_adamw_host<PT_BF16, false, false>))
+        : (masked ? (gf32 ? k_adamw_host<PT_FP16, true, true> : k_adamw_host<PT_FP16, true, false>)
+                  : (gf32 ? k_adamw_host<PT_FP16, false, true> : k_adamw_host<PT_FP16, false, false>));
+    hipLaunchKernelGGL(kern, dim3(HOST_GROUPS * N_XCD), dim3(HOST_TH), 0, stream, c, ctx->d_state, k, mask_chunk0 + i, units, tiles,
+                       ctx->d_nd_begin, ctx->d_nd_ranges);
+    PT_LAUNCH_CHECK(ctx, "k_adamw_host");
+  }
   return PT_OK;
 }
 

@@ -55,6 +55,7 @@ enum PtRow : int {
 };
 
 constexpr uint32_t PT_MAX_SLOTS = 8;
+constexpr uint32_t PT_DIRECT_CHUNKS = 16;         // host chunks one launch of the in-place streamed update takes
 constexpr uint32_t PT_ADAMW_LDS = 14848;           // unused LDS of an update workgroup: 11 workgroups fit a unit's 160 KiB
 constexpr uint32_t PT_NORM_BLOCK_ELEMS = 32768;  // elements one block of the norm kernel reduces
 constexpr uint32_t PT_PACK_TILE_ELEMS = 8192;    // chunk-space tile of the pack kernel (one 4-vector batch per lane)
@@ -146,8 +147,11 @@ struct pt_ctx {
   bool duplex_tested = false, duplex_ok = false;
   uint32_t duplex_attempts = 0;
   bool slot_used[PT_MAX_SLOTS] = {};
-  bool stream_pending = false;
+  bool stream_pending = false;          // a streamed update of this step has not been joined yet ...
+  bool slots_pending = false, direct_pending = false;   // ... through the chunk buffers / in place
   uint32_t last_slot = 0;
+  hipEvent_t ev_direct = nullptr;       // behind the last in-place launch on s_comp
+  bool direct_used = false;             // ev_direct has been recorded
 
   // weight-decay groups: per chunk, sorted disjoint element ranges kept out of the decay
   uint32_t* d_nd_begin = nullptr;        // [C + 1] indices into d_nd_ranges (NULL: no ranges set)
@@ -258,6 +262,9 @@ inline bool pt_adamw_nt(const pt_ctx* ctx, uint32_t n_cols) {
 }
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
                     uint32_t mask_chunk0, bool zero_grads);
+// The update of n chunks in pinned host memory, in place (at[i]: gradient, master, m, v, param16 of chunk i as device
+// addresses; fp32 arrays 16-byte, 16-bit ones 8-byte aligned).  A skipped step recasts param16.
+int pt_launch_adamw_host(pt_ctx* ctx, const uint64_t (*at)[5], uint32_t n, hipStream_t stream, uint32_t mask_chunk0);
 
 // ---- implemented in pt_stream.hip ----------------------------------------------------------
 // Destroys the streamed path's streams and events and frees its chunk buffers (no-op when none).

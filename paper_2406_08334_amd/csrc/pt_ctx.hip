@@ -316,8 +316,9 @@ extern "C" int pt_step_end(pt_ctx* ctx, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   if (ctx->stream_pending) {
     // offloads complete in order on one stream: the last one recorded covers them all
-    PT_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_down[ctx->last_slot], 0));
-    ctx->stream_pending = false;
+    if (ctx->slots_pending) PT_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_down[ctx->last_slot], 0));
+    if (ctx->direct_pending) PT_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_direct, 0));
+    ctx->stream_pending = ctx->slots_pending = ctx->direct_pending = false;
   }
   if (int rc = pt_flush_pending(ctx, st); rc != PT_OK) return rc;     // a step without an update still needs its found_inf
   hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state);

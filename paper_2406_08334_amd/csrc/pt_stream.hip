@@ -1,10 +1,14 @@
-// Streamed update of host-resident chunks through a ring of device chunk
-// buffers: upload, update and offload run on three side streams ordered by
-// events, so that H2D(i+1), the kernel of chunk i and D2H(i-1) overlap each other
-// and whatever the caller runs on its own stream.
+// Streamed update of host-resident chunks, in one of two ways:
+//  * in place (pinned, aligned arrays: the usual case): one kernel on a side stream reads and writes the host's arrays
+//    over the link (k_adamw_host in pt_adamw.hip);
+//  * through a ring of device chunk buffers (any other memory the copy calls take): upload, update and offload run on
+//    three side streams ordered by events, so that H2D(i+1), the kernel of chunk i and D2H(i-1) overlap each other.
+// Either overlaps whatever the caller runs on its own stream.
 //
-// Link-bound: 14 bytes up and 14 bytes down per element over the host link
-// against 28 bytes of HBM traffic in the kernel.
+// Link-bound: 14 bytes up and 14 bytes down per element over the host link.  Half of a 12-block model's chunks (seven of
+// 2^23 elements), steps in a row: in place 16.9 ms a step; through the buffers 18.8 ms with one context and the GPU waited
+// for after each step, 27 to 52 ms with three contexts in turn, whose side streams share hardware queues.  One such chunk
+// of 15: 2.5 against 4.4 ms (through the buffers its upload and its offload run one after the other).
 #include <chrono>
 #include <vector>
 
@@ -30,6 +34,8 @@ void pt_stream_release(pt_ctx* ctx) {
   if (ctx->s_comp) { (void)hipStreamDestroy(ctx->s_comp); ctx->s_comp = nullptr; }
   if (ctx->s_down) { (void)hipStreamDestroy(ctx->s_down); ctx->s_down = nullptr; }
   if (ctx->ev_fork) { (void)hipEventDestroy(ctx->ev_fork); ctx->ev_fork = nullptr; }
+  if (ctx->ev_direct) { (void)hipEventDestroy(ctx->ev_direct); ctx->ev_direct = nullptr; }
+  ctx->direct_used = false;
   if (ctx->ev_t0) { (void)hipEventDestroy(ctx->ev_t0); ctx->ev_t0 = nullptr; }
   if (ctx->ev_t1) { (void)hipEventDestroy(ctx->ev_t1); ctx->ev_t1 = nullptr; }
   ctx->health_pending = false;
@@ -59,6 +65,7 @@ static int reserve_slots(pt_ctx* ctx, uint32_t n_slots) {
   PT_HIP(ctx, hipStreamCreateWithFlags(&ctx->s_comp, hipStreamNonBlocking));
   PT_HIP(ctx, hipStreamCreateWithFlags(&ctx->s_down, hipStreamNonBlocking));
   PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
+  PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_direct, hipEventDisableTiming));
   PT_HIP(ctx, hipEventCreate(&ctx->ev_t0));
   PT_HIP(ctx, hipEventCreate(&ctx->ev_t1));
   for (uint32_t s = 0; s < n_slots; ++s) {
@@ -212,9 +219,29 @@ extern "C" int pt_stream_status(const pt_ctx* ctx, int32_t* duplex_tested, int32
   return PT_OK;
 }
 
+// New side streams, tried out.  Everything the old ones were given must have run.
+static int rebuild_side_streams(pt_ctx* ctx) {
+  ctx->opt_force_unhealthy = 0;
+  std::vector<hipStream_t> retired;
+  int rc = replace_side_streams(ctx, true, retired);
+  if (rc != PT_OK) return rc;
+  for (hipStream_t s : retired) (void)hipStreamDestroy(s);
+  ctx->stream_rebuilds += 1;
+  return duplex_self_test(ctx);
+}
+
 // Reads the verdict on the last streamed step, if it is in, and replaces the side streams after a serialised one.
+// A step in place cannot be serialised and is not timed: only the verdict that tests force applies to it.
 static int look_at_last_step(pt_ctx* ctx) {
-  if (!ctx->health_pending) return PT_OK;
+  if (!ctx->health_pending) {
+    if (!ctx->opt_force_unhealthy || !ctx->direct_used || !ctx->duplex_tested || ctx->stream_rebuilds >= PT_MAX_STREAM_REBUILDS)
+      return PT_OK;
+    if (hipEventQuery(ctx->ev_direct) != hipSuccess) {
+      (void)hipGetLastError();
+      return PT_OK;
+    }
+    return rebuild_side_streams(ctx);
+  }
   if (hipEventQuery(ctx->ev_t1) != hipSuccess) {
     (void)hipGetLastError();      // "not ready" is no error of this call: the step is looked at next time
     return PT_OK;
@@ -228,14 +255,46 @@ static int look_at_last_step(pt_ctx* ctx) {
   const double rate = double(ctx->health_bytes) / (double(ms) * 1e-3);
   const bool serialised = ctx->health_chunks >= 6 && rate < 0.65 * ctx->link_one_dir_Bps;
   if (!(serialised || ctx->opt_force_unhealthy) || ctx->stream_rebuilds >= PT_MAX_STREAM_REBUILDS) return PT_OK;
-  ctx->opt_force_unhealthy = 0;
-  // ev_t1 is done, so everything the side streams were given has run: they are idle
-  std::vector<hipStream_t> retired;
-  int rc = replace_side_streams(ctx, true, retired);
-  if (rc != PT_OK) return rc;
-  for (hipStream_t s : retired) (void)hipStreamDestroy(s);
-  ctx->stream_rebuilds += 1;
-  return duplex_self_test(ctx);
+  // ev_t1 is done, so everything the copy streams were given has run; a step in place may still be open
+  if (ctx->direct_used && hipEventQuery(ctx->ev_direct) != hipSuccess) {
+    (void)hipGetLastError();
+    return PT_OK;
+  }
+  return rebuild_side_streams(ctx);
+}
+
+// The device's address of [p, p + bytes) if that is pinned host memory of this context's device, aligned to `align`;
+// 0 if it is anything else (pageable, managed or device memory, a range that leaves its allocation).
+static uint64_t pinned_on_device(const pt_ctx* ctx, const void* p, size_t bytes, size_t align) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) { (void)hipGetLastError(); return 0; }
+  if (a.type != hipMemoryTypeHost || a.isManaged || a.device != ctx->device || !a.devicePointer) return 0;
+  const uint64_t d = (uint64_t)(uintptr_t)a.devicePointer;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)a.devicePointer) != hipSuccess) { (void)hipGetLastError(); return 0; }
+  const uint64_t lo = (uint64_t)(uintptr_t)base;
+  if (d < lo || bytes > size || d - lo > size - bytes || d % align) return 0;
+  return d;
+}
+
+// at[i] = the five arrays of chunk i as the device addresses them; false unless every one of them can be updated in
+// place.  Gradient and param16 may be one array (every unit is read before it is written, by one lane), but not two
+// overlapping ones.  Costs two look-ups of 0.1 us per array.
+static bool in_place(const pt_ctx* ctx, uint32_t n, const void* const* h_grad, float* const* h_master, float* const* h_m,
+                     float* const* h_v, void* const* h_param16, std::vector<uint64_t>& at) {
+  const size_t S = ctx->S, gb = grad_bytes(ctx);
+  at.resize(size_t(5) * n);
+  for (uint32_t i = 0; i < n; ++i) {
+    uint64_t* a = at.data() + size_t(5) * i;
+    if (!(a[0] = pinned_on_device(ctx, h_grad[i], gb * S, 4 * gb)) || !(a[1] = pinned_on_device(ctx, h_master[i], 4 * S, 16)) ||
+        !(a[2] = pinned_on_device(ctx, h_m[i], 4 * S, 16)) || !(a[3] = pinned_on_device(ctx, h_v[i], 4 * S, 16)) ||
+        !(a[4] = pinned_on_device(ctx, h_param16[i], 2 * S, 8)))
+      return false;
+    const bool same = a[0] == a[4] && gb == 2;
+    if (!same && a[0] < a[4] + 2 * S && a[4] < a[0] + gb * S) return false;
+  }
+  return true;
 }
 
 extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t first_chunk, uint32_t n_chunks,
@@ -261,8 +320,23 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
   if (rc != PT_OK) return rc;
   rc = pt_prepare_consts(ctx, hp, st);
   if (rc != PT_OK) return rc;
+  std::vector<uint64_t> at;
+  bool direct = false;
+  rc = pt_guarded(ctx, "pt_chunk_stream_step", [&] {
+    direct = in_place(ctx, n_chunks, h_grad, h_master, h_m, h_v, h_param16, at);
+    return int(PT_OK);
+  });
+  if (rc != PT_OK) return rc;
   // side streams start after everything already enqueued on the caller's stream
   PT_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
+  if (direct) {
+    PT_HIP(ctx, hipStreamWaitEvent(ctx->s_comp, ctx->ev_fork, 0));
+    rc = pt_launch_adamw_host(ctx, (const uint64_t(*)[5])at.data(), n_chunks, ctx->s_comp, first_chunk);
+    if (rc != PT_OK) return rc;
+    PT_HIP(ctx, hipEventRecord(ctx->ev_direct, ctx->s_comp));
+    ctx->direct_used = ctx->direct_pending = ctx->stream_pending = true;
+    return PT_OK;
+  }
   PT_HIP(ctx, hipStreamWaitEvent(ctx->s_up, ctx->ev_fork, 0));
   PT_HIP(ctx, hipStreamWaitEvent(ctx->s_comp, ctx->ev_fork, 0));
   // bracket the step with two timed events, unless the last bracket has not been read yet
@@ -292,7 +366,7 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
     PT_HIP(ctx, hipEventRecord(ctx->ev_down[s], ctx->s_down));
     ctx->slot_used[s] = true;
     ctx->last_slot = s;
-    ctx->stream_pending = true;
+    ctx->stream_pending = ctx->slots_pending = true;
   }
   if (watch) {
     PT_HIP(ctx, hipEventRecord(ctx->ev_t1, ctx->s_down));

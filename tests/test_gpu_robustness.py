@@ -266,3 +266,48 @@ def test_stream_reserve_tries_its_copy_streams_out_and_ends_with_a_pair_that_ove
         torch.cuda.synchronize()
         for ctx in ctxs:
             B.pt_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype,grad_fp32", [(torch.bfloat16, False), (torch.float16, True)])
+@pytest.mark.parametrize("S,n_host", [(8, 1), (1024, 3), (5000, 17)])      # one unit; whole tiles; ragged, two launches
+@pytest.mark.parametrize("memory", ["pinned", "shared", "offset", "pageable"])
+@pytest.mark.parametrize("inf", [False, True])
+def test_streamed_update_by_the_kind_of_host_memory(dtype, grad_fp32, S, n_host, memory, inf):
+    """Pinned and aligned arrays are updated in place (also where gradient and parameters share one), pinned ones off the
+    alignment and pageable ones through the chunk buffers: the bits of the resident update, skipped steps included."""
+    if memory == "shared" and grad_fp32:
+        pytest.skip("fp32 gradients and 16-bit parameters are two arrays")
+    st = ChunkedState([S * n_host - 3 if S > 8 else 5], S, dtype=dtype, grad_fp32=grad_fp32)
+    try:
+        assert st.C == n_host
+        hp_b, _, _ = hp_pair()
+        st.set_no_decay(runs=[(c, 1, S // 2) for c in range(n_host)])
+        st.set_grads(1)
+        if grad_fp32:
+            st.accum(True, True)
+        else:
+            st.pack()
+        arenas = {"g": st.grads, "w": st.w, "m": st.m, "v": st.v, "p": st.p16}
+
+        def host_copy(row):
+            if memory == "pageable":
+                return row.cpu()
+            off = 1 if memory == "offset" else 0
+            t = torch.empty(S + off, dtype=row.dtype, pin_memory=True)[off:]
+            return t.copy_(row)
+        host = {k: [host_copy(a[c]) for c in range(n_host)] for k, a in arenas.items()}
+        if memory == "shared":
+            host["p"] = host["g"]
+        B.pt_stream_reserve(st.ctx, 2)
+        B.pt_step_override(st.ctx, 0.5, inf)
+        B.pt_chunk_stream_step(st.ctx, hp_b, 0, n_host, host["g"], host["w"], host["m"], host["v"], host["p"])
+        torch.cuda.synchronize()
+        st.adamw(hp_b)
+        st.end()
+        torch.cuda.synchronize()
+        for k in ("w", "m", "v", "p"):
+            for c in range(n_host):
+                bits = torch.int16 if k == "p" else torch.int32
+                assert torch.equal(host[k][c].view(bits), arenas[k][c].cpu().view(bits)), (k, c)
+    finally:
+        st.close()
