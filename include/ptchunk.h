@@ -142,8 +142,8 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
  *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 (default).  With neither this nor adamw_unroll
  *                   set the library takes its own shape: workgroups of one wave, few of them per compute unit
  *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4 or 8
- *   "adamw_nt"      non-temporal hints on the update's loads and stores: 1 = always, 0 = never, 2 = the library
- *                   chooses by launch size (default): none while the launch's state fits the 256 MB Infinity Cache
+ *   "adamw_nt"      non-temporal hints on the update's loads and stores: 0 = none, 1 or 2 (default) = on all of them,
+ *                   but on the gradient loads only where the context's gradient chunks exceed the 256 MB Infinity Cache
  *   "pack_tile_elems"  elements one workgroup of pack/unpack moves; read by pt_pack_plan_create
  *   "stream_test_reject"  for tests of pt_stream_reserve: its trial of the copy streams rejects that many
  *                   stream pairs (0..5) whatever it measures, so that the replacement runs

@@ -103,7 +103,7 @@ struct pt_ctx {
   uint32_t opt_adamw_grid = 0;      // workgroups of the update kernel; 0 = one per tile
   uint32_t opt_adamw_unroll = 0;    // 4-element units per lane per tile: 1, 2, 4 or 8; 0 = the library's shape (pt_adamw_shape)
   uint32_t opt_adamw_threads = 0;   // workgroup size of the update kernel: 256, 512, or 0 = the library's shape
-  uint32_t opt_adamw_nt = 2;        // non-temporal hints on the update's loads and stores: 0 no, 1 yes, 2 = by launch size (pt_adamw_nt)
+  uint32_t opt_adamw_nt = 2;        // non-temporal hints on the update's loads and stores: 0 no, 1 or 2 yes (pt_adamw_hints)
   uint32_t opt_pack_tile_elems = PT_PACK_TILE_ELEMS;  // read when a pack plan is created
   bool scaler = false;
   bool grad_f32 = false;            // gradient chunks hold fp32 (accumulated micro-batches), option "grad_fp32"
@@ -252,13 +252,18 @@ inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
   const uint32_t by_size = ctx->S * uint64_t(n_cols) >= (uint64_t(1) << 28) ? 512u : 256u;
   return {ctx->opt_adamw_threads ? ctx->opt_adamw_threads : by_size, ctx->opt_adamw_unroll ? ctx->opt_adamw_unroll : 4u, 0};
 }
-// Non-temporal hints for an update launch over n_cols chunks: the option if set, else by the state the launch
-// touches (16 bytes per element).  A state that fits the 256 MB Infinity Cache is re-read from it step after
-// step, and hints that keep it out of the cache cost 10 % there (21.4 against 22.7 us for 64 MiB, 71 against 80 us
-// for 256 MiB); beyond it the streams have no reuse and the hints gain 4-10 % (120 against 133 us for 384 MiB).
-inline bool pt_adamw_nt(const pt_ctx* ctx, uint32_t n_cols) {
-  if (ctx->opt_adamw_nt != 2) return ctx->opt_adamw_nt != 0;
-  return 16 * ctx->S * uint64_t(n_cols) > (uint64_t(256) << 20);
+// Non-temporal hints of an update launch.  On unless switched off: in the library's shape they gain 4-15 % at every size,
+// whether the state was last touched a step ago or 512 MB of other traffic earlier (update with and without hints: 16 MB
+// of state 16.0 / 17.8 us, 108 MB 45.3 / 51.8, 108 MB touched just before 44.6 / 48.2, 733 MB 217 / 237).
+// The gradient words are the exception: pack has just written them, and where the context's gradient chunks fit the 256 MB
+// Infinity Cache together, pack's stores and the update's gradient loads go without hints, so that the update finds them
+// there (step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615; beyond it the cache holds too little: 667 M 3261 ->
+// 3325).  fp32 gradient chunks keep the hints.
+enum PtHints : int { PT_HINT_NONE = 0, PT_HINT_STATE = 1, PT_HINT_ALL = 2 };     // STATE: all but the gradient loads
+inline bool pt_grads_cached(const pt_ctx* ctx) { return !ctx->grad_f32 && 2 * ctx->S * uint64_t(ctx->C) <= (uint64_t(256) << 20); }
+inline PtHints pt_adamw_hints(const pt_ctx* ctx) {
+  if (ctx->opt_adamw_nt == 0) return PT_HINT_NONE;
+  return pt_grads_cached(ctx) ? PT_HINT_STATE : PT_HINT_ALL;
 }
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
                     uint32_t mask_chunk0, bool zero_grads);

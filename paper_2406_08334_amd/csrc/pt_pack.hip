@@ -52,6 +52,11 @@ __device__ __forceinline__ void accum_vec(const u32x4& q, double inv_scale, doub
   }
 }
 
+template <bool NT>
+__device__ __forceinline__ void store_vec(const u32x4& q, PT_GLOBAL u32x4* p) {
+  if (NT) __builtin_nontemporal_store(q, p); else *p = q;
+}
+
 __device__ __forceinline__ u32x4 load_vec_unaligned16(const PT_GLOBAL uint16_t* s) {
   // eight 16-bit loads: the source is only 2-byte aligned relative to the destination
   u32x4 q;
@@ -64,7 +69,8 @@ __device__ __forceinline__ u32x4 load_vec_unaligned16(const PT_GLOBAL uint16_t* 
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
-template <int DT, int DIR>
+// NTS: non-temporal stores; without them the gradient words stay in the Infinity Cache for the update (pt_grads_cached).
+template <int DT, int DIR, bool NTS>
 __global__ void __launch_bounds__(PK_THREADS)
 k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag) {
@@ -109,10 +115,10 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
       u32x4 q1 = __builtin_nontemporal_load(sv + i + PK_THREADS);
       u32x4 q2 = __builtin_nontemporal_load(sv + i + 2 * PK_THREADS);
       u32x4 q3 = __builtin_nontemporal_load(sv + i + 3 * PK_THREADS);
-      __builtin_nontemporal_store(q0, db + i);
-      __builtin_nontemporal_store(q1, db + i + PK_THREADS);
-      __builtin_nontemporal_store(q2, db + i + 2 * PK_THREADS);
-      __builtin_nontemporal_store(q3, db + i + 3 * PK_THREADS);
+      store_vec<NTS>(q0, db + i);
+      store_vec<NTS>(q1, db + i + PK_THREADS);
+      store_vec<NTS>(q2, db + i + 2 * PK_THREADS);
+      store_vec<NTS>(q3, db + i + 3 * PK_THREADS);
       if (DIR == 0) {
         accum_vec<DT>(q0, inv_scale, a0, a1, flag);
         accum_vec<DT>(q1, inv_scale, a0, a1, flag);
@@ -122,7 +128,7 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
     }
     for (; i < nvec; i += PK_THREADS) {
       u32x4 q = __builtin_nontemporal_load(sv + i);
-      __builtin_nontemporal_store(q, db + i);
+      store_vec<NTS>(q, db + i);
       if (DIR == 0) accum_vec<DT>(q, inv_scale, a0, a1, flag);
     }
   } else {
@@ -283,12 +289,11 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
   // workgroups per compute unit than with the eight that fit (4.24 against 4.96 ms for 6.7e9 elements).
   // Unused dynamic LDS (52 KiB of the unit's 160) sets that limit.  Pack itself is indifferent to it.
   const size_t lds = DIR == 1 ? 53248 : 0;
-  if (ctx->dtype == PT_BF16)
-    hipLaunchKernelGGL((k_pack<PT_BF16, DIR>), grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row),
-                       ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
-  else
-    hipLaunchKernelGGL((k_pack<PT_FP16, DIR>), grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row),
-                       ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
+  const bool bf16 = ctx->dtype == PT_BF16, nts = DIR == 1 || !pt_grads_cached(ctx);
+  auto kern = nts ? (bf16 ? k_pack<PT_BF16, DIR, true> : k_pack<PT_FP16, DIR, true>)
+                  : (bf16 ? k_pack<PT_BF16, DIR, DIR == 1> : k_pack<PT_FP16, DIR, DIR == 1>);
+  hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), ctx->d_state, plan->d_tile_sq,
+                     plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
     rc = pt_launch_chunk_reduce(ctx, plan->d_tile_sq, plan->d_tile_flag, plan->d_chunk_tile_begin, 0, ctx->C, 0, st, plan,
