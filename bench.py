@@ -242,7 +242,7 @@ def run_resident(workload, steps, warmup, fp16=False, grad_sets=3, layout="dense
         "steps": K, "warmup": warmup, "value": round(value, 1), "ms_per_step": round(ms_step, 4),
         "ms_per_step_median_of_event_pairs": round(median(step_ev_ms), 4) if step_ev_ms else None,
         "pct_of_hbm_peak": round(100.0 * value / HBM_PEAK_GBPS, 2),
-        "kernels_ms": {("accum_grads x%d+chunk_reduce" % A if A else "pack_grads+chunk_reduce"): round(mean(pack_ms), 4),
+        "kernels_ms": {("accum_grads x%d" % A if A else "pack_grads"): round(mean(pack_ms), 4),
                        "finalize": round(mean(norm_ms), 4), "adamw(+prepare)": round(mean(adamw_ms), 4)},
         "fill_GBps": round(fill_bytes / (mean(pack_ms) * 1e-3) / 1e9, 1),
         "step_report": {"norm": rep.norm, "clip_coef": rep.clip_coef, "found_inf": rep.found_inf, "step": rep.step,

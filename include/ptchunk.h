@@ -278,8 +278,8 @@ int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks, uint32_t f
  * serving loops, harnesses that forbid hipMalloc.  Computes what pt_chunk_grad_sqnorm(grad_chunks, 0,
  * n_chunks, finalize) computes - same kernels, same fixed reduction order, the same bits - without a
  * context: the block partials and per-chunk sums live in a file-scope device array of the library
- * (6.05 MiB per GPU, held until the process ends) instead of memory a context allocated.  Calls no
- * hipMalloc / hipFree and no allocating routine; enqueues three kernels on `stream` and returns.
+ * (6.1 MiB per GPU, held until the process ends) instead of memory a context allocated.  Calls no
+ * hipMalloc / hipFree and no allocating routine; enqueues two kernels on `stream` and returns.
  *   grad_arena       device: n_chunks gradient chunks of chunk_elems 16-bit words each, back to back
  *                    (chunk c starts at element c * chunk_elems); 16-byte aligned; read only
  *   dtype            PT_BF16 or PT_FP16 (how the words decode)

@@ -163,14 +163,14 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   const uint64_t* h = ctx->h_table.data() + size_t(ROW_PACK) * ctx->table_cols;
   for (uint32_t c : plan->touched)
     if (!h[c]) return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_accum_grads: chunk %u is used by the plan but its pointer is NULL", c);
+  if (take_norm && (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
   hipLaunchKernelGGL(kern, dim3(plan->n_tiles), dim3(AC_THREADS), 0, st, plan->d_tiles, pt_row(ctx, ROW_PACK),
                      ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {
-    rc = pt_launch_chunk_reduce(ctx, plan->d_tile_sq, plan->d_tile_flag, plan->d_chunk_tile_begin, 0, ctx->C, 0, st, plan,
-                                plan->n_tiles, uint32_t(plan->touched.size()));
+    rc = pt_reduce_plan(ctx, plan, st);
     if (rc != PT_OK) return rc;
     for (uint32_t c : plan->touched) ctx->chunk_fresh[c] = 1;
   }

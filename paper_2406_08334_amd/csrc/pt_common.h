@@ -74,6 +74,9 @@ struct pt_pack_plan {
   uint32_t* d_chunk_tile_begin = nullptr;  // n_chunks + 1 entries (tiles sorted by chunk)
   double* d_tile_sq = nullptr;
   uint32_t* d_tile_flag = nullptr;
+  uint32_t segs = 1;                       // reduction workgroups per chunk, for the chunk with the most tiles
+  double* d_seg_sum = nullptr;             // [chunks from the first to the last touched one * segs], if segs > 1
+  uint32_t* d_seg_flag = nullptr;
   uint64_t total_elems = 0;
   uint64_t id = 0;                         // never reused within a context (a destroyed plan's address may be)
   std::vector<uint32_t> touched;           // chunks that own at least one tile
@@ -81,16 +84,19 @@ struct pt_pack_plan {
 
 namespace pt_host { class Pool; }
 
-// A per-chunk reduction of partial sums that has been put off (see pt_norm.hip).
+// A per-chunk reduction of partial sums that has been put off (see pt_norm.hip).  seg_sum / seg_flag: room for n * segs
+// sums where a chunk has more partials than one workgroup takes (segs > 1).
 struct PtPendingReduce {
-  bool active = false;
   const double* part = nullptr;
   const uint32_t* flag = nullptr;
   const uint32_t* tile_begin = nullptr;
-  uint32_t first = 0, n = 0, per_chunk = 0;
-  hipStream_t stream = nullptr;          // where it was asked for (used if the plan goes away first)
-  const pt_pack_plan* plan = nullptr;    // owner of part / flag / tile_begin
+  uint32_t first = 0, n = 0, per_chunk = 0, segs = 1;
+  double* seg_sum = nullptr;
+  uint32_t* seg_flag = nullptr;
+  const pt_pack_plan* plan = nullptr;    // owner of part / flag / tile_begin (NULL: the context)
 };
+constexpr uint32_t PT_REDUCE_SEG = 2048;         // partial sums one workgroup adds up, eight per lane
+inline uint32_t pt_segs(uint64_t partials) { return uint32_t(partials ? (partials + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG : 1); }
 
 struct pt_ctx {
   int device = 0;
@@ -116,6 +122,10 @@ struct pt_ctx {
   uint32_t* d_chunk_flag = nullptr;     // [C]
   double* d_norm_part = nullptr;        // [C * norm_blocks]
   uint32_t* d_norm_flag = nullptr;      // [C * norm_blocks]
+  uint32_t norm_segs = 1;               // reduction workgroups per chunk of a recompute
+  double* d_norm_seg_sum = nullptr;     // [C * norm_segs], if norm_segs > 1
+  uint32_t* d_norm_seg_flag = nullptr;
+  uint32_t* d_ticket = nullptr;         // workgroups of the scalar kernel that have finished (0 between launches)
 
   // host-side step bookkeeping
   std::vector<uint64_t> chunk_packed_by;   // [C] id of the pack plan whose partial sum is the chunk's value in this step, 0 = none
@@ -123,8 +133,12 @@ struct pt_ctx {
   std::vector<uint8_t> chunk_fresh;     // [C] 1 = the chunk's sum of squares was taken in this step (since pt_step_end)
   bool norm_finalized = false;
   bool prepared = false;
-  PtPendingReduce pend_reduce;          // scalar work put off to be fused into one launch (pt_norm.hip)
+  std::vector<PtPendingReduce> pend_reduce;   // scalar work put off to be fused into one launch (pt_norm.hip), in order
   bool pend_finalize = false;
+  hipStream_t finalize_stream = nullptr;      // where the pending finalize was asked for
+  hipEvent_t ev_order = nullptr;
+  bool carry = false;                   // the norm was finalized with PT_FINALIZE_CARRY: some chunks' gradients are elsewhere
+  bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them
   pt_hparams prepared_hp{};
 
   // streamed path
@@ -160,7 +174,7 @@ struct pt_ctx {
   std::vector<uint64_t> h_nd_ranges;
 
   // host-side update: a side stream and a pinned landing buffer for the step's scalars
-  PtDevState* h_state_dev = nullptr;    // h_state as the device addresses it (the scalar kernels mirror the state there)
+  PtDevState* h_state_dev = nullptr;    // h_state as the device addresses it (the scalar kernels leave the constants there)
   hipEvent_t ev_scalar = nullptr;
   PtDevState* h_state = nullptr;
   pt_host::Pool* host_pool = nullptr;   // worker threads of the host-side update, started on first use
@@ -284,17 +298,18 @@ void pt_host_pool_destroy(pt_ctx* ctx);
 // pt_chunk_grad_sqnorm_noalloc works in; out may be NULL.  Called by pt_ctx_create, so that a process
 // with a context never pays the lookup inside a hot call.
 int pt_static_scratch_setup(void** out);
-// Sums per-block partials into per-chunk values.  uniform mode (tile_begin == NULL):
-// chunk first+i owns partials [i*per_chunk, (i+1)*per_chunk).  With a plan whose n_touched chunks and
-// n_partials partial sums are few, the reduction is put off and runs inside the launch that finalizes
-// the norm (plan == NULL: always at once).
-int pt_launch_chunk_reduce(pt_ctx* ctx, const double* part, const uint32_t* flag,
-                           const uint32_t* tile_begin, uint32_t first, uint32_t n,
-                           uint32_t per_chunk, hipStream_t stream, const pt_pack_plan* plan, uint32_t n_partials,
-                           uint32_t n_touched);
-// Launches, on `stream`, whatever scalar work of the step has been put off (per-chunk reduction, finalize).
-// Every call that reads the step's scalars or replaces what is pending goes through this first.
+// Sums partials into per-chunk values: tile_begin == NULL: chunk first+i owns partials [i*per_chunk, (i+1)*per_chunk),
+// else [tile_begin[c], tile_begin[c+1]).  Put off until the norm is finalized or read; `now`: launched on `stream` at once.
+int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream);
+// The reduction of a plan's tile sums (pack, accumulate).
+int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);
+// Launches, on `stream`, whatever scalar work of the step has been put off (per-chunk reductions, finalize).
+// Every call that reads the step's scalars goes through this first.
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream);
+// Before a kernel on `stream` that writes partial sums.
+int pt_before_partials(pt_ctx* ctx, hipStream_t stream);
 // Derives this step's update constants from `hp` if that has not happened yet - in one launch together
 // with any pending reduction and finalize.
 int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream);
+// Makes sure the prepared constants are on their way to h_state, with ev_scalar behind them.
+int pt_mirror_consts(pt_ctx* ctx, hipStream_t stream);

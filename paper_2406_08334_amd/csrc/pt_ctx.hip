@@ -95,6 +95,7 @@ static void ctx_free_all(pt_ctx* ctx) {
   pt_host_pool_destroy(ctx);
   pt_stream_release(ctx);
   if (ctx->ev_scalar) (void)hipEventDestroy(ctx->ev_scalar);
+  if (ctx->ev_order) (void)hipEventDestroy(ctx->ev_order);
   if (ctx->h_state) (void)hipHostFree(ctx->h_state);
   if (ctx->d_nd_begin) (void)hipFree(ctx->d_nd_begin);
   if (ctx->d_nd_ranges) (void)hipFree(ctx->d_nd_ranges);
@@ -104,6 +105,9 @@ static void ctx_free_all(pt_ctx* ctx) {
   if (ctx->d_chunk_flag) (void)hipFree(ctx->d_chunk_flag);
   if (ctx->d_norm_part) (void)hipFree(ctx->d_norm_part);
   if (ctx->d_norm_flag) (void)hipFree(ctx->d_norm_flag);
+  if (ctx->d_norm_seg_sum) (void)hipFree(ctx->d_norm_seg_sum);
+  if (ctx->d_norm_seg_flag) (void)hipFree(ctx->d_norm_seg_flag);
+  if (ctx->d_ticket) (void)hipFree(ctx->d_ticket);
 }
 
 static int ctx_alloc(pt_ctx* ctx, const pt_scaler_cfg* sc) {
@@ -123,7 +127,15 @@ static int ctx_alloc(pt_ctx* ctx, const pt_scaler_cfg* sc) {
   size_t np = size_t(ctx->C) * ctx->norm_blocks;
   PT_HIP(ctx, hipMalloc(&ctx->d_norm_part, np * sizeof(double)));
   PT_HIP(ctx, hipMalloc(&ctx->d_norm_flag, np * sizeof(uint32_t)));
+  ctx->norm_segs = pt_segs(ctx->norm_blocks);
+  if (ctx->norm_segs > 1) {
+    PT_HIP(ctx, hipMalloc(&ctx->d_norm_seg_sum, size_t(ctx->C) * ctx->norm_segs * sizeof(double)));
+    PT_HIP(ctx, hipMalloc(&ctx->d_norm_seg_flag, size_t(ctx->C) * ctx->norm_segs * sizeof(uint32_t)));
+  }
+  PT_HIP(ctx, hipMalloc(&ctx->d_ticket, sizeof(uint32_t)));
+  PT_HIP(ctx, hipMemset(ctx->d_ticket, 0, sizeof(uint32_t)));
   PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_scalar, hipEventDisableTiming));
+  PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_order, hipEventDisableTiming));
   PT_HIP(ctx, hipHostMalloc((void**)&ctx->h_state, sizeof(PtDevState), hipHostMallocDefault));
   std::memset(ctx->h_state, 0, sizeof(PtDevState));
   PT_HIP(ctx, hipHostGetDevicePointer((void**)&ctx->h_state_dev, ctx->h_state, 0));

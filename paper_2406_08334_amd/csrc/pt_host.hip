@@ -43,9 +43,12 @@ extern "C" int pt_chunk_host_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint3
   // bits.  Only the scalar kernels are waited for, not the bulk work queued behind them.
   int rc = pt_prepare_consts(ctx, hp, st);
   if (rc != PT_OK) return rc;
-  // ev_scalar was recorded right behind the scalar kernel of this step (pt_prepare_consts), which left a copy
-  // of the scalars in pinned host memory: waiting for that event is all it takes - no stream of the library's
-  // own, whose copy could end up behind the resident update in a shared hardware queue
+  // ev_scalar is right behind the scalar kernel of this step (pt_prepare_consts), which left the constants in pinned host
+  // memory: waiting for that event is all it takes - no stream of the library's own, whose copy could end up behind the
+  // resident update in a shared hardware queue.  A context that has shown no sign of a host part before its first host-side update gets
+  // the event here, behind whatever is queued on the stream.
+  rc = pt_mirror_consts(ctx, st);
+  if (rc != PT_OK) return rc;
   PT_HIP(ctx, hipEventSynchronize(ctx->ev_scalar));
   PtDevState hs;
   std::memcpy(&hs, ctx->h_state, sizeof hs);

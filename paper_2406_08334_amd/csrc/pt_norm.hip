@@ -11,6 +11,7 @@
 
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <mutex>
 
 namespace {
@@ -94,7 +95,7 @@ k_sqnorm(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
   uint32_t flag;
   sqnorm_block<DT>(base, S, b, 1.0 / st->loss_scale, acc, flag);
   if (threadIdx.x == 0) {
-    size_t slot = size_t(i) * gridDim.x + b;
+    size_t slot = size_t(first + i) * gridDim.x + b;
     part[slot] = acc;
     flagout[slot] = flag;
   }
@@ -147,170 +148,294 @@ k_sqnorm_f32(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
   double acc = a0 + a1;
   pt_block_sum(acc, flag);
   if (threadIdx.x == 0) {
-    size_t slot = size_t(i) * gridDim.x + b;
+    size_t slot = size_t(first + i) * gridDim.x + b;
     part[slot] = acc;
     flagout[slot] = flag;
   }
 }
 
-// One block per chunk: sums that chunk's partials (lane-strided serial sums, then
-// the fixed block tree).  tile_begin == NULL: chunk first+i owns
-// [i*per_chunk, (i+1)*per_chunk); otherwise [tile_begin[c], tile_begin[c+1]) and a
-// chunk with an empty range keeps its previous value.
-__global__ void __launch_bounds__(NB_THREADS)
-k_chunk_reduce(const double* __restrict__ part, const uint32_t* __restrict__ flag,
-               const uint32_t* __restrict__ tile_begin, uint32_t first, uint32_t per_chunk,
-               double* __restrict__ chunk_sq, uint32_t* __restrict__ chunk_flag) {
-  const uint32_t i = blockIdx.x, c = first + i;
-  uint32_t lo, hi;
-  if (tile_begin) { lo = tile_begin[c]; hi = tile_begin[c + 1]; if (lo == hi) return; }
-  else { lo = i * per_chunk; hi = lo + per_chunk; }
-  double acc = 0.0;
-  uint32_t f = 0;
-  for (uint32_t k = lo + threadIdx.x; k < hi; k += NB_THREADS) { acc += part[k]; f |= flag[k]; }
-  pt_block_sum(acc, f);
-  if (threadIdx.x == 0) { chunk_sq[c] = acc; chunk_flag[c] = f; }
-}
+// ---- the scalar work of a step in one launch ---------------------------------------------------
+//
+// Grid (segs, n): workgroup (s, i) adds up partial sums [s * PT_REDUCE_SEG, (s + 1) * PT_REDUCE_SEG) of chunk first+i
+// (lane-strided serial sums, then the fixed block tree); the workgroup that finishes last adds the segments of each chunk
+// in order, then - do_finalize - the values of all chunks in chunk order, and publishes norm and found_inf, and - do_prepare -
+// derives the nine fp32 constants of the update.  Every order is fixed: who comes last does not change a bit.
+//
+// Latency is all it costs, so the chain is kept short: a lane's eight loads are in flight together, two waves take the
+// powers of beta while the others wait for the sums, the chunk values pass through LDS, and nothing that was
+// just computed is read back.  Reduction, finalize and constants, for 15 chunks of 1024 partials: 8.8 us in two launches
+// and 5.5 us of a gap behind an event before, 7.0 us in one launch now (a kernel that does nothing takes 4.7 there); 47 of
+// 4096: 14.0 -> 10.3; 10 of 8192: 15.6 -> 8.8 us.
+constexpr int SC_THREADS = NB_THREADS + 128;     // two more waves for the powers
 
-// Sums the per-chunk values of all chunks in chunk order (single thread: C is a
-// few hundred at most) and publishes the step's scalars.
-__device__ __forceinline__ void finalize_body(const double* chunk_sq, const uint32_t* chunk_flag, uint32_t C, PtDevState* st) {
-  double t = 0.0;
-  uint32_t f = 0;
-  for (uint32_t c = 0; c < C; ++c) { t += chunk_sq[c]; f |= chunk_flag[c]; }
-  st->sqnorm = t;
-  st->norm = sqrt(t);
-  st->found_inf = f ? 1 : 0;
-  st->override_active = 0;
-}
+struct ScalarArgs {
+  PtPendingReduce r;             // r.n == 0: nothing to reduce (grid 1 x 1)
+  double* chunk_sq;
+  uint32_t* chunk_flag;
+  uint32_t C;
+  uint32_t* ticket;
+  PtDevState* st;                // NULL: the norm for a caller without a context, into out_*
+  double* out_sq_norm;
+  int32_t* out_found_inf;
+  int do_finalize, do_prepare;
+  pt_hparams hp;
+  PtDevState* mirror;            // pinned host memory that receives the constants, or NULL
+};
 
-__global__ void k_finalize(const double* chunk_sq, const uint32_t* chunk_flag, uint32_t C, PtDevState* st) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  finalize_body(chunk_sq, chunk_flag, C, st);
-}
+// Values other workgroups of the same launch have written (or will read): past this XCD's caches.
+template <class T> __device__ __forceinline__ T ld_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T> __device__ __forceinline__ void st_agent(T* p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Derives the nine fp32 constants of this update from the fp64 hyper-parameters
-// and the step's device scalars (Adam bias correction with t = applied updates
-// + 1; clip coefficient min(1, c/(norm+1e-6)); unscale by the loss scale).
-__device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& hp) {
-  const double t = double(st->step + 1);
+// The nine fp32 constants of this update from the fp64 hyper-parameters and the step's device scalars (Adam bias
+// correction with t = applied updates + 1; clip coefficient min(1, c/(norm+1e-6)); unscale by the loss scale).
+// bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
+__device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& hp, double bc1, double bc2, double norm, double loss_scale,
+                                             bool override_active, int32_t found_inf, PtDevState* mirror) {
   double clip = 1.0;
-  float gm;
-  if (st->override_active) {
-    gm = st->override_grad_mult;
+  float c[9];
+  if (override_active) {
+    c[8] = st->override_grad_mult;
   } else {
     if (hp.max_norm > 0.0) {
-      double c = hp.max_norm / (st->norm + 1e-6);
-      clip = c < 1.0 ? c : 1.0;
+      const double q = hp.max_norm / (norm + 1e-6);
+      clip = q < 1.0 ? q : 1.0;
     }
-    gm = float(clip / st->loss_scale);
+    c[8] = float(clip / loss_scale);
   }
+  c[0] = float(hp.beta1);
+  c[1] = float(hp.beta2);
+  c[2] = float(1.0 - hp.beta1);
+  c[3] = float(1.0 - hp.beta2);
+  c[4] = float(1.0 - hp.lr * hp.weight_decay);
+  c[5] = float(hp.lr / bc1);
+  c[6] = float(1.0 / sqrt(bc2));
+  c[7] = float(hp.eps);
   st->clip_coef = clip;
-  st->c[0] = float(hp.beta1);
-  st->c[1] = float(hp.beta2);
-  st->c[2] = float(1.0 - hp.beta1);
-  st->c[3] = float(1.0 - hp.beta2);
-  st->c[4] = float(1.0 - hp.lr * hp.weight_decay);
-  st->c[5] = float(hp.lr / (1.0 - pow(hp.beta1, t)));
-  st->c[6] = float(1.0 / sqrt(1.0 - pow(hp.beta2, t)));
-  st->c[7] = float(hp.eps);
-  st->c[8] = gm;
-  st->skip = st->found_inf ? 1 : 0;
-}
-
-// `mirror`: a copy of the step's scalars in pinned host memory that the device addresses directly.  The
-// host-side update reads its constants there after waiting for the event behind this kernel - no stream, no
-// copy, nothing that could queue up behind the resident update.
-__global__ void k_prepare(PtDevState* st, pt_hparams hp, PtDevState* mirror) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  prepare_body(st, hp);
-  *mirror = *st;
-  __threadfence_system();
-}
-
-// The scalar work of a step in ONE launch, for small states where launches are what a step costs:
-// one block walks the chunks one after the other - each chunk's partial sums reduced exactly as
-// k_chunk_reduce does it - then its thread 0 sums the chunks (k_finalize) and derives the update's
-// constants (k_prepare).  Same operations in the same order as the three separate kernels.
-//   n_reduce == 0: no per-chunk reduction (already done);  do_finalize == 0: the norm is already final.
-__global__ void __launch_bounds__(NB_THREADS)
-k_reduce_finalize_prepare(const double* __restrict__ part, const uint32_t* __restrict__ flag,
-                          const uint32_t* __restrict__ tile_begin, uint32_t first, uint32_t n_reduce, uint32_t per_chunk,
-                          double* chunk_sq, uint32_t* chunk_flag, uint32_t C, PtDevState* st, pt_hparams hp,
-                          int do_finalize, int do_prepare, PtDevState* mirror) {
-  for (uint32_t i = 0; i < n_reduce; ++i) {
-    const uint32_t c = first + i;
-    uint32_t lo, hi;
-    if (tile_begin) { lo = tile_begin[c]; hi = tile_begin[c + 1]; if (lo == hi) continue; }
-    else { lo = i * per_chunk; hi = lo + per_chunk; }
-    double acc = 0.0;
-    uint32_t f = 0;
-    for (uint32_t k = lo + threadIdx.x; k < hi; k += NB_THREADS) { acc += part[k]; f |= flag[k]; }
-    pt_block_sum(acc, f);
-    if (threadIdx.x == 0) { chunk_sq[c] = acc; chunk_flag[c] = f; }
-    __syncthreads();                 // the reduction's LDS slots are reused by the next chunk
-  }
-  if (threadIdx.x != 0) return;
-  // thread 0 wrote every per-chunk value of this launch itself; the others come from earlier kernels
-  if (do_finalize) finalize_body(chunk_sq, chunk_flag, C, st);
-  if (do_prepare) {
-    prepare_body(st, hp);
-    *mirror = *st;
+  const int32_t skip = found_inf ? 1 : 0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) st->c[k] = c[k];
+  st->skip = skip;
+  // The host-side update reads its constants there after waiting for the event behind this kernel - no stream, no copy,
+  // nothing that could queue up behind the resident update.
+  if (mirror) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) mirror->c[k] = c[k];
+    mirror->skip = skip;
     __threadfence_system();
   }
 }
 
+__global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
+  __shared__ double s_sum[NB_THREADS / 64], s_val[NB_THREADS], s_bc[2];
+  __shared__ uint32_t s_flag[NB_THREADS / 64], s_f[NB_THREADS], s_last;
+  const PtPendingReduce& r = a.r;
+  const uint32_t tid = threadIdx.x, c = r.first + blockIdx.y;
+  uint32_t lo = 0, hi = 0;
+  if (r.n) {
+    if (r.tile_begin) { lo = r.tile_begin[c]; hi = r.tile_begin[c + 1]; }
+    else { lo = blockIdx.y * r.per_chunk; hi = lo + r.per_chunk; }
+  }
+  const uint32_t own = hi - lo;                  // partials of the chunk; the segment's are [lo, hi) from here on
+  lo = min(hi, lo + blockIdx.x * PT_REDUCE_SEG);
+  hi = min(hi, lo + PT_REDUCE_SEG);
+  double acc = 0.0;
+  uint32_t f = 0;
+  if (tid < NB_THREADS) {
+    constexpr int D = PT_REDUCE_SEG / NB_THREADS;
+    double x[D];
+    uint32_t y[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      const uint32_t k = lo + tid + j * NB_THREADS;
+      x[j] = k < hi ? r.part[k] : 0.0;
+      y[j] = k < hi ? r.flag[k] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) { acc += x[j]; f |= y[j]; }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+    f = __any(f != 0) ? 1u : 0u;
+    if ((tid & 63) == 0) { s_sum[tid >> 6] = acc; s_flag[tid >> 6] = f; }
+  } else if (a.do_prepare && (tid & 63) == 0) {
+    const double t = double(a.st->step + 1);
+    s_bc[(tid - NB_THREADS) >> 6] = 1.0 - pow(tid == NB_THREADS ? a.hp.beta1 : a.hp.beta2, t);
+  }
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int i = 1; i < NB_THREADS / 64; ++i) { acc += s_sum[i]; f |= s_flag[i]; }
+    if (own && lo < hi) {
+      if (r.segs > 1) {
+        st_agent(r.seg_sum + size_t(blockIdx.y) * r.segs + blockIdx.x, acc);
+        st_agent(r.seg_flag + size_t(blockIdx.y) * r.segs + blockIdx.x, f);
+      } else {
+        st_agent(a.chunk_sq + c, acc);
+        st_agent(a.chunk_flag + c, f);
+      }
+    }
+    const uint32_t total = gridDim.x * gridDim.y;
+    if (total > 1) {
+      __threadfence();
+      s_last = atomicAdd(a.ticket, 1u) == total - 1 ? 1u : 0u;
+    } else {
+      s_last = 1u;
+    }
+  }
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  if (tid == 0) st_agent(a.ticket, 0u);
+  if (r.segs > 1) {
+    for (uint32_t i = tid; i < r.n; i += SC_THREADS) {
+      const uint32_t cc = r.first + i, have = r.tile_begin ? r.tile_begin[cc + 1] - r.tile_begin[cc] : r.per_chunk;
+      if (!have) continue;
+      const uint32_t ns = (have + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG;
+      double t = 0.0;
+      uint32_t g = 0;
+      for (uint32_t k = 0; k < ns; ++k) {
+        t += ld_agent(r.seg_sum + size_t(i) * r.segs + k);
+        g |= ld_agent(r.seg_flag + size_t(i) * r.segs + k);
+      }
+      st_agent(a.chunk_sq + cc, t);
+      st_agent(a.chunk_flag + cc, g);
+    }
+    __threadfence();
+    __syncthreads();
+  }
+  double sq = 0.0, norm = 0.0;
+  uint32_t inf = 0;
+  if (a.do_finalize) {
+    for (uint32_t base = 0; base < a.C; base += NB_THREADS) {
+      if (tid < NB_THREADS && base + tid < a.C) {
+        s_val[tid] = ld_agent(a.chunk_sq + base + tid);
+        s_f[tid] = ld_agent(a.chunk_flag + base + tid);
+      }
+      __syncthreads();
+      if (tid == 0) {
+        const uint32_t k1 = min(uint32_t(NB_THREADS), a.C - base);
+        for (uint32_t k = 0; k < k1; ++k) { sq += s_val[k]; inf |= s_f[k]; }
+      }
+      __syncthreads();
+    }
+  }
+  if (tid != 0) return;
+  if (a.do_finalize) {
+    norm = sqrt(sq);
+    if (a.st) {
+      a.st->sqnorm = sq;
+      a.st->norm = norm;
+      a.st->found_inf = inf ? 1 : 0;
+      a.st->override_active = 0;
+    } else {
+      a.out_sq_norm[0] = sq;
+      a.out_sq_norm[1] = norm;
+      *a.out_found_inf = inf ? 1 : 0;
+    }
+  }
+  if (a.do_prepare) {
+    if (a.do_finalize) prepare_body(a.st, a.hp, s_bc[0], s_bc[1], norm, a.st->loss_scale, false, int32_t(inf), a.mirror);
+    else prepare_body(a.st, a.hp, s_bc[0], s_bc[1], a.st->norm, a.st->loss_scale, a.st->override_active != 0, a.st->found_inf, a.mirror);
+  }
+}
+
+// The constants of a prepared step into pinned host memory, for a host-side update nobody had announced.
+__global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
+  if (threadIdx.x < 9) mirror->c[threadIdx.x] = st->c[threadIdx.x];
+  if (threadIdx.x == 9) mirror->skip = st->skip;
+  __threadfence_system();
+}
+
 }  // namespace
 
-// ---- scalar work of a step: launched at once, or deferred and fused -------------------------
+// ---- scalar work of a step: put off and fused -----------------------------------------------
 //
-// A step's scalar kernels (per-chunk reduction of the partial sums, finalize, prepare) are tiny;
-// for a small state their launches are most of the step.  So the finalize is always deferred to
-// the first call that needs its result - normally the update, which then derives its constants in
-// the same launch - and the per-chunk reduction of a pack / accumulate plan is deferred with it
-// when the plan is small enough for one block to walk (PT_FUSE_MAX_CHUNKS chunks,
-// PT_FUSE_MAX_PARTIALS partial sums).  Every call that reads or replaces what is pending flushes it
-// first (pt_flush_pending): results and their order are those of the separate kernels.
+// The reductions of partial sums and the finalize are put off to the first call that needs the result - normally the update,
+// which then derives its constants in the same launch.  They wait in order (a later reduction of a chunk replaces an
+// earlier one) and run on the stream of the call that needs them, which is ordered behind the packs anyway.
+// A plan captured into a graph is different: a replay puts nothing off, and what the graph does not hold would not
+// happen.  Reductions that are captured are launched at once, except for small plans (PT_FUSE_MAX_*), whose
+// capture has always had to hold the finalize too.
 
 constexpr uint32_t PT_FUSE_MAX_CHUNKS = 8;
 constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 
-static int launch_reduce_now(pt_ctx* ctx, const PtPendingReduce& r, hipStream_t stream) {
-  if (r.n == 0) return PT_OK;
-  hipLaunchKernelGGL(k_chunk_reduce, dim3(r.n), dim3(NB_THREADS), 0, stream, r.part, r.flag, r.tile_begin,
-                     r.first, r.per_chunk, ctx->d_chunk_sq, ctx->d_chunk_flag);
-  PT_LAUNCH_CHECK(ctx, "k_chunk_reduce");
+static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
+  ScalarArgs a{};
+  if (r) a.r = *r;
+  a.chunk_sq = ctx->d_chunk_sq; a.chunk_flag = ctx->d_chunk_flag; a.C = ctx->C; a.ticket = ctx->d_ticket; a.st = ctx->d_state;
+  a.do_finalize = finalize ? 1 : 0;
+  a.do_prepare = hp ? 1 : 0;
+  if (hp) a.hp = *hp;
+  a.mirror = mirror;
+  hipLaunchKernelGGL(k_scalars, dim3(a.r.segs, r ? std::max(1u, r->n) : 1u), dim3(SC_THREADS), 0, stream, a);
+  PT_LAUNCH_CHECK(ctx, "k_scalars");
+  return PT_OK;
+}
+
+// Everything put off, the constants of `hp` behind it if there are any: the last reduction shares its launch with the
+// finalize and the constants, earlier ones (several plans in a step) have launches of their own.
+static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
+  const size_t n = ctx->pend_reduce.size();
+  for (size_t k = 0; k + 1 < n; ++k) {
+    const int rc = launch_scalars(ctx, &ctx->pend_reduce[k], false, nullptr, nullptr, stream);
+    if (rc != PT_OK) return rc;
+  }
+  const int rc = launch_scalars(ctx, n ? &ctx->pend_reduce[n - 1] : nullptr, ctx->pend_finalize, hp, mirror, stream);
+  if (rc != PT_OK) return rc;
+  ctx->pend_reduce.clear();
+  ctx->pend_finalize = false;
   return PT_OK;
 }
 
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream) {
-  if (ctx->pend_reduce.active) {
-    ctx->pend_reduce.active = false;
-    int rc = launch_reduce_now(ctx, ctx->pend_reduce, stream);
-    if (rc != PT_OK) return rc;
-  }
-  if (ctx->pend_finalize) {
-    ctx->pend_finalize = false;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, stream, ctx->d_chunk_sq, ctx->d_chunk_flag, ctx->C, ctx->d_state);
-    PT_LAUNCH_CHECK(ctx, "k_finalize");
-  }
+  if (ctx->pend_reduce.empty() && !ctx->pend_finalize) return PT_OK;
+  return launch_pending(ctx, nullptr, nullptr, stream);
+}
+
+// A call is about to write partial sums: a finalize that is still waiting takes the old ones first, on its own stream.
+int pt_before_partials(pt_ctx* ctx, hipStream_t stream) {
+  if (!ctx->pend_finalize) return PT_OK;
+  const hipStream_t own = ctx->finalize_stream;
+  const int rc = pt_flush_pending(ctx, own);
+  if (rc != PT_OK || own == stream) return rc;
+  PT_HIP(ctx, hipEventRecord(ctx->ev_order, own));
+  PT_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_order, 0));
   return PT_OK;
 }
 
-int pt_launch_chunk_reduce(pt_ctx* ctx, const double* part, const uint32_t* flag,
-                           const uint32_t* tile_begin, uint32_t first, uint32_t n,
-                           uint32_t per_chunk, hipStream_t stream, const pt_pack_plan* plan, uint32_t n_partials,
-                           uint32_t n_touched) {
-  if (n == 0) return PT_OK;
-  // whatever is pending comes first: a later reduction of the same chunk replaces an earlier one
-  int rc = pt_flush_pending(ctx, stream);
-  if (rc != PT_OK) return rc;
-  PtPendingReduce r{true, part, flag, tile_begin, first, n, per_chunk, stream, plan};
-  if (plan && n_touched <= PT_FUSE_MAX_CHUNKS && n <= 64 && n_partials <= PT_FUSE_MAX_PARTIALS) {
-    ctx->pend_reduce = r;            // runs inside the launch that finalizes the norm
-    return PT_OK;
+static bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cs != hipStreamCaptureStatusNone;
+}
+
+int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream) {
+  if (r.n == 0) return PT_OK;
+  if (now) {
+    // whatever is pending comes first: a later reduction of the same chunk replaces an earlier one
+    const int rc = pt_flush_pending(ctx, stream);
+    return rc != PT_OK ? rc : launch_scalars(ctx, &r, false, nullptr, nullptr, stream);
   }
-  return launch_reduce_now(ctx, r, stream);
+  return pt_guarded(ctx, "reduction of the partial sums", [&] {
+    // the same partial sums again: taken once, with the values they will then hold
+    if (!ctx->pend_reduce.empty()) {
+      const PtPendingReduce& l = ctx->pend_reduce.back();
+      if (l.plan == r.plan && l.part == r.part && l.first == r.first && l.n == r.n) return int(PT_OK);
+    }
+    ctx->pend_reduce.push_back(r);
+    return int(PT_OK);
+  });
+}
+
+int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
+  if (plan->touched.empty()) return PT_OK;
+  PtPendingReduce r;
+  r.part = plan->d_tile_sq; r.flag = plan->d_tile_flag; r.tile_begin = plan->d_chunk_tile_begin;
+  r.first = plan->touched.front(); r.n = plan->touched.back() - r.first + 1;
+  r.segs = plan->segs; r.seg_sum = plan->d_seg_sum; r.seg_flag = plan->d_seg_flag;
+  r.plan = plan;
+  const bool small = plan->touched.size() <= PT_FUSE_MAX_CHUNKS && ctx->C <= 64 && plan->n_tiles <= PT_FUSE_MAX_PARTIALS;
+  return pt_add_chunk_reduce(ctx, r, !small && capturing(stream), stream);
 }
 
 int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream) {
@@ -319,23 +444,27 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream) {
     if (ctx->stream_pending)
       return pt_fail(ctx, PT_ERR_STATE, "hyper-parameters changed while a streamed update of this step is in flight");
   }
-  if (ctx->pend_reduce.active || ctx->pend_finalize) {
-    const PtPendingReduce r = ctx->pend_reduce;
-    const bool red = r.active;
-    hipLaunchKernelGGL(k_reduce_finalize_prepare, dim3(1), dim3(NB_THREADS), 0, stream, red ? r.part : nullptr,
-                       red ? r.flag : nullptr, red ? r.tile_begin : nullptr, red ? r.first : 0u, red ? r.n : 0u,
-                       red ? r.per_chunk : 0u, ctx->d_chunk_sq, ctx->d_chunk_flag, ctx->C, ctx->d_state, *hp,
-                       ctx->pend_finalize ? 1 : 0, 1, ctx->h_state_dev);
-    PT_LAUNCH_CHECK(ctx, "k_reduce_finalize_prepare");
-    ctx->pend_reduce.active = false;
-    ctx->pend_finalize = false;
-  } else {
-    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(1), 0, stream, ctx->d_state, *hp, ctx->h_state_dev);
-    PT_LAUNCH_CHECK(ctx, "k_prepare");
+  // The event that lets a host-side update read the constants early costs the update behind it 5 us: recorded where such a
+  // call is likely - there was one before, or chunks carry their norms and no chunk buffers are reserved.
+  const bool mirror = ctx->host_pool != nullptr || (ctx->carry && !ctx->n_slots);
+  ctx->mirrored = false;
+  const int rc = launch_pending(ctx, hp, mirror ? ctx->h_state_dev : nullptr, stream);
+  if (rc != PT_OK) return rc;
+  if (mirror) {
+    PT_HIP(ctx, hipEventRecord(ctx->ev_scalar, stream));
+    ctx->mirrored = true;
   }
-  PT_HIP(ctx, hipEventRecord(ctx->ev_scalar, stream));   // lets the host-side update read the scalars early
   ctx->prepared = true;
   ctx->prepared_hp = *hp;
+  return PT_OK;
+}
+
+int pt_mirror_consts(pt_ctx* ctx, hipStream_t stream) {
+  if (ctx->mirrored) return PT_OK;
+  hipLaunchKernelGGL(k_mirror, dim3(1), dim3(64), 0, stream, ctx->d_state, ctx->h_state_dev);
+  PT_LAUNCH_CHECK(ctx, "k_mirror");
+  PT_HIP(ctx, hipEventRecord(ctx->ev_scalar, stream));
+  ctx->mirrored = true;
   return PT_OK;
 }
 
@@ -350,7 +479,7 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_grad_sqnorm: finalize must be 0, PT_FINALIZE_STRICT or PT_FINALIZE_CARRY");
   if (grad_chunks && n_chunks) {
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st, nullptr);
-    if (rc != PT_OK) return rc;
+    if (rc != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
     dim3 grid(ctx->norm_blocks, n_chunks);
     if (ctx->grad_f32)
       hipLaunchKernelGGL(k_sqnorm_f32, grid, dim3(NB_THREADS), 0, st, pt_row(ctx, ROW_PACK), first_chunk,
@@ -362,8 +491,16 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
       hipLaunchKernelGGL(k_sqnorm<PT_FP16>, grid, dim3(NB_THREADS), 0, st, pt_row(ctx, ROW_PACK), first_chunk,
                          ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     PT_LAUNCH_CHECK(ctx, "k_sqnorm");
-    int rc2 = pt_launch_chunk_reduce(ctx, ctx->d_norm_part, ctx->d_norm_flag, nullptr, first_chunk, n_chunks,
-                                     ctx->norm_blocks, st, nullptr, 0, n_chunks);
+    // each chunk has its own partials, so that several recomputes of one step can wait for the finalize together
+    PtPendingReduce r;
+    r.part = ctx->d_norm_part + size_t(first_chunk) * ctx->norm_blocks;
+    r.flag = ctx->d_norm_flag + size_t(first_chunk) * ctx->norm_blocks;
+    r.first = first_chunk; r.n = n_chunks; r.per_chunk = ctx->norm_blocks; r.segs = ctx->norm_segs;
+    if (r.segs > 1) {
+      r.seg_sum = ctx->d_norm_seg_sum + size_t(first_chunk) * r.segs;
+      r.seg_flag = ctx->d_norm_seg_flag + size_t(first_chunk) * r.segs;
+    }
+    int rc2 = pt_add_chunk_reduce(ctx, r, capturing(st), st);
     if (rc2 != PT_OK) return rc2;
     // a recompute covers the whole chunk: whatever plan packed it, its value is complete now
     for (uint32_t c = first_chunk; c < first_chunk + n_chunks; ++c) { ctx->chunk_fresh[c] = 1; ctx->chunk_packed_by[c] = 0; }
@@ -382,6 +519,8 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
     // The sum over the chunks runs with the first call that needs it: the update (in the launch that
     // derives its constants), a read-back, or pt_step_end.
     ctx->pend_finalize = true;
+    ctx->finalize_stream = st;
+    ctx->carry = finalize == PT_FINALIZE_CARRY;
     ctx->norm_finalized = true;
     ctx->prepared = false;
   }
@@ -399,16 +538,22 @@ constexpr uint32_t PT_STATIC_MAX_PARTIALS = 1u << 19;   // blocks of PT_NORM_BLO
 constexpr uint32_t PT_STATIC_MAX_CHUNKS = 4096;
 constexpr int PT_STATIC_MAX_DEVICES = 64;
 
+// workgroups of the reduction: n * ceil(per_chunk / PT_REDUCE_SEG) <= n + partials / PT_REDUCE_SEG
+constexpr uint32_t PT_STATIC_MAX_SEGS = PT_STATIC_MAX_CHUNKS + PT_STATIC_MAX_PARTIALS / PT_REDUCE_SEG;
+
 struct PtStaticScratch {
   double part[PT_STATIC_MAX_PARTIALS];
-  uint32_t flag[PT_STATIC_MAX_PARTIALS];
   double chunk_sq[PT_STATIC_MAX_CHUNKS];
+  double seg_sum[PT_STATIC_MAX_SEGS];
+  uint32_t flag[PT_STATIC_MAX_PARTIALS];
   uint32_t chunk_flag[PT_STATIC_MAX_CHUNKS];
+  uint32_t seg_flag[PT_STATIC_MAX_SEGS];
+  uint32_t ticket;
 };
 
 }  // namespace
 
-// 6.05 MiB per GPU the library runs on, held until the process ends.  In host code this name is only a
+// 6.1 MiB per GPU the library runs on, held until the process ends.  In host code this name is only a
 // stand-in for the symbol: the device address comes from hipGetSymbolAddress (scratch_of_current_device).
 static __device__ __align__(256) unsigned char scratch[sizeof(PtStaticScratch)];
 
@@ -418,29 +563,18 @@ namespace {
 template <int DT>
 __global__ void __launch_bounds__(NB_THREADS)
 k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, double* __restrict__ part,
-               uint32_t* __restrict__ flagout) {
+               uint32_t* __restrict__ flagout, uint32_t* __restrict__ ticket) {
   const uint32_t b = blockIdx.x, i = blockIdx.y;
   const PT_GLOBAL u32x4* base = (const PT_GLOBAL u32x4*)((uint64_t)(uintptr_t)arena + 2ull * S * i);
   double acc;
   uint32_t flag;
   sqnorm_block<DT>(base, S, b, 1.0 / loss_scale, acc, flag);
   if (threadIdx.x == 0) {
+    if (b == 0 && i == 0) *ticket = 0;       // whatever calls that overlapped in time have left there
     size_t slot = size_t(i) * gridDim.x + b;
     part[slot] = acc;
     flagout[slot] = flag;
   }
-}
-
-// As k_finalize, into the caller's outputs.
-__global__ void k_finalize_out(const double* __restrict__ chunk_sq, const uint32_t* __restrict__ chunk_flag,
-                               uint32_t C, double* __restrict__ out_sq_norm, int32_t* __restrict__ out_found_inf) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double t = 0.0;
-  uint32_t f = 0;
-  for (uint32_t c = 0; c < C; ++c) { t += chunk_sq[c]; f |= chunk_flag[c]; }
-  out_sq_norm[0] = t;
-  out_sq_norm[1] = sqrt(t);
-  *out_found_inf = f ? 1 : 0;
 }
 
 std::mutex g_scratch_mutex;
@@ -503,16 +637,18 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   // earlier, larger call are never read.
   if (dtype == PT_BF16)
     hipLaunchKernelGGL(k_sqnorm_arena<PT_BF16>, grid, dim3(NB_THREADS), 0, st, grad_arena, chunk_elems, loss_scale,
-                       sc->part, sc->flag);
+                       sc->part, sc->flag, &sc->ticket);
   else
     hipLaunchKernelGGL(k_sqnorm_arena<PT_FP16>, grid, dim3(NB_THREADS), 0, st, grad_arena, chunk_elems, loss_scale,
-                       sc->part, sc->flag);
+                       sc->part, sc->flag, &sc->ticket);
   if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_sqnorm_arena failed");
-  hipLaunchKernelGGL(k_chunk_reduce, dim3(n_chunks), dim3(NB_THREADS), 0, st, sc->part, sc->flag,
-                     (const uint32_t*)nullptr, 0u, (uint32_t)blocks_per_chunk, sc->chunk_sq, sc->chunk_flag);
-  if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_chunk_reduce failed");
-  hipLaunchKernelGGL(k_finalize_out, dim3(1), dim3(64), 0, st, sc->chunk_sq, sc->chunk_flag, n_chunks, out_sqnorm_norm,
-                     out_found_inf);
-  if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_finalize_out failed");
+  ScalarArgs a{};
+  a.r.part = sc->part; a.r.flag = sc->flag; a.r.n = n_chunks; a.r.per_chunk = (uint32_t)blocks_per_chunk;
+  a.r.segs = pt_segs(blocks_per_chunk); a.r.seg_sum = sc->seg_sum; a.r.seg_flag = sc->seg_flag;
+  a.chunk_sq = sc->chunk_sq; a.chunk_flag = sc->chunk_flag; a.C = n_chunks; a.ticket = &sc->ticket;
+  a.out_sq_norm = out_sqnorm_norm; a.out_found_inf = out_found_inf;
+  a.do_finalize = 1;
+  hipLaunchKernelGGL(k_scalars, dim3(a.r.segs, n_chunks), dim3(SC_THREADS), 0, st, a);
+  if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_scalars failed");
   return PT_OK;
 }

@@ -158,6 +158,8 @@ static void plan_free(pt_pack_plan* p) {
   if (p->d_chunk_tile_begin) (void)hipFree(p->d_chunk_tile_begin);
   if (p->d_tile_sq) (void)hipFree(p->d_tile_sq);
   if (p->d_tile_flag) (void)hipFree(p->d_tile_flag);
+  if (p->d_seg_sum) (void)hipFree(p->d_seg_sum);
+  if (p->d_seg_flag) (void)hipFree(p->d_seg_flag);
 }
 
 static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_pack_plan** out);
@@ -225,11 +227,14 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   std::unique_ptr<pt_pack_plan> hold(p);            // freed on every early return and on an exception
   p->ctx = ctx; p->n_tiles = uint32_t(tiles.size()); p->total_elems = total;
   p->id = ++ctx->plan_ids;
+  uint32_t most = 0;
   for (uint32_t c = 0; c < ctx->C; ++c)
-    if (begin[c + 1] > begin[c]) p->touched.push_back(c);
+    if (begin[c + 1] > begin[c]) { p->touched.push_back(c); most = std::max(most, begin[c + 1] - begin[c]); }
+  p->segs = pt_segs(most);
   auto bail = [&](hipError_t e, const char* what) {
     plan_free(p);
     p->d_tiles = nullptr; p->d_chunk_tile_begin = nullptr; p->d_tile_sq = nullptr; p->d_tile_flag = nullptr;
+    p->d_seg_sum = nullptr; p->d_seg_flag = nullptr;
     return pt_fail(ctx, PT_ERR_HIP, "pt_pack_plan_create: %s failed: %s", what, hipGetErrorString(e));
   };
   hipError_t e;
@@ -238,6 +243,11 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   if ((e = hipMalloc(&p->d_chunk_tile_begin, begin.size() * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(begin)");
   if ((e = hipMalloc(&p->d_tile_sq, nt * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(tile_sq)");
   if ((e = hipMalloc(&p->d_tile_flag, nt * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(tile_flag)");
+  if (p->segs > 1) {
+    const size_t ns = size_t(p->touched.back() - p->touched.front() + 1) * p->segs;
+    if ((e = hipMalloc(&p->d_seg_sum, ns * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(seg_sum)");
+    if ((e = hipMalloc(&p->d_seg_flag, ns * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(seg_flag)");
+  }
   if (!tiles.empty() &&
       (e = hipMemcpy(p->d_tiles, tiles.data(), tiles.size() * sizeof(PtTile), hipMemcpyHostToDevice)) != hipSuccess)
     return bail(e, "hipMemcpy(tiles)");
@@ -249,10 +259,16 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
 
 extern "C" int pt_pack_plan_destroy(pt_pack_plan* plan) {
   if (!plan) return PT_OK;
-  // a reduction of this plan's partial sums that was put off runs now, before they are freed
-  if (plan->ctx && plan->ctx->pend_reduce.active && plan->ctx->pend_reduce.plan == plan)
-    (void)pt_flush_pending(plan->ctx, plan->ctx->pend_reduce.stream);
   (void)hipDeviceSynchronize();
+  // a reduction of this plan's partial sums that was put off runs now, before they are freed (the device is idle: any
+  // stream will do, and the one of the pack may be gone)
+  if (plan->ctx)
+    for (const PtPendingReduce& r : plan->ctx->pend_reduce)
+      if (r.plan == plan) {
+        (void)pt_flush_pending(plan->ctx, nullptr);
+        (void)hipDeviceSynchronize();
+        break;
+      }
   if (plan->ctx)      // a plan that no longer exists does not stand in another plan's way
     for (uint32_t c : plan->touched)
       if (plan->ctx->chunk_packed_by[c] == plan->id) plan->ctx->chunk_packed_by[c] = 0;
@@ -283,6 +299,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
         return pt_fail(ctx, PT_ERR_STATE, "%s: chunk %u already holds the gradients of another plan of this step; its sum of "
                        "squares would be replaced, not added to - pack a chunk with one plan per step (or recompute the "
                        "norm from the chunks with pt_chunk_grad_sqnorm(grad_chunks, ...) before packing again)", who, c);
+    if ((rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
   dim3 grid(plan->n_tiles);
   // The inverse copy has no arithmetic to pace it; measured on MI355X it runs 15 % faster with three
@@ -296,8 +313,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
                      plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
-    rc = pt_launch_chunk_reduce(ctx, plan->d_tile_sq, plan->d_tile_flag, plan->d_chunk_tile_begin, 0, ctx->C, 0, st, plan,
-                                plan->n_tiles, uint32_t(plan->touched.size()));
+    rc = pt_reduce_plan(ctx, plan, st);
     if (rc != PT_OK) return rc;
     for (uint32_t c : plan->touched) { ctx->chunk_fresh[c] = 1; ctx->chunk_packed_by[c] = plan->id; }
   }

@@ -311,3 +311,97 @@ def test_streamed_update_by_the_kind_of_host_memory(dtype, grad_fp32, S, n_host,
                 assert torch.equal(host[k][c].view(bits), arenas[k][c].cpu().view(bits)), (k, c)
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("tiles", [1, 255, 2048, 2049, 4097])        # one workgroup's lanes, one workgroup, segments
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("inf", [False, True])
+def test_norm_of_many_partial_sums(tiles, dtype, inf):
+    """The sum over a chunk's partials in one workgroup or in segments, several plans of one step put off together, from
+    two streams: against the sum in 64 bits.  Squares of 16-bit words are exact there and every partial is a sum of
+    non-negative terms, so n terms in any order are within n * 2^-53 of each other."""
+    S = max(8, (tiles - 1) * 1024 + 8)
+    C = 3
+    ctx = B.pt_ctx_create(B.PT_BF16 if dtype == torch.bfloat16 else B.PT_FP16, S, C, None)
+    plans = []
+    try:
+        B.pt_ctx_set_option(ctx, "pack_tile_elems", 1024)
+        src = torch.empty(C, S, dtype=dtype, device="cuda")
+        synth.normal_16(synth.SEED_GRADS, 1, 0, 0, C * S, 1e-2, dtype, "cuda", out=src.view(-1))
+        if inf:
+            src[1, S - 1] = float("inf")
+        dst = torch.zeros(C, S, dtype=dtype, device="cuda")
+        plans = [B.pt_pack_plan_create(ctx, [B.pt_segment(src[c].data_ptr(), 0, S, 0, c, c) for c in cs]) for cs in ((0, 2), (1,))]
+        rows = [dst[c] for c in range(C)]
+        side = torch.cuda.Stream()
+        torch.cuda.synchronize()
+
+        def want():
+            return float(src.double().square().sum())
+
+        def check(rep):
+            assert rep.found_inf == int(inf)
+            assert inf or abs(rep.sqnorm - want()) <= C * S * 2.0 ** -53 * want()
+        B.pt_chunk_pack_grads(ctx, plans[0], rows)
+        B.pt_chunk_pack_grads(ctx, plans[1], rows, side)
+        torch.cuda.current_stream().wait_stream(side)
+        B.pt_chunk_grad_sqnorm(ctx, None, 0, C, True)
+        check(B.pt_step_report_read(ctx))
+        assert torch.equal(dst.view(torch.int16), src.view(torch.int16))
+        B.pt_step_end(ctx)
+        # a finalize that waits takes the sums as they were when it was asked for
+        old = want()
+        for k in range(2):
+            B.pt_chunk_pack_grads(ctx, plans[k], rows)
+        B.pt_chunk_grad_sqnorm(ctx, None, 0, C, True)
+        src[0] *= 2
+        side.wait_stream(torch.cuda.current_stream())
+        B.pt_chunk_pack_grads(ctx, plans[0], rows, side)
+        torch.cuda.current_stream().wait_stream(side)
+        # the report reads what the finalize published: the pack that came after it is not in the norm
+        rep = B.pt_step_report_read(ctx)
+        assert rep.found_inf == int(inf) and (inf or abs(rep.sqnorm - old) <= C * S * 2.0 ** -53 * old)
+        B.pt_step_end(ctx)
+        # recomputed from the chunks, in two calls that are put off together
+        B.pt_chunk_grad_sqnorm(ctx, rows, 0, 2, False)
+        B.pt_chunk_grad_sqnorm(ctx, rows, 2, 1, True)
+        check(B.pt_step_report_read(ctx))
+        B.pt_step_end(ctx)
+    finally:
+        torch.cuda.synchronize()
+        for p in plans:
+            B.pt_pack_plan_destroy(p)
+        B.pt_ctx_destroy(ctx)
+
+
+def test_plan_destroyed_before_its_partial_sums_were_read():
+    """The sums of a plan that is destroyed before the norm is finalized still enter it."""
+    st = ChunkedState([5000, 3000], 4096)
+    try:
+        st.set_grads(1, std=1e-2)
+        st.pack()
+        B.pt_pack_plan_destroy(st.plan)
+        st.plan = B.pt_pack_plan_create(st.ctx, st.segs)
+        st.norm()
+        want = float(st.grad_src.double().square().sum())
+        assert abs(st.report().sqnorm - want) <= 8000 * 2.0 ** -53 * want
+    finally:
+        st.close()
+
+
+def test_norm_without_a_context_over_a_chunk_of_several_segments():
+    """More than 2048 blocks of 32768 elements in a chunk: the same bits as the context's recompute."""
+    S = 2048 * 32768 + 8
+    g = torch.empty(S, dtype=torch.bfloat16, device="cuda")
+    synth.normal_16(synth.SEED_GRADS, 1, 0, 0, S, 1e-3, torch.bfloat16, "cuda", out=g)
+    ctx = B.pt_ctx_create(B.PT_BF16, S, 1, None)
+    try:
+        B.pt_chunk_grad_sqnorm(ctx, [g], 0, 1, True)
+        rep = B.pt_step_report_read(ctx)
+        out, inf = torch.zeros(2, dtype=torch.float64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        B.pt_chunk_grad_sqnorm_noalloc(g, B.PT_BF16, S, 1, 1.0, out, inf)
+        assert (float(out[0]), float(out[1]), int(inf[0])) == (rep.sqnorm, rep.norm, rep.found_inf)
+        want = float(g.double().square().sum())
+        assert abs(rep.sqnorm - want) <= S * 2.0 ** -53 * want
+    finally:
+        B.pt_ctx_destroy(ctx)
