@@ -7,7 +7,7 @@
 // when adding.  Work unit = 4 consecutive elements per lane: one 8-byte load on the tensor
 // side, one 16-byte load and store on the chunk side, so that every wave instruction covers
 // one contiguous span (512 B / 1 KiB); the body is aligned on the chunk side (16 bytes); a
-// tensor side that is not congruent (8 bytes) falls back to 16-bit loads.
+// tensor side that is not congruent (8 bytes) is read with 8-byte loads at 2-byte alignment.
 // Each element is one binary32 addition of the stored sum and the exactly decoded word.
 #include "pt_common.h"
 
@@ -17,7 +17,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int AC_THREADS = PT_REDUCE_THREADS;
+constexpr int AC_THREADS = 64;
 
 template <int DT>
 __device__ __forceinline__ float word_to_f32(uint32_t w16) {
@@ -51,27 +51,61 @@ __device__ __forceinline__ void add4(const u32x2& q, f32x4& acc, double inv_scal
   }
 }
 
-__device__ __forceinline__ u32x2 load4_unaligned(const PT_GLOBAL uint16_t* s) {
-  u32x2 q;
-  q.x = uint32_t(s[0]) | (uint32_t(s[1]) << 16);
-  q.y = uint32_t(s[2]) | (uint32_t(s[3]) << 16);
-  return q;
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));   // global memory takes an 8-byte load at any address
+
+template <bool ALIGNED>
+__device__ __forceinline__ u32x2 load4(const PT_GLOBAL uint16_t* s) {
+  if (ALIGNED) return __builtin_nontemporal_load((const PT_GLOBAL u32x2*)s);
+  return __builtin_nontemporal_load((const PT_GLOBAL u32x2_a2*)s);
 }
+
+// nvec units of four elements from sb onto db: two per lane in flight.
+template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED>
+__device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBAL f32x4* db, uint32_t nvec, double inv_scale, double& a0,
+                                          double& a1, uint32_t& flag) {
+  constexpr int U = 2;
+  uint32_t i = threadIdx.x;
+  for (; i + (U - 1) * AC_THREADS < nvec; i += U * AC_THREADS) {
+    u32x2 q[U];
+    f32x4 a[U];
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      q[r] = load4<ALIGNED>(sb + size_t(i + r * AC_THREADS) * 4);
+      if (OVERWRITE) a[r] = f32x4{};
+      else a[r] = __builtin_nontemporal_load(db + i + r * AC_THREADS);
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      add4<DT, OVERWRITE, NORM>(q[r], a[r], inv_scale, a0, a1, flag);
+      __builtin_nontemporal_store(a[r], db + i + r * AC_THREADS);
+    }
+  }
+  for (; i < nvec; i += AC_THREADS) {
+    const u32x2 q = load4<ALIGNED>(sb + size_t(i) * 4);
+    f32x4 a = {};
+    if (!OVERWRITE) a = __builtin_nontemporal_load(db + i);
+    add4<DT, OVERWRITE, NORM>(q, a, inv_scale, a0, a1, flag);
+    __builtin_nontemporal_store(a, db + i);
+  }
+}
+
+// As for pack, DRAM row locality decides: one wave adds 1024 elements, two units per lane in flight, and unused
+// LDS keeps about 12 waves on a compute unit.  Adding 3.3e8 words: 520 us with workgroups of four waves and tiles of 4096
+// taken from two ends of the list, 510 with three of those on a unit, 495 now (6.6 TB/s) - 507 with four units per lane in
+// flight, 513 without the limit, 535-550 with 2048 elements per wave.
+constexpr uint32_t ACCUM_LDS = 13000;
 
 template <int DT, bool OVERWRITE, bool NORM>
 __global__ void __launch_bounds__(AC_THREADS)
-k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
+k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row, uint32_t subs, uint32_t sub_elems,
         const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag) {
-  // Even workgroups walk the first half of the tile list (sorted by chunk), odd ones the second half:
-  // the read-modify-write traffic of a moment then falls on two distant parts of the chunks.  Measured
-  // on MI355X: 9 % faster when the two halves of the gradient chunks lie in different 96 GiB regions of
-  // the memory, no slower when they do not.
-  const uint32_t half = (gridDim.x + 1) >> 1;
-  const uint32_t tidx = (blockIdx.x & 1u) ? half + (blockIdx.x >> 1) : (blockIdx.x >> 1);
-  const PtTile t = tiles[tidx];
-  PT_GLOBAL float* dst = (PT_GLOBAL float*)(chunk_row[t.chunk]) + t.chunk_off;
-  const PT_GLOBAL uint16_t* src = (const PT_GLOBAL uint16_t*)(t.tensor_addr);
-  const uint32_t len = t.len;
+  const uint32_t tile = blockIdx.x / subs;
+  const PtTile t = tiles[tile];
+  uint32_t lo, hi;
+  pt_sub_range(t, blockIdx.x - tile * subs, sub_elems, lo, hi);
+  PT_GLOBAL float* dst = (PT_GLOBAL float*)(chunk_row[t.chunk]) + t.chunk_off + lo;
+  const PT_GLOBAL uint16_t* src = (const PT_GLOBAL uint16_t*)(t.tensor_addr) + lo;
+  const uint32_t len = hi - lo;
 
   // elements before the chunk side reaches a 16-byte boundary
   uint32_t head = uint32_t(((16u - (uint32_t((uintptr_t)dst) & 15u)) & 15u) >> 2);
@@ -83,6 +117,11 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
   double a0 = 0.0, a1 = 0.0;
   uint32_t flag = 0;
 
+  const PT_GLOBAL uint16_t* sb = src + head;
+  PT_GLOBAL f32x4* db = (PT_GLOBAL f32x4*)(dst + head);
+  if (((uintptr_t)sb & 7u) == 0) add_units<DT, OVERWRITE, NORM, true>(sb, db, nvec, inv_scale, a0, a1, flag);
+  else add_units<DT, OVERWRITE, NORM, false>(sb, db, nvec, inv_scale, a0, a1, flag);
+
   // head and tail: at most 3 elements each, one lane per element
   if (threadIdx.x < head) {
     const float x = word_to_f32<DT>(src[threadIdx.x]);
@@ -90,56 +129,25 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
     dst[threadIdx.x] = a;
     if (NORM) take(a, inv_scale, a0, flag);
   }
-  if (threadIdx.x >= 64 && threadIdx.x - 64 < len - tail0) {
-    const uint32_t e = tail0 + (threadIdx.x - 64);
+  if (threadIdx.x < len - tail0) {
+    const uint32_t e = tail0 + threadIdx.x;
     const float x = word_to_f32<DT>(src[e]);
     const float a = OVERWRITE ? x : dst[e] + x;
     dst[e] = a;
     if (NORM) take(a, inv_scale, a1, flag);
   }
 
-  const PT_GLOBAL uint16_t* sb = src + head;
-  PT_GLOBAL f32x4* db = (PT_GLOBAL f32x4*)(dst + head);
-  const bool src_aligned = ((uintptr_t)sb & 7u) == 0;
-  const PT_GLOBAL u32x2* sv = (const PT_GLOBAL u32x2*)sb;
-  uint32_t i = threadIdx.x;
-  if (src_aligned) {
-    constexpr int D = 4;               // units per lane in flight
-    for (; i + (D - 1) * AC_THREADS < nvec; i += D * AC_THREADS) {
-      u32x2 q[D];
-      f32x4 a[D];
-#pragma unroll
-      for (int r = 0; r < D; ++r) {
-        q[r] = __builtin_nontemporal_load(sv + i + r * AC_THREADS);
-        if (OVERWRITE) a[r] = f32x4{};
-        else a[r] = __builtin_nontemporal_load(db + i + r * AC_THREADS);
-      }
-#pragma unroll
-      for (int r = 0; r < D; ++r) {
-        add4<DT, OVERWRITE, NORM>(q[r], a[r], inv_scale, a0, a1, flag);
-        __builtin_nontemporal_store(a[r], db + i + r * AC_THREADS);
-      }
-    }
-  }
-  for (; i < nvec; i += AC_THREADS) {
-    u32x2 q = src_aligned ? sv[i] : load4_unaligned(sb + size_t(i) * 4);
-    f32x4 a = {};
-    if (!OVERWRITE) a = db[i];
-    add4<DT, OVERWRITE, NORM>(q, a, inv_scale, a0, a1, flag);
-    db[i] = a;
-  }
-
   if (NORM) {
     double acc = a0 + a1;
-    pt_block_sum(acc, flag);
+    pt_wave_sum(acc, flag);
     if (threadIdx.x == 0) {
-      tile_sq[tidx] = acc;
-      tile_flag[tidx] = flag;
+      tile_sq[blockIdx.x] = acc;
+      tile_flag[blockIdx.x] = flag;
     }
   }
 }
 
-typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, const PtDevState*, double*, uint32_t*);
+typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, uint32_t, uint32_t, const PtDevState*, double*, uint32_t*);
 
 template <int DT>
 accum_kernel_t pick(bool overwrite, bool norm) {
@@ -166,8 +174,8 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   if (take_norm && (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
-  hipLaunchKernelGGL(kern, dim3(plan->n_tiles), dim3(AC_THREADS), 0, st, plan->d_tiles, pt_row(ctx, ROW_PACK),
-                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
+  hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), ACCUM_LDS, st, plan->d_tiles, pt_row(ctx, ROW_PACK),
+                     plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {
     rc = pt_reduce_plan(ctx, plan, st);

@@ -58,21 +58,25 @@ constexpr uint32_t PT_MAX_SLOTS = 8;
 constexpr uint32_t PT_DIRECT_CHUNKS = 16;         // host chunks one launch of the in-place streamed update takes
 constexpr uint32_t PT_ADAMW_LDS = 14848;           // unused LDS of an update workgroup: 11 workgroups fit a unit's 160 KiB
 constexpr uint32_t PT_NORM_BLOCK_ELEMS = 32768;  // elements one block of the norm kernel reduces
-constexpr uint32_t PT_PACK_TILE_ELEMS = 8192;    // chunk-space tile of the pack kernel (one 4-vector batch per lane)
+constexpr uint32_t PT_PACK_TILE_ELEMS = 8192;    // chunk-space tile of a pack plan
+constexpr uint32_t PT_PACK_SUBS = 4;             // waves that share a tile of the default size: a quarter each
 
-struct PtTile {        // one block of work of the pack / unpack kernels
+struct PtTile {        // one piece of work of the pack / unpack / accumulate kernels
   uint64_t tensor_addr;  // byte address of the first element on the tensor side
   uint64_t chunk_off;    // first element on the chunk side
   uint32_t chunk;
   uint32_t len;          // 1 .. tile size of the plan
+  uint32_t phase;        // chunk_off modulo the tile size: the waves' quarters are cut on its grid
+  uint32_t pad;
 };
 
 struct pt_pack_plan {
   pt_ctx* ctx = nullptr;
   uint32_t n_tiles = 0;
+  uint32_t subs = 1, sub_elems = 0;        // waves per tile, elements of the tile each of them takes
   PtTile* d_tiles = nullptr;
   uint32_t* d_chunk_tile_begin = nullptr;  // n_chunks + 1 entries (tiles sorted by chunk)
-  double* d_tile_sq = nullptr;
+  double* d_tile_sq = nullptr;             // [n_tiles * subs]
   uint32_t* d_tile_flag = nullptr;
   uint32_t segs = 1;                       // reduction workgroups per chunk, for the chunk with the most tiles
   double* d_seg_sum = nullptr;             // [chunks from the first to the last touched one * segs], if segs > 1
@@ -91,11 +95,12 @@ struct PtPendingReduce {
   const uint32_t* flag = nullptr;
   const uint32_t* tile_begin = nullptr;
   uint32_t first = 0, n = 0, per_chunk = 0, segs = 1;
+  uint32_t per_tile = 1;                 // partial sums per entry of tile_begin
   double* seg_sum = nullptr;
   uint32_t* seg_flag = nullptr;
   const pt_pack_plan* plan = nullptr;    // owner of part / flag / tile_begin (NULL: the context)
 };
-constexpr uint32_t PT_REDUCE_SEG = 2048;         // partial sums one workgroup adds up, eight per lane
+constexpr uint32_t PT_REDUCE_SEG = 4096;         // partial sums one workgroup adds up, eight per lane
 inline uint32_t pt_segs(uint64_t partials) { return uint32_t(partials ? (partials + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG : 1); }
 
 struct pt_ctx {
@@ -215,21 +220,25 @@ inline int pt_guarded(pt_ctx* ctx, const char* who, F&& body) noexcept {
                      hipGetErrorString(e__));                                          \
   } while (0)
 
-// ---- fixed-order block reduction (device) --------------------------------------------
-// Sum of `acc` and OR of `flag` over a workgroup of 256 threads, in a fixed order: a 64-lane
-// shuffle tree per wave, then the four waves one after the other through LDS.  No atomics, so a
-// result does not depend on timing.  The result is valid in thread 0 only.  Every kernel that
-// leaves a partial sum of squares (pack, accumulate, the standalone norm, the per-chunk sums)
-// reduces through this one function, so their partials are interchangeable bit for bit.
+// ---- fixed-order reductions (device) ---------------------------------------------------
+// Sum of `acc` and OR of `flag` over a wave, by a 64-lane shuffle tree: a fixed order, no atomics, so a result does
+// not depend on timing.  Valid in lane 0 only.
+__device__ __forceinline__ void pt_wave_sum(double& acc, uint32_t& flag) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  flag = __any(flag != 0) ? 1u : 0u;
+}
+
+// The same over a workgroup of 256 threads: the tree per wave, then the four waves one after the other through LDS.
+// Valid in thread 0 only.
 constexpr int PT_REDUCE_THREADS = 256;
 
 __device__ __forceinline__ void pt_block_sum(double& acc, uint32_t& flag) {
   __shared__ double s_sum[PT_REDUCE_THREADS / 64];
   __shared__ uint32_t s_flag[PT_REDUCE_THREADS / 64];
   double w = acc;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) w += __shfl_down(w, off, 64);
-  const uint32_t f = __any(flag != 0) ? 1u : 0u;
+  uint32_t f = flag;
+  pt_wave_sum(w, f);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   if (lane == 0) { s_sum[wid] = w; s_flag[wid] = f; }
   __syncthreads();
@@ -240,6 +249,14 @@ __device__ __forceinline__ void pt_block_sum(double& acc, uint32_t& flag) {
     for (int i = 1; i < PT_REDUCE_THREADS / 64; ++i) { t += s_sum[i]; g |= s_flag[i]; }
     acc = t; flag = g;
   }
+}
+
+// The part of tile t that the wave blockIdx.x takes: elements [lo, hi) of the tile, possibly none.
+__device__ __forceinline__ void pt_sub_range(const PtTile& t, uint32_t sub, uint32_t sub_elems, uint32_t& lo, uint32_t& hi) {
+  const uint64_t end = uint64_t(t.phase) + t.len, a = uint64_t(sub) * sub_elems;      // on the tile's grid
+  const uint64_t l = a > t.phase ? a : t.phase, h = a + sub_elems < end ? a + sub_elems : end;
+  lo = uint32_t(l - t.phase);
+  hi = h > l ? uint32_t(h - t.phase) : lo;
 }
 
 // ---- helpers implemented in pt_ctx.hip ---------------------------------------------

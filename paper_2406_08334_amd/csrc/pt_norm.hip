@@ -162,11 +162,13 @@ k_sqnorm_f32(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
 // derives the nine fp32 constants of the update.  Every order is fixed: who comes last does not change a bit.
 //
 // Latency is all it costs, so the chain is kept short: a lane's eight loads are in flight together, two waves take the
-// powers of beta while the others wait for the sums, the chunk values pass through LDS, and nothing that was
-// just computed is read back.  Reduction, finalize and constants, for 15 chunks of 1024 partials: 8.8 us in two launches
-// and 5.5 us of a gap behind an event before, 7.0 us in one launch now (a kernel that does nothing takes 4.7 there); 47 of
-// 4096: 14.0 -> 10.3; 10 of 8192: 15.6 -> 8.8 us.
-constexpr int SC_THREADS = NB_THREADS + 128;     // two more waves for the powers
+// powers of beta while the others wait for the sums, the chunk values pass through LDS, nothing that was just computed is
+// read back, and no cache is written back or invalidated: what workgroups hand each other goes past the caches
+// (agent scope), and a workgroup counts itself in when its store has arrived.  Reduction,
+// finalize and constants: 15 chunks, 1.2e8 elements: 8.8 us in two launches and 5.5 us of a gap behind an event before, 6.8 us
+// in one launch now (a kernel that does nothing takes 4.7 there); 47 chunks, 1.56e9 elements: 14.0 -> 8.8 us; one block's two
+// chunks 6.5 -> 4.4 us.  With fences for the whole L2 instead: 9.5, 17 and 7.6 us.
+constexpr int SC_SUM = PT_REDUCE_SEG / 8, SC_THREADS = SC_SUM + 128;     // two more waves for the powers
 
 struct ScalarArgs {
   PtPendingReduce r;             // r.n == 0: nothing to reduce (grid 1 x 1)
@@ -225,98 +227,90 @@ __device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& h
   }
 }
 
+// Partial sums of chunk first + i.
+__device__ __forceinline__ uint32_t partials_of(const PtPendingReduce& r, uint32_t i, uint32_t& lo) {
+  if (!r.tile_begin) { lo = i * r.per_chunk; return r.per_chunk; }
+  lo = r.tile_begin[r.first + i] * r.per_tile;
+  return r.tile_begin[r.first + i + 1] * r.per_tile - lo;
+}
+
 __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
-  __shared__ double s_sum[NB_THREADS / 64], s_val[NB_THREADS], s_bc[2];
-  __shared__ uint32_t s_flag[NB_THREADS / 64], s_f[NB_THREADS], s_last;
+  __shared__ double s_sum[SC_SUM / 64], s_val[SC_SUM], s_bc[2];
+  __shared__ uint32_t s_flag[SC_SUM / 64], s_f[SC_SUM], s_last;
   const PtPendingReduce& r = a.r;
   const uint32_t tid = threadIdx.x, c = r.first + blockIdx.y;
   uint32_t lo = 0, hi = 0;
-  if (r.n) {
-    if (r.tile_begin) { lo = r.tile_begin[c]; hi = r.tile_begin[c + 1]; }
-    else { lo = blockIdx.y * r.per_chunk; hi = lo + r.per_chunk; }
-  }
-  const uint32_t own = hi - lo;                  // partials of the chunk; the segment's are [lo, hi) from here on
+  if (r.n) hi = partials_of(r, blockIdx.y, lo);          // a number here
+  hi = min(hi, (blockIdx.x + 1) * PT_REDUCE_SEG) + lo;
   lo = min(hi, lo + blockIdx.x * PT_REDUCE_SEG);
-  hi = min(hi, lo + PT_REDUCE_SEG);
   double acc = 0.0;
   uint32_t f = 0;
-  if (tid < NB_THREADS) {
-    constexpr int D = PT_REDUCE_SEG / NB_THREADS;
-    double x[D];
-    uint32_t y[D];
+  if (tid < SC_SUM) {
+    double x[8];
+    uint32_t y[8];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const uint32_t k = lo + tid + j * NB_THREADS;
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t k = lo + tid + j * SC_SUM;
       x[j] = k < hi ? r.part[k] : 0.0;
       y[j] = k < hi ? r.flag[k] : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < D; ++j) { acc += x[j]; f |= y[j]; }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    f = __any(f != 0) ? 1u : 0u;
+    for (int j = 0; j < 8; ++j) { acc += x[j]; f |= y[j]; }
+    pt_wave_sum(acc, f);
     if ((tid & 63) == 0) { s_sum[tid >> 6] = acc; s_flag[tid >> 6] = f; }
   } else if (a.do_prepare && (tid & 63) == 0) {
     const double t = double(a.st->step + 1);
-    s_bc[(tid - NB_THREADS) >> 6] = 1.0 - pow(tid == NB_THREADS ? a.hp.beta1 : a.hp.beta2, t);
+    s_bc[(tid - SC_SUM) >> 6] = 1.0 - pow(tid == SC_SUM ? a.hp.beta1 : a.hp.beta2, t);
   }
   __syncthreads();
   if (tid == 0) {
 #pragma unroll
-    for (int i = 1; i < NB_THREADS / 64; ++i) { acc += s_sum[i]; f |= s_flag[i]; }
-    if (own && lo < hi) {
-      if (r.segs > 1) {
-        st_agent(r.seg_sum + size_t(blockIdx.y) * r.segs + blockIdx.x, acc);
-        st_agent(r.seg_flag + size_t(blockIdx.y) * r.segs + blockIdx.x, f);
-      } else {
-        st_agent(a.chunk_sq + c, acc);
-        st_agent(a.chunk_flag + c, f);
-      }
+    for (int i = 1; i < SC_SUM / 64; ++i) { acc += s_sum[i]; f |= s_flag[i]; }
+    if (lo < hi) {
+      const size_t slot = size_t(blockIdx.y) * r.segs + blockIdx.x;
+      st_agent(r.segs > 1 ? r.seg_sum + slot : a.chunk_sq + c, acc);
+      st_agent(r.segs > 1 ? r.seg_flag + slot : a.chunk_flag + c, f);
     }
     const uint32_t total = gridDim.x * gridDim.y;
-    if (total > 1) {
-      __threadfence();
-      s_last = atomicAdd(a.ticket, 1u) == total - 1 ? 1u : 0u;
-    } else {
-      s_last = 1u;
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    s_last = total == 1 || __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1 ? 1u : 0u;
   }
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   if (tid == 0) st_agent(a.ticket, 0u);
-  if (r.segs > 1) {
-    for (uint32_t i = tid; i < r.n; i += SC_THREADS) {
-      const uint32_t cc = r.first + i, have = r.tile_begin ? r.tile_begin[cc + 1] - r.tile_begin[cc] : r.per_chunk;
-      if (!have) continue;
-      const uint32_t ns = (have + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG;
-      double t = 0.0;
-      uint32_t g = 0;
-      for (uint32_t k = 0; k < ns; ++k) {
-        t += ld_agent(r.seg_sum + size_t(i) * r.segs + k);
-        g |= ld_agent(r.seg_flag + size_t(i) * r.segs + k);
-      }
-      st_agent(a.chunk_sq + cc, t);
-      st_agent(a.chunk_flag + cc, g);
-    }
-    __threadfence();
-    __syncthreads();
-  }
   double sq = 0.0, norm = 0.0;
   uint32_t inf = 0;
-  if (a.do_finalize) {
-    for (uint32_t base = 0; base < a.C; base += NB_THREADS) {
-      if (tid < NB_THREADS && base + tid < a.C) {
-        s_val[tid] = ld_agent(a.chunk_sq + base + tid);
-        s_f[tid] = ld_agent(a.chunk_flag + base + tid);
+  // the chunks of this launch, or - to finalize - all of them
+  const uint32_t c0 = a.do_finalize ? 0 : r.first, c1 = a.do_finalize ? a.C : r.first + r.n;
+  for (uint32_t base = c0; base < c1; base += SC_SUM) {
+    const uint32_t cc = base + tid;
+    if (tid < SC_SUM && cc < c1) {
+      double t;
+      uint32_t g, p0;
+      const uint32_t ns = r.segs > 1 && cc >= r.first && cc - r.first < r.n
+                              ? (partials_of(r, cc - r.first, p0) + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG : 0;
+      if (ns) {
+        t = 0.0; g = 0;
+        for (uint32_t k = 0; k < ns; ++k) {
+          t += ld_agent(r.seg_sum + size_t(cc - r.first) * r.segs + k);
+          g |= ld_agent(r.seg_flag + size_t(cc - r.first) * r.segs + k);
+        }
+        a.chunk_sq[cc] = t;
+        a.chunk_flag[cc] = g;
+      } else {
+        t = ld_agent(a.chunk_sq + cc);
+        g = ld_agent(a.chunk_flag + cc);
       }
-      __syncthreads();
-      if (tid == 0) {
-        const uint32_t k1 = min(uint32_t(NB_THREADS), a.C - base);
-        for (uint32_t k = 0; k < k1; ++k) { sq += s_val[k]; inf |= s_f[k]; }
-      }
-      __syncthreads();
+      s_val[tid] = t;
+      s_f[tid] = g;
     }
+    if (!a.do_finalize) continue;
+    __syncthreads();
+    if (tid == 0) {
+      const uint32_t k1 = min(uint32_t(SC_SUM), c1 - base);
+      for (uint32_t k = 0; k < k1; ++k) { sq += s_val[k]; inf |= s_f[k]; }
+    }
+    __syncthreads();
   }
   if (tid != 0) return;
   if (a.do_finalize) {
@@ -431,7 +425,7 @@ int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
   if (plan->touched.empty()) return PT_OK;
   PtPendingReduce r;
   r.part = plan->d_tile_sq; r.flag = plan->d_tile_flag; r.tile_begin = plan->d_chunk_tile_begin;
-  r.first = plan->touched.front(); r.n = plan->touched.back() - r.first + 1;
+  r.first = plan->touched.front(); r.n = plan->touched.back() - r.first + 1; r.per_tile = plan->subs;
   r.segs = plan->segs; r.seg_sum = plan->d_seg_sum; r.seg_flag = plan->d_seg_flag;
   r.plan = plan;
   const bool small = plan->touched.size() <= PT_FUSE_MAX_CHUNKS && ctx->C <= 64 && plan->n_tiles <= PT_FUSE_MAX_PARTIALS;

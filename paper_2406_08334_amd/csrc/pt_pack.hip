@@ -1,13 +1,13 @@
-// Pack gradients into chunks (and the inverse copy), one block per tile of a
-// precomputed work list, fused with the per-tile sum of squares and the
+// Pack gradients into chunks (and the inverse copy), one wave per quarter of a tile of a
+// precomputed work list, fused with the wave's sum of squares and the
 // non-finite scan.
 //
 // HBM-bound: 2 bytes read + 2 bytes written per element.  Tiles are cut in
 // CHUNK space at multiples of the tile size (PT_PACK_TILE_ELEMS by default), so many tiny tensors and a few
-// huge ones give equally sized blocks.  Words are moved as 16-bit integers,
+// huge ones give equally sized workgroups.  Words are moved as 16-bit integers,
 // never through a float.  The 16-byte vector body is aligned on the destination;
 // when source and destination are not congruent modulo 16 bytes the source side
-// falls back to 16-bit loads (the transformer shapes used here are congruent).
+// is read with 16-byte loads at 2-byte alignment.
 #include "pt_common.h"
 
 #include <hip/hip_fp16.h>
@@ -19,10 +19,12 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int PK_THREADS = PT_REDUCE_THREADS;
+constexpr int PK_THREADS = 64;
 
+// The square of one word joins the sum (two 16-bit significands multiply exactly: only the addition rounds).
 template <int DT>
-__device__ __forceinline__ double word_sq(uint32_t w16, double inv_scale) {
+__device__ __forceinline__ void take(uint32_t w16, double inv_scale, double& sum, uint32_t& flag) {
+  constexpr uint32_t E = DT == PT_BF16 ? 0x7f80u : 0x7c00u;
   double x;
   if (DT == PT_BF16) {
     x = (double)__uint_as_float(w16 << 16);
@@ -31,24 +33,16 @@ __device__ __forceinline__ double word_sq(uint32_t w16, double inv_scale) {
     x = (double)__half2float(__half(r));
   }
   x *= inv_scale;
-  return x * x;
+  sum = fma(x, x, sum);
+  flag |= (w16 & E) == E;
 }
 
 template <int DT>
-__device__ __forceinline__ uint32_t word_nonfinite(uint32_t w16) {
-  constexpr uint32_t E = DT == PT_BF16 ? 0x7f80u : 0x7c00u;
-  return (w16 & E) == E;
-}
-
-template <int DT>
-__device__ __forceinline__ void accum_vec(const u32x4& q, double inv_scale, double& a0, double& a1,
-                                          uint32_t& flag) {
-  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+__device__ __forceinline__ void take_vec(const u32x4& q, double inv_scale, double& a0, double& a1, uint32_t& flag) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    a0 += word_sq<DT>(w[k] & 0xffffu, inv_scale);
-    a1 += word_sq<DT>(w[k] >> 16, inv_scale);
-    flag |= word_nonfinite<DT>(w[k] & 0xffffu) | word_nonfinite<DT>(w[k] >> 16);
+    take<DT>(q[k] & 0xffffu, inv_scale, a0, flag);
+    take<DT>(q[k] >> 16, inv_scale, a1, flag);
   }
 }
 
@@ -57,30 +51,62 @@ __device__ __forceinline__ void store_vec(const u32x4& q, PT_GLOBAL u32x4* p) {
   if (NT) __builtin_nontemporal_store(q, p); else *p = q;
 }
 
-__device__ __forceinline__ u32x4 load_vec_unaligned16(const PT_GLOBAL uint16_t* s) {
-  // eight 16-bit loads: the source is only 2-byte aligned relative to the destination
-  u32x4 q;
-  q.x = uint32_t(s[0]) | (uint32_t(s[1]) << 16);
-  q.y = uint32_t(s[2]) | (uint32_t(s[3]) << 16);
-  q.z = uint32_t(s[4]) | (uint32_t(s[5]) << 16);
-  q.w = uint32_t(s[6]) | (uint32_t(s[7]) << 16);
-  return q;
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));   // global memory takes a 16-byte load at any address
+
+template <bool ALIGNED>
+__device__ __forceinline__ u32x4 load_vec(const PT_GLOBAL uint16_t* s) {
+  if (ALIGNED) return __builtin_nontemporal_load((const PT_GLOBAL u32x4*)s);
+  return __builtin_nontemporal_load((const PT_GLOBAL u32x4_a2*)s);
+}
+
+// nvec vectors from sb to db: U per lane in flight.
+template <int DT, int DIR, bool NTS, bool ALIGNED>
+__device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBAL u32x4* db, uint32_t nvec, double inv_scale,
+                                          double& a0, double& a1, uint32_t& flag) {
+  constexpr int U = DIR == 0 ? 4 : 2;
+  uint32_t i = threadIdx.x;
+  for (; i + (U - 1) * PK_THREADS < nvec; i += U * PK_THREADS) {
+    u32x4 q[U];
+#pragma unroll
+    for (int r = 0; r < U; ++r) q[r] = load_vec<ALIGNED>(sb + size_t(i + r * PK_THREADS) * 8);
+#pragma unroll
+    for (int r = 0; r < U; ++r) store_vec<NTS>(q[r], db + i + r * PK_THREADS);
+    if (DIR == 0)
+#pragma unroll
+      for (int r = 0; r < U; ++r) take_vec<DT>(q[r], inv_scale, a0, a1, flag);
+  }
+  for (; i < nvec; i += PK_THREADS) {
+    const u32x4 q = load_vec<ALIGNED>(sb + size_t(i) * 8);
+    store_vec<NTS>(q, db + i);
+    if (DIR == 0) take_vec<DT>(q, inv_scale, a0, a1, flag);
+  }
 }
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
 // NTS: non-temporal stores; without them the gradient words stay in the Infinity Cache for the update (pt_grads_cached).
+//
+// As for the update, DRAM row locality decides: few bytes in flight, in address order.  One wave moves 4 KiB and
+// unused LDS (PACK_LDS, UNPACK_LDS) keeps about 17 and 14 of them on a compute unit.  Against workgroups of four waves
+// with 16 KiB, eight on a unit: pack of 1.56e9 elements 1012 -> 957 us (6.5 TB/s), 6.7e8 fp16 words 438 -> 412; the same
+// below 1.3e8; unpack of 6.7e8 425 -> 404 us (6.6 TB/s).  2 KiB per wave cost pack 20 % (too little work behind the look-up
+// of a tile), 8 KiB 6-8 %, no limit 1-3 %.  Two vectors per lane in flight suit unpack better (404 against 411 us), four pack.
+constexpr uint32_t PACK_LDS = 9000, UNPACK_LDS = 11500;
+
 template <int DT, int DIR, bool NTS>
 __global__ void __launch_bounds__(PK_THREADS)
-k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
+k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row, uint32_t subs, uint32_t sub_elems,
        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag) {
-  const PtTile t = tiles[blockIdx.x];
+  const uint32_t tile = blockIdx.x / subs;
+  const PtTile t = tiles[tile];
+  uint32_t lo, hi;
+  pt_sub_range(t, blockIdx.x - tile * subs, sub_elems, lo, hi);
   // both sides are device (global) memory: typed so, to get global_* instead of flat_* accesses
-  PT_GLOBAL uint16_t* chunk_side = (PT_GLOBAL uint16_t*)(chunk_row[t.chunk]) + t.chunk_off;
-  PT_GLOBAL uint16_t* tensor_side = (PT_GLOBAL uint16_t*)(t.tensor_addr);
+  PT_GLOBAL uint16_t* chunk_side = (PT_GLOBAL uint16_t*)(chunk_row[t.chunk]) + t.chunk_off + lo;
+  PT_GLOBAL uint16_t* tensor_side = (PT_GLOBAL uint16_t*)(t.tensor_addr) + lo;
   const PT_GLOBAL uint16_t* src = DIR == 0 ? tensor_side : chunk_side;
   PT_GLOBAL uint16_t* dst = DIR == 0 ? chunk_side : tensor_side;
-  const uint32_t len = t.len;
+  const uint32_t len = hi - lo;
 
   // elements before the destination reaches a 16-byte boundary
   uint32_t head = uint32_t(((16u - (uint32_t((uintptr_t)dst) & 15u)) & 15u) >> 1);
@@ -92,56 +118,27 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
   double a0 = 0.0, a1 = 0.0;
   uint32_t flag = 0;
 
-  // head and tail: at most 7 elements each, one lane per element
-  if (threadIdx.x < head) {
-    uint16_t w = src[threadIdx.x];
-    dst[threadIdx.x] = w;
-    if (DIR == 0) { a0 += word_sq<DT>(w, inv_scale); flag |= word_nonfinite<DT>(w); }
-  }
-  if (threadIdx.x >= 64 && threadIdx.x - 64 < len - tail0) {
-    uint32_t e = tail0 + (threadIdx.x - 64);
-    uint16_t w = src[e];
-    dst[e] = w;
-    if (DIR == 0) { a1 += word_sq<DT>(w, inv_scale); flag |= word_nonfinite<DT>(w); }
-  }
-
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL u32x4* db = (PT_GLOBAL u32x4*)(dst + head);
-  if (((uintptr_t)sb & 15u) == 0) {
-    const PT_GLOBAL u32x4* sv = (const PT_GLOBAL u32x4*)sb;
-    uint32_t i = threadIdx.x;
-    for (; i + 3 * PK_THREADS < nvec; i += 4 * PK_THREADS) {
-      u32x4 q0 = __builtin_nontemporal_load(sv + i);
-      u32x4 q1 = __builtin_nontemporal_load(sv + i + PK_THREADS);
-      u32x4 q2 = __builtin_nontemporal_load(sv + i + 2 * PK_THREADS);
-      u32x4 q3 = __builtin_nontemporal_load(sv + i + 3 * PK_THREADS);
-      store_vec<NTS>(q0, db + i);
-      store_vec<NTS>(q1, db + i + PK_THREADS);
-      store_vec<NTS>(q2, db + i + 2 * PK_THREADS);
-      store_vec<NTS>(q3, db + i + 3 * PK_THREADS);
-      if (DIR == 0) {
-        accum_vec<DT>(q0, inv_scale, a0, a1, flag);
-        accum_vec<DT>(q1, inv_scale, a0, a1, flag);
-        accum_vec<DT>(q2, inv_scale, a0, a1, flag);
-        accum_vec<DT>(q3, inv_scale, a0, a1, flag);
-      }
-    }
-    for (; i < nvec; i += PK_THREADS) {
-      u32x4 q = __builtin_nontemporal_load(sv + i);
-      store_vec<NTS>(q, db + i);
-      if (DIR == 0) accum_vec<DT>(q, inv_scale, a0, a1, flag);
-    }
-  } else {
-    for (uint32_t i = threadIdx.x; i < nvec; i += PK_THREADS) {
-      u32x4 q = load_vec_unaligned16(sb + size_t(i) * 8);
-      db[i] = q;
-      if (DIR == 0) accum_vec<DT>(q, inv_scale, a0, a1, flag);
-    }
+  if (((uintptr_t)sb & 15u) == 0) move_vecs<DT, DIR, NTS, true>(sb, db, nvec, inv_scale, a0, a1, flag);
+  else move_vecs<DT, DIR, NTS, false>(sb, db, nvec, inv_scale, a0, a1, flag);
+
+  // head and tail: at most 7 elements each, one lane per element
+  if (threadIdx.x < head) {
+    const uint16_t w = src[threadIdx.x];
+    dst[threadIdx.x] = w;
+    if (DIR == 0) take<DT>(w, inv_scale, a0, flag);
+  }
+  if (threadIdx.x < len - tail0) {
+    const uint32_t e = tail0 + threadIdx.x;
+    const uint16_t w = src[e];
+    dst[e] = w;
+    if (DIR == 0) take<DT>(w, inv_scale, a1, flag);
   }
 
   if (DIR == 0) {
     double acc = a0 + a1;
-    pt_block_sum(acc, flag);
+    pt_wave_sum(acc, flag);
     if (threadIdx.x == 0) {
       tile_sq[blockIdx.x] = acc;
       tile_flag[blockIdx.x] = flag;
@@ -197,10 +194,13 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   }
   // cut into tiles at multiples of the tile size in chunk space
   // With fp32 gradient chunks the plan feeds the accumulate kernel, which moves 2.5 times the
-  // bytes per element: half the tile gives it the same short-lived workgroups (measured best).
+  // bytes per element: half the tile (figures at k_accum).
   const uint64_t tile_elems = ctx->grad_f32 ? std::max<uint64_t>(1024, ctx->opt_pack_tile_elems / 2)
                                             : ctx->opt_pack_tile_elems;
   std::vector<PtTile> tiles;
+  uint64_t room_for = 0;
+  for (uint32_t i = 0; i < n_segs; ++i) room_for += segs[i].len / tile_elems + 2;
+  tiles.reserve(room_for);
   std::vector<uint32_t> begin(size_t(ctx->C) + 1, 0);
   uint64_t total = 0;
   for (uint32_t k = 0; k < n_segs; ++k) {
@@ -212,14 +212,18 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
       uint64_t run = std::min<uint64_t>(room, s.len - done);
       PtTile t;
       t.tensor_addr = uint64_t(reinterpret_cast<uintptr_t>(s.src)) + 2 * (s.src_off + done);
-      t.chunk_off = coff; t.chunk = s.chunk; t.len = uint32_t(run);
+      t.chunk_off = coff; t.chunk = s.chunk; t.len = uint32_t(run); t.phase = uint32_t(coff % tile_elems); t.pad = 0;
       tiles.push_back(t);
       begin[s.chunk + 1] += 1;
       done += run;
     }
     total += s.len;
   }
-  if (tiles.size() > 0x7fffffffull) return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_pack_plan_create: too many tiles");
+  // a tile of the default size goes to four waves; one of another size to as many, if it has 2048 (1024) elements for each
+  const uint64_t least = ctx->grad_f32 ? 1024 : 2048;
+  const uint32_t subs = uint32_t(std::min<uint64_t>(PT_PACK_SUBS, (tile_elems + least - 1) / least));
+  const uint32_t sub_elems = uint32_t(((tile_elems + subs - 1) / subs + 7) & ~uint64_t(7));
+  if (tiles.size() * subs > 0x7fffffffull) return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_pack_plan_create: too many tiles");
   for (uint32_t c = 0; c < ctx->C; ++c) begin[c + 1] += begin[c];
 
   pt_pack_plan* p = new (std::nothrow) pt_pack_plan();
@@ -230,7 +234,8 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   uint32_t most = 0;
   for (uint32_t c = 0; c < ctx->C; ++c)
     if (begin[c + 1] > begin[c]) { p->touched.push_back(c); most = std::max(most, begin[c + 1] - begin[c]); }
-  p->segs = pt_segs(most);
+  p->subs = subs; p->sub_elems = sub_elems;
+  p->segs = pt_segs(uint64_t(most) * subs);
   auto bail = [&](hipError_t e, const char* what) {
     plan_free(p);
     p->d_tiles = nullptr; p->d_chunk_tile_begin = nullptr; p->d_tile_sq = nullptr; p->d_tile_flag = nullptr;
@@ -241,8 +246,8 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   size_t nt = std::max<size_t>(tiles.size(), 1);
   if ((e = hipMalloc(&p->d_tiles, nt * sizeof(PtTile))) != hipSuccess) return bail(e, "hipMalloc(tiles)");
   if ((e = hipMalloc(&p->d_chunk_tile_begin, begin.size() * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(begin)");
-  if ((e = hipMalloc(&p->d_tile_sq, nt * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(tile_sq)");
-  if ((e = hipMalloc(&p->d_tile_flag, nt * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(tile_flag)");
+  if ((e = hipMalloc(&p->d_tile_sq, nt * subs * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(tile_sq)");
+  if ((e = hipMalloc(&p->d_tile_flag, nt * subs * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(tile_flag)");
   if (p->segs > 1) {
     const size_t ns = size_t(p->touched.back() - p->touched.front() + 1) * p->segs;
     if ((e = hipMalloc(&p->d_seg_sum, ns * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(seg_sum)");
@@ -301,16 +306,13 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
                        "norm from the chunks with pt_chunk_grad_sqnorm(grad_chunks, ...) before packing again)", who, c);
     if ((rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
-  dim3 grid(plan->n_tiles);
-  // The inverse copy has no arithmetic to pace it; measured on MI355X it runs 15 % faster with three
-  // workgroups per compute unit than with the eight that fit (4.24 against 4.96 ms for 6.7e9 elements).
-  // Unused dynamic LDS (52 KiB of the unit's 160) sets that limit.  Pack itself is indifferent to it.
-  const size_t lds = DIR == 1 ? 53248 : 0;
+  dim3 grid(plan->n_tiles * plan->subs);
+  const size_t lds = DIR == 1 ? UNPACK_LDS : PACK_LDS;
   const bool bf16 = ctx->dtype == PT_BF16, nts = DIR == 1 || !pt_grads_cached(ctx);
   auto kern = nts ? (bf16 ? k_pack<PT_BF16, DIR, true> : k_pack<PT_FP16, DIR, true>)
                   : (bf16 ? k_pack<PT_BF16, DIR, DIR == 1> : k_pack<PT_FP16, DIR, DIR == 1>);
-  hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), ctx->d_state, plan->d_tile_sq,
-                     plan->d_tile_flag);
+  hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), plan->subs, plan->sub_elems,
+                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
     rc = pt_reduce_plan(ctx, plan, st);

@@ -313,7 +313,7 @@ def test_streamed_update_by_the_kind_of_host_memory(dtype, grad_fp32, S, n_host,
         st.close()
 
 
-@pytest.mark.parametrize("tiles", [1, 255, 2048, 2049, 4097])        # one workgroup's lanes, one workgroup, segments
+@pytest.mark.parametrize("tiles", [1, 511, 4096, 4097, 8193])        # one workgroup's lanes, one workgroup, segments
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("inf", [False, True])
 def test_norm_of_many_partial_sums(tiles, dtype, inf):
@@ -390,8 +390,8 @@ def test_plan_destroyed_before_its_partial_sums_were_read():
 
 
 def test_norm_without_a_context_over_a_chunk_of_several_segments():
-    """More than 2048 blocks of 32768 elements in a chunk: the same bits as the context's recompute."""
-    S = 2048 * 32768 + 8
+    """More than 4096 blocks of 32768 elements in a chunk: the same bits as the context's recompute."""
+    S = 4096 * 32768 + 8
     g = torch.empty(S, dtype=torch.bfloat16, device="cuda")
     synth.normal_16(synth.SEED_GRADS, 1, 0, 0, S, 1e-3, torch.bfloat16, "cuda", out=g)
     ctx = B.pt_ctx_create(B.PT_BF16, S, 1, None)
@@ -405,3 +405,50 @@ def test_norm_without_a_context_over_a_chunk_of_several_segments():
         assert abs(rep.sqnorm - want) <= S * 2.0 ** -53 * want
     finally:
         B.pt_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 505, 1023, 1024, 1025, 2047, 2048, 2049, 4099])
+def test_pack_unpack_and_accumulate_at_the_edges_of_a_tile(dtype, n):
+    """Every alignment of the tensor against the chunk (in elements), lengths around one wave's tile, with the words
+    around the tensor's place left alone."""
+    S = 8192
+    gaps = [(s, d) for s in range(8) for d in range(8)]
+    C = len(gaps)
+    src = torch.zeros(C, S, dtype=dtype, device="cuda")
+    synth.normal_16(synth.SEED_GRADS, 1, 0, 0, C * S, 1e-2, dtype, "cuda", out=src.view(-1))
+    segs = [B.pt_segment(src[c].data_ptr(), s, n, d, c, c) for c, (s, d) in enumerate(gaps)]
+    for fp32 in (False, True):
+        ctx = B.pt_ctx_create(B.PT_BF16 if dtype == torch.bfloat16 else B.PT_FP16, S, C, None)
+        plan = None
+        try:
+            B.pt_ctx_set_option(ctx, "grad_fp32", int(fp32))
+            plan = B.pt_pack_plan_create(ctx, segs)
+            dst = torch.full((C, S), 3.0, dtype=torch.float32 if fp32 else dtype, device="cuda")
+            want = dst.clone()
+            for c, (s, d) in enumerate(gaps):
+                want[c, d:d + n] = src[c, s:s + n]
+            rows = [dst[c] for c in range(C)]
+            if fp32:
+                B.pt_chunk_accum_grads(ctx, plan, rows, True, False)
+                assert torch.equal(dst, want)
+                B.pt_chunk_accum_grads(ctx, plan, rows, False, True)
+                for c, (s, d) in enumerate(gaps):
+                    want[c, d:d + n] += src[c, s:s + n].float()
+            else:
+                B.pt_chunk_pack_grads(ctx, plan, rows)
+            assert torch.equal(dst, want)
+            B.pt_chunk_grad_sqnorm(ctx, None, 0, C, True)
+            sq = sum(float(want[c, d:d + n].double().square().sum()) for c, (s, d) in enumerate(gaps))
+            assert abs(B.pt_step_report_read(ctx).sqnorm - sq) <= C * n * 2.0 ** -53 * sq
+            if not fp32:
+                back = src.clone()
+                for c, (s, d) in enumerate(gaps):
+                    src[c, s:s + n] = 0
+                B.pt_chunk_unpack(ctx, plan, rows)
+                assert torch.equal(src, back)
+        finally:
+            torch.cuda.synchronize()
+            if plan is not None:
+                B.pt_pack_plan_destroy(plan)
+            B.pt_ctx_destroy(ctx)
