@@ -311,8 +311,8 @@ int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, uint64_t chu
  * all n_chunks chunks.
  * grad/master/m/v/param16: host arrays of n_chunks device pointers (entry i is
  * chunk first_chunk+i).  The context keeps a device copy of these tables; when a
- * call presents pointers that differ from the copy, the table is re-uploaded
- * after a hipStreamSynchronize(stream) — the only host synchronisation of a hot
+ * call presents pointers that differ from the copy, the table is rewritten behind the work on `stream`, which is then
+ * synchronised — the only host synchronisation of a hot
  * call, and it happens on the first call and whenever chunks move.
  * Requires a finalized norm in this step (else PT_ERR_STATE). */
 int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t first_chunk, uint32_t n_chunks,

@@ -500,11 +500,9 @@ extern "C" int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t f
     return pt_fail(ctx, PT_ERR_STATE, "pt_chunk_adamw_step: no finalized gradient norm in this step");
   if (n_chunks == 0) return PT_OK;
   int rc;
-  if ((rc = pt_table_bind(ctx, ROW_GRAD, first_chunk, n_chunks, grad, false, st, nullptr)) != PT_OK) return rc;
-  if ((rc = pt_table_bind(ctx, ROW_MASTER, first_chunk, n_chunks, (const void* const*)master, false, st, nullptr)) != PT_OK) return rc;
-  if ((rc = pt_table_bind(ctx, ROW_M, first_chunk, n_chunks, (const void* const*)m, false, st, nullptr)) != PT_OK) return rc;
-  if ((rc = pt_table_bind(ctx, ROW_V, first_chunk, n_chunks, (const void* const*)v, false, st, nullptr)) != PT_OK) return rc;
-  if ((rc = pt_table_bind(ctx, ROW_P16, first_chunk, n_chunks, (const void* const*)param16, false, st, nullptr)) != PT_OK) return rc;
+  const PtBind binds[5] = {{ROW_GRAD, grad}, {ROW_MASTER, (const void* const*)master}, {ROW_M, (const void* const*)m},
+                           {ROW_V, (const void* const*)v}, {ROW_P16, (const void* const*)param16}};
+  if ((rc = pt_table_bind(ctx, binds, 5, first_chunk, n_chunks, false, st)) != PT_OK) return rc;
   if ((rc = pt_prepare_consts(ctx, hp, st)) != PT_OK) return rc;
   return pt_launch_adamw(ctx, first_chunk, n_chunks, st, false, first_chunk, ctx->opt_zero_grads != 0);
 }

@@ -38,6 +38,7 @@ struct PtDevState {
   // constants of the update in flight (see pt_update_consts)
   float c[9];
   int32_t skip;
+  uint32_t ticket;       // workgroups of the scalar kernel that have finished (0 between launches)
 };
 
 // Rows of the per-context device pointer table.  Each row has n_chunks + n_slots
@@ -130,7 +131,6 @@ struct pt_ctx {
   uint32_t norm_segs = 1;               // reduction workgroups per chunk of a recompute
   double* d_norm_seg_sum = nullptr;     // [C * norm_segs], if norm_segs > 1
   uint32_t* d_norm_seg_flag = nullptr;
-  uint32_t* d_ticket = nullptr;         // workgroups of the scalar kernel that have finished (0 between launches)
 
   // host-side step bookkeeping
   std::vector<uint64_t> chunk_packed_by;   // [C] id of the pack plan whose partial sum is the chunk's value in this step, 0 = none
@@ -141,7 +141,7 @@ struct pt_ctx {
   std::vector<PtPendingReduce> pend_reduce;   // scalar work put off to be fused into one launch (pt_norm.hip), in order
   bool pend_finalize = false;
   hipStream_t finalize_stream = nullptr;      // where the pending finalize was asked for
-  hipEvent_t ev_order = nullptr;
+  hipEvent_t ev_order = nullptr;              // made when first needed
   bool carry = false;                   // the norm was finalized with PT_FINALIZE_CARRY: some chunks' gradients are elsewhere
   bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them
   pt_hparams prepared_hp{};
@@ -260,11 +260,15 @@ __device__ __forceinline__ void pt_sub_range(const PtTile& t, uint32_t sub, uint
 }
 
 // ---- helpers implemented in pt_ctx.hip ---------------------------------------------
-// Makes rows[r][first .. first+n) of the device pointer table equal to ptrs[0..n);
-// re-uploads (after synchronising `stream`) only when something changed.
+// Makes rows[r][first .. first+n) of the device pointer table equal to ptrs[0..n), for each of n_binds rows; uploads (on
+// `stream`, which it synchronises) only when something changed.
 // allow_null: NULL entries are accepted (and stored as 0).
-int pt_table_bind(pt_ctx* ctx, int row, uint32_t first, uint32_t n, const void* const* ptrs,
-                  bool allow_null, hipStream_t stream, bool* changed);
+struct PtBind { int row; const void* const* ptrs; };
+int pt_table_bind(pt_ctx* ctx, const PtBind* binds, int n_binds, uint32_t first, uint32_t n, bool allow_null, hipStream_t stream);
+inline int pt_table_bind(pt_ctx* ctx, int row, uint32_t first, uint32_t n, const void* const* ptrs, bool allow_null, hipStream_t stream) {
+  const PtBind b{row, ptrs};
+  return pt_table_bind(ctx, &b, 1, first, n, allow_null, stream);
+}
 inline const uint64_t* pt_row(const pt_ctx* ctx, int row) {
   return ctx->d_table + size_t(row) * ctx->table_cols;
 }

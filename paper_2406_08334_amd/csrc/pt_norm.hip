@@ -361,7 +361,7 @@ constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
   ScalarArgs a{};
   if (r) a.r = *r;
-  a.chunk_sq = ctx->d_chunk_sq; a.chunk_flag = ctx->d_chunk_flag; a.C = ctx->C; a.ticket = ctx->d_ticket; a.st = ctx->d_state;
+  a.chunk_sq = ctx->d_chunk_sq; a.chunk_flag = ctx->d_chunk_flag; a.C = ctx->C; a.ticket = &ctx->d_state->ticket; a.st = ctx->d_state;
   a.do_finalize = finalize ? 1 : 0;
   a.do_prepare = hp ? 1 : 0;
   if (hp) a.hp = *hp;
@@ -397,6 +397,7 @@ int pt_before_partials(pt_ctx* ctx, hipStream_t stream) {
   const hipStream_t own = ctx->finalize_stream;
   const int rc = pt_flush_pending(ctx, own);
   if (rc != PT_OK || own == stream) return rc;
+  if (!ctx->ev_order) PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_order, hipEventDisableTiming));
   PT_HIP(ctx, hipEventRecord(ctx->ev_order, own));
   PT_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_order, 0));
   return PT_OK;
@@ -477,7 +478,7 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
   if (finalize < 0 || finalize > PT_FINALIZE_CARRY)
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_grad_sqnorm: finalize must be 0, PT_FINALIZE_STRICT or PT_FINALIZE_CARRY");
   if (grad_chunks && n_chunks) {
-    int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st, nullptr);
+    int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);
     if (rc != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
     dim3 grid(ctx->norm_blocks, n_chunks);
     if (ctx->grad_f32)

@@ -78,18 +78,9 @@ static int reserve_slots(pt_ctx* ctx, uint32_t n_slots) {
                      "pt_stream_reserve: hipMalloc of chunk buffer %u (%llu bytes) failed: %s", s,
                      (unsigned long long)slot_bytes(ctx), hipGetErrorString(e));
     // the buffer's five arrays become column C+s of the pointer table
-    const void* p;
-    int rc;
-    p = slot_grad(ctx, s);
-    if ((rc = pt_table_bind(ctx, ROW_GRAD, ctx->C + s, 1, &p, false, nullptr, nullptr)) != PT_OK) return rc;
-    p = slot_master(ctx, s);
-    if ((rc = pt_table_bind(ctx, ROW_MASTER, ctx->C + s, 1, &p, false, nullptr, nullptr)) != PT_OK) return rc;
-    p = slot_m(ctx, s);
-    if ((rc = pt_table_bind(ctx, ROW_M, ctx->C + s, 1, &p, false, nullptr, nullptr)) != PT_OK) return rc;
-    p = slot_v(ctx, s);
-    if ((rc = pt_table_bind(ctx, ROW_V, ctx->C + s, 1, &p, false, nullptr, nullptr)) != PT_OK) return rc;
-    p = slot_p16(ctx, s);
-    if ((rc = pt_table_bind(ctx, ROW_P16, ctx->C + s, 1, &p, false, nullptr, nullptr)) != PT_OK) return rc;
+    const void* p[5] = {slot_grad(ctx, s), slot_master(ctx, s), slot_m(ctx, s), slot_v(ctx, s), slot_p16(ctx, s)};
+    const PtBind binds[5] = {{ROW_GRAD, &p[0]}, {ROW_MASTER, &p[1]}, {ROW_M, &p[2]}, {ROW_V, &p[3]}, {ROW_P16, &p[4]}};
+    if (int rc = pt_table_bind(ctx, binds, 5, ctx->C + s, 1, false, nullptr); rc != PT_OK) return rc;
   }
   PT_HIP(ctx, hipDeviceSynchronize());
   // The three streams made above are given up again for three made while they still exist.  Measured with

@@ -389,20 +389,26 @@ def test_plan_destroyed_before_its_partial_sums_were_read():
         st.close()
 
 
-def test_norm_without_a_context_over_a_chunk_of_several_segments():
-    """More than 4096 blocks of 32768 elements in a chunk: the same bits as the context's recompute."""
-    S = 4096 * 32768 + 8
-    g = torch.empty(S, dtype=torch.bfloat16, device="cuda")
-    synth.normal_16(synth.SEED_GRADS, 1, 0, 0, S, 1e-3, torch.bfloat16, "cuda", out=g)
-    ctx = B.pt_ctx_create(B.PT_BF16, S, 1, None)
+@pytest.mark.parametrize("S,C", [(8, 1), (8, 17), (32768 * 513, 3), (4096 * 32768, 1), (4096 * 32768 + 8, 1)])   # to two segments
+@pytest.mark.parametrize("inf", [False, True])
+def test_norm_without_a_context_by_size(S, C, inf):
+    """Chunks of one block, of more than a lane's share, of one and of two segments: the same bits as the context's recompute, call
+    after call."""
+    g = torch.empty(C, S, dtype=torch.bfloat16, device="cuda")
+    synth.normal_16(synth.SEED_GRADS, 1, 0, 0, C * S, 1e-3, torch.bfloat16, "cuda", out=g.view(-1))
+    if inf:
+        g[C - 1, S - 1] = float("-inf")
+    ctx = B.pt_ctx_create(B.PT_BF16, S, C, None)
     try:
-        B.pt_chunk_grad_sqnorm(ctx, [g], 0, 1, True)
+        B.pt_chunk_grad_sqnorm(ctx, [g[c] for c in range(C)], 0, C, True)
         rep = B.pt_step_report_read(ctx)
-        out, inf = torch.zeros(2, dtype=torch.float64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
-        B.pt_chunk_grad_sqnorm_noalloc(g, B.PT_BF16, S, 1, 1.0, out, inf)
-        assert (float(out[0]), float(out[1]), int(inf[0])) == (rep.sqnorm, rep.norm, rep.found_inf)
+        for _ in range(3):
+            out, found = torch.zeros(2, dtype=torch.float64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+            B.pt_chunk_grad_sqnorm_noalloc(g, B.PT_BF16, S, C, 1.0, out, found)
+            assert int(found[0]) == rep.found_inf == int(inf)
+            assert inf or (float(out[0]), float(out[1])) == (rep.sqnorm, rep.norm)
         want = float(g.double().square().sum())
-        assert abs(rep.sqnorm - want) <= S * 2.0 ** -53 * want
+        assert inf or abs(rep.sqnorm - want) <= C * S * 2.0 ** -53 * want
     finally:
         B.pt_ctx_destroy(ctx)
 
@@ -452,3 +458,29 @@ def test_pack_unpack_and_accumulate_at_the_edges_of_a_tile(dtype, n):
             if plan is not None:
                 B.pt_pack_plan_destroy(plan)
             B.pt_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("C", [1, 48, 49, 192, 193])        # 5 pointers a chunk: one launch of 240, two, four, a copy
+def test_chunk_pointers_of_any_number_reach_the_device(C):
+    """Many small chunks give what one large chunk gives, also after every chunk has moved."""
+    many, one = ChunkedState([8 * C], 8), ChunkedState([8 * C], 8 * C)
+    try:
+        assert many.C == C and one.C == 1
+        hp_b, _, _ = hp_pair()
+        for step in (1, 2):
+            for st in (many, one):
+                st.set_grads(step, std=1.0)
+                st.pack()
+                B.pt_step_override(st.ctx, 0.5, False)
+                st.adamw(hp_b)
+                st.end()
+            for k in ("g16", "w", "m", "v", "p16"):
+                bits = torch.int16 if k in ("g16", "p16") else torch.int32
+                assert torch.equal(getattr(many, k).view(-1).view(bits), getattr(one, k).view(-1).view(bits)), (step, k)
+                # the old places hold something else from now on
+                old = getattr(many, k)
+                setattr(many, k, old.clone())
+                old.fill_(7)
+    finally:
+        many.close()
+        one.close()
