@@ -90,9 +90,10 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 }
 
 // As for pack, DRAM row locality decides: one wave adds 1024 elements, two units per lane in flight, and unused
-// LDS keeps about 12 waves on a compute unit.  Adding 3.3e8 words: 520 us with workgroups of four waves and tiles of 4096
-// taken from two ends of the list, 510 with three of those on a unit, 495 now (6.6 TB/s) - 507 with four units per lane in
-// flight, 513 without the limit, 535-550 with 2048 elements per wave.
+// LDS keeps about 12 waves on a compute unit.  Adding 3.3e8 words: 521 us with workgroups of four waves and tiles of 4096
+// taken from two ends of the list, 510 with three of those on a unit, 493 now (6.6 TB/s) - 507 with four units per lane in
+// flight, 513 without the limit, 535-550 with 2048 elements per wave.  Four launches over 6.7e9 elements whose halves lie in
+// different 96 GiB regions of the memory: 37.5 to 41.5 ms from process to process before, 38.6-38.9 now.
 constexpr uint32_t ACCUM_LDS = 13000;
 
 template <int DT, bool OVERWRITE, bool NORM>
