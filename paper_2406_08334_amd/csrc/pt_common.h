@@ -138,7 +138,7 @@ struct pt_ctx {
   std::vector<uint8_t> chunk_fresh;     // [C] 1 = the chunk's sum of squares was taken in this step (since pt_step_end)
   bool norm_finalized = false;
   bool prepared = false;
-  std::vector<PtPendingReduce> pend_reduce;   // scalar work put off to be fused into one launch (pt_norm.hip), in order
+  PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;
   hipStream_t finalize_stream = nullptr;      // where the pending finalize was asked for
   hipEvent_t ev_order = nullptr;              // made when first needed
@@ -320,11 +320,11 @@ void pt_host_pool_destroy(pt_ctx* ctx);
 // with a context never pays the lookup inside a hot call.
 int pt_static_scratch_setup(void** out);
 // Sums partials into per-chunk values: tile_begin == NULL: chunk first+i owns partials [i*per_chunk, (i+1)*per_chunk),
-// else [tile_begin[c], tile_begin[c+1]).  Put off until the norm is finalized or read; `now`: launched on `stream` at once.
+// else [tile_begin[c], tile_begin[c+1]).  `now`: launched on `stream`, else put off until the norm is read or another call's sums come.
 int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream);
 // The reduction of a plan's tile sums (pack, accumulate).
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);
-// Launches, on `stream`, whatever scalar work of the step has been put off (per-chunk reductions, finalize).
+// Launches, on `stream`, whatever scalar work of the step has been put off (a per-chunk reduction, the finalize).
 // Every call that reads the step's scalars goes through this first.
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream);
 // Before a kernel on `stream` that writes partial sums.

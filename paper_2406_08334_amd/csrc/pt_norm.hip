@@ -244,6 +244,7 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
   __shared__ uint32_t s_flag[SC_SUM / 64], s_f[SC_SUM], s_last;
   const PtPendingReduce& r = a.r;
   const uint32_t tid = threadIdx.x, c = r.first + blockIdx.y;
+  const bool alone = r.segs == 1 && !a.do_finalize && !a.do_prepare;      // a chunk's sum each, and nothing behind it
   uint32_t lo = 0, hi = 0;
   if (r.n) hi = partials_of(r, blockIdx.y, lo);          // a number here
   hi = min(hi, (blockIdx.x + 1) * PT_REDUCE_SEG) + lo;
@@ -276,12 +277,12 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
       st_agent(r.segs > 1 ? r.seg_sum + slot : a.chunk_sq + c, acc);
       st_agent(r.segs > 1 ? r.seg_flag + slot : a.chunk_flag + c, f);
     }
-    const uint32_t total = gridDim.x * gridDim.y;
+    const uint32_t total = alone ? 1u : gridDim.x * gridDim.y;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     s_last = total == 1 || __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1 ? 1u : 0u;
   }
   __syncthreads();
-  if (!s_last) return;
+  if (!s_last || alone) return;
   if (tid == 0) st_agent(a.ticket, 0u);
   double sq = 0.0, norm = 0.0;
   uint32_t inf = 0;
@@ -348,12 +349,12 @@ __global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
 
 // ---- scalar work of a step: put off and fused -----------------------------------------------
 //
-// The reductions of partial sums and the finalize are put off to the first call that needs the result - normally the update,
-// which then derives its constants in the same launch.  They wait in order (a later reduction of a chunk replaces an
-// earlier one) and run on the stream of the call that needs them, which is ordered behind the packs anyway.
-// A plan captured into a graph is different: a replay puts nothing off, and what the graph does not hold would not
-// happen.  Reductions that are captured are launched at once, except for small plans (PT_FUSE_MAX_*), whose
-// capture has always had to hold the finalize too.
+// The finalize is put off to the first call that needs its result - normally the update, which then derives its constants in
+// the same launch - and the reduction of a small plan's partial sums (PT_FUSE_MAX_*) with it: for a small state launches are
+// what a step costs.  What waits runs on the stream of the call that needs it, which is ordered behind the packs anyway.
+// Every other reduction belongs to its own call.  A program that packs eagerly and replays a graph of norm, update and step
+// end makes no call that could launch it, and the plan may be gone by then.  Nor does a larger step gain by putting it off:
+// put off and at once, 14 chunks of 5e6 elements 358 and 357 us, 15 of 2^23 614 and 618 us, 47 of 2^25 7.76 and 7.75 ms.
 
 constexpr uint32_t PT_FUSE_MAX_CHUNKS = 8;
 constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
@@ -371,23 +372,17 @@ static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, 
   return PT_OK;
 }
 
-// Everything put off, the constants of `hp` behind it if there are any: the last reduction shares its launch with the
-// finalize and the constants, earlier ones (several plans in a step) have launches of their own.
+// Everything put off, the constants of `hp` behind it if there are any, in one launch.
 static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
-  const size_t n = ctx->pend_reduce.size();
-  for (size_t k = 0; k + 1 < n; ++k) {
-    const int rc = launch_scalars(ctx, &ctx->pend_reduce[k], false, nullptr, nullptr, stream);
-    if (rc != PT_OK) return rc;
-  }
-  const int rc = launch_scalars(ctx, n ? &ctx->pend_reduce[n - 1] : nullptr, ctx->pend_finalize, hp, mirror, stream);
+  const int rc = launch_scalars(ctx, ctx->pend_reduce.n ? &ctx->pend_reduce : nullptr, ctx->pend_finalize, hp, mirror, stream);
   if (rc != PT_OK) return rc;
-  ctx->pend_reduce.clear();
+  ctx->pend_reduce = PtPendingReduce{};
   ctx->pend_finalize = false;
   return PT_OK;
 }
 
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream) {
-  if (ctx->pend_reduce.empty() && !ctx->pend_finalize) return PT_OK;
+  if (!ctx->pend_reduce.n && !ctx->pend_finalize) return PT_OK;
   return launch_pending(ctx, nullptr, nullptr, stream);
 }
 
@@ -403,28 +398,16 @@ int pt_before_partials(pt_ctx* ctx, hipStream_t stream) {
   return PT_OK;
 }
 
-static bool capturing(hipStream_t stream) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) { (void)hipGetLastError(); return false; }
-  return cs != hipStreamCaptureStatusNone;
-}
-
 int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream) {
   if (r.n == 0) return PT_OK;
-  if (now) {
-    // whatever is pending comes first: a later reduction of the same chunk replaces an earlier one
-    const int rc = pt_flush_pending(ctx, stream);
-    return rc != PT_OK ? rc : launch_scalars(ctx, &r, false, nullptr, nullptr, stream);
-  }
-  return pt_guarded(ctx, "reduction of the partial sums", [&] {
-    // the same partial sums again: taken once, with the values they will then hold
-    if (!ctx->pend_reduce.empty()) {
-      const PtPendingReduce& l = ctx->pend_reduce.back();
-      if (l.plan == r.plan && l.part == r.part && l.first == r.first && l.n == r.n) return int(PT_OK);
-    }
-    ctx->pend_reduce.push_back(r);
-    return int(PT_OK);
-  });
+  // the same partial sums again: taken once, with the values they will then hold
+  if (!now && ctx->pend_reduce.n && ctx->pend_reduce.plan == r.plan) return PT_OK;
+  // whatever is pending comes first: a later reduction of the same chunk replaces an earlier one
+  const int rc = pt_flush_pending(ctx, stream);
+  if (rc != PT_OK) return rc;
+  if (now) return launch_scalars(ctx, &r, false, nullptr, nullptr, stream);
+  ctx->pend_reduce = r;
+  return PT_OK;
 }
 
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
@@ -435,7 +418,7 @@ int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
   r.segs = plan->segs; r.seg_sum = plan->d_seg_sum; r.seg_flag = plan->d_seg_flag;
   r.plan = plan;
   const bool small = plan->touched.size() <= PT_FUSE_MAX_CHUNKS && ctx->C <= 64 && plan->n_tiles <= PT_FUSE_MAX_PARTIALS;
-  return pt_add_chunk_reduce(ctx, r, !small && capturing(stream), stream);
+  return pt_add_chunk_reduce(ctx, r, !small, stream);
 }
 
 int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream) {
@@ -491,7 +474,6 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
       hipLaunchKernelGGL(k_sqnorm<PT_FP16>, grid, dim3(NB_THREADS), NORM_LDS, st, pt_row(ctx, ROW_PACK), first_chunk,
                          ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     PT_LAUNCH_CHECK(ctx, "k_sqnorm");
-    // each chunk has its own partials, so that several recomputes of one step can wait for the finalize together
     PtPendingReduce r;
     r.part = ctx->d_norm_part + size_t(first_chunk) * ctx->norm_blocks;
     r.flag = ctx->d_norm_flag + size_t(first_chunk) * ctx->norm_blocks;
@@ -500,7 +482,7 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
       r.seg_sum = ctx->d_norm_seg_sum + size_t(first_chunk) * r.segs;
       r.seg_flag = ctx->d_norm_seg_flag + size_t(first_chunk) * r.segs;
     }
-    int rc2 = pt_add_chunk_reduce(ctx, r, capturing(st), st);
+    int rc2 = pt_add_chunk_reduce(ctx, r, true, st);
     if (rc2 != PT_OK) return rc2;
     // a recompute covers the whole chunk: whatever plan packed it, its value is complete now
     for (uint32_t c = first_chunk; c < first_chunk + n_chunks; ++c) { ctx->chunk_fresh[c] = 1; ctx->chunk_packed_by[c] = 0; }

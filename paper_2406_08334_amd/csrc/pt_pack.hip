@@ -267,13 +267,10 @@ extern "C" int pt_pack_plan_destroy(pt_pack_plan* plan) {
   (void)hipDeviceSynchronize();
   // a reduction of this plan's partial sums that was put off runs now, before they are freed (the device is idle: any
   // stream will do, and the one of the pack may be gone)
-  if (plan->ctx)
-    for (const PtPendingReduce& r : plan->ctx->pend_reduce)
-      if (r.plan == plan) {
-        (void)pt_flush_pending(plan->ctx, nullptr);
-        (void)hipDeviceSynchronize();
-        break;
-      }
+  if (plan->ctx && plan->ctx->pend_reduce.n && plan->ctx->pend_reduce.plan == plan) {
+    (void)pt_flush_pending(plan->ctx, nullptr);
+    (void)hipDeviceSynchronize();
+  }
   if (plan->ctx)      // a plan that no longer exists does not stand in another plan's way
     for (uint32_t c : plan->touched)
       if (plan->ctx->chunk_packed_by[c] == plan->id) plan->ctx->chunk_packed_by[c] = 0;

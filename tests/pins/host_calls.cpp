@@ -1,0 +1,132 @@
+// What the library asks of the HIP runtime, call by call, on a stand-in for it (fake_hip.h): no GPU, nothing runs.
+// Usage: host_calls <check>.  Exit code 0 = the check held.
+#include "fake_hip.h"
+
+#include "ptchunk.h"
+
+#define EXPECT(cond)                                                                                     \
+  do {                                                                                                   \
+    if (!(cond)) {                                                                                       \
+      fprintf(stderr, "%s:%d: check failed: %s\ncalls:\n%s", __FILE__, __LINE__, #cond, fake::text().c_str()); \
+      return 1;                                                                                          \
+    }                                                                                                    \
+  } while (0)
+#define OK(call) EXPECT((call) == PT_OK)
+
+namespace {
+
+const pt_hparams HP = {1e-4, 0.9, 0.95, 1e-8, 0.1, 1.0};
+
+// C chunks of S elements in device memory and a context for them; the plan's tensors are the chunks themselves, one each.
+struct State {
+  uint64_t S;
+  uint32_t C;
+  pt_ctx* ctx = nullptr;
+  std::vector<void*> g, p;
+  std::vector<float*> w, m, v;
+  std::vector<pt_pack_plan*> plans;
+
+  State(uint32_t n, uint64_t elems, bool fp32 = false) : S(elems), C(n) {
+    if (pt_ctx_create(&ctx, PT_BF16, S, C, nullptr) != PT_OK || (fp32 && pt_ctx_set_option(ctx, "grad_fp32", 1) != PT_OK)) die(nullptr);
+    for (uint32_t c = 0; c < C; ++c) {
+      g.push_back(device(4 * S)); p.push_back(device(2 * S));
+      w.push_back((float*)device(4 * S)); m.push_back((float*)device(4 * S)); v.push_back((float*)device(4 * S));
+    }
+  }
+  ~State() {
+    for (pt_pack_plan* q : plans) pt_pack_plan_destroy(q);
+    pt_ctx_destroy(ctx);
+  }
+  static void die(const pt_ctx* c) { fprintf(stderr, "setup failed: %s\n", pt_last_error(c)); exit(3); }
+  static void* device(size_t n) { void* q = nullptr; (void)hipMalloc(&q, n); return q; }
+  static void* pinned(size_t n) { void* q = nullptr; (void)hipHostMalloc(&q, n, 0); return q; }
+  pt_pack_plan* plan() {
+    std::vector<pt_segment> segs;
+    for (uint32_t c = 0; c < C; ++c) segs.push_back({device(2 * S), 0, S, 0, c, c});
+    pt_pack_plan* q = nullptr;
+    if (pt_pack_plan_create(ctx, segs.data(), C, &q) != PT_OK) die(ctx);
+    plans.push_back(q);
+    return q;
+  }
+  int pack(pt_pack_plan* q, hipStream_t s = nullptr) { return pt_chunk_pack_grads(ctx, q, g.data(), s); }
+  int accum(pt_pack_plan* q, hipStream_t s = nullptr) { return pt_chunk_accum_grads(ctx, q, (float* const*)g.data(), 0, 1, s); }
+  int finalize(int how, hipStream_t s = nullptr) { return pt_chunk_grad_sqnorm(ctx, nullptr, 0, C, how, s); }
+  int update(hipStream_t s = nullptr) { return update(0, C, s); }
+  int update(uint32_t first, uint32_t n, hipStream_t s = nullptr) {
+    return pt_chunk_adamw_step(ctx, &HP, first, n, g.data() + first, w.data() + first, m.data() + first, v.data() + first,
+                               p.data() + first, s);
+  }
+  // one eager step, after which every pointer is known to the device
+  int step(pt_pack_plan* q) {
+    int rc = pack(q);
+    if (rc == PT_OK) rc = finalize(PT_FINALIZE_STRICT);
+    if (rc == PT_OK) rc = update();
+    if (rc == PT_OK) rc = pt_step_end(ctx, nullptr);
+    return rc;
+  }
+};
+
+// A graph of norm, update and step end that is captured without the pack - before one or behind an eager one - holds no
+// reduction, and an eager pack of a plan beyond the fused sizes (8 chunks) has launched its own: replays see the sums of
+// the pack in front of them, whichever plan it was.
+int captured_without_the_pack() {
+  State s(9, 4096);
+  pt_pack_plan* q = s.plan();
+  OK(s.step(q));
+  const hipStream_t cap = fake::stream(0xc0);
+  for (int pending = 0; pending < 2; ++pending) {
+    size_t at = fake::ops.size();
+    if (pending) {
+      OK(s.pack(q));
+      EXPECT(fake::launches("k_scalars", at).size() == 1);
+    }
+    at = fake::ops.size();
+    fake::capturing[0xc0] = true;
+    OK(s.finalize(PT_FINALIZE_CARRY, cap));
+    OK(s.update(cap));
+    OK(pt_step_end(s.ctx, cap));
+    fake::capturing[0xc0] = false;
+    const auto in_graph = fake::launches("k_scalars", at);
+    EXPECT(in_graph.size() == 1 && in_graph[0].grid.x == 1 && in_graph[0].grid.y == 1);
+  }
+  // eager packs between the replays
+  for (int k = 0; k < 3; ++k) {
+    const size_t at = fake::ops.size();
+    OK(s.pack(s.plan()));
+    const auto red = fake::launches("k_scalars", at);
+    EXPECT(red.size() == 1 && red[0].grid.y == 9);
+    OK(pt_step_end(s.ctx, nullptr));
+  }
+  // recomputed from the chunks
+  const size_t at = fake::ops.size();
+  OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 9, 0, nullptr));
+  EXPECT(fake::launches("k_scalars", at).size() == 1);
+  return 0;
+}
+
+// Sums that are put off don't pile up: two plans taken in turn leave one reduction to the call that needs the norm.
+int put_off_at_most_once() {
+  State s(2, 4096, true);
+  pt_pack_plan *a = s.plan(), *b = s.plan();
+  for (int k = 0; k < 50; ++k) { OK(s.accum(a)); OK(s.accum(b)); }
+  const size_t at = fake::ops.size();
+  OK(s.finalize(PT_FINALIZE_STRICT));
+  OK(s.update());
+  EXPECT(fake::launches("k_scalars", at).size() == 1);
+  return 0;
+}
+
+const std::map<std::string, int (*)()> checks = {
+    {"captured_without_the_pack", captured_without_the_pack},
+    {"put_off_at_most_once", put_off_at_most_once},
+};
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const auto it = argc == 2 ? checks.find(argv[1]) : checks.end();
+  if (it == checks.end()) { fprintf(stderr, "no such check\n"); return 2; }
+  const int rc = it->second();
+  if (rc == 0) puts("held");
+  return rc;
+}

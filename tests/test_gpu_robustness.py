@@ -484,3 +484,50 @@ def test_chunk_pointers_of_any_number_reach_the_device(C):
     finally:
         many.close()
         one.close()
+
+
+@pytest.mark.parametrize("pending", [False, True])       # nothing packed at the capture; an eager pack right before it
+def test_graph_of_norm_update_and_step_end_replayed_behind_eager_packs(pending):
+    """A plan of more than eight chunks is reduced by its own call: a graph that was captured without the pack sees the sums
+    of whatever plan packed in front of the replay, and plans may come and go.  Against the same steps without a graph."""
+    sizes, S, C = [9 * 4096 - 5], 4096, 9
+    a, b = ChunkedState(sizes, S), ChunkedState(sizes, S)          # replayed, eager
+    side = torch.cuda.Stream()
+    try:
+        assert a.C == C
+        hp, _, _ = hp_pair(max_norm=0.05)
+        for st in (a, b):                                          # a first step binds every pointer
+            st.set_grads(1)
+            st.step(hp)
+        for st in (a, b):
+            st.set_grads(2)
+        if pending:
+            a.pack()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            B.pt_chunk_grad_sqnorm(a.ctx, None, 0, C, B.PT_FINALIZE_CARRY)
+            a.adamw(hp)
+            a.end()
+        for step in range(2, 7):
+            if step > 2 or not pending:
+                for st in (a, b):
+                    B.pt_pack_plan_destroy(st.plan)
+                    st.grad_src = st.grad_src.clone()              # the gradients have moved
+                    for g in st.segs:
+                        g.src = st.grad_src.data_ptr()
+                    st.plan = B.pt_pack_plan_create(st.ctx, st.segs)
+                    st.set_grads(step, std=1e-3 * step)
+                a.pack()
+            graph.replay()
+            torch.cuda.synchronize()
+            rb = b.step(hp)
+            ra = a.report()
+            assert (ra.norm, ra.found_inf) == (rb.norm, rb.found_inf), step
+            for k in ("g16", "w", "m", "v", "p16"):
+                bits = torch.int16 if k in ("g16", "p16") else torch.int32
+                assert torch.equal(getattr(a, k).view(bits), getattr(b, k).view(bits)), (step, k)
+    finally:
+        torch.cuda.synchronize()
+        a.close()
+        b.close()

@@ -1,0 +1,34 @@
+"""What the library asks of the HIP runtime - launches, streams, events, copies - on a stand-in for it that writes the calls
+down (tests/pins/fake_hip.h).  No GPU: the kernels don't run."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PINS = os.path.join(ROOT, "tests", "pins")
+PKG = os.path.join(ROOT, "paper_2406_08334_amd")
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    from paper_2406_08334_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2406_08334_amd import build
+        build.build()
+    out = str(tmp_path_factory.mktemp("host_calls") / "host_calls")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-rdynamic", "-Wno-unused-result", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I",
+           os.path.join(ROOT, "include"), os.path.join(PINS, "host_calls.cpp"), "-o", out, "-L", PKG, "-lptchunk",
+           "-Wl,-rpath," + PKG, "-Wl,--allow-shlib-undefined"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    return out
+
+
+@pytest.mark.parametrize("check", [
+    "captured_without_the_pack",
+    "put_off_at_most_once",
+])
+def test_calls(exe, check):
+    res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, (res.stdout + res.stderr)[-6000:]
