@@ -140,8 +140,6 @@ struct pt_ctx {
   bool prepared = false;
   PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;
-  hipStream_t finalize_stream = nullptr;      // where the pending finalize was asked for
-  hipEvent_t ev_order = nullptr;              // made when first needed
   bool carry = false;                   // the norm was finalized with PT_FINALIZE_CARRY: some chunks' gradients are elsewhere
   bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them
   pt_hparams prepared_hp{};

@@ -96,7 +96,6 @@ static void ctx_free_all(pt_ctx* ctx) {
   pt_host_pool_destroy(ctx);
   pt_stream_release(ctx);
   if (ctx->ev_scalar) (void)hipEventDestroy(ctx->ev_scalar);
-  if (ctx->ev_order) (void)hipEventDestroy(ctx->ev_order);
   if (ctx->h_state) (void)hipHostFree(ctx->h_state);
   if (ctx->d_nd_begin) (void)hipFree(ctx->d_nd_begin);
   if (ctx->d_nd_ranges) (void)hipFree(ctx->d_nd_ranges);

@@ -386,17 +386,8 @@ int pt_flush_pending(pt_ctx* ctx, hipStream_t stream) {
   return launch_pending(ctx, nullptr, nullptr, stream);
 }
 
-// A call is about to write partial sums: a finalize that is still waiting takes the old ones first, on its own stream.
-int pt_before_partials(pt_ctx* ctx, hipStream_t stream) {
-  if (!ctx->pend_finalize) return PT_OK;
-  const hipStream_t own = ctx->finalize_stream;
-  const int rc = pt_flush_pending(ctx, own);
-  if (rc != PT_OK || own == stream) return rc;
-  if (!ctx->ev_order) PT_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_order, hipEventDisableTiming));
-  PT_HIP(ctx, hipEventRecord(ctx->ev_order, own));
-  PT_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_order, 0));
-  return PT_OK;
-}
+// A call is about to write partial sums: a finalize that is still waiting takes the old ones first.
+int pt_before_partials(pt_ctx* ctx, hipStream_t stream) { return ctx->pend_finalize ? pt_flush_pending(ctx, stream) : int(PT_OK); }
 
 int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream) {
   if (r.n == 0) return PT_OK;
@@ -501,7 +492,6 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
     // The sum over the chunks runs with the first call that needs it: the update (in the launch that
     // derives its constants), a read-back, or pt_step_end.
     ctx->pend_finalize = true;
-    ctx->finalize_stream = st;
     ctx->carry = finalize == PT_FINALIZE_CARRY;
     ctx->norm_finalized = true;
     ctx->prepared = false;

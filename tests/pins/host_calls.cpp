@@ -116,9 +116,32 @@ int put_off_at_most_once() {
   return 0;
 }
 
+// A finalize that waits runs on the stream of the call that needs it out of the way: the stream it was asked for on may be
+// gone by then.
+int finalize_on_a_stream_that_is_gone() {
+  State s(2, 4096);
+  pt_pack_plan* q = s.plan();
+  OK(s.step(q));
+  for (int how = 0; how < 3; ++how) {
+    OK(s.pack(q, fake::stream(0xa0)));
+    OK(s.finalize(PT_FINALIZE_STRICT, fake::stream(0xa0)));
+    const size_t at = fake::ops.size();
+    if (how == 0) OK(s.pack(q, fake::stream(0xb0)));
+    if (how == 1) OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 2, 0, fake::stream(0xb0)));
+    if (how == 2) OK(s.update(fake::stream(0xb0)));
+    EXPECT(fake::ops.size() > at && fake::launches("k_scalars", at).size() >= 1);
+    for (size_t i = at; i < fake::ops.size(); ++i) EXPECT(fake::ops[i].stream != 0xa0);
+    // the waiting norm comes first
+    EXPECT(fake::ops[at].what == "launch" && fake::ops[at].kernel == "k_scalars");
+    OK(pt_step_end(s.ctx, fake::stream(0xb0)));
+  }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
+    {"finalize_on_a_stream_that_is_gone", finalize_on_a_stream_that_is_gone},
 };
 
 }  // namespace

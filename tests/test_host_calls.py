@@ -28,6 +28,7 @@ def exe(tmp_path_factory):
 @pytest.mark.parametrize("check", [
     "captured_without_the_pack",
     "put_off_at_most_once",
+    "finalize_on_a_stream_that_is_gone",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
