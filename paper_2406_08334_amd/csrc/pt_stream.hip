@@ -323,10 +323,12 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
   if (direct) {
     PT_HIP(ctx, hipStreamWaitEvent(ctx->s_comp, ctx->ev_fork, 0));
     rc = pt_launch_adamw_host(ctx, (const uint64_t(*)[5])at.data(), n_chunks, ctx->s_comp, first_chunk);
-    if (rc != PT_OK) return rc;
-    PT_HIP(ctx, hipEventRecord(ctx->ev_direct, ctx->s_comp));
-    ctx->direct_used = ctx->direct_pending = ctx->stream_pending = true;
-    return PT_OK;
+    // also behind a launch that failed: earlier ones of the call may be running, and pt_step_end joins them
+    const hipError_t e = hipEventRecord(ctx->ev_direct, ctx->s_comp);
+    if (e != hipSuccess) (void)hipStreamSynchronize(ctx->s_comp);
+    else ctx->direct_used = ctx->direct_pending = ctx->stream_pending = true;
+    if (rc != PT_OK || e == hipSuccess) return rc;
+    return pt_fail(ctx, PT_ERR_HIP, "pt_chunk_stream_step: hipEventRecord failed: %s", hipGetErrorString(e));
   }
   PT_HIP(ctx, hipStreamWaitEvent(ctx->s_up, ctx->ev_fork, 0));
   PT_HIP(ctx, hipStreamWaitEvent(ctx->s_comp, ctx->ev_fork, 0));

@@ -138,10 +138,51 @@ int finalize_on_a_stream_that_is_gone() {
   return 0;
 }
 
+// Chunks [first, C) of a state in pinned host memory, one allocation per array.
+struct HostPart {
+  std::vector<void*> g, p;
+  std::vector<float*> w, m, v;
+  uint32_t first;
+  HostPart(const State& s, uint32_t from) : first(from) {
+    for (uint32_t c = from; c < s.C; ++c) {
+      g.push_back(State::pinned(2 * s.S)); p.push_back(State::pinned(2 * s.S));
+      w.push_back((float*)State::pinned(4 * s.S)); m.push_back((float*)State::pinned(4 * s.S)); v.push_back((float*)State::pinned(4 * s.S));
+    }
+  }
+  int stream(State& s, hipStream_t st = nullptr) {
+    return pt_chunk_stream_step(s.ctx, &HP, first, uint32_t(g.size()), g.data(), w.data(), m.data(), v.data(), p.data(), st);
+  }
+};
+
+// More host chunks than one launch takes, and a later launch that fails: the step's end still waits for the earlier one.
+int failed_launch_in_place() {
+  State s(40, 4096);
+  HostPart h(s, 0);
+  OK(pt_stream_reserve(s.ctx, 2));
+  OK(pt_step_override(s.ctx, 1.0f, 0, nullptr));
+  const size_t at = fake::ops.size();
+  fake::fail_kernel = "k_adamw_host";
+  fake::fail_after = 1;
+  EXPECT(h.stream(s) == PT_ERR_HIP);
+  fake::fail_after = -1;
+  const auto run = fake::launches("k_adamw_host", at);
+  EXPECT(run.size() == 1);
+  OK(pt_step_end(s.ctx, fake::stream(0xa0)));
+  uintptr_t behind = 0;                          // the last event behind that launch
+  for (size_t i = at; i < fake::ops.size(); ++i)
+    if (fake::ops[i].what == "record" && fake::ops[i].stream == run[0].stream) behind = fake::ops[i].event;
+  bool waits = false;
+  for (size_t i = at; i < fake::ops.size(); ++i)
+    waits = waits || (behind && fake::ops[i].what == "wait" && fake::ops[i].stream == 0xa0 && fake::ops[i].event == behind);
+  EXPECT(waits);
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
     {"finalize_on_a_stream_that_is_gone", finalize_on_a_stream_that_is_gone},
+    {"failed_launch_in_place", failed_launch_in_place},
 };
 
 }  // namespace
