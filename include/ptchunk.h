@@ -345,9 +345,9 @@ int pt_stream_status(const pt_ctx* ctx, int32_t* duplex_tested, int32_t* duplex_
  * (paper: non-persistent chunks are offloaded to CPU memory and moved over the
  * CPU-GPU link, "Hierarchical Chunk Management for Model States"; upload/offload
  * terms of Appendix A.1).  If every array of the range is pinned memory the device can address (hipHostMalloc on
- * the context's device; fp32 arrays 16-byte, 16-bit arrays 8-byte aligned, fp32 gradients 16), one kernel on a side
- * stream updates them in place over the link and the chunk buffers stay unused; h_grad[i] and h_param16[i] may then
- * be one array.  Otherwise, for chunk i of the range, slot = i mod n_slots:
+ * the context's device; fp32 arrays 16-byte, 16-bit arrays 8-byte aligned, fp32 gradients 16) and none that is written
+ * overlaps another one (h_grad[i] and h_param16[i] may be one array), one kernel on a side stream updates them in place
+ * over the link and the chunk buffers stay unused.  Otherwise, for chunk i of the range, slot = i mod n_slots:
  *     upload stream : wait slot free; H2D grad(2B) + master, m, v (12B) per element
  *     compute stream: wait upload;    the same update kernel on the slot
  *     offload stream: wait kernel;    D2H master, m, v (12B) + param16 (2B); slot free

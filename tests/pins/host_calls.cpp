@@ -178,11 +178,37 @@ int failed_launch_in_place() {
   return 0;
 }
 
+// In place only where no array that is written overlaps another one: the copies go in a fixed order (of two chunks with one
+// parameter array the later one's words stay), waves of one launch do not.
+int overlapping_host_arrays() {
+  enum { APART, OWN_GRADIENT, ONE_GRADIENT, ONE_PARAM, NEXT_GRADIENT, OVERLAPPED_PARAM, ONE_MOMENT, N };
+  for (int how = 0; how < N; ++how) {
+    State s(3, 4096);
+    HostPart h(s, 0);
+    OK(pt_stream_reserve(s.ctx, 2));
+    if (how == OWN_GRADIENT) h.p = h.g;
+    if (how == ONE_GRADIENT) h.g[2] = h.g[0];                                   // only read
+    if (how == ONE_PARAM) h.p[2] = h.p[0];
+    if (how == NEXT_GRADIENT) h.p[0] = h.g[1];
+    if (how == OVERLAPPED_PARAM) { h.p[0] = State::pinned(4 * 4096); h.p[1] = (char*)h.p[0] + 4096; }
+    if (how == ONE_MOMENT) h.v[1] = h.m[1];
+    OK(pt_step_override(s.ctx, 1.0f, 0, nullptr));
+    const size_t at = fake::ops.size();
+    OK(h.stream(s));
+    const bool in_place = how <= ONE_GRADIENT;
+    EXPECT(fake::launches("k_adamw_host", at).size() == (in_place ? 1u : 0u));
+    EXPECT(fake::launches("k_adamw", at).size() == (in_place ? 0u : 3u));
+    OK(pt_step_end(s.ctx, nullptr));
+  }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
     {"finalize_on_a_stream_that_is_gone", finalize_on_a_stream_that_is_gone},
     {"failed_launch_in_place", failed_launch_in_place},
+    {"overlapping_host_arrays", overlapping_host_arrays},
 };
 
 }  // namespace

@@ -30,6 +30,7 @@ def exe(tmp_path_factory):
     "put_off_at_most_once",
     "finalize_on_a_stream_that_is_gone",
     "failed_launch_in_place",
+    "overlapping_host_arrays",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
