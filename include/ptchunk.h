@@ -379,7 +379,8 @@ int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t first_chunk
  * Model States", Appendix A.1 T_CPU_OPTIM).  Same arithmetic and the same nine fp32 constants
  * as pt_chunk_adamw_step - the scalar kernel of the step leaves them in pinned host memory as
  * well, and the call waits for the event behind that kernel only, not for bulk work queued after
- * it - so results are bit-identical to the device paths.  BLOCKING: returns when n_threads host threads (this one
+ * it (one exception: a context's first such call, in a step whose first update call was
+ * pt_chunk_stream_step or took every chunk, waits for what `stream` holds) - so results are bit-identical to the device paths.  BLOCKING: returns when n_threads host threads (this one
  * included) have updated master, m, v and param16 of chunks [first_chunk, first_chunk+n_chunks)
  * in place.  Queue pt_chunk_adamw_step for the resident chunks first and the two run side by
  * side.  h_*: host arrays of n_chunks host pointers (pinned or not).  A skipped step leaves the

@@ -503,7 +503,7 @@ extern "C" int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t f
   const PtBind binds[5] = {{ROW_GRAD, grad}, {ROW_MASTER, (const void* const*)master}, {ROW_M, (const void* const*)m},
                            {ROW_V, (const void* const*)v}, {ROW_P16, (const void* const*)param16}};
   if ((rc = pt_table_bind(ctx, binds, 5, first_chunk, n_chunks, false, st)) != PT_OK) return rc;
-  if ((rc = pt_prepare_consts(ctx, hp, st)) != PT_OK) return rc;
+  if ((rc = pt_prepare_consts(ctx, hp, n_chunks < ctx->C, st)) != PT_OK) return rc;
   return pt_launch_adamw(ctx, first_chunk, n_chunks, st, false, first_chunk, ctx->opt_zero_grads != 0);
 }
 

@@ -140,7 +140,6 @@ struct pt_ctx {
   bool prepared = false;
   PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;
-  bool carry = false;                   // the norm was finalized with PT_FINALIZE_CARRY: some chunks' gradients are elsewhere
   bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them
   pt_hparams prepared_hp{};
 
@@ -328,7 +327,7 @@ int pt_flush_pending(pt_ctx* ctx, hipStream_t stream);
 // Before a kernel on `stream` that writes partial sums.
 int pt_before_partials(pt_ctx* ctx, hipStream_t stream);
 // Derives this step's update constants from `hp` if that has not happened yet - in one launch together
-// with any pending reduction and finalize.
-int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream);
+// with any pending reduction and finalize.  host_part: chunks the calling update leaves out may be updated on the host.
+int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStream_t stream);
 // Makes sure the prepared constants are on their way to h_state, with ev_scalar behind them.
 int pt_mirror_consts(pt_ctx* ctx, hipStream_t stream);

@@ -41,12 +41,12 @@ extern "C" int pt_chunk_host_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint3
 
   // The step's constants come from the device, so that host and device updates use the same
   // bits.  Only the scalar kernels are waited for, not the bulk work queued behind them.
-  int rc = pt_prepare_consts(ctx, hp, st);
+  int rc = pt_prepare_consts(ctx, hp, true, st);
   if (rc != PT_OK) return rc;
   // ev_scalar is right behind the scalar kernel of this step (pt_prepare_consts), which left the constants in pinned host
   // memory: waiting for that event is all it takes - no stream of the library's own, whose copy could end up behind the
-  // resident update in a shared hardware queue.  A context that has shown no sign of a host part before its first host-side update gets
-  // the event here, behind whatever is queued on the stream.
+  // resident update in a shared hardware queue.  Where an update of every chunk, or a streamed one, prepared the step and this is
+  // the context's first host-side call, the event comes here instead, behind whatever is queued on the stream.
   rc = pt_mirror_consts(ctx, st);
   if (rc != PT_OK) return rc;
   PT_HIP(ctx, hipEventSynchronize(ctx->ev_scalar));

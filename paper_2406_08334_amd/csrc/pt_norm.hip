@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
   }
 }
 
-// The constants of a prepared step into pinned host memory, for a host-side update nobody had announced.
+// The constants of a prepared step into pinned host memory, for a host-side update that nothing pointed to.
 __global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
   if (threadIdx.x < 9) mirror->c[threadIdx.x] = st->c[threadIdx.x];
   if (threadIdx.x == 9) mirror->skip = st->skip;
@@ -412,15 +412,15 @@ int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
   return pt_add_chunk_reduce(ctx, r, !small, stream);
 }
 
-int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, hipStream_t stream) {
+int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStream_t stream) {
   if (ctx->prepared) {
     if (std::memcmp(&ctx->prepared_hp, hp, sizeof *hp) == 0) return PT_OK;
     if (ctx->stream_pending)
       return pt_fail(ctx, PT_ERR_STATE, "hyper-parameters changed while a streamed update of this step is in flight");
   }
-  // The event that lets a host-side update read the constants early costs the update behind it 5 us: recorded where such a
-  // call is likely - there was one before, or chunks carry their norms and no chunk buffers are reserved.
-  const bool mirror = ctx->host_pool != nullptr || (ctx->carry && !ctx->n_slots);
+  // The event that lets a host-side update read the constants early costs the update behind it 5 us: recorded only where such
+  // a call can be on its way, or has been made before.
+  const bool mirror = host_part || ctx->host_pool != nullptr;
   ctx->mirrored = false;
   const int rc = launch_pending(ctx, hp, mirror ? ctx->h_state_dev : nullptr, stream);
   if (rc != PT_OK) return rc;
@@ -492,7 +492,6 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
     // The sum over the chunks runs with the first call that needs it: the update (in the launch that
     // derives its constants), a read-back, or pt_step_end.
     ctx->pend_finalize = true;
-    ctx->carry = finalize == PT_FINALIZE_CARRY;
     ctx->norm_finalized = true;
     ctx->prepared = false;
   }

@@ -322,7 +322,7 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
 
   int rc = look_at_last_step(ctx);
   if (rc != PT_OK) return rc;
-  rc = pt_prepare_consts(ctx, hp, st);
+  rc = pt_prepare_consts(ctx, hp, false, st);      // the other chunks are resident ones, as a rule
   if (rc != PT_OK) return rc;
   std::vector<uint64_t> at;
   bool direct = false;

@@ -203,12 +203,48 @@ int overlapping_host_arrays() {
   return 0;
 }
 
+// The host-side update waits for an event behind the step's scalar kernel and in front of the resident update that was
+// queued before it - from a context's first host-side call on, with chunk buffers reserved or without.
+int host_update_beside_the_resident_one() {
+  for (int buffers = 0; buffers < 2; ++buffers) {
+    State s(3, 4096);
+    HostPart h(s, 2);
+    if (buffers) OK(pt_stream_reserve(s.ctx, 2));
+    pt_pack_plan* q = s.plan();
+    for (int step = 0; step < 2; ++step) {
+      OK(s.pack(q));
+      OK(s.finalize(PT_FINALIZE_STRICT));
+      const size_t at = fake::ops.size();
+      OK(s.update(0, 2));
+      OK(pt_chunk_host_adamw_step(s.ctx, &HP, 2, 1, h.g.data(), h.w.data(), h.m.data(), h.v.data(), h.p.data(), 2, nullptr));
+      size_t event = 0, update = 0;
+      uintptr_t waited = 0;
+      for (size_t i = at; i < fake::ops.size(); ++i) {
+        if (fake::ops[i].what == "launch" && fake::ops[i].kernel == "k_adamw") update = i;
+        if (fake::ops[i].what == "sync event") waited = fake::ops[i].event;
+      }
+      for (size_t i = at; i < fake::ops.size(); ++i)
+        if (fake::ops[i].what == "record" && fake::ops[i].event == waited) event = i;
+      EXPECT(waited && event && update && event < update);
+      OK(pt_step_end(s.ctx, nullptr));
+    }
+  }
+  // and a step that updates every chunk on the device records no event
+  State s(3, 4096);
+  pt_pack_plan* q = s.plan();
+  const size_t at = fake::ops.size();
+  OK(s.step(q));
+  for (size_t i = at; i < fake::ops.size(); ++i) EXPECT(fake::ops[i].what != "record");
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
     {"finalize_on_a_stream_that_is_gone", finalize_on_a_stream_that_is_gone},
     {"failed_launch_in_place", failed_launch_in_place},
     {"overlapping_host_arrays", overlapping_host_arrays},
+    {"host_update_beside_the_resident_one", host_update_beside_the_resident_one},
 };
 
 }  // namespace

@@ -31,6 +31,7 @@ def exe(tmp_path_factory):
     "finalize_on_a_stream_that_is_gone",
     "failed_launch_in_place",
     "overlapping_host_arrays",
+    "host_update_beside_the_resident_one",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
