@@ -8,9 +8,13 @@
 // lane-serial, then a 64-lane shuffle tree, then the four waves through LDS, then
 // one slot per block - no floating-point atomics, so results are bitwise reproducible.
 //
-// Unused LDS (NORM_LDS) leaves four workgroups on a compute unit instead of eight: fewer DRAM rows in use.  8.1e8 fp16 words
-// 245 -> 239 us with the scalar kernel (6.9 TB/s; three or five workgroups 240 and 242, ten 260); small arenas are
-// indifferent to it.
+// Unused LDS (norm_lds) leaves four workgroups on a compute unit instead of eight, which large arenas read a little faster,
+// presumably for fewer DRAM rows in use.  With the scalar kernel, eight and four: 8.1e8 words 242 and 240 us (6.8 TB/s),
+// 2.1e8 72.3 and 69.8, 9e7 34.0 and 33.2.  The line is where a second set of 1024 workgroups is three quarters full:
+// below it eight at once are faster (4e7 words 19.2 and 20.0 us, 5e7 in fp16 21.4 and 22.5) or it makes no
+// difference (5.8e7 24.3 and 24.5, fp16 24.8 and 24.5; up to one full set).  fp32 chunks are twice the bytes for as many
+// workgroups and gain from four full sets on: 4.2e7 words 31.5 and 36.4 us with the step end, 1.0e8 66.3 and 66.8, 2.0e8
+// 125.1 and 122.8.
 #include "pt_common.h"
 
 #include <hip/hip_fp16.h>
@@ -23,7 +27,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NB_THREADS = PT_REDUCE_THREADS;
-constexpr uint32_t NORM_LDS = 36000;
+inline uint32_t norm_lds(uint64_t elems, bool fp32) { return elems >= (fp32 ? 4096ull : 1792ull) * PT_NORM_BLOCK_ELEMS ? 36000 : 0; }
 
 template <int DT>
 __device__ __forceinline__ double word_to_f64(uint32_t w16) {
@@ -455,14 +459,15 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);
     if (rc != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
     dim3 grid(ctx->norm_blocks, n_chunks);
+    const uint32_t lds = norm_lds(ctx->S * n_chunks, ctx->grad_f32);
     if (ctx->grad_f32)
-      hipLaunchKernelGGL(k_sqnorm_f32, grid, dim3(NB_THREADS), NORM_LDS, st, pt_row(ctx, ROW_PACK), first_chunk,
+      hipLaunchKernelGGL(k_sqnorm_f32, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
                          ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     else if (ctx->dtype == PT_BF16)
-      hipLaunchKernelGGL(k_sqnorm<PT_BF16>, grid, dim3(NB_THREADS), NORM_LDS, st, pt_row(ctx, ROW_PACK), first_chunk,
+      hipLaunchKernelGGL(k_sqnorm<PT_BF16>, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
                          ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     else
-      hipLaunchKernelGGL(k_sqnorm<PT_FP16>, grid, dim3(NB_THREADS), NORM_LDS, st, pt_row(ctx, ROW_PACK), first_chunk,
+      hipLaunchKernelGGL(k_sqnorm<PT_FP16>, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
                          ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     PT_LAUNCH_CHECK(ctx, "k_sqnorm");
     PtPendingReduce r;
@@ -603,14 +608,15 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   PtStaticScratch* sc = static_cast<PtStaticScratch*>(base);
   hipStream_t st = (hipStream_t)stream;
   dim3 grid((uint32_t)blocks_per_chunk, n_chunks);
+  const uint32_t lds = norm_lds(chunk_elems * n_chunks, false);
   // Nothing here has to start at zero: each launch writes every partial and per-chunk slot that the
   // next one reads (n_chunks * blocks_per_chunk partials, n_chunks sums), so stale contents of an
   // earlier, larger call are never read.
   if (dtype == PT_BF16)
-    hipLaunchKernelGGL(k_sqnorm_arena<PT_BF16>, grid, dim3(NB_THREADS), NORM_LDS, st, grad_arena, chunk_elems, loss_scale,
+    hipLaunchKernelGGL(k_sqnorm_arena<PT_BF16>, grid, dim3(NB_THREADS), lds, st, grad_arena, chunk_elems, loss_scale,
                        sc->part, sc->flag, &sc->ticket);
   else
-    hipLaunchKernelGGL(k_sqnorm_arena<PT_FP16>, grid, dim3(NB_THREADS), NORM_LDS, st, grad_arena, chunk_elems, loss_scale,
+    hipLaunchKernelGGL(k_sqnorm_arena<PT_FP16>, grid, dim3(NB_THREADS), lds, st, grad_arena, chunk_elems, loss_scale,
                        sc->part, sc->flag, &sc->ticket);
   if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_sqnorm_arena failed");
   ScalarArgs a{};

@@ -2,6 +2,8 @@
 // Usage: host_calls <check>.  Exit code 0 = the check held.
 #include "fake_hip.h"
 
+#include <tuple>
+
 #include "ptchunk.h"
 
 #define EXPECT(cond)                                                                                     \
@@ -238,6 +240,33 @@ int host_update_beside_the_resident_one() {
   return 0;
 }
 
+// The norm holds its workgroups to four a compute unit (1024 at once) from 1792 of them on, with fp32 chunks from 4096:
+// smaller arenas are read faster, or as fast, by eight.
+int norm_occupancy_by_size() {
+  for (const auto& [blocks, limited] : {std::pair{1u, false}, {1024u, false}, {1025u, false}, {1791u, false}, {1792u, true}, {4000u, true}}) {
+    void* g = State::device(16);
+    double out[2];
+    int32_t inf;
+    size_t at = fake::ops.size();
+    OK(pt_chunk_grad_sqnorm_noalloc(g, PT_BF16, 32768, blocks, 1.0, out, &inf, nullptr));
+    auto run = fake::launches("k_sqnorm_arena", at);
+    EXPECT(run.size() == 1 && run[0].grid.x * run[0].grid.y == blocks && (run[0].lds != 0) == limited);
+  }
+  const void* at16[4096];
+  for (const void*& q : at16) q = State::device(16);
+  for (const auto& [blocks, fp32, limited] : {std::tuple{1791u, false, false}, {1792u, false, true}, {4095u, true, false}, {4096u, true, true}}) {
+    pt_ctx* ctx = nullptr;
+    OK(pt_ctx_create(&ctx, PT_FP16, 32768, blocks, nullptr));
+    OK(pt_ctx_set_option(ctx, "grad_fp32", fp32));
+    const size_t at = fake::ops.size();
+    OK(pt_chunk_grad_sqnorm(ctx, at16, 0, blocks, 0, nullptr));
+    const auto run = fake::launches(fp32 ? "k_sqnorm_f32" : "k_sqnorm", at);
+    EXPECT(run.size() == 1 && (run[0].lds != 0) == limited);
+    OK(pt_ctx_destroy(ctx));
+  }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -245,6 +274,7 @@ const std::map<std::string, int (*)()> checks = {
     {"failed_launch_in_place", failed_launch_in_place},
     {"overlapping_host_arrays", overlapping_host_arrays},
     {"host_update_beside_the_resident_one", host_update_beside_the_resident_one},
+    {"norm_occupancy_by_size", norm_occupancy_by_size},
 };
 
 }  // namespace
