@@ -86,12 +86,17 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // DIR 1: chunk -> tensor (unpack), no reduction.
 // NTS: non-temporal stores; without them the gradient words stay in the Infinity Cache for the update (pt_grads_cached).
 //
-// As for the update, DRAM row locality decides: few bytes in flight, in address order.  One wave moves 4 KiB and
-// unused LDS (PACK_LDS, UNPACK_LDS) keeps about 17 and 14 of them on a compute unit.  Against workgroups of four waves
-// with 16 KiB, eight on a unit: pack of 1.56e9 elements 1012 -> 957 us (6.5 TB/s), 6.7e8 fp16 words 438 -> 412; the same
-// below 1.3e8; unpack of 6.7e8 425 -> 404 us (6.6 TB/s).  2 KiB per wave cost pack 20 % (too little work behind the look-up
-// of a tile), 8 KiB 6-8 %, no limit 1-3 %.  Two vectors per lane in flight suit unpack better (404 against 411 us), four pack.
-constexpr uint32_t PACK_LDS = 9000, UNPACK_LDS = 11500;
+// Few bytes in flight, in address order, are moved fastest (as in the update).  One wave moves 4 KiB and unused LDS keeps
+// about 17 waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of 1.56e9
+// elements 1012 -> 957 us (6.5 TB/s), 6.7e8 fp16 words 438 -> 412; the same below 1.3e8; unpack of 6.7e8 425 -> 404 us
+// (6.6 TB/s).  2 KiB per wave cost pack 20 % (too little work behind the look-up of a tile), 8 KiB 6-8 %.  Two vectors per
+// lane in flight suit unpack better (404 against 411 us), four pack.
+// The limit itself is worth little to pack (6.7e8 fp16 words 418 -> 413 us, nothing at 0.8e6, 7e6, 6e7, 1.2e8 and 4e8) and 2-5 %
+// to unpack: 1e7 words 8.1 -> 7.9 us, 3.7e7 24.7 -> 23.7, 1.25e8 79.8 -> 77.0, 6.3e8 404 -> 386.  About 14 waves are
+// better still for unpack from 2^28 words on (4.1e8 262.5 and 259.2 us, 1.4e9 858 and 849) and worse below (2.0e7 13.7 and
+// 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6).
+constexpr uint32_t PACK_LDS = 9000, UNPACK_LARGE_LDS = 11500;
+constexpr uint64_t UNPACK_LARGE = uint64_t(1) << 28;
 
 template <int DT, int DIR, bool NTS>
 __global__ void __launch_bounds__(PK_THREADS)
@@ -304,7 +309,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
     if ((rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
   dim3 grid(plan->n_tiles * plan->subs);
-  const size_t lds = DIR == 1 ? UNPACK_LDS : PACK_LDS;
+  const size_t lds = DIR == 1 && plan->total_elems >= UNPACK_LARGE ? UNPACK_LARGE_LDS : PACK_LDS;
   const bool bf16 = ctx->dtype == PT_BF16, nts = DIR == 1 || !pt_grads_cached(ctx);
   auto kern = nts ? (bf16 ? k_pack<PT_BF16, DIR, true> : k_pack<PT_FP16, DIR, true>)
                   : (bf16 ? k_pack<PT_BF16, DIR, DIR == 1> : k_pack<PT_FP16, DIR, DIR == 1>);

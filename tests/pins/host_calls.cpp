@@ -267,6 +267,28 @@ int norm_occupancy_by_size() {
   return 0;
 }
 
+// Unpack holds fewer waves on a compute unit from 2^28 elements of the plan on.
+int unpack_occupancy_by_size() {
+  size_t lds[2];
+  for (int large = 0; large < 2; ++large) {
+    State s(1, 1 << 20);
+    pt_ctx* ctx = nullptr;
+    const uint64_t n = (1ull << 28) - (large ? 0 : 8);
+    OK(pt_ctx_create(&ctx, PT_BF16, 1ull << 28, 1, nullptr));
+    const pt_segment seg = {s.g[0], 0, n, 0, 0, 0};
+    pt_pack_plan* q = nullptr;
+    OK(pt_pack_plan_create(ctx, &seg, 1, &q));
+    const size_t at = fake::ops.size();
+    OK(pt_chunk_unpack(ctx, q, (const void* const*)s.g.data(), nullptr));
+    EXPECT(fake::launches("k_pack", at).size() == 1);
+    lds[large] = fake::launches("k_pack", at)[0].lds;
+    OK(pt_pack_plan_destroy(q));
+    OK(pt_ctx_destroy(ctx));
+  }
+  EXPECT(lds[0] == 9000 && lds[1] == 11500);
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -275,6 +297,7 @@ const std::map<std::string, int (*)()> checks = {
     {"overlapping_host_arrays", overlapping_host_arrays},
     {"host_update_beside_the_resident_one", host_update_beside_the_resident_one},
     {"norm_occupancy_by_size", norm_occupancy_by_size},
+    {"unpack_occupancy_by_size", unpack_occupancy_by_size},
 };
 
 }  // namespace

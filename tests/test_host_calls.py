@@ -33,6 +33,7 @@ def exe(tmp_path_factory):
     "overlapping_host_arrays",
     "host_update_beside_the_resident_one",
     "norm_occupancy_by_size",
+    "unpack_occupancy_by_size",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
