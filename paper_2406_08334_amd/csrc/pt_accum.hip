@@ -89,12 +89,16 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
   }
 }
 
-// As for pack, DRAM row locality decides: one wave adds 1024 elements, two units per lane in flight, and unused
-// LDS keeps about 12 waves on a compute unit.  Adding 3.3e8 words: 521 us with workgroups of four waves and tiles of 4096
+// As in pack: one wave adds 1024 elements, two units per lane in flight, and unused LDS (accum_lds) keeps 12 or 17 waves on a
+// compute unit.  Adding 3.3e8 words: 521 us with workgroups of four waves and tiles of 4096
 // taken from two ends of the list, 510 with three of those on a unit, 493 now (6.6 TB/s) - 507 with four units per lane in
-// flight, 513 without the limit, 535-550 with 2048 elements per wave.  Four launches over 6.7e9 elements whose halves lie in
+// flight, 513 without the limit, 535-550 with 2048 elements per wave.
+// 12 waves suit large sums; small ones, and a first micro-batch that only writes its sums (6 bytes an element instead of 10),
+// want 17.  With 12 and 17, adding: 4e6 words 9.4 and 8.7 us, 1.5e7 26.0 and 25.1, 3e7 48.0 and 47.1, 6e7 91.8 and 92.7,
+// 3.3e8 493 and 507; writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298; writing with the norm: 3e7 39.7 and
+// 34.3, 3.3e8 401 and 326.  Four launches over 6.7e9 elements whose halves lie in
 // different 96 GiB regions of the memory: 37.5 to 41.5 ms from process to process before, 38.6-38.9 now.
-constexpr uint32_t ACCUM_LDS = 13000;
+inline uint32_t accum_lds(bool overwrite, uint64_t elems) { return overwrite || elems < (1ull << 25) ? 9000 : 13000; }
 
 template <int DT, bool OVERWRITE, bool NORM>
 __global__ void __launch_bounds__(AC_THREADS)
@@ -175,7 +179,7 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   if (take_norm && (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
-  hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), ACCUM_LDS, st, plan->d_tiles, pt_row(ctx, ROW_PACK),
+  hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st, plan->d_tiles, pt_row(ctx, ROW_PACK),
                      plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {

@@ -267,25 +267,44 @@ int norm_occupancy_by_size() {
   return 0;
 }
 
-// Unpack holds fewer waves on a compute unit from 2^28 elements of the plan on.
-int unpack_occupancy_by_size() {
-  size_t lds[2];
-  for (int large = 0; large < 2; ++large) {
-    State s(1, 1 << 20);
-    pt_ctx* ctx = nullptr;
-    const uint64_t n = (1ull << 28) - (large ? 0 : 8);
-    OK(pt_ctx_create(&ctx, PT_BF16, 1ull << 28, 1, nullptr));
-    const pt_segment seg = {s.g[0], 0, n, 0, 0, 0};
-    pt_pack_plan* q = nullptr;
-    OK(pt_pack_plan_create(ctx, &seg, 1, &q));
-    const size_t at = fake::ops.size();
-    OK(pt_chunk_unpack(ctx, q, (const void* const*)s.g.data(), nullptr));
-    EXPECT(fake::launches("k_pack", at).size() == 1);
-    lds[large] = fake::launches("k_pack", at)[0].lds;
-    OK(pt_pack_plan_destroy(q));
-    OK(pt_ctx_destroy(ctx));
+// A context and a plan of n elements in one chunk; the pointers are only looked at.
+struct OnePlan {
+  pt_ctx* ctx = nullptr;
+  pt_pack_plan* q = nullptr;
+  void* at = nullptr;
+  OnePlan(uint64_t n, bool fp32 = false) {
+    at = State::device(16);
+    const pt_segment seg = {at, 0, n, 0, 0, 0};
+    if (pt_ctx_create(&ctx, PT_BF16, (n + 7) / 8 * 8, 1, nullptr) != PT_OK || pt_ctx_set_option(ctx, "grad_fp32", fp32) != PT_OK ||
+        pt_pack_plan_create(ctx, &seg, 1, &q) != PT_OK)
+      State::die(ctx);
   }
-  EXPECT(lds[0] == 9000 && lds[1] == 11500);
+  ~OnePlan() {
+    pt_pack_plan_destroy(q);
+    pt_ctx_destroy(ctx);
+  }
+};
+
+// Unpack holds fewer waves on a compute unit the larger the plan is: lines at 2^24 and 2^28 elements.
+int unpack_occupancy_by_size() {
+  for (const auto& [n, lds] : {std::pair{(1ull << 24) - 1, size_t(0)}, {1ull << 24, 9000}, {(1ull << 28) - 1, 9000}, {1ull << 28, 11500}}) {
+    OnePlan p(n);
+    const size_t at = fake::ops.size();
+    OK(pt_chunk_unpack(p.ctx, p.q, &p.at, nullptr));
+    EXPECT(fake::launches("k_pack", at).size() == 1 && fake::launches("k_pack", at)[0].lds == lds);
+  }
+  return 0;
+}
+
+// Adding to sums holds fewer waves on a compute unit from 2^25 elements on; writing them never does.
+int accumulate_occupancy_by_size() {
+  for (const auto& [n, overwrite, lds] : {std::tuple{(1ull << 25) - 1, 0, 9000u}, {1ull << 25, 0, 13000u}, {1ull << 25, 1, 9000u}}) {
+    OnePlan p(n, true);
+    const size_t at = fake::ops.size();
+    float* acc = (float*)p.at;
+    OK(pt_chunk_accum_grads(p.ctx, p.q, &acc, overwrite, 0, nullptr));
+    EXPECT(fake::launches("k_accum", at).size() == 1 && fake::launches("k_accum", at)[0].lds == lds);
+  }
   return 0;
 }
 
@@ -298,6 +317,7 @@ const std::map<std::string, int (*)()> checks = {
     {"host_update_beside_the_resident_one", host_update_beside_the_resident_one},
     {"norm_occupancy_by_size", norm_occupancy_by_size},
     {"unpack_occupancy_by_size", unpack_occupancy_by_size},
+    {"accumulate_occupancy_by_size", accumulate_occupancy_by_size},
 };
 
 }  // namespace

@@ -34,6 +34,7 @@ def exe(tmp_path_factory):
     "host_update_beside_the_resident_one",
     "norm_occupancy_by_size",
     "unpack_occupancy_by_size",
+    "accumulate_occupancy_by_size",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
