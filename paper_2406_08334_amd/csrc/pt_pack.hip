@@ -53,10 +53,14 @@ __device__ __forceinline__ void store_vec(const u32x4& q, PT_GLOBAL u32x4* p) {
 
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));   // global memory takes a 16-byte load at any address
 
-template <bool ALIGNED>
+// Off the alignment every line at a lane's or a wave's end is read twice, and unpack takes it without the hint: with and
+// without, from memory 15e6 words 16.4 and 16.2 us, 6e7 51.5 and 51.8 (8-byte aligned 49.4 and 47.0), 3.3e8 251 and 252
+// (237 and 224); from the Infinity Cache 15e6 14.9 and 10.2, 6e7 49.8 and 33.7.  Pack, whose words come from a backward pass,
+// is 5 % faster with it from memory (3e7 words 23.6 and 24.9 us).
+template <int DIR, bool ALIGNED>
 __device__ __forceinline__ u32x4 load_vec(const PT_GLOBAL uint16_t* s) {
   if (ALIGNED) return __builtin_nontemporal_load((const PT_GLOBAL u32x4*)s);
-  return __builtin_nontemporal_load((const PT_GLOBAL u32x4_a2*)s);
+  return DIR == 1 ? *(const PT_GLOBAL u32x4_a2*)s : __builtin_nontemporal_load((const PT_GLOBAL u32x4_a2*)s);
 }
 
 // nvec vectors from sb to db: U per lane in flight.
@@ -68,7 +72,7 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
   for (; i + (U - 1) * PK_THREADS < nvec; i += U * PK_THREADS) {
     u32x4 q[U];
 #pragma unroll
-    for (int r = 0; r < U; ++r) q[r] = load_vec<ALIGNED>(sb + size_t(i + r * PK_THREADS) * 8);
+    for (int r = 0; r < U; ++r) q[r] = load_vec<DIR, ALIGNED>(sb + size_t(i + r * PK_THREADS) * 8);
 #pragma unroll
     for (int r = 0; r < U; ++r) store_vec<NTS>(q[r], db + i + r * PK_THREADS);
     if (DIR == 0)
@@ -76,7 +80,7 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
       for (int r = 0; r < U; ++r) take_vec<DT>(q[r], inv_scale, a0, a1, flag);
   }
   for (; i < nvec; i += PK_THREADS) {
-    const u32x4 q = load_vec<ALIGNED>(sb + size_t(i) * 8);
+    const u32x4 q = load_vec<DIR, ALIGNED>(sb + size_t(i) * 8);
     store_vec<NTS>(q, db + i);
     if (DIR == 0) take_vec<DT>(q, inv_scale, a0, a1, flag);
   }
@@ -94,9 +98,9 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // The limit itself is worth little to pack (6.7e8 fp16 words 418 -> 413 us, nothing at 0.8e6, 7e6, 6e7, 1.2e8 and 4e8) and 2-5 %
 // to unpack: 1e7 words 8.1 -> 7.9 us, 3.7e7 24.7 -> 23.7, 1.25e8 79.8 -> 77.0, 6.3e8 404 -> 386.  About 14 waves are
 // better still for unpack from 2^28 words on (4.1e8 262.5 and 259.2 us, 1.4e9 858 and 849) and worse below (2.0e7 13.7 and
-// 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6).
-constexpr uint32_t PACK_LDS = 9000, UNPACK_LARGE_LDS = 11500;
-constexpr uint64_t UNPACK_LARGE = uint64_t(1) << 28;
+// 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6); below 2^24 words it runs without a limit (1.5e7 11.6, with one 11.8).
+constexpr uint32_t PACK_LDS = 9000;
+inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : elems < (1ull << 28) ? 9000 : 11500; }
 
 template <int DT, int DIR, bool NTS>
 __global__ void __launch_bounds__(PK_THREADS)
@@ -309,7 +313,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
     if ((rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
   dim3 grid(plan->n_tiles * plan->subs);
-  const size_t lds = DIR == 1 && plan->total_elems >= UNPACK_LARGE ? UNPACK_LARGE_LDS : PACK_LDS;
+  const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : PACK_LDS;
   const bool bf16 = ctx->dtype == PT_BF16, nts = DIR == 1 || !pt_grads_cached(ctx);
   auto kern = nts ? (bf16 ? k_pack<PT_BF16, DIR, true> : k_pack<PT_FP16, DIR, true>)
                   : (bf16 ? k_pack<PT_BF16, DIR, DIR == 1> : k_pack<PT_FP16, DIR, DIR == 1>);
