@@ -143,9 +143,9 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
 /* Options (host state only, take effect at the next call).  Launch shape - none of these
  * changes a result bit:
  *   "adamw_grid"    workgroups of the update kernel; 0 = one per tile (default)
- *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 (default).  With neither this nor adamw_unroll
- *                   set the library takes its own shape: workgroups of one wave, few of them per compute unit
- *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4 or 8
+ *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 (default).  With both this and adamw_unroll 0
+ *                   the library takes its own shape: workgroups of one wave, few of them per compute unit
+ *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4, 8, or 0 (default)
  *   "adamw_nt"      non-temporal hints on the update's loads and stores: 0 = none, 1 or 2 (default) = on all of them,
  *                   but on the gradient loads only where the context's gradient chunks exceed the 256 MB Infinity Cache
  *   "pack_tile_elems"  elements one workgroup of pack/unpack moves; read by pt_pack_plan_create

@@ -213,8 +213,8 @@ extern "C" int pt_ctx_set_option(pt_ctx* ctx, const char* name, int64_t value) {
     return PT_OK;
   }
   if (std::strcmp(name, "adamw_unroll") == 0) {
-    if (value != 1 && value != 2 && value != 4 && value != 8)
-      return pt_fail(ctx, PT_ERR_INVALID_ARG, "adamw_unroll must be 1, 2, 4 or 8");
+    if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8)
+      return pt_fail(ctx, PT_ERR_INVALID_ARG, "adamw_unroll must be 0, 1, 2, 4 or 8");
     ctx->opt_adamw_unroll = uint32_t(value);
     return PT_OK;
   }

@@ -308,6 +308,25 @@ int accumulate_occupancy_by_size() {
   return 0;
 }
 
+// The launch-shape options go back to the default shape.
+int launch_shape_options_and_back() {
+  State s(2, 4096);
+  pt_pack_plan* q = s.plan();
+  OK(s.step(q));
+  const auto shape = [&] { return fake::launches("k_adamw").back(); };
+  const fake::Op own = shape();
+  for (const char* name : {"adamw_unroll", "adamw_threads", "adamw_grid"}) {
+    OK(pt_ctx_set_option(s.ctx, name, strcmp(name, "adamw_unroll") == 0 ? 4 : strcmp(name, "adamw_threads") == 0 ? 256 : 1));
+    OK(s.step(q));
+    EXPECT(shape().block.x != own.block.x || shape().grid.x != own.grid.x);
+    OK(pt_ctx_set_option(s.ctx, name, 0));
+    OK(s.step(q));
+    EXPECT(shape().block.x == own.block.x && shape().grid.x == own.grid.x && shape().grid.y == own.grid.y && shape().lds == own.lds);
+  }
+  EXPECT(pt_ctx_set_option(s.ctx, "adamw_unroll", 3) == PT_ERR_INVALID_ARG);
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -318,6 +337,7 @@ const std::map<std::string, int (*)()> checks = {
     {"norm_occupancy_by_size", norm_occupancy_by_size},
     {"unpack_occupancy_by_size", unpack_occupancy_by_size},
     {"accumulate_occupancy_by_size", accumulate_occupancy_by_size},
+    {"launch_shape_options_and_back", launch_shape_options_and_back},
 };
 
 }  // namespace

@@ -35,6 +35,7 @@ def exe(tmp_path_factory):
     "norm_occupancy_by_size",
     "unpack_occupancy_by_size",
     "accumulate_occupancy_by_size",
+    "launch_shape_options_and_back",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
