@@ -277,7 +277,13 @@ extern "C" int pt_pack_plan_destroy(pt_pack_plan* plan) {
   // a reduction of this plan's partial sums that was put off runs now, before they are freed (the device is idle: any
   // stream will do, and the one of the pack may be gone)
   if (plan->ctx && plan->ctx->pend_reduce.n && plan->ctx->pend_reduce.plan == plan) {
-    (void)pt_flush_pending(plan->ctx, nullptr);
+    pt_ctx* ctx = plan->ctx;
+    if (pt_flush_pending(ctx, nullptr) != PT_OK) {
+      // the sums are lost with the plan: nothing may read them, and their chunks have no value from this step
+      ctx->pend_reduce = PtPendingReduce{};
+      if (ctx->pend_finalize) ctx->pend_finalize = ctx->norm_finalized = false;
+      for (uint32_t c : plan->touched) ctx->chunk_fresh[c] = 0;
+    }
     (void)hipDeviceSynchronize();
   }
   if (plan->ctx)      // a plan that no longer exists does not stand in another plan's way

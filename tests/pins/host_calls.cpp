@@ -327,6 +327,30 @@ int launch_shape_options_and_back() {
   return 0;
 }
 
+// A plan whose waiting sums cannot be reduced any more takes them with it: its arrays are gone, nothing may read them, and
+// the chunks have no value from this step.
+int plan_destroyed_and_its_reduction_fails() {
+  for (int finalized = 0; finalized < 2; ++finalized) {
+    State s(2, 4096);
+    pt_pack_plan* q = s.plan();
+    OK(s.step(q));
+    OK(s.pack(q));
+    if (finalized) OK(s.finalize(PT_FINALIZE_STRICT));
+    fake::fail_kernel = "k_scalars";
+    fake::fail_after = 0;
+    (void)pt_pack_plan_destroy(q);
+    s.plans.clear();
+    fake::fail_after = -1;
+    const size_t at = fake::ops.size();
+    if (finalized) EXPECT(s.update() == PT_ERR_STATE);
+    else EXPECT(s.finalize(PT_FINALIZE_STRICT) == PT_ERR_STATE);
+    OK(pt_step_end(s.ctx, nullptr));
+    for (const fake::Op& o : fake::launches("k_scalars", at)) EXPECT(o.grid.x == 1 && o.grid.y == 1);
+    OK(s.step(s.plan()));
+  }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -338,6 +362,7 @@ const std::map<std::string, int (*)()> checks = {
     {"unpack_occupancy_by_size", unpack_occupancy_by_size},
     {"accumulate_occupancy_by_size", accumulate_occupancy_by_size},
     {"launch_shape_options_and_back", launch_shape_options_and_back},
+    {"plan_destroyed_and_its_reduction_fails", plan_destroyed_and_its_reduction_fails},
 };
 
 }  // namespace

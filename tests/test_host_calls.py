@@ -36,6 +36,7 @@ def exe(tmp_path_factory):
     "unpack_occupancy_by_size",
     "accumulate_occupancy_by_size",
     "launch_shape_options_and_back",
+    "plan_destroyed_and_its_reduction_fails",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
