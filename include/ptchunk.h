@@ -151,8 +151,10 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
  *   "pack_tile_elems"  elements one workgroup of pack/unpack moves; read by pt_pack_plan_create
  *   "stream_test_reject"  for tests of pt_stream_reserve: its trial of the copy streams rejects that many
  *                   stream pairs (0..5) whatever it measures, so that the replacement runs
- *   "stream_test_unhealthy"  for tests: 1 = the next look at a finished streamed step finds it serialised
- *                   whatever it measured, so that the replacement of the side streams runs
+ *   "stream_test_unhealthy"  for tests: 1 = the next look at a finished streamed step through the chunk buffers finds
+ *                   it serialised whatever it measured, so that the replacement of the side streams runs
+ *   "stream_in_place"  pt_chunk_stream_step updates host arrays in place over the link: 1 = where it can (default),
+ *                   0 = never, 2 = PT_ERR_UNSUPPORTED where it cannot
  * Gradient storage (variants of the path; the paper's gradients are the 16-bit array):
  *   "grad_fp32"     1 = the gradient chunks of this context hold fp32 (micro-batches accumulated
  *                   by pt_chunk_accum_grads): every `grad` / `h_grad` argument of the norm, the

@@ -117,6 +117,7 @@ struct pt_ctx {
   uint32_t opt_adamw_threads = 0;   // workgroup size of the update kernel: 256, 512, or 0 = the library's shape
   uint32_t opt_adamw_nt = 2;        // non-temporal hints on the update's loads and stores: 0 no, 1 or 2 yes (pt_adamw_hints)
   uint32_t opt_pack_tile_elems = PT_PACK_TILE_ELEMS;  // read when a pack plan is created
+  uint32_t opt_in_place = 1;        // streamed update in place: 0 never, 1 where it can be, 2 or not at all
   bool scaler = false;
   bool grad_f32 = false;            // gradient chunks hold fp32 (accumulated micro-batches), option "grad_fp32"
   uint32_t opt_zero_grads = 0;      // pt_chunk_adamw_step zeroes the gradient chunks it has read

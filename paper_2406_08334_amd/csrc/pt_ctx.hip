@@ -242,6 +242,11 @@ extern "C" int pt_ctx_set_option(pt_ctx* ctx, const char* name, int64_t value) {
     ctx->opt_adamw_nt = uint32_t(value);
     return PT_OK;
   }
+  if (std::strcmp(name, "stream_in_place") == 0) {
+    if (value < 0 || value > 2) return pt_fail(ctx, PT_ERR_INVALID_ARG, "stream_in_place must be 0, 1 or 2");
+    ctx->opt_in_place = uint32_t(value);
+    return PT_OK;
+  }
   if (std::strcmp(name, "adamw_zero_grads") == 0) {
     ctx->opt_zero_grads = value != 0;
     return PT_OK;

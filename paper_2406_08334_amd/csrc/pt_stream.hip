@@ -223,17 +223,9 @@ static int rebuild_side_streams(pt_ctx* ctx) {
 }
 
 // Reads the verdict on the last streamed step, if it is in, and replaces the side streams after a serialised one.
-// A step in place cannot be serialised and is not timed: only the verdict that tests force applies to it.
+// A step in place cannot be serialised and is not timed.
 static int look_at_last_step(pt_ctx* ctx) {
-  if (!ctx->health_pending) {
-    if (!ctx->opt_force_unhealthy || !ctx->direct_used || !ctx->duplex_tested || ctx->stream_rebuilds >= PT_MAX_STREAM_REBUILDS)
-      return PT_OK;
-    if (hipEventQuery(ctx->ev_direct) != hipSuccess) {
-      (void)hipGetLastError();
-      return PT_OK;
-    }
-    return rebuild_side_streams(ctx);
-  }
+  if (!ctx->health_pending) return PT_OK;
   if (hipEventQuery(ctx->ev_t1) != hipSuccess) {
     (void)hipGetLastError();      // "not ready" is no error of this call: the step is looked at next time
     return PT_OK;
@@ -320,16 +312,18 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
       return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_stream_step: NULL host pointer for chunk %u", first_chunk + i);
   if (n_chunks == 0) return PT_OK;
 
-  int rc = look_at_last_step(ctx);
-  if (rc != PT_OK) return rc;
-  rc = pt_prepare_consts(ctx, hp, false, st);      // the other chunks are resident ones, as a rule
-  if (rc != PT_OK) return rc;
   std::vector<uint64_t> at;
   bool direct = false;
-  rc = pt_guarded(ctx, "pt_chunk_stream_step", [&] {
-    direct = in_place(ctx, n_chunks, h_grad, h_master, h_m, h_v, h_param16, at);
+  int rc = pt_guarded(ctx, "pt_chunk_stream_step", [&] {
+    direct = ctx->opt_in_place && in_place(ctx, n_chunks, h_grad, h_master, h_m, h_v, h_param16, at);
     return int(PT_OK);
   });
+  if (rc != PT_OK) return rc;
+  if (!direct && ctx->opt_in_place == 2)
+    return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_chunk_stream_step: these arrays cannot be updated in place (pinned, aligned, apart "
+                   "from each other), and the option stream_in_place asks for it");
+  if ((rc = look_at_last_step(ctx)) != PT_OK) return rc;
+  rc = pt_prepare_consts(ctx, hp, false, st);      // the other chunks are resident ones, as a rule
   if (rc != PT_OK) return rc;
   // side streams start after everything already enqueued on the caller's stream
   PT_HIP(ctx, hipEventRecord(ctx->ev_fork, st));

@@ -351,6 +351,36 @@ int plan_destroyed_and_its_reduction_fails() {
   return 0;
 }
 
+// Only steps through the chunk buffers are looked at for copy streams that got in each other's way; the option that sends
+// every step there, or none.
+int side_streams_are_judged_by_their_own_steps() {
+  State s(2, 1 << 21);                            // chunk buffers large enough to try the copy streams out
+  HostPart h(s, 0);
+  OK(pt_stream_reserve(s.ctx, 2));
+  OK(pt_ctx_set_option(s.ctx, "stream_test_unhealthy", 1));
+  const auto step = [&](int in_place) {
+    int rc = pt_ctx_set_option(s.ctx, "stream_in_place", in_place);
+    if (rc == PT_OK) rc = pt_step_override(s.ctx, 1.0f, 0, nullptr);
+    if (rc == PT_OK) rc = h.stream(s);
+    return rc == PT_OK ? pt_step_end(s.ctx, nullptr) : rc;
+  };
+  int32_t rebuilds = -1;
+  size_t at = fake::ops.size();
+  for (int k = 0; k < 3; ++k) OK(step(2));
+  EXPECT(fake::launches("k_adamw_host", at).size() == 3 && fake::launches("k_adamw", at).empty());
+  OK(pt_stream_status(s.ctx, nullptr, nullptr, nullptr, &rebuilds));
+  EXPECT(rebuilds == 0);
+  at = fake::ops.size();
+  for (int k = 0; k < 3; ++k) OK(step(0));
+  EXPECT(fake::launches("k_adamw_host", at).empty() && fake::launches("k_adamw", at).size() == 6);
+  OK(pt_stream_status(s.ctx, nullptr, nullptr, nullptr, &rebuilds));
+  EXPECT(rebuilds == 1);                          // the verdict was asked for once
+  h.p[0] = (char*)h.p[0] + 2;                     // off the alignment
+  at = fake::ops.size();
+  EXPECT(step(2) == PT_ERR_UNSUPPORTED && fake::launches("k_adamw", at).empty() && fake::launches("k_adamw_host", at).empty());
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -363,6 +393,7 @@ const std::map<std::string, int (*)()> checks = {
     {"accumulate_occupancy_by_size", accumulate_occupancy_by_size},
     {"launch_shape_options_and_back", launch_shape_options_and_back},
     {"plan_destroyed_and_its_reduction_fails", plan_destroyed_and_its_reduction_fails},
+    {"side_streams_are_judged_by_their_own_steps", side_streams_are_judged_by_their_own_steps},
 };
 
 }  // namespace

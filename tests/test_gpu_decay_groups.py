@@ -111,9 +111,11 @@ def test_streamed_and_host_updated_chunks_honour_the_runs(orc, dtype, scaler):
     ref = run_mixed(sizes, S, 6, 2, steps=2, dtype=dtype, scaler=scaler, no_decay_runs=runs, orc=orc)
     plain = run_mixed(sizes, S, 6, 2, steps=2, dtype=dtype, scaler=scaler)
     assert not torch.equal(ref["w"], plain["w"])
-    for n_persist, n_slots, host_update in ((3, 2, False), (0, 3, False), (5, 2, False), (3, 2, True), (0, 2, True)):
+    for n_persist, n_slots, host_update, in_place in ((3, 2, False, False), (0, 3, False, False), (5, 2, False, False),
+                                                      (0, 2, False, True), (3, 2, False, True), (3, 2, True, False),
+                                                      (0, 2, True, False)):
         got = run_mixed(sizes, S, n_persist, n_slots, steps=2, dtype=dtype, scaler=scaler, host_update=host_update,
-                        no_decay_runs=runs, orc=orc)     # every chunk, wherever it is updated, against the oracle
+                        no_decay_runs=runs, orc=orc, in_place=in_place)   # every chunk, wherever it is updated, against the oracle
         for name in ("p16", "w", "m", "v"):
             view = torch.int16 if got[name].element_size() == 2 else torch.int32
-            assert torch.equal(got[name].view(view), ref[name].view(view)), (name, n_persist, n_slots, host_update)
+            assert torch.equal(got[name].view(view), ref[name].view(view)), (name, n_persist, n_slots, host_update, in_place)

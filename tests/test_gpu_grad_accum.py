@@ -285,7 +285,7 @@ def test_end_to_end_fp16_loss_scaling_with_an_inf_in_the_middle_micro_batch(orc)
 
 def run_split(n_persist, mode, dtype, scaler, steps=2, micro=2, masked=True, orc=None):
     """6 chunks with fp32 gradient chunks; chunks >= n_persist live in pinned host memory and are
-    streamed through chunk buffers (mode 'stream') or updated by host threads (mode 'host').  With
+    streamed (mode 'buffers' or 'in place') or updated by host threads (mode 'host').  With
     `orc` the oracle accumulates the same seeded micro-batches and takes every step itself; all
     chunks must end up with its bits."""
     S = 40_000
@@ -304,8 +304,9 @@ def run_split(n_persist, mode, dtype, scaler, steps=2, micro=2, masked=True, orc
             ost = orc.new_state(sc_o)
             og32 = np.zeros(C * S, np.float32)
         if n_persist < C:
-            if mode == "stream":
+            if mode in ("buffers", "in place"):
                 B.pt_stream_reserve(st.ctx, 3)
+                B.pt_ctx_set_option(st.ctx, "stream_in_place", 2 if mode == "in place" else 0)
             for name, arena in (("g32", st.g32), ("p16", st.p16), ("w", st.w), ("m", st.m), ("v", st.v)):
                 host[name] = [torch.empty(S, dtype=arena.dtype, pin_memory=True) for _ in range(n_persist, C)]
             for name, arena in (("p16", st.p16), ("w", st.w), ("m", st.m), ("v", st.v)):
@@ -326,7 +327,7 @@ def run_split(n_persist, mode, dtype, scaler, steps=2, micro=2, masked=True, orc
                 host["g32"][i].copy_(st.g32[c])
             torch.cuda.synchronize()
             st.norm()
-            if n_persist < C and mode == "stream":
+            if n_persist < C and mode in ("buffers", "in place"):
                 B.pt_chunk_stream_step(st.ctx, hp_b, n_persist, C - n_persist, host["g32"], host["w"], host["m"],
                                        host["v"], host["p16"])
             if n_persist > 0:
@@ -353,8 +354,8 @@ def run_split(n_persist, mode, dtype, scaler, steps=2, micro=2, masked=True, orc
 
 @pytest.mark.parametrize("dtype,scaler", [(torch.bfloat16, None), (torch.float16, SCALER_B)])
 def test_streamed_and_host_updated_chunks_with_fp32_gradients_equal_the_oracle_and_the_resident_bits(orc, dtype, scaler):
-    ref = run_split(6, "stream", dtype, scaler, orc=orc)
-    for n_persist, mode in ((3, "stream"), (0, "stream"), (5, "stream"), (3, "host"), (0, "host")):
+    ref = run_split(6, "buffers", dtype, scaler, orc=orc)
+    for n_persist, mode in ((3, "buffers"), (0, "buffers"), (5, "buffers"), (3, "in place"), (0, "in place"), (3, "host"), (0, "host")):
         got = run_split(n_persist, mode, dtype, scaler, orc=orc)
         for name in ("p16", "w", "m", "v"):
             view = torch.int16 if got[name].element_size() == 2 else torch.int32

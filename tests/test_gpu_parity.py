@@ -401,9 +401,9 @@ def test_loss_scale_growth_on_device(orc):
 # ------------------------------------------------------------------- streamed == resident
 
 def run_mixed(sizes, S, n_persist, n_slots, steps, dtype=torch.bfloat16, scaler=None, inf_step=None, host_update=False,
-              no_decay_runs=None, orc=None):
-    """Chunks [0, n_persist) resident, the rest in pinned host memory: streamed through chunk buffers, or
-    (host_update) updated by host threads.  With `orc` the oracle takes every step beside the device on
+              no_decay_runs=None, orc=None, in_place=True):
+    """Chunks [0, n_persist) resident, the rest in pinned host memory: streamed, in place over the link or through
+    n_slots chunk buffers, or (host_update) updated by host threads.  With `orc` the oracle takes every step beside the device on
     the same seeded inputs (its own pack, norm, constants and fp32 sequence) and the final state of ALL
     chunks - resident, streamed or host-updated - must equal the oracle's bit for bit."""
     st = ChunkedState(sizes, S, dtype=dtype, scaler=scaler)
@@ -422,6 +422,7 @@ def run_mixed(sizes, S, n_persist, n_slots, steps, dtype=torch.bfloat16, scaler=
         if n_persist < C:
             if not host_update:
                 B.pt_stream_reserve(st.ctx, n_slots)
+                B.pt_ctx_set_option(st.ctx, "stream_in_place", 2 if in_place else 0)
             for name, arena in (("g16", st.g16), ("p16", st.p16), ("w", st.w), ("m", st.m), ("v", st.v)):
                 host[name] = [torch.empty(S, dtype=arena.dtype).pin_memory() for _ in range(n_persist, C)]
             for name, arena in (("p16", st.p16), ("w", st.w), ("m", st.m), ("v", st.v)):
@@ -473,12 +474,14 @@ def run_mixed(sizes, S, n_persist, n_slots, steps, dtype=torch.bfloat16, scaler=
 def test_streamed_and_host_updated_chunks_equal_the_oracle_and_the_resident_bits(orc, dtype, scaler, inf_step):
     sizes, S = [6 * 40_000 - 24], 40_000                        # 6 chunks, last one padded
     ref = run_mixed(sizes, S, 6, 2, steps=3, dtype=dtype, scaler=scaler, inf_step=inf_step, orc=orc)
-    for n_persist, n_slots in ((3, 2), (0, 2), (0, 3), (2, 3), (5, 2)):
-        got = run_mixed(sizes, S, n_persist, n_slots, steps=3, dtype=dtype, scaler=scaler, inf_step=inf_step, orc=orc)
+    for n_persist, n_slots, in_place in ((3, 2, False), (0, 2, False), (0, 3, False), (2, 3, False), (5, 2, False),
+                                         (0, 2, True), (2, 2, True), (5, 2, True)):
+        got = run_mixed(sizes, S, n_persist, n_slots, steps=3, dtype=dtype, scaler=scaler, inf_step=inf_step, orc=orc,
+                        in_place=in_place)
         for name in ("p16", "w", "m", "v"):
             assert torch.equal(got[name].view(torch.int16 if got[name].element_size() == 2 else torch.int32),
                                ref[name].view(torch.int16 if ref[name].element_size() == 2 else torch.int32)), \
-                (name, n_persist, n_slots)
+                (name, n_persist, n_slots, in_place)
         assert got["report"].step == ref["report"].step and got["report"].loss_scale == ref["report"].loss_scale
     # the paper's placement: non-persistent chunks updated by host threads, same bits again
     for n_persist in (3, 0, 5):

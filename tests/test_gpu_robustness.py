@@ -2,6 +2,8 @@
 random segment tables (gaps, partial tensors, shuffled order, odd alignments) through pack,
 unpack and accumulate; forty steps with loss-scale back-offs and growths, bit for bit;
 two contexts stepping on two streams at once."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -224,6 +226,7 @@ def test_stream_reserve_tries_its_copy_streams_out_and_ends_with_a_pair_that_ove
         # kept; the streamed update through the replaced stream still gives the resident bits
         forced = B.pt_ctx_create(B.PT_BF16, S, 4, None)
         ctxs.append(forced)
+        B.pt_ctx_set_option(forced, "stream_in_place", 0)          # through the copy streams
         B.pt_ctx_set_option(forced, "stream_test_reject", 2)
         B.pt_stream_reserve(forced, 2)
         st = B.pt_stream_status(forced)
@@ -300,7 +303,16 @@ def test_streamed_update_by_the_kind_of_host_memory(dtype, grad_fp32, S, n_host,
             host["p"] = host["g"]
         B.pt_stream_reserve(st.ctx, 2)
         B.pt_step_override(st.ctx, 0.5, inf)
-        B.pt_chunk_stream_step(st.ctx, hp_b, 0, n_host, host["g"], host["w"], host["m"], host["v"], host["p"])
+        stream = lambda: B.pt_chunk_stream_step(st.ctx, hp_b, 0, n_host, host["g"], host["w"], host["m"], host["v"], host["p"])
+        B.pt_ctx_set_option(st.ctx, "stream_in_place", 2)
+        if memory in ("pinned", "shared"):
+            stream()
+        else:
+            with pytest.raises(B.PtError) as e:
+                stream()
+            assert e.value.status == B.PT_ERR_UNSUPPORTED
+            B.pt_ctx_set_option(st.ctx, "stream_in_place", 1)
+            stream()
         torch.cuda.synchronize()
         st.adamw(hp_b)
         st.end()
@@ -531,3 +543,84 @@ def test_graph_of_norm_update_and_step_end_replayed_behind_eager_packs(pending):
         torch.cuda.synchronize()
         a.close()
         b.close()
+
+
+def non_coherent_pinned(n, dtype):
+    """n elements of pinned host memory that the device caches between synchronisations (hipHostMallocNonCoherent), and
+    what gives it back."""
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    p = ctypes.c_void_p()
+    size = n * torch.empty(0, dtype=dtype).element_size()
+    assert hip.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(size), ctypes.c_uint(0x80000000)) == 0
+    t = torch.frombuffer((ctypes.c_char * size).from_address(p.value), dtype=dtype)
+    return t, lambda: hip.hipHostFree(p)
+
+
+@pytest.mark.parametrize("kind", ["coherent", "non-coherent", "graph"])
+def test_streamed_update_in_place_step_after_step(kind):
+    """Two contexts on streams of their own, four steps without a wait between them, new gradients in host memory each time;
+    memory the device caches; the same steps replayed from a graph.  Against a resident copy of the same state, bit for bit."""
+    S, n = 5000, 3
+    B.lib()
+    free, pairs = [], []
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    hp, _, _ = hp_pair()
+    try:
+        for seed in (0, 1):
+            st, ref = ChunkedState([S * n - 3], S, seed=seed), ChunkedState([S * n - 3], S, seed=seed)
+            pairs.append((st, ref, {}))
+            for k, a in (("g", st.g16), ("p", st.p16), ("w", st.w), ("m", st.m), ("v", st.v)):
+                pairs[-1][2][k] = []
+                for c in range(n):
+                    if kind == "non-coherent":
+                        t, give_back = non_coherent_pinned(S, a.dtype)
+                        free.append(give_back)
+                    else:
+                        t = torch.empty(S, dtype=a.dtype, pin_memory=True)
+                    pairs[-1][2][k].append(t.copy_(a[c]))
+            B.pt_stream_reserve(st.ctx, 2)
+            B.pt_ctx_set_option(st.ctx, "stream_in_place", 2)
+
+        def step(st, host, stream):
+            B.pt_step_override(st.ctx, 0.5, False, stream)
+            B.pt_chunk_stream_step(st.ctx, hp, 0, n, host["g"], host["w"], host["m"], host["v"], host["p"], stream)
+            B.pt_step_end(st.ctx, stream)
+        graphs = []
+        if kind == "graph":
+            for (st, _, host), stream in zip(pairs, streams):
+                torch.cuda.synchronize()
+                graphs.append(torch.cuda.CUDAGraph())
+                with torch.cuda.graph(graphs[-1], stream=stream):
+                    step(st, host, torch.cuda.current_stream())
+        for t in (1, 2, 3, 4):
+            for st, ref, host in pairs:
+                ref.set_grads(t)
+                ref.pack()
+                torch.cuda.synchronize()
+                for c in range(n):
+                    host["g"][c].copy_(ref.g16[c])
+            for i, ((st, ref, host), stream) in enumerate(zip(pairs, streams)):      # both enqueued before either is waited for
+                if graphs:
+                    with torch.cuda.stream(stream):
+                        graphs[i].replay()
+                else:
+                    step(st, host, stream)
+            for stream in streams:
+                stream.synchronize()
+            for st, ref, host in pairs:
+                B.pt_step_override(ref.ctx, 0.5, False)
+                ref.adamw(hp)
+                ref.end()
+                for k, a in (("p", ref.p16), ("w", ref.w), ("m", ref.m), ("v", ref.v)):
+                    bits = torch.int16 if k == "p" else torch.int32
+                    for c in range(n):
+                        assert torch.equal(host[k][c].view(bits), a[c].cpu().view(bits)), (kind, t, k, c)
+    finally:
+        torch.cuda.synchronize()
+        for st, ref, _ in pairs:
+            st.close()
+            ref.close()
+        pairs.clear()
+        for give_back in free:
+            give_back()

@@ -37,6 +37,7 @@ def exe(tmp_path_factory):
     "accumulate_occupancy_by_size",
     "launch_shape_options_and_back",
     "plan_destroyed_and_its_reduction_fails",
+    "side_streams_are_judged_by_their_own_steps",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
