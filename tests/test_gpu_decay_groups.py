@@ -13,7 +13,7 @@ from test_gpu_parity import end_to_end, run_mixed, run_oracle_f32seq
 
 pytestmark = pytest.mark.gpu
 
-TILE = 4096                       # elements of one kernel tile at the default unroll
+TILE = 4096                       # elements of a kernel tile of 256 lanes with four units each; the library's own has 256
 
 
 def awkward_runs(S):
@@ -27,14 +27,15 @@ def awkward_runs(S):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("unroll,threads", [(4, 512), (1, 512), (8, 512), (4, 256), (8, 256)])
-def test_masked_kernel_is_bit_exact_against_the_masked_f32_sequence(orc, dtype, unroll, threads):
+@pytest.mark.parametrize("unroll,threads,nt", [(4, 512, 1), (1, 512, 1), (8, 512, 0), (4, 256, 1), (8, 256, 0),
+                                               (0, 0, 2), (0, 0, 0)])       # the library's own shape, with hints and without
+def test_masked_kernel_is_bit_exact_against_the_masked_f32_sequence(orc, dtype, unroll, threads, nt):
     S, C = TILE * 5 + 40, 4
     st = ChunkedState([S * C - 5], S, dtype=dtype)
     try:
         B.pt_ctx_set_option(st.ctx, "adamw_unroll", unroll)
         B.pt_ctx_set_option(st.ctx, "adamw_threads", threads)
-        B.pt_ctx_set_option(st.ctx, "adamw_nt", 1 if unroll != 8 else 2)     # hinted accesses too (a small state gets none by default)
+        B.pt_ctx_set_option(st.ctx, "adamw_nt", nt)
         hp_b, hp_o, _ = hp_pair()
         mask = st.set_no_decay(runs=awkward_runs(S))
         assert 0 < mask.sum() < mask.size

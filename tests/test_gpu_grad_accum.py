@@ -91,14 +91,15 @@ def test_fused_norm_of_the_last_micro_batch_equals_the_recomputed_one(orc, dtype
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("unroll,zero,masked", [(4, False, False), (1, True, False), (8, False, True), (4, True, True)])
-def test_update_from_fp32_gradients_is_bit_exact_against_the_f32_sequence(orc, dtype, unroll, zero, masked):
+@pytest.mark.parametrize("unroll,zero,masked,nt", [(4, False, False, 1), (1, True, False, 1), (8, False, True, 0), (4, True, True, 1),
+                                                   (0, False, True, 2), (0, True, False, 2), (0, True, True, 0), (0, False, False, 0)])
+def test_update_from_fp32_gradients_is_bit_exact_against_the_f32_sequence(orc, dtype, unroll, zero, masked, nt):
     S, C = 4096 * 3 + 40, 3
     st = ChunkedState([S * C - 5], S, dtype=dtype, grad_fp32=True)
     try:
         B.pt_ctx_set_option(st.ctx, "adamw_unroll", unroll)
         B.pt_ctx_set_option(st.ctx, "adamw_zero_grads", int(zero))
-        B.pt_ctx_set_option(st.ctx, "adamw_nt", 1 if unroll != 8 else 2)     # hinted accesses too (a small state gets none by default)
+        B.pt_ctx_set_option(st.ctx, "adamw_nt", nt)
         mask = st.set_no_decay(runs=[(0, 100, 5000), (1, 0, S), (2, S - 41, 41)]) if masked else None
         hp_b, hp_o, hpd = hp_pair()
         host = st.host_state()

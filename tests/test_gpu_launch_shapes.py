@@ -41,3 +41,40 @@ def test_update_in_its_default_shape(orc, dtype, S, C, grid, masked):
                 assert_same_bits(got[name], host[name], (name, t))
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("masked", [False, True])
+def test_hints_by_the_size_of_the_gradient_chunks_change_no_bit(orc, dtype, masked):
+    """A context whose 16-bit gradient chunks exceed the 256 MB Infinity Cache packs and updates with non-temporal hints on
+    the gradients too.  Only three of its chunks exist here: their bits are the oracle's."""
+    S, n = 4096 * 3 + 40, 3
+    C = (256 << 20) // (2 * S) + 1
+    small = ChunkedState([S * n - 5], S, dtype=dtype)
+    ctx = B.pt_ctx_create(small.pt_dtype, S, C, None)
+    plan = B.pt_pack_plan_create(ctx, small.segs)
+    try:
+        assert 2 * S * C > 256 << 20 >= 2 * S * (C - 1)
+        hp_b, hp_o, _ = hp_pair()
+        runs = [(0, 0, 3), (n - 1, S - 1, 1), (1, 0, S), (2, S // 2 - 2, 5)] if masked else []
+        mask = small.set_no_decay(runs=runs) if masked else None
+        if masked:
+            B.pt_ctx_set_no_decay(ctx, [B.pt_segment(0, 0, ln, off, c, 0) for c, off, ln in runs])
+        host = small.host_state()
+        for t in (1, 2):
+            small.set_grads(t)
+            B.pt_chunk_pack_grads(ctx, plan, small.rows(small.g16) + [None] * (C - n))
+            B.pt_step_override(ctx, 0.0121, False)
+            B.pt_chunk_adamw_step(ctx, hp_b, 0, n, small.rows(small.g16), small.rows(small.w), small.rows(small.m),
+                                  small.rows(small.v), small.rows(small.p16))
+            B.pt_step_end(ctx)
+            host["g16"] = small.oracle_packed(orc)
+            run_oracle_f32seq(orc, orc.consts_f32(hp_o, t, float(np.float32(0.0121))), host, small.orc_dtype, no_decay=mask)
+            got = small.host_state()
+            for name in ("g16", "w", "m", "v", "p16"):
+                assert_same_bits(got[name], host[name], (name, t))
+    finally:
+        torch.cuda.synchronize()
+        B.pt_pack_plan_destroy(plan)
+        B.pt_ctx_destroy(ctx)
+        small.close()

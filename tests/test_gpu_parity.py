@@ -163,7 +163,7 @@ def test_adamw_kernel_isolated_is_bit_exact_against_f32_sequence(orc, dtype, S, 
     st = ChunkedState([S * C - 5], S, dtype=dtype)
     try:
         B.pt_ctx_set_option(st.ctx, "adamw_threads", threads)
-        B.pt_ctx_set_option(st.ctx, "adamw_nt", nt)          # with, without, or chosen by launch size: same bits
+        B.pt_ctx_set_option(st.ctx, "adamw_nt", nt)          # with or without hints: same bits
         hp_b, hp_o, hpd = hp_pair()
         host = st.host_state()
         h64 = {k: a.copy() for k, a in host.items()}
@@ -254,8 +254,9 @@ def test_access_pattern_calibration_leaves_the_state_as_it_is(dtype):
             st.set_grads(t)
             st.step(hp_b)
         before = st.host_state()
-        for unroll in (4, 1, 8):
+        for unroll, nt in ((0, 2), (0, 0), (4, 1), (1, 2), (8, 0)):      # 0: the library's own shape
             B.pt_ctx_set_option(st.ctx, "adamw_unroll", unroll)
+            B.pt_ctx_set_option(st.ctx, "adamw_nt", nt)
             B.pt_calib_adamw_pattern(st.ctx, 0, st.C)
             B.pt_calib_adamw_pattern(st.ctx, 1, 2)
         after = st.host_state()
