@@ -39,8 +39,8 @@ PACK_BYTES_PER_ELEM = 4            # read 2 + write 2
 # HBM traffic of one AdamW launch from rocprofv3 --pmc (FETCH_SIZE / WRITE_SIZE, scaled by the
 # same counters on pt_calib_copy); filled from the summaries under profiles/.  bytes per launch.
 MEASURED_TRAFFIC = {
-    # profiles/k_adamw_llama7b_hbm_traffic.md: (46 334 527.47 x 1.999776 + 92 669 076.19 x 0.999986) KiB
-    "llama_7b": 189_774_262_972,
+    # profiles/k_adamw_llama7b_hbm_traffic.md: (46 334 778.72 x 1.999761 + 92 667 997.31 x 0.999988) KiB
+    "llama_7b": 189_773_212_215,
 }
 
 

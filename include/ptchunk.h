@@ -18,7 +18,8 @@
  * One optimizer step is the call sequence
  *     pt_chunk_pack_grads      gradients -> gradient chunks (+ per-chunk sum of squares, non-finite flag)
  *     pt_chunk_grad_sqnorm     (optional recompute from chunks) + finalize: global norm, found_inf
- *     pt_chunk_stream_step     host-resident chunks: H2D -> update -> D2H on side streams  (optional)
+ *     pt_chunk_stream_step     host-resident chunks: updated over the link on side streams, in place or
+ *                              H2D -> update -> D2H  (optional)
  *     pt_chunk_adamw_step      GPU-resident chunks, one launch
  *     pt_step_end              joins the side streams, advances the step counter / loss scale
  * Everything is enqueued asynchronously; nothing in these five calls allocates or
@@ -148,7 +149,7 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
  *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4, 8, or 0 (default)
  *   "adamw_nt"      non-temporal hints on the update's loads and stores: 0 = none, 1 or 2 (default) = on all of them,
  *                   but on the gradient loads only where the context's gradient chunks exceed the 256 MB Infinity Cache
- *   "pack_tile_elems"  elements one workgroup of pack/unpack moves; read by pt_pack_plan_create
+ *   "pack_tile_elems"  elements of a tile of pack/unpack, which up to four workgroups share; read by pt_pack_plan_create
  *   "stream_test_reject"  for tests of pt_stream_reserve: its trial of the copy streams rejects that many
  *                   stream pairs (0..5) whatever it measures, so that the replacement runs
  *   "stream_test_unhealthy"  for tests: 1 = the next look at a finished streamed step through the chunk buffers finds
@@ -363,7 +364,8 @@ int pt_stream_status(const pt_ctx* ctx, int32_t* duplex_tested, int32_t* duplex_
  * as round-to-nearest-even(master), which is what it held if it was produced by
  * this library or initialised from the master weights.
  * h_*: host arrays of n_chunks PINNED pointers (entry i is chunk first_chunk+i).
- * Requires pt_stream_reserve and a finalized norm in this step.
+ * Requires pt_stream_reserve (also where every chunk is updated in place, which needs its streams but none of its
+ * buffers: two slots do) and a finalized norm in this step.
  * Through the chunk buffers the upload and offload streams want hardware queues of their own: in a process that holds many other
  * streams (HIP maps streams onto GPU_MAX_HW_QUEUES hardware queues, 4 by default) the two directions can
  * end up behind each other, and the link then carries one direction at a time.  pt_stream_reserve checks

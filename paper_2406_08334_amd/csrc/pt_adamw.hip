@@ -5,8 +5,8 @@
 // p16); 16 read with fp32 gradient chunks, and 2 or 4 more written when the gradients are
 // zeroed on the way out.  Work unit = 4 consecutive elements per lane: one 16-byte access per fp32
 // array and one 8-byte access per 16-bit array, so that every wave instruction
-// touches one contiguous 1 KiB (fp32) or 512 B (16-bit) span.  The launch shape keeps the set of
-// DRAM rows in use small (see k_adamw).
+// touches one contiguous 1 KiB (fp32) or 512 B (16-bit) span.  The launch shape keeps few bytes in
+// flight, in address order (see k_adamw).
 // Arithmetic: the fp32 operation sequence below with correctly rounded *, fma,
 // sqrt and / (this file is compiled with contraction off and without fast-math).
 #include "pt_common.h"
@@ -116,11 +116,13 @@ __device__ __forceinline__ void update_unit(const Consts& k, const float (&dk)[4
 // it; workgroups are dispatched in this order, so the traffic of a moment is one narrow window that slides over each
 // array.  A grid smaller than the tiles (option adamw_grid, or a dimension beyond its limit) walks on from there.
 //
-// What bounds the launch is DRAM row locality.  HBM is three regions of 96 GiB; four read and four write streams that
-// all fall into one of them - what plain allocation gives a state of up to about 100 GB - run out of open rows long
-// before they run out of bandwidth.  What helps is few bytes in flight, in address order: workgroups of ONE wave, one
-// unit per lane, and only 11 of them per compute unit (PT_ADAMW_LDS of unused LDS each; about 7 MB in flight chip-wide)
-// instead of 24 waves with four units each.  Moving the same bytes without the arithmetic over 2^28 elements: all
+// What bounds the launch is the memory's service time for four read and four write streams.  It grows with the bytes in
+// flight and where all arrays fall into one of the memory's three regions of 96 GiB - what plain allocation gives a state
+// of up to about 100 GB; DRAM rows that are opened too often would explain both, but no counter shows them.  What helps is
+// few bytes in flight, in address order: workgroups of ONE wave, one unit per lane, and only 11 of them per compute unit
+// (PT_ADAMW_LDS of unused LDS each; their loads together are 10 MB chip-wide at most) instead of 24 waves with four units
+// each.  Counted over 6.8e9 elements: 26 700 reads of 128 bytes in flight instead of 30 200, each back after 2400 L2
+// cycles instead of 3130.  Moving the same bytes without the arithmetic over 2^28 elements: all
 // arrays in one region 5.4 -> 6.5 TB/s, spread over the regions 6.39 -> 6.55 TB/s.  The whole step of the GPT-2-XL
 // shape (plain allocations): 9.35 -> 7.8 ms; 9 or 13 waves per unit 8.1 and 8.0 ms, 128 lanes 8.1, two units per lane
 // 8.2, no limit on the waves 8.6 ms.
@@ -328,7 +330,7 @@ k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_
 // block-to-tile mapping, the same four loads and four stores per unit with the same hints; master,
 // momentum and variance are stored back as loaded and param16 is re-derived from the master weight
 // (which is what it holds already), so the state does not change.  What this kernel attains is what the
-// memory system gives this mix of streams on this placement; the update itself cannot be faster.
+// memory system gives this mix of streams on this placement; the update runs within 2 % of it, on either side.
 template <int TH, int DT, int UNROLL, int HINT>
 __global__ void __launch_bounds__(TH)
 k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_col, uint32_t n_cols,
@@ -380,8 +382,8 @@ typedef void (*adamw_kernel_t)(const uint64_t*, const PtDevState*, uint32_t, uin
                                int, int, const uint32_t*, const uint64_t*);
 typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*);
 
-// The instantiation for a launch shape: `K<threads, unroll>::adamw / ::pattern` for the shapes there are (the default
-// one, and what the options adamw_threads and adamw_unroll ask for).
+// The instantiation for a launch shape: the library's own (64 lanes, one unit each), and what the options adamw_threads and
+// adamw_unroll ask for.  The latter lose to the former at every size measured; they stay for the options.
 template <int DT, int HINT, bool MASKED, bool GF32>
 struct Kernels {
   template <int TH, int U> static adamw_kernel_t adamw() { return k_adamw<TH, DT, U, HINT, MASKED, GF32>; }

@@ -62,7 +62,7 @@ constexpr uint32_t PT_NORM_BLOCK_ELEMS = 32768;  // elements one block of the no
 constexpr uint32_t PT_PACK_TILE_ELEMS = 8192;    // chunk-space tile of a pack plan
 constexpr uint32_t PT_PACK_SUBS = 4;             // waves that share a tile of the default size: a quarter each
 
-struct PtTile {        // one piece of work of the pack / unpack / accumulate kernels
+struct PtTile {        // one piece of work of the pack / unpack / accumulate kernels, shared by `subs` waves of its plan
   uint64_t tensor_addr;  // byte address of the first element on the tensor side
   uint64_t chunk_off;    // first element on the chunk side
   uint32_t chunk;
@@ -176,7 +176,7 @@ struct pt_ctx {
   std::vector<uint32_t> h_nd_begin;
   std::vector<uint64_t> h_nd_ranges;
 
-  // host-side update: a side stream and a pinned landing buffer for the step's scalars
+  // host-side update: a pinned landing buffer for the step's constants and the event behind the kernel that fills it
   PtDevState* h_state_dev = nullptr;    // h_state as the device addresses it (the scalar kernels leave the constants there)
   hipEvent_t ev_scalar = nullptr;
   PtDevState* h_state = nullptr;
