@@ -89,7 +89,8 @@ struct pt_pack_plan {
 
 namespace pt_host { class Pool; }
 
-// A per-chunk reduction of partial sums that has been put off (see pt_norm.hip).  seg_sum / seg_flag: room for n * segs
+// A per-chunk reduction of partial sums, to be launched or put off (see pt_norm.hip).  tile_begin == NULL: chunk first+i owns
+// partials [i*per_chunk, (i+1)*per_chunk), else [tile_begin[c], tile_begin[c+1]) * per_tile.  seg_sum / seg_flag: room for n * segs
 // sums where a chunk has more partials than one workgroup takes (segs > 1).
 struct PtPendingReduce {
   const double* part = nullptr;
@@ -317,10 +318,8 @@ void pt_host_pool_destroy(pt_ctx* ctx);
 // pt_chunk_grad_sqnorm_noalloc works in; out may be NULL.  Called by pt_ctx_create, so that a process
 // with a context never pays the lookup inside a hot call.
 int pt_static_scratch_setup(void** out);
-// Sums partials into per-chunk values: tile_begin == NULL: chunk first+i owns partials [i*per_chunk, (i+1)*per_chunk),
-// else [tile_begin[c], tile_begin[c+1]).  `now`: launched on `stream`, else put off until the norm is read or another call's sums come.
-int pt_add_chunk_reduce(pt_ctx* ctx, const PtPendingReduce& r, bool now, hipStream_t stream);
-// The reduction of a plan's tile sums (pack, accumulate).
+// The reduction of a plan's tile sums (pack, accumulate) to per-chunk values: launched on `stream`, a small plan's put off until the
+// norm is read or another call's sums come.
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);
 // Launches, on `stream`, whatever scalar work of the step has been put off (a per-chunk reduction, the finalize).
 // Every call that reads the step's scalars goes through this first.

@@ -381,6 +381,30 @@ int side_streams_are_judged_by_their_own_steps() {
   return 0;
 }
 
+// A recompute that finalizes takes the chunks' sums and the norm in one launch of its own; one that is refused has still
+// taken its chunks' sums.
+int recompute_and_norm_in_one_launch() {
+  State s(12, 4096);
+  size_t at = fake::ops.size();
+  OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 12, PT_FINALIZE_STRICT, nullptr));
+  EXPECT(fake::launches("k_scalars", at).size() == 1 && fake::launches("k_scalars", at)[0].grid.y == 12);
+  at = fake::ops.size();
+  pt_step_report rep;
+  OK(pt_step_report_read(s.ctx, &rep, nullptr));
+  EXPECT(fake::launches("k_scalars", at).empty());
+  OK(s.update());                                // the constants
+  EXPECT(fake::launches("k_scalars", at).size() == 1 && fake::launches("k_scalars", at)[0].grid.y == 1);
+  OK(pt_step_end(s.ctx, nullptr));
+  at = fake::ops.size();
+  EXPECT(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 5, PT_FINALIZE_STRICT, nullptr) == PT_ERR_STATE);
+  EXPECT(fake::launches("k_scalars", at).size() == 1 && fake::launches("k_scalars", at)[0].grid.y == 5);
+  EXPECT(s.update() == PT_ERR_STATE);
+  OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 5, 7, PT_FINALIZE_STRICT, nullptr));
+  EXPECT(fake::launches("k_scalars", at).size() == 2);
+  OK(s.update());
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
@@ -394,6 +418,7 @@ const std::map<std::string, int (*)()> checks = {
     {"launch_shape_options_and_back", launch_shape_options_and_back},
     {"plan_destroyed_and_its_reduction_fails", plan_destroyed_and_its_reduction_fails},
     {"side_streams_are_judged_by_their_own_steps", side_streams_are_judged_by_their_own_steps},
+    {"recompute_and_norm_in_one_launch", recompute_and_norm_in_one_launch},
 };
 
 }  // namespace
