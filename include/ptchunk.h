@@ -43,7 +43,8 @@
  *    each call's stream wait (event) for the previous call's.  Tiny scalar kernels of a call
  *    may be enqueued later, by the next call of the step that needs them and on THAT call's
  *    stream - which is behind the earlier call under this rule: the final norm (unless the call
- *    that asks for it recomputes from chunks), and the per-chunk sums of a small plan (at most 8 chunks and 16384 tiles, in a context of at most 64 chunks).
+ *    that asks for it recomputes from chunks), and the per-chunk sums of a small plan (at most 8
+ *    chunks and 16384 tiles, in a context of at most 64 chunks).
  *    All other per-chunk sums are enqueued by the call that packs, accumulates or recomputes, so that
  *    a graph of norm, update and step end may be captured without it and replayed behind it.
  *    With a small plan the graph holds the pack too, and the plan outlives the graph.
