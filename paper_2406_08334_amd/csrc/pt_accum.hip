@@ -176,7 +176,7 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   const uint64_t* h = ctx->h_table.data() + size_t(ROW_PACK) * ctx->table_cols;
   for (uint32_t c : plan->touched)
     if (!h[c]) return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_accum_grads: chunk %u is used by the plan but its pointer is NULL", c);
-  if (take_norm && (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
+  if (take_norm && ((rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK)) return rc;
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
   hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st, plan->d_tiles, pt_row(ctx, ROW_PACK),

@@ -39,7 +39,33 @@ struct PtDevState {
   float c[9];
   int32_t skip;
   uint32_t ticket;       // workgroups of the scalar kernel that have finished (0 between launches)
+  // a step that was ended together with its constants (pt_end_early): its number, and what the end has changed
+  uint32_t ended;
+  int32_t old_step, old_good_steps, old_override;
+  double old_loss_scale;
 };
+
+// The end of a step - loss-scale machine and step counter (dynamic loss scaling with skip on non-finite gradients; the counter
+// does not move on a skipped step) - from the step's found_inf; a forced multiplier lasts one step.
+__device__ __forceinline__ void pt_advance(PtDevState& s, bool found_inf) {
+  if (found_inf) {
+    if (s.scaler_enabled) {
+      const double b = s.loss_scale * s.backoff;
+      s.loss_scale = b > 1.0 ? b : 1.0;
+      s.good_steps = 0;
+    }
+  } else {
+    s.step += 1;
+    if (s.scaler_enabled) {
+      s.good_steps += 1;
+      if (s.good_steps >= s.growth_interval) {
+        s.loss_scale = s.loss_scale * s.growth;
+        s.good_steps = 0;
+      }
+    }
+  }
+  s.override_active = 0;
+}
 
 // Rows of the per-context device pointer table.  Each row has n_chunks + n_slots
 // entries; entries [n_chunks, n_chunks + n_slots) are the device chunk buffers
@@ -140,6 +166,9 @@ struct pt_ctx {
   std::vector<uint8_t> chunk_fresh;     // [C] 1 = the chunk's sum of squares was taken in this step (since pt_step_end)
   bool norm_finalized = false;
   bool prepared = false;
+  uint32_t step_no = 1;                 // steps opened so far; never 0
+  bool ended_early = false;             // the launch that derived this step's constants has advanced the step counter and loss scale too
+  bool captured = false;                // a call of this context has been captured into a graph
   PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;
   bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them
@@ -321,6 +350,10 @@ int pt_static_scratch_setup(void** out);
 // The reduction of a plan's tile sums (pack, accumulate) to per-chunk values: launched on `stream`, a small plan's put off until the
 // norm is read or another call's sums come.
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);
+// True if `stream` is being captured; the context remembers that it ever was.
+bool pt_capturing(pt_ctx* ctx, hipStream_t stream);
+// Before a call on `stream` that reads or changes what the end of a step changes: takes an early end of this step back.
+int pt_reopen_step(pt_ctx* ctx, hipStream_t stream);
 // Launches, on `stream`, whatever scalar work of the step has been put off (a per-chunk reduction, the finalize).
 // Every call that reads the step's scalars goes through this first.
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream);

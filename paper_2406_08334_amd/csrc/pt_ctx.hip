@@ -33,6 +33,7 @@ __global__ void k_init_state(PtDevState* st, double loss_scale, double growth, d
   for (int i = 0; i < 9; ++i) st->c[i] = 0.0f;
   st->skip = 0;
   st->ticket = 0;
+  st->ended = 0;
 }
 
 __global__ void k_set_state(PtDevState* st, int32_t step, double loss_scale, int32_t good_steps) {
@@ -46,27 +47,21 @@ __global__ void k_override(PtDevState* st, float grad_mult, int32_t found_inf) {
   st->sqnorm = 0.0; st->norm = 0.0;
 }
 
-// Loss-scale machine and step counter (dynamic loss scaling with skip on
-// non-finite gradients; the counter does not move on a skipped step).
-__global__ void k_step_end(PtDevState* st) {
+// The end of step `step_no`, unless the launch that derived its constants has been its end too.
+__global__ void k_step_end(PtDevState* st, uint32_t step_no) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (st->found_inf) {
-    if (st->scaler_enabled) {
-      double s = st->loss_scale * st->backoff;
-      st->loss_scale = s > 1.0 ? s : 1.0;
-      st->good_steps = 0;
-    }
-  } else {
-    st->step += 1;
-    if (st->scaler_enabled) {
-      st->good_steps += 1;
-      if (st->good_steps >= st->growth_interval) {
-        st->loss_scale = st->loss_scale * st->growth;
-        st->good_steps = 0;
-      }
-    }
-  }
-  st->override_active = 0;
+  if (st->ended == step_no) { st->ended = 0; return; }
+  PtDevState s = *st;
+  pt_advance(s, s.found_inf != 0);
+  st->step = s.step; st->loss_scale = s.loss_scale; st->good_steps = s.good_steps; st->override_active = s.override_active;
+}
+
+// Takes the early end of step `step_no` back.
+__global__ void k_reopen(PtDevState* st, uint32_t step_no) {
+  if (threadIdx.x != 0 || blockIdx.x != 0 || st->ended != step_no) return;
+  st->step = st->old_step; st->loss_scale = st->old_loss_scale; st->good_steps = st->old_good_steps;
+  st->override_active = st->old_override;
+  st->ended = 0;
 }
 
 // ---- public: misc -------------------------------------------------------------------------
@@ -197,6 +192,7 @@ extern "C" int pt_ctx_set_state(pt_ctx* ctx, int32_t step, double loss_scale, in
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_ctx_set_state: step, good_steps >= 0 and loss_scale >= 1 required");
   if (!ctx->scaler && loss_scale != 1.0)
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_ctx_set_state: context has no scaler, loss_scale must be 1");
+  if (int rc = pt_reopen_step(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   if (int rc = pt_flush_pending(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   hipLaunchKernelGGL(k_set_state, dim3(1), dim3(1), 0, (hipStream_t)stream, ctx->d_state, step,
                      loss_scale, good_steps);
@@ -315,6 +311,7 @@ extern "C" int pt_step_override(pt_ctx* ctx, float grad_mult, int32_t found_inf,
   if (ctx->stream_pending)
     return pt_fail(ctx, PT_ERR_STATE, "pt_step_override: a streamed update is still open (its kernels read the step's "
                    "scalars); close the step with pt_step_end first");
+  if (int rc = pt_reopen_step(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   if (int rc = pt_flush_pending(ctx, (hipStream_t)stream); rc != PT_OK) return rc;   // a computed norm, if any, comes first
   hipLaunchKernelGGL(k_override, dim3(1), dim3(1), 0, (hipStream_t)stream, ctx->d_state, grad_mult,
                      found_inf ? 1 : 0);
@@ -334,12 +331,34 @@ extern "C" int pt_step_end(pt_ctx* ctx, void* stream) {
     ctx->stream_pending = ctx->slots_pending = ctx->direct_pending = false;
   }
   if (int rc = pt_flush_pending(ctx, st); rc != PT_OK) return rc;     // a step without an update still needs its found_inf
-  hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state);
-  PT_LAUNCH_CHECK(ctx, "k_step_end");
+  // Nothing to launch where the step has ended with its constants.  Under capture the kernel goes into the graph either way:
+  // it looks whether the step it is replayed in has ended.
+  if (!ctx->ended_early || pt_capturing(ctx, st)) {
+    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state, ctx->step_no);
+    PT_LAUNCH_CHECK(ctx, "k_step_end");
+  }
   ctx->norm_finalized = false;
   ctx->prepared = false;
+  ctx->ended_early = false;
+  if (++ctx->step_no == 0) ctx->step_no = 1;
   std::fill(ctx->chunk_fresh.begin(), ctx->chunk_fresh.end(), uint8_t(0));   // the next step needs new partial sums
   std::fill(ctx->chunk_packed_by.begin(), ctx->chunk_packed_by.end(), uint64_t(0));
+  return PT_OK;
+}
+
+bool pt_capturing(pt_ctx* ctx, hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+  const bool yes = cs != hipStreamCaptureStatusNone;
+  ctx->captured = ctx->captured || yes;
+  return yes;
+}
+
+int pt_reopen_step(pt_ctx* ctx, hipStream_t stream) {
+  if (!ctx->ended_early) return PT_OK;
+  hipLaunchKernelGGL(k_reopen, dim3(1), dim3(1), 0, stream, ctx->d_state, ctx->step_no);
+  PT_LAUNCH_CHECK(ctx, "k_reopen");
+  ctx->ended_early = false;
   return PT_OK;
 }
 
@@ -349,6 +368,7 @@ extern "C" int pt_step_report_read(pt_ctx* ctx, pt_step_report* out, void* strea
   PtDevState h;
   PT_HIP(ctx, hipMemcpyAsync(&h, ctx->d_state, sizeof h, hipMemcpyDeviceToHost, (hipStream_t)stream));
   PT_HIP(ctx, hipStreamSynchronize((hipStream_t)stream));
+  if (ctx->ended_early) { h.loss_scale = h.old_loss_scale; h.step = h.old_step; h.good_steps = h.old_good_steps; }   // still open for the caller
   out->sqnorm = h.sqnorm; out->norm = h.norm; out->clip_coef = h.clip_coef;
   out->loss_scale = h.loss_scale; out->grad_mult = h.c[8]; out->found_inf = h.found_inf;
   out->step = h.step; out->good_steps = h.good_steps;
@@ -401,9 +421,7 @@ int pt_table_bind(pt_ctx* ctx, const PtBind* binds, int n_binds, uint32_t first,
   // new pointers only once the device table holds them, so a failed upload is retried by the next call instead of being
   // taken for done.
   const uint64_t total = uint64_t(n) * n_binds;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
-  if (cs != hipStreamCaptureStatusNone || total > uint64_t(BIND_PTRS) * BIND_LAUNCHES) {
+  if (pt_capturing(ctx, stream) || total > uint64_t(BIND_PTRS) * BIND_LAUNCHES) {
     PT_HIP(ctx, hipStreamSynchronize(stream));        // refused while the stream is captured: pointers are bound before
     for (int b = 0; b < n_binds; ++b)
       PT_HIP(ctx, hipMemcpy(ctx->d_table + size_t(binds[b].row) * ctx->table_cols + first, binds[b].ptrs, n * sizeof(uint64_t),

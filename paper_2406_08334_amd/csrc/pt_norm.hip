@@ -189,6 +189,7 @@ struct ScalarArgs {
   double* out_sq_norm;
   int32_t* out_found_inf;
   int do_finalize, do_prepare;
+  uint32_t end_step;             // do_prepare: number of the step that ends with it, or 0
   pt_hparams hp;
   PtDevState* mirror;            // pinned host memory that receives the constants, or NULL
 };
@@ -201,11 +202,11 @@ template <class T> __device__ __forceinline__ void st_agent(T* p, T x) { __hip_a
 // correction with t = applied updates + 1; clip coefficient min(1, c/(norm+1e-6)); unscale by the loss scale).
 // bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
 __device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& hp, double bc1, double bc2, double norm, double loss_scale,
-                                             bool override_active, int32_t found_inf, PtDevState* mirror) {
+                                             bool override_active, float override_grad_mult, int32_t found_inf, PtDevState* mirror) {
   double clip = 1.0;
   float c[9];
   if (override_active) {
-    c[8] = st->override_grad_mult;
+    c[8] = override_grad_mult;
   } else {
     if (hp.max_norm > 0.0) {
       const double q = hp.max_norm / (norm + 1e-6);
@@ -236,6 +237,16 @@ __device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& h
   }
 }
 
+// The update reads nothing but the constants and `skip`, so the step can end here, without a launch of its own behind the update
+// (4.8 us; pt_step_end then launches nothing).  What changes is kept: a call of the same step that depends on it takes the
+// end back first (pt_reopen_step).  s: the state this step began with.
+__device__ __forceinline__ void pt_end_early(PtDevState* st, PtDevState s, bool found_inf, uint32_t step_no) {
+  st->old_step = s.step; st->old_good_steps = s.good_steps; st->old_override = s.override_active; st->old_loss_scale = s.loss_scale;
+  pt_advance(s, found_inf);
+  st->step = s.step; st->good_steps = s.good_steps; st->override_active = s.override_active; st->loss_scale = s.loss_scale;
+  st->ended = step_no;
+}
+
 // Partial sums of chunk first + i.
 __device__ __forceinline__ uint32_t partials_of(const PtPendingReduce& r, uint32_t i, uint32_t& lo) {
   if (!r.tile_begin) { lo = i * r.per_chunk; return r.per_chunk; }
@@ -255,6 +266,8 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
   lo = min(hi, lo + blockIdx.x * PT_REDUCE_SEG);
   double acc = 0.0;
   uint32_t f = 0;
+  PtDevState s;                                          // what the last lines need of it, on its way while the sums are taken
+  if (a.do_prepare) s = *a.st;
   if (tid < SC_SUM) {
     double x[8];
     uint32_t y[8];
@@ -269,7 +282,7 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
     pt_wave_sum(acc, f);
     if ((tid & 63) == 0) { s_sum[tid >> 6] = acc; s_flag[tid >> 6] = f; }
   } else if (a.do_prepare && (tid & 63) == 0) {
-    const double t = double(a.st->step + 1);
+    const double t = double(s.step + 1);
     s_bc[(tid - SC_SUM) >> 6] = 1.0 - pow(tid == SC_SUM ? a.hp.beta1 : a.hp.beta2, t);
   }
   __syncthreads();
@@ -329,7 +342,7 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
       a.st->sqnorm = sq;
       a.st->norm = norm;
       a.st->found_inf = inf ? 1 : 0;
-      a.st->override_active = 0;
+      a.st->override_active = s.override_active = 0;
     } else {
       a.out_sq_norm[0] = sq;
       a.out_sq_norm[1] = norm;
@@ -337,8 +350,9 @@ __global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
     }
   }
   if (a.do_prepare) {
-    if (a.do_finalize) prepare_body(a.st, a.hp, s_bc[0], s_bc[1], norm, a.st->loss_scale, false, int32_t(inf), a.mirror);
-    else prepare_body(a.st, a.hp, s_bc[0], s_bc[1], a.st->norm, a.st->loss_scale, a.st->override_active != 0, a.st->found_inf, a.mirror);
+    if (!a.do_finalize) { norm = s.norm; inf = uint32_t(s.found_inf); }
+    prepare_body(a.st, a.hp, s_bc[0], s_bc[1], norm, s.loss_scale, s.override_active != 0, s.override_grad_mult, int32_t(inf), a.mirror);
+    if (a.end_step) pt_end_early(a.st, s, inf != 0, a.end_step);
   }
 }
 
@@ -363,13 +377,15 @@ __global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
 constexpr uint32_t PT_FUSE_MAX_CHUNKS = 8;
 constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 
-static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
+static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror,
+                          hipStream_t stream) {
   ScalarArgs a{};
   if (r) a.r = *r;
   a.chunk_sq = ctx->d_chunk_sq; a.chunk_flag = ctx->d_chunk_flag; a.C = ctx->C; a.ticket = &ctx->d_state->ticket; a.st = ctx->d_state;
   a.do_finalize = finalize ? 1 : 0;
   a.do_prepare = hp ? 1 : 0;
   if (hp) a.hp = *hp;
+  a.end_step = end_step;
   a.mirror = mirror;
   hipLaunchKernelGGL(k_scalars, dim3(a.r.segs, r ? std::max(1u, r->n) : 1u), dim3(SC_THREADS), 0, stream, a);
   PT_LAUNCH_CHECK(ctx, "k_scalars");
@@ -377,8 +393,8 @@ static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, 
 }
 
 // Everything put off, the constants of `hp` behind it if there are any, in one launch.
-static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, PtDevState* mirror, hipStream_t stream) {
-  const int rc = launch_scalars(ctx, ctx->pend_reduce.n ? &ctx->pend_reduce : nullptr, ctx->pend_finalize, hp, mirror, stream);
+static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror, hipStream_t stream) {
+  const int rc = launch_scalars(ctx, ctx->pend_reduce.n ? &ctx->pend_reduce : nullptr, ctx->pend_finalize, hp, end_step, mirror, stream);
   if (rc != PT_OK) return rc;
   ctx->pend_reduce = PtPendingReduce{};
   ctx->pend_finalize = false;
@@ -387,7 +403,7 @@ static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, PtDevState* mirror,
 
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream) {
   if (!ctx->pend_reduce.n && !ctx->pend_finalize) return PT_OK;
-  return launch_pending(ctx, nullptr, nullptr, stream);
+  return launch_pending(ctx, nullptr, 0, nullptr, stream);
 }
 
 // A call is about to write partial sums: a finalize that is still waiting takes the old ones first.
@@ -405,7 +421,7 @@ int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream) {
   if (small && ctx->pend_reduce.n && ctx->pend_reduce.plan == plan) return PT_OK;
   // whatever is pending comes first: a later reduction of the same chunk replaces an earlier one
   const int rc = pt_flush_pending(ctx, stream);
-  if (rc != PT_OK || !small) return rc != PT_OK ? rc : launch_scalars(ctx, &r, false, nullptr, nullptr, stream);
+  if (rc != PT_OK || !small) return rc != PT_OK ? rc : launch_scalars(ctx, &r, false, nullptr, 0, nullptr, stream);
   ctx->pend_reduce = r;
   return PT_OK;
 }
@@ -420,8 +436,14 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
   // a call can be on its way, or has been made before.
   const bool mirror = host_part || ctx->host_pool != nullptr;
   ctx->mirrored = false;
-  const int rc = launch_pending(ctx, hp, mirror ? ctx->h_state_dev : nullptr, stream);
+  int rc = pt_reopen_step(ctx, stream);              // other hyper-parameters: the constants are derived anew
   if (rc != PT_OK) return rc;
+  // The launch is the step's end too (pt_end_early), but not in a graph, whose replays may be followed by a step end outside it, nor
+  // in a context that has graphs.
+  const bool end = !pt_capturing(ctx, stream) && !ctx->captured;
+  rc = launch_pending(ctx, hp, end ? ctx->step_no : 0, mirror ? ctx->h_state_dev : nullptr, stream);
+  if (rc != PT_OK) return rc;
+  ctx->ended_early = end;
   if (mirror) {
     PT_HIP(ctx, hipEventRecord(ctx->ev_scalar, stream));
     ctx->mirrored = true;
@@ -452,7 +474,7 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
   PtPendingReduce r;                             // of a recompute
   if (grad_chunks && n_chunks) {
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);
-    if (rc != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
+    if (rc != PT_OK || (rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
     dim3 grid(ctx->norm_blocks, n_chunks);
     const uint32_t lds = norm_lds(ctx->S * n_chunks, ctx->grad_f32);
     if (ctx->grad_f32)
@@ -491,11 +513,12 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
   // a recompute's own launch takes the sum over the chunks along (recompute, norm and step end of 4e6 words 13.9 -> 12.6 us,
   // of 6.7e7 28.9 -> 27.7)
   if (r.n)
-    if (const int rc = launch_scalars(ctx, &r, final, nullptr, nullptr, st); rc != PT_OK) {
+    if (const int rc = launch_scalars(ctx, &r, final, nullptr, 0, nullptr, st); rc != PT_OK) {
       std::fill_n(ctx->chunk_fresh.begin() + first_chunk, n_chunks, uint8_t(0));
       return rc;
     }
   if (final) {
+    if (const int rc = pt_reopen_step(ctx, st); rc != PT_OK) return rc;
     // Else it runs with the first call that needs it: the update (in the launch that derives its constants), a read-back, or
     // pt_step_end.
     ctx->pend_finalize = !r.n;

@@ -316,7 +316,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
         return pt_fail(ctx, PT_ERR_STATE, "%s: chunk %u already holds the gradients of another plan of this step; its sum of "
                        "squares would be replaced, not added to - pack a chunk with one plan per step (or recompute the "
                        "norm from the chunks with pt_chunk_grad_sqnorm(grad_chunks, ...) before packing again)", who, c);
-    if ((rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
+    if ((rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
   dim3 grid(plan->n_tiles * plan->subs);
   const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : PACK_LDS;

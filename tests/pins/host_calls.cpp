@@ -405,7 +405,43 @@ int recompute_and_norm_in_one_launch() {
   return 0;
 }
 
+// The launch that derives a step's constants is its end too: pt_step_end launches nothing, unless a call of the same step that
+// depends on the step counter or loss scale came in between (which takes the end back), or the context has graphs.
+int step_ends_with_its_constants() {
+  State s(2, 4096);
+  pt_pack_plan* q = s.plan();
+  pt_step_report rep;
+  const hipStream_t cap = fake::stream(0xc0);
+  enum { NOTHING, REPORT, AGAIN, PACK, FINALIZE, RECOMPUTE, OVERRIDE, STATE, OTHER, NO_UPDATE, CAPTURED, AFTERWARDS, N };
+  for (int how = 0; how < N; ++how) {
+    OK(s.pack(q));
+    OK(s.finalize(PT_FINALIZE_STRICT));
+    size_t at = fake::ops.size();
+    if (how != NO_UPDATE) OK(s.update());
+    if (how == REPORT) OK(pt_step_report_read(s.ctx, &rep, nullptr));
+    if (how == AGAIN) OK(s.update(1, 1));
+    if (how == PACK) OK(s.pack(q));
+    if (how == FINALIZE) OK(s.finalize(PT_FINALIZE_CARRY));
+    if (how == RECOMPUTE) OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 1, 0, nullptr));
+    if (how == OVERRIDE) OK(pt_step_override(s.ctx, 1.0f, 0, nullptr));
+    if (how == STATE) OK(pt_ctx_set_state(s.ctx, 3, 1.0, 0, nullptr));
+    pt_hparams hp = HP;
+    hp.lr = 1.0;
+    if (how == OTHER) OK(pt_chunk_adamw_step(s.ctx, &hp, 0, 2, s.g.data(), s.w.data(), s.m.data(), s.v.data(), s.p.data(), nullptr));
+    const bool taken_back = how >= PACK && how <= OTHER;
+    EXPECT(fake::launches("k_reopen", at).size() == (taken_back ? 1u : 0u));
+    at = fake::ops.size();
+    if (how == CAPTURED) fake::capturing[0xc0] = true;
+    OK(pt_step_end(s.ctx, how == CAPTURED ? cap : nullptr));
+    fake::capturing[0xc0] = false;
+    const bool of_its_own = (taken_back && how != OTHER) || how >= NO_UPDATE;      // other constants: ended by their launch again
+    EXPECT(fake::launches("k_step_end", at).size() == (of_its_own ? 1u : 0u));
+  }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
+    {"step_ends_with_its_constants", step_ends_with_its_constants},
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},
     {"finalize_on_a_stream_that_is_gone", finalize_on_a_stream_that_is_gone},

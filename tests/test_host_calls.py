@@ -39,6 +39,7 @@ def exe(tmp_path_factory):
     "plan_destroyed_and_its_reduction_fails",
     "side_streams_are_judged_by_their_own_steps",
     "recompute_and_norm_in_one_launch",
+    "step_ends_with_its_constants",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
