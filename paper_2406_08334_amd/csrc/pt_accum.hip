@@ -29,25 +29,23 @@ __device__ __forceinline__ float word_to_f32(uint32_t w16) {
   }
 }
 
-__device__ __forceinline__ void take(float a, double inv_scale, double& sum, uint32_t& flag) {
-  const double x = (double)a * inv_scale;
+__device__ __forceinline__ void take(float a, double& sum) {
+  const double x = (double)a;
   sum = fma(x, x, sum);
-  flag |= (__float_as_uint(a) & 0x7f800000u) == 0x7f800000u;
 }
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // q: four 16-bit words; acc: the four sums they are added to (or that they replace)
 template <int DT, bool OVERWRITE, bool NORM>
-__device__ __forceinline__ void add4(const u32x2& q, f32x4& acc, double inv_scale, double& a0, double& a1,
-                                     uint32_t& flag) {
+__device__ __forceinline__ void add4(const u32x2& q, f32x4& acc, double& a0, double& a1) {
   const float x[4] = {word_to_f32<DT>(q.x & 0xffffu), word_to_f32<DT>(q.x >> 16),
                       word_to_f32<DT>(q.y & 0xffffu), word_to_f32<DT>(q.y >> 16)};
 #pragma unroll
   for (int k = 0; k < 4; ++k) acc[k] = OVERWRITE ? x[k] : acc[k] + x[k];
   if (NORM) {
-    take(acc[0], inv_scale, a0, flag); take(acc[1], inv_scale, a1, flag);
-    take(acc[2], inv_scale, a0, flag); take(acc[3], inv_scale, a1, flag);
+    take(acc[0], a0); take(acc[1], a1);
+    take(acc[2], a0); take(acc[3], a1);
   }
 }
 
@@ -61,8 +59,7 @@ __device__ __forceinline__ u32x2 load4(const PT_GLOBAL uint16_t* s) {
 
 // nvec units of four elements from sb onto db: two per lane in flight.
 template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED>
-__device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBAL f32x4* db, uint32_t nvec, double inv_scale, double& a0,
-                                          double& a1, uint32_t& flag) {
+__device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBAL f32x4* db, uint32_t nvec, double& a0, double& a1) {
   constexpr int U = 2;
   uint32_t i = threadIdx.x;
   for (; i + (U - 1) * AC_THREADS < nvec; i += U * AC_THREADS) {
@@ -76,7 +73,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
     }
 #pragma unroll
     for (int r = 0; r < U; ++r) {
-      add4<DT, OVERWRITE, NORM>(q[r], a[r], inv_scale, a0, a1, flag);
+      add4<DT, OVERWRITE, NORM>(q[r], a[r], a0, a1);
       __builtin_nontemporal_store(a[r], db + i + r * AC_THREADS);
     }
   }
@@ -84,7 +81,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
     const u32x2 q = load4<ALIGNED>(sb + size_t(i) * 4);
     f32x4 a = {};
     if (!OVERWRITE) a = __builtin_nontemporal_load(db + i);
-    add4<DT, OVERWRITE, NORM>(q, a, inv_scale, a0, a1, flag);
+    add4<DT, OVERWRITE, NORM>(q, a, a0, a1);
     __builtin_nontemporal_store(a, db + i);
   }
 }
@@ -120,30 +117,31 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
 
   const double inv_scale = NORM ? 1.0 / st->loss_scale : 1.0;
   double a0 = 0.0, a1 = 0.0;
-  uint32_t flag = 0;
 
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL f32x4* db = (PT_GLOBAL f32x4*)(dst + head);
-  if (((uintptr_t)sb & 7u) == 0) add_units<DT, OVERWRITE, NORM, true>(sb, db, nvec, inv_scale, a0, a1, flag);
-  else add_units<DT, OVERWRITE, NORM, false>(sb, db, nvec, inv_scale, a0, a1, flag);
+  if (((uintptr_t)sb & 7u) == 0) add_units<DT, OVERWRITE, NORM, true>(sb, db, nvec, a0, a1);
+  else add_units<DT, OVERWRITE, NORM, false>(sb, db, nvec, a0, a1);
 
   // head and tail: at most 3 elements each, one lane per element
   if (threadIdx.x < head) {
     const float x = word_to_f32<DT>(src[threadIdx.x]);
     const float a = OVERWRITE ? x : dst[threadIdx.x] + x;
     dst[threadIdx.x] = a;
-    if (NORM) take(a, inv_scale, a0, flag);
+    if (NORM) take(a, a0);
   }
   if (threadIdx.x < len - tail0) {
     const uint32_t e = tail0 + threadIdx.x;
     const float x = word_to_f32<DT>(src[e]);
     const float a = OVERWRITE ? x : dst[e] + x;
     dst[e] = a;
-    if (NORM) take(a, inv_scale, a1, flag);
+    if (NORM) take(a, a1);
   }
 
   if (NORM) {
-    double acc = a0 + a1;
+    double acc;
+    uint32_t flag;
+    pt_close_sum(a0 + a1, inv_scale, acc, flag);
     pt_wave_sum(acc, flag);
     if (threadIdx.x == 0) {
       tile_sq[blockIdx.x] = acc;

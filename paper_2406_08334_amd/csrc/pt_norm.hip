@@ -4,17 +4,22 @@
 // HBM-bound: 2 bytes read per element.  Each lane issues 16-byte loads that are
 // contiguous across the wavefront (1 KiB per wave instruction), converts every
 // 16-bit word to fp64 and accumulates squares in fp64 (two 16-bit significands
-// multiply exactly, so only the additions round).  Reduction order is fixed:
+// multiply exactly, so only the additions round); the loss scale and the scan for
+// non-finite words cost nothing per element (pt_close_sum).  Reduction order is fixed:
 // lane-serial, then a 64-lane shuffle tree, then the four waves through LDS, then
 // one slot per block - no floating-point atomics, so results are bitwise reproducible.
 //
-// Unused LDS (norm_lds) leaves four workgroups on a compute unit instead of eight, which large arenas read a little faster,
-// presumably for fewer DRAM rows in use.  With the scalar kernel, eight and four: 8.1e8 words 242 and 240 us (6.8 TB/s),
-// 2.1e8 72.3 and 69.8, 9e7 34.0 and 33.2.  The line is where a second set of 1024 workgroups is three quarters full:
-// below it eight at once are faster (4e7 words 19.2 and 20.0 us, 5e7 in fp16 21.4 and 22.5) or it makes no
-// difference (5.8e7 24.3 and 24.5, fp16 24.8 and 24.5; up to one full set).  fp32 chunks are twice the bytes for as many
-// workgroups and gain from four full sets on: 4.2e7 words 31.5 and 36.4 us with the step end, 1.0e8 66.3 and 66.8, 2.0e8
-// 125.1 and 122.8.
+// Three shapes by the size of the call (norm_shape), all with the same order of additions.  Up to 1024 workgroups (four a
+// compute unit, all of them running at once) a lane has all of its loads in flight: what such a call costs is how often it
+// waits.  8.4e6 words 9.3 us with four loads, 8.8 with sixteen (from there on down the host's two launches are the limit), 3.3e7
+// 15.9 and 15.3; 1e8 34.8 and 41.7.  Large arenas are read fastest with few bytes in flight: two loads a lane, and unused LDS that
+// leaves four workgroups on a compute unit instead of eight.  8.1e8 words 233 us (7.2 TB/s with the scalar kernel's 5 us), with
+// four loads 239, one load 291, two loads and no limit 241, six workgroups 237, three 245; 2.5e8 77.0 / 78.5 / 96.3 / 79.2 / 77.9 /
+// 81.4.  The line is where a second set of 1024 workgroups is three quarters full: below it eight at once are faster or
+// it makes no difference (4.5e7 fp16 words 19.7 us either way, 6e7 23.7 with the limit and 25.3 without).  In between four loads
+// are as good as two or better (6e7 23.65, 1e8 34.8 against 35.1).  fp32 chunks are twice the bytes for as many
+// workgroups and gain from the limit from four full sets on: 6.7e7 words 50.8 us with it and two loads, 47.3 with four loads and
+// without it, 1.3e8 88.6 and 86.7, 4e8 239 and 241.
 #include "pt_common.h"
 
 #include <hip/hip_fp16.h>
@@ -27,7 +32,13 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NB_THREADS = PT_REDUCE_THREADS;
-inline uint32_t norm_lds(uint64_t elems, bool fp32) { return elems >= (fp32 ? 4096ull : 1792ull) * PT_NORM_BLOCK_ELEMS ? 36000 : 0; }
+struct NormShape { int unroll; uint32_t lds; };        // 16-byte loads of a lane in flight, unused LDS of a workgroup
+inline NormShape norm_shape(uint64_t elems, bool fp32) {
+  if (elems <= 1024ull * PT_NORM_BLOCK_ELEMS) return {16, 0};
+  return elems < (fp32 ? 4096ull : 1792ull) * PT_NORM_BLOCK_ELEMS ? NormShape{4, 0} : NormShape{2, 36000};
+}
+typedef void (*norm_kernel_t)(const uint64_t*, uint32_t, uint64_t, const PtDevState*, double*, uint32_t*);
+typedef void (*norm_arena_kernel_t)(const void*, uint64_t, double, double*, uint32_t*, uint32_t*);
 
 template <int DT>
 __device__ __forceinline__ double word_to_f64(uint32_t w16) {
@@ -40,61 +51,67 @@ __device__ __forceinline__ double word_to_f64(uint32_t w16) {
 }
 
 template <int DT>
-__device__ __forceinline__ uint32_t pair_nonfinite(uint32_t two_words) {
-  // exponent field all ones in either half
-  constexpr uint32_t E = DT == PT_BF16 ? 0x7f80u : 0x7c00u;
-  uint32_t lo = two_words & E, hi = (two_words >> 16) & E;
-  return (lo == E) | (hi == E);
-}
-
-template <int DT>
-__device__ __forceinline__ void accum_vec(const u32x4& q, double inv_scale, double& a0, double& a1,
-                                          uint32_t& flag) {
+__device__ __forceinline__ void accum_vec(const u32x4& q, double& a0, double& a1) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    double x0 = word_to_f64<DT>(w[k] & 0xffffu) * inv_scale;
-    double x1 = word_to_f64<DT>(w[k] >> 16) * inv_scale;
+    const double x0 = word_to_f64<DT>(w[k] & 0xffffu), x1 = word_to_f64<DT>(w[k] >> 16);
     a0 = fma(x0, x0, a0);
     a1 = fma(x1, x1, a1);
-    flag |= pair_nonfinite<DT>(w[k]);
+  }
+}
+
+__device__ __forceinline__ void accum_vec_f32(const u32x4& q, double& a0, double& a1) {
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {
+    const double x0 = (double)__uint_as_float(q[k]), x1 = (double)__uint_as_float(q[k + 1]);
+    a0 = fma(x0, x0, a0);
+    a1 = fma(x1, x1, a1);
   }
 }
 
 // One block's share of a chunk: the fp64 sum of (g/scale)^2 and the non-finite flag over elements
-// [b*PT_NORM_BLOCK_ELEMS, min(S, (b+1)*PT_NORM_BLOCK_ELEMS)) of the chunk at `base`; valid in thread 0.
-template <int DT>
+// [b*PT_NORM_BLOCK_ELEMS, min(S, (b+1)*PT_NORM_BLOCK_ELEMS)) of the chunk at `base`; valid in thread 0.  U 16-byte loads of a lane
+// are in flight together; neither U nor the end of a chunk changes the order of the additions.
+template <int DT, int U, bool F32 = false>
 __device__ __forceinline__ void sqnorm_block(const PT_GLOBAL u32x4* base, uint64_t S, uint32_t b, double inv_scale,
                                              double& acc, uint32_t& flag) {
-  const uint64_t vec_total = S / 8;
-  const uint64_t v0 = uint64_t(b) * (PT_NORM_BLOCK_ELEMS / 8);
-  uint64_t v1 = v0 + PT_NORM_BLOCK_ELEMS / 8;
-  if (v1 > vec_total) v1 = vec_total;
+  constexpr uint32_t PER_VEC = F32 ? 4 : 8, BLOCK_VECS = PT_NORM_BLOCK_ELEMS / PER_VEC;
+  static_assert(BLOCK_VECS % (U * NB_THREADS) == 0, "a whole block is a number of whole rounds");
+  const uint64_t v0 = uint64_t(b) * BLOCK_VECS, left = S / PER_VEC - v0;
+  base += v0;
   double a0 = 0.0, a1 = 0.0;
-  flag = 0;
-  uint64_t v = v0 + threadIdx.x;
-  // four independent 16-byte loads in flight per lane
-  for (; v + 3 * NB_THREADS < v1; v += 4 * NB_THREADS) {
-    u32x4 q0 = __builtin_nontemporal_load(base + v);
-    u32x4 q1 = __builtin_nontemporal_load(base + v + NB_THREADS);
-    u32x4 q2 = __builtin_nontemporal_load(base + v + 2 * NB_THREADS);
-    u32x4 q3 = __builtin_nontemporal_load(base + v + 3 * NB_THREADS);
-    accum_vec<DT>(q0, inv_scale, a0, a1, flag);
-    accum_vec<DT>(q1, inv_scale, a0, a1, flag);
-    accum_vec<DT>(q2, inv_scale, a0, a1, flag);
-    accum_vec<DT>(q3, inv_scale, a0, a1, flag);
+  auto take = [&](const u32x4& q) {
+    if constexpr (F32) accum_vec_f32(q, a0, a1);
+    else accum_vec<DT>(q, a0, a1);
+  };
+  if (left >= BLOCK_VECS) {
+    for (uint32_t v = threadIdx.x; v < BLOCK_VECS; v += U * NB_THREADS) {
+      u32x4 q[U];
+#pragma unroll
+      for (int r = 0; r < U; ++r) q[r] = __builtin_nontemporal_load(base + v + r * NB_THREADS);
+#pragma unroll
+      for (int r = 0; r < U; ++r) take(q[r]);
+    }
+  } else {                               // the end of a chunk: what lies beyond it counts as zeros
+    for (uint32_t v = threadIdx.x; v < left; v += U * NB_THREADS) {
+      u32x4 q[U];
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        q[r] = u32x4{0, 0, 0, 0};
+        if (v + r * NB_THREADS < left) q[r] = __builtin_nontemporal_load(base + v + r * NB_THREADS);
+      }
+#pragma unroll
+      for (int r = 0; r < U; ++r) take(q[r]);
+    }
   }
-  for (; v < v1; v += NB_THREADS) {
-    u32x4 q = __builtin_nontemporal_load(base + v);
-    accum_vec<DT>(q, inv_scale, a0, a1, flag);
-  }
-  acc = a0 + a1;
+  pt_close_sum(a0 + a1, inv_scale, acc, flag);
   pt_block_sum(acc, flag);
 }
 
 // grid = (norm_blocks, n_chunks).  Block (b, i) reduces its share of chunk first+i, whose base
 // pointer comes from the context's pointer table.
-template <int DT>
+template <int DT, int U>
 __global__ void __launch_bounds__(NB_THREADS)
 k_sqnorm(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
          const PtDevState* __restrict__ st, double* __restrict__ part, uint32_t* __restrict__ flagout) {
@@ -102,7 +119,7 @@ k_sqnorm(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
   const PT_GLOBAL u32x4* base = (const PT_GLOBAL u32x4*)(grad_row[first + i]);   // global_* loads
   double acc;
   uint32_t flag;
-  sqnorm_block<DT>(base, S, b, 1.0 / st->loss_scale, acc, flag);
+  sqnorm_block<DT, U>(base, S, b, 1.0 / st->loss_scale, acc, flag);
   if (threadIdx.x == 0) {
     size_t slot = size_t(first + i) * gridDim.x + b;
     part[slot] = acc;
@@ -111,57 +128,25 @@ k_sqnorm(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
 }
 
 // The same reduction over fp32 gradient chunks (accumulated micro-batches): 4 bytes read per
-// element, every value widened to fp64 before it is scaled and squared.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ void accum_vec_f32(const f32x4& q, double inv_scale, double& a0, double& a1,
-                                              uint32_t& flag) {
-#pragma unroll
-  for (int k = 0; k < 4; k += 2) {
-    double x0 = (double)q[k] * inv_scale;
-    double x1 = (double)q[k + 1] * inv_scale;
-    a0 = fma(x0, x0, a0);
-    a1 = fma(x1, x1, a1);
-    flag |= uint32_t((__float_as_uint(q[k]) & 0x7f800000u) == 0x7f800000u) |
-            uint32_t((__float_as_uint(q[k + 1]) & 0x7f800000u) == 0x7f800000u);
-  }
-}
-
+// element, every value widened to fp64 before it is squared.
+template <int U>
 __global__ void __launch_bounds__(NB_THREADS)
 k_sqnorm_f32(const uint64_t* __restrict__ grad_row, uint32_t first, uint64_t S,
              const PtDevState* __restrict__ st, double* __restrict__ part, uint32_t* __restrict__ flagout) {
   const uint32_t b = blockIdx.x, i = blockIdx.y;
-  const PT_GLOBAL f32x4* base = (const PT_GLOBAL f32x4*)(grad_row[first + i]);
-  const uint64_t vec_total = S / 4;
-  const uint64_t v0 = uint64_t(b) * (PT_NORM_BLOCK_ELEMS / 4);
-  uint64_t v1 = v0 + PT_NORM_BLOCK_ELEMS / 4;
-  if (v1 > vec_total) v1 = vec_total;
-  const double inv_scale = 1.0 / st->loss_scale;
-  double a0 = 0.0, a1 = 0.0;
-  uint32_t flag = 0;
-  uint64_t v = v0 + threadIdx.x;
-  for (; v + 3 * NB_THREADS < v1; v += 4 * NB_THREADS) {
-    f32x4 q0 = __builtin_nontemporal_load(base + v);
-    f32x4 q1 = __builtin_nontemporal_load(base + v + NB_THREADS);
-    f32x4 q2 = __builtin_nontemporal_load(base + v + 2 * NB_THREADS);
-    f32x4 q3 = __builtin_nontemporal_load(base + v + 3 * NB_THREADS);
-    accum_vec_f32(q0, inv_scale, a0, a1, flag);
-    accum_vec_f32(q1, inv_scale, a0, a1, flag);
-    accum_vec_f32(q2, inv_scale, a0, a1, flag);
-    accum_vec_f32(q3, inv_scale, a0, a1, flag);
-  }
-  for (; v < v1; v += NB_THREADS) {
-    f32x4 q = __builtin_nontemporal_load(base + v);
-    accum_vec_f32(q, inv_scale, a0, a1, flag);
-  }
-  double acc = a0 + a1;
-  pt_block_sum(acc, flag);
+  const PT_GLOBAL u32x4* base = (const PT_GLOBAL u32x4*)(grad_row[first + i]);
+  double acc;
+  uint32_t flag;
+  sqnorm_block<0, U, true>(base, S, b, 1.0 / st->loss_scale, acc, flag);
   if (threadIdx.x == 0) {
     size_t slot = size_t(first + i) * gridDim.x + b;
     part[slot] = acc;
     flagout[slot] = flag;
   }
 }
+
+template <int DT> norm_kernel_t pick_norm(int u) { return u == 16 ? k_sqnorm<DT, 16> : u == 4 ? k_sqnorm<DT, 4> : k_sqnorm<DT, 2>; }
+inline norm_kernel_t pick_norm_f32(int u) { return u == 16 ? k_sqnorm_f32<16> : u == 4 ? k_sqnorm_f32<4> : k_sqnorm_f32<2>; }
 
 // ---- the scalar work of a step in one launch ---------------------------------------------------
 //
@@ -475,17 +460,12 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
   if (grad_chunks && n_chunks) {
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);
     if (rc != PT_OK || (rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
-    dim3 grid(ctx->norm_blocks, n_chunks);
-    const uint32_t lds = norm_lds(ctx->S * n_chunks, ctx->grad_f32);
-    if (ctx->grad_f32)
-      hipLaunchKernelGGL(k_sqnorm_f32, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
-                         ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
-    else if (ctx->dtype == PT_BF16)
-      hipLaunchKernelGGL(k_sqnorm<PT_BF16>, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
-                         ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
-    else
-      hipLaunchKernelGGL(k_sqnorm<PT_FP16>, grid, dim3(NB_THREADS), lds, st, pt_row(ctx, ROW_PACK), first_chunk,
-                         ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
+    const NormShape shape = norm_shape(ctx->S * n_chunks, ctx->grad_f32);
+    norm_kernel_t kern = ctx->grad_f32          ? pick_norm_f32(shape.unroll)
+                         : ctx->dtype == PT_BF16 ? pick_norm<PT_BF16>(shape.unroll)
+                                                 : pick_norm<PT_FP16>(shape.unroll);
+    hipLaunchKernelGGL(kern, dim3(ctx->norm_blocks, n_chunks), dim3(NB_THREADS), shape.lds, st, pt_row(ctx, ROW_PACK), first_chunk,
+                       ctx->S, ctx->d_state, ctx->d_norm_part, ctx->d_norm_flag);
     PT_LAUNCH_CHECK(ctx, "k_sqnorm");
     r.part = ctx->d_norm_part + size_t(first_chunk) * ctx->norm_blocks;
     r.flag = ctx->d_norm_flag + size_t(first_chunk) * ctx->norm_blocks;
@@ -561,7 +541,7 @@ static __device__ __align__(256) unsigned char scratch[sizeof(PtStaticScratch)];
 namespace {
 
 // As k_sqnorm, for chunks that lie back to back in one arena; the loss scale comes by value.
-template <int DT>
+template <int DT, int U>
 __global__ void __launch_bounds__(NB_THREADS)
 k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, double* __restrict__ part,
                uint32_t* __restrict__ flagout, uint32_t* __restrict__ ticket) {
@@ -569,13 +549,17 @@ k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, do
   const PT_GLOBAL u32x4* base = (const PT_GLOBAL u32x4*)((uint64_t)(uintptr_t)arena + 2ull * S * i);
   double acc;
   uint32_t flag;
-  sqnorm_block<DT>(base, S, b, 1.0 / loss_scale, acc, flag);
+  sqnorm_block<DT, U>(base, S, b, 1.0 / loss_scale, acc, flag);
   if (threadIdx.x == 0) {
     if (b == 0 && i == 0) *ticket = 0;       // whatever calls that overlapped in time have left there
     size_t slot = size_t(i) * gridDim.x + b;
     part[slot] = acc;
     flagout[slot] = flag;
   }
+}
+
+template <int DT> norm_arena_kernel_t pick_norm_arena(int u) {
+  return u == 16 ? k_sqnorm_arena<DT, 16> : u == 4 ? k_sqnorm_arena<DT, 4> : k_sqnorm_arena<DT, 2>;
 }
 
 std::mutex g_scratch_mutex;
@@ -633,16 +617,12 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   PtStaticScratch* sc = static_cast<PtStaticScratch*>(base);
   hipStream_t st = (hipStream_t)stream;
   dim3 grid((uint32_t)blocks_per_chunk, n_chunks);
-  const uint32_t lds = norm_lds(chunk_elems * n_chunks, false);
+  const NormShape shape = norm_shape(chunk_elems * n_chunks, false);
   // Nothing here has to start at zero: each launch writes every partial and per-chunk slot that the
   // next one reads (n_chunks * blocks_per_chunk partials, n_chunks sums), so stale contents of an
   // earlier, larger call are never read.
-  if (dtype == PT_BF16)
-    hipLaunchKernelGGL(k_sqnorm_arena<PT_BF16>, grid, dim3(NB_THREADS), lds, st, grad_arena, chunk_elems, loss_scale,
-                       sc->part, sc->flag, &sc->ticket);
-  else
-    hipLaunchKernelGGL(k_sqnorm_arena<PT_FP16>, grid, dim3(NB_THREADS), lds, st, grad_arena, chunk_elems, loss_scale,
-                       sc->part, sc->flag, &sc->ticket);
+  norm_arena_kernel_t kern = dtype == PT_BF16 ? pick_norm_arena<PT_BF16>(shape.unroll) : pick_norm_arena<PT_FP16>(shape.unroll);
+  hipLaunchKernelGGL(kern, grid, dim3(NB_THREADS), shape.lds, st, grad_arena, chunk_elems, loss_scale, sc->part, sc->flag, &sc->ticket);
   if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_sqnorm_arena failed");
   ScalarArgs a{};
   a.r.part = sc->part; a.r.flag = sc->flag; a.r.n = n_chunks; a.r.per_chunk = (uint32_t)blocks_per_chunk;

@@ -23,8 +23,7 @@ constexpr int PK_THREADS = 64;
 
 // The square of one word joins the sum (two 16-bit significands multiply exactly: only the addition rounds).
 template <int DT>
-__device__ __forceinline__ void take(uint32_t w16, double inv_scale, double& sum, uint32_t& flag) {
-  constexpr uint32_t E = DT == PT_BF16 ? 0x7f80u : 0x7c00u;
+__device__ __forceinline__ void take(uint32_t w16, double& sum) {
   double x;
   if (DT == PT_BF16) {
     x = (double)__uint_as_float(w16 << 16);
@@ -32,17 +31,15 @@ __device__ __forceinline__ void take(uint32_t w16, double inv_scale, double& sum
     __half_raw r; r.x = (unsigned short)w16;
     x = (double)__half2float(__half(r));
   }
-  x *= inv_scale;
   sum = fma(x, x, sum);
-  flag |= (w16 & E) == E;
 }
 
 template <int DT>
-__device__ __forceinline__ void take_vec(const u32x4& q, double inv_scale, double& a0, double& a1, uint32_t& flag) {
+__device__ __forceinline__ void take_vec(const u32x4& q, double& a0, double& a1) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    take<DT>(q[k] & 0xffffu, inv_scale, a0, flag);
-    take<DT>(q[k] >> 16, inv_scale, a1, flag);
+    take<DT>(q[k] & 0xffffu, a0);
+    take<DT>(q[k] >> 16, a1);
   }
 }
 
@@ -65,8 +62,7 @@ __device__ __forceinline__ u32x4 load_vec(const PT_GLOBAL uint16_t* s) {
 
 // nvec vectors from sb to db: U per lane in flight.
 template <int DT, int DIR, bool NTS, bool ALIGNED>
-__device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBAL u32x4* db, uint32_t nvec, double inv_scale,
-                                          double& a0, double& a1, uint32_t& flag) {
+__device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBAL u32x4* db, uint32_t nvec, double& a0, double& a1) {
   constexpr int U = DIR == 0 ? 4 : 2;
   uint32_t i = threadIdx.x;
   for (; i + (U - 1) * PK_THREADS < nvec; i += U * PK_THREADS) {
@@ -77,12 +73,12 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
     for (int r = 0; r < U; ++r) store_vec<NTS>(q[r], db + i + r * PK_THREADS);
     if (DIR == 0)
 #pragma unroll
-      for (int r = 0; r < U; ++r) take_vec<DT>(q[r], inv_scale, a0, a1, flag);
+      for (int r = 0; r < U; ++r) take_vec<DT>(q[r], a0, a1);
   }
   for (; i < nvec; i += PK_THREADS) {
     const u32x4 q = load_vec<DIR, ALIGNED>(sb + size_t(i) * 8);
     store_vec<NTS>(q, db + i);
-    if (DIR == 0) take_vec<DT>(q, inv_scale, a0, a1, flag);
+    if (DIR == 0) take_vec<DT>(q, a0, a1);
   }
 }
 
@@ -125,28 +121,29 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
 
   const double inv_scale = DIR == 0 ? 1.0 / st->loss_scale : 1.0;
   double a0 = 0.0, a1 = 0.0;
-  uint32_t flag = 0;
 
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL u32x4* db = (PT_GLOBAL u32x4*)(dst + head);
-  if (((uintptr_t)sb & 15u) == 0) move_vecs<DT, DIR, NTS, true>(sb, db, nvec, inv_scale, a0, a1, flag);
-  else move_vecs<DT, DIR, NTS, false>(sb, db, nvec, inv_scale, a0, a1, flag);
+  if (((uintptr_t)sb & 15u) == 0) move_vecs<DT, DIR, NTS, true>(sb, db, nvec, a0, a1);
+  else move_vecs<DT, DIR, NTS, false>(sb, db, nvec, a0, a1);
 
   // head and tail: at most 7 elements each, one lane per element
   if (threadIdx.x < head) {
     const uint16_t w = src[threadIdx.x];
     dst[threadIdx.x] = w;
-    if (DIR == 0) take<DT>(w, inv_scale, a0, flag);
+    if (DIR == 0) take<DT>(w, a0);
   }
   if (threadIdx.x < len - tail0) {
     const uint32_t e = tail0 + threadIdx.x;
     const uint16_t w = src[e];
     dst[e] = w;
-    if (DIR == 0) take<DT>(w, inv_scale, a1, flag);
+    if (DIR == 0) take<DT>(w, a1);
   }
 
   if (DIR == 0) {
-    double acc = a0 + a1;
+    double acc;
+    uint32_t flag;
+    pt_close_sum(a0 + a1, inv_scale, acc, flag);
     pt_wave_sum(acc, flag);
     if (threadIdx.x == 0) {
       tile_sq[blockIdx.x] = acc;
