@@ -57,8 +57,14 @@ __device__ __forceinline__ u32x2 load4(const PT_GLOBAL uint16_t* s) {
   return __builtin_nontemporal_load((const PT_GLOBAL u32x2_a2*)s);
 }
 
+// KEEP: sums that stay in the Infinity Cache (pt_in_cache) are loaded without the hint; stores need none of that.
+template <bool KEEP> __device__ __forceinline__ f32x4 load_sums(const PT_GLOBAL f32x4* p) {
+  if constexpr (KEEP) return *p;
+  else return __builtin_nontemporal_load(p);
+}
+
 // nvec units of four elements from sb onto db: two per lane in flight.
-template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED>
+template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED, bool KEEP>
 __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBAL f32x4* db, uint32_t nvec, double& a0, double& a1) {
   constexpr int U = 2;
   uint32_t i = threadIdx.x;
@@ -69,7 +75,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
     for (int r = 0; r < U; ++r) {
       q[r] = load4<ALIGNED>(sb + size_t(i + r * AC_THREADS) * 4);
       if (OVERWRITE) a[r] = f32x4{};
-      else a[r] = __builtin_nontemporal_load(db + i + r * AC_THREADS);
+      else a[r] = load_sums<KEEP>(db + i + r * AC_THREADS);
     }
 #pragma unroll
     for (int r = 0; r < U; ++r) {
@@ -80,7 +86,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
   for (; i < nvec; i += AC_THREADS) {
     const u32x2 q = load4<ALIGNED>(sb + size_t(i) * 4);
     f32x4 a = {};
-    if (!OVERWRITE) a = __builtin_nontemporal_load(db + i);
+    if (!OVERWRITE) a = load_sums<KEEP>(db + i);
     add4<DT, OVERWRITE, NORM>(q, a, a0, a1);
     __builtin_nontemporal_store(a, db + i);
   }
@@ -90,9 +96,10 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // compute unit.  Adding 3.3e8 words: 521 us with workgroups of four waves and tiles of 4096
 // taken from two ends of the list, 510 with three of those on a unit, 493 now (6.6 TB/s) - 507 with four units per lane in
 // flight, 513 without the limit, 535-550 with 2048 elements per wave.
-// 12 waves suit large sums; small ones, and a first micro-batch that only writes its sums (6 bytes an element instead of 10),
-// want 17.  With 12 and 17, adding: 4e6 words 9.4 and 8.7 us, 1.5e7 26.0 and 25.1, 3e7 48.0 and 47.1, 6e7 91.8 and 92.7,
-// 3.3e8 493 and 507; writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298; writing with the norm: 3e7 39.7 and
+// 12 waves suit large sums; small ones, which lie in the cache (pt_in_cache), and a first micro-batch that only writes its
+// sums (6 bytes an element instead of 10), want 17.  With 12 and 17, four added and the update: 7e6 words 108.5 and 104.1 us, 1.5e7
+// 199 and 189, 3e7 364 and 352, 6e7 696 and 683, 8.5e7 966 and 954, 1.24e8 1365 and 1360, 2.0e8 2302 and 2360, 3.3e8 3630 and 3720
+// (four units a lane in flight with 12: 6e7 690, 2e6 44.4 -> 46.9); writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298; writing with the norm: 3e7 39.7 and
 // 34.3, 3.3e8 401 and 326.  Four launches over 6.7e9 elements whose halves lie in
 // different 96 GiB regions of the memory: 37.5 to 41.5 ms from process to process before, 38.6-38.9 now.
 inline uint32_t accum_lds(bool overwrite, uint64_t elems) { return overwrite || elems < (1ull << 25) ? 9000 : 13000; }
@@ -100,7 +107,7 @@ inline uint32_t accum_lds(bool overwrite, uint64_t elems) { return overwrite || 
 template <int DT, bool OVERWRITE, bool NORM>
 __global__ void __launch_bounds__(AC_THREADS)
 k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row, uint32_t subs, uint32_t sub_elems,
-        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag) {
+        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag, uint64_t S, uint64_t cached) {
   const uint32_t tile = blockIdx.x / subs;
   const PtTile t = tiles[tile];
   uint32_t lo, hi;
@@ -120,8 +127,14 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
 
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL f32x4* db = (PT_GLOBAL f32x4*)(dst + head);
-  if (((uintptr_t)sb & 7u) == 0) add_units<DT, OVERWRITE, NORM, true>(sb, db, nvec, a0, a1);
-  else add_units<DT, OVERWRITE, NORM, false>(sb, db, nvec, a0, a1);
+  const bool aligned = ((uintptr_t)sb & 7u) == 0;
+  if (!OVERWRITE && pt_in_cache(t.chunk, S, t.chunk_off, cached)) {
+    if (aligned) add_units<DT, OVERWRITE, NORM, true, true>(sb, db, nvec, a0, a1);
+    else add_units<DT, OVERWRITE, NORM, false, true>(sb, db, nvec, a0, a1);
+  } else {
+    if (aligned) add_units<DT, OVERWRITE, NORM, true, false>(sb, db, nvec, a0, a1);
+    else add_units<DT, OVERWRITE, NORM, false, false>(sb, db, nvec, a0, a1);
+  }
 
   // head and tail: at most 3 elements each, one lane per element
   if (threadIdx.x < head) {
@@ -150,7 +163,7 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
   }
 }
 
-typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, uint32_t, uint32_t, const PtDevState*, double*, uint32_t*);
+typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, uint32_t, uint32_t, const PtDevState*, double*, uint32_t*, uint64_t, uint64_t);
 
 template <int DT>
 accum_kernel_t pick(bool overwrite, bool norm) {
@@ -177,8 +190,8 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   if (take_norm && ((rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK)) return rc;
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
-  hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st, plan->d_tiles, pt_row(ctx, ROW_PACK),
-                     plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
+  hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st,
+                     plan->d_tiles, pt_row(ctx, ROW_PACK), plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {
     rc = pt_reduce_plan(ctx, plan, st);

@@ -163,14 +163,13 @@ __device__ __forceinline__ ChunkPtrs<GF32> chunk_ptrs(uint64_t g, uint64_t w, ui
           uint32_t(w >> 4) & (LINE_UNITS - 1)};
 }
 
-// Tile `tile` of a chunk.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
-template <int TH, int DT, int UNROLL, int HINT, bool MASKED, bool GF32>
+// Tile `tile` of a chunk.  gcached: its gradients are kept in the cache (pt_in_cache).  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
 __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
-                                            uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
+                                            bool gcached, uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
                                             const uint64_t* __restrict__ nd_ranges) {
   typedef typename GradUnit<GF32>::vec gvec;
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
-  constexpr bool NT = HINT != PT_HINT_NONE, NTG = HINT == PT_HINT_ALL;
   const gvec gzero = {};
   // first unit of the tile; "negative" (wrapped around, above `units`) for the idle lanes of the first tile
   const uint64_t ub = tile * TILE_UNITS - x.back;
@@ -180,7 +179,7 @@ __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const
 #pragma unroll
     for (int r = 0; r < UNROLL; ++r) {
       const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-      g[r] = ld_stream<NTG>(x.g + ub + o);
+      g[r] = !NT || gcached ? ld_stream<false>(x.g + ub + o) : ld_stream<true>(x.g + ub + o);
       w[r] = ld_stream<NT>(x.w + ub + o);
       m[r] = ld_stream<NT>(x.m + ub + o);
       v[r] = ld_stream<NT>(x.v + ub + o);
@@ -261,11 +260,11 @@ __device__ __forceinline__ Consts load_consts(const PtDevState* __restrict__ st)
   return k;
 }
 
-template <int TH, int DT, int UNROLL, int HINT, bool MASKED, bool GF32>
+template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
 __global__ void __launch_bounds__(TH)
 k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, uint32_t table_cols, uint32_t first_col,
         uint32_t n_cols, uint32_t mask_chunk0, uint64_t units, uint64_t tiles, int recast_on_skip, int zero_grads,
-        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges) {
+        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges, uint64_t cached) {
   const int32_t skip = st->skip;
   const Consts k = load_consts(st);
   for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
@@ -274,8 +273,8 @@ k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, u
                                                t[size_t(ROW_M) * table_cols], t[size_t(ROW_V) * table_cols],
                                                t[size_t(ROW_P16) * table_cols]);
     for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-      update_tile<TH, DT, UNROLL, HINT, MASKED, GF32>(k, skip, x, tile, units, mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin,
-                                                    nd_ranges);
+      update_tile<TH, DT, UNROLL, NT, MASKED, GF32>(k, skip, x, tile, units, pt_in_cache(first_col + ci, units, tile * (TH * UNROLL), cached),
+                                                  mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin, nd_ranges);
   }
 }
 
@@ -310,7 +309,7 @@ k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_
     const ChunkPtrs<GF32> x = chunk_ptrs<GF32>(a[0], a[1], a[2], a[3], a[4]);
     for (; tile < tiles; tile += groups) {
       if (!skip) {
-        update_tile<HOST_TH, DT, 1, PT_HINT_ALL, MASKED, GF32>(k, 0, x, tile, units, mask_chunk0 + ci, 0, 0, nd_begin, nd_ranges);
+        update_tile<HOST_TH, DT, 1, true, MASKED, GF32>(k, 0, x, tile, units, false, mask_chunk0 + ci, 0, 0, nd_begin, nd_ranges);
         continue;
       }
       // a skipped step leaves param16 as the recast of the master weights, as the chunk buffers do
@@ -331,12 +330,11 @@ k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_
 // momentum and variance are stored back as loaded and param16 is re-derived from the master weight
 // (which is what it holds already), so the state does not change.  What this kernel attains is what the
 // memory system gives this mix of streams on this placement; the update runs within 2 % of it, on either side.
-template <int TH, int DT, int UNROLL, int HINT>
+template <int TH, int DT, int UNROLL, bool NT>
 __global__ void __launch_bounds__(TH)
 k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_col, uint32_t n_cols,
-                uint64_t units, uint64_t tiles, uint32_t* __restrict__ sink) {
+                uint64_t units, uint64_t tiles, uint32_t* __restrict__ sink, uint64_t cached) {
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
-  constexpr bool NT = HINT != PT_HINT_NONE, NTG = HINT == PT_HINT_ALL;
   uint32_t keep = 0;
   for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
     const uint32_t col = first_col + ci;
@@ -349,12 +347,13 @@ k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_
     const uint32_t back = uint32_t(wa >> 4) & (LINE_UNITS - 1);
     for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
       const uint64_t ub = tile * TILE_UNITS - back;
+      const bool gcached = pt_in_cache(col, units, tile * TILE_UNITS, cached);
       if (!(ub < units && units - ub >= TILE_UNITS)) continue;      // first and last tiles are left out (a few KiB per chunk)
       u32x2 g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
 #pragma unroll
       for (int r = 0; r < UNROLL; ++r) {
         const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-        g[r] = ld_stream<NTG>(gp + ub + o);
+        g[r] = gcached ? ld_stream<false>(gp + ub + o) : ld_stream<NT>(gp + ub + o);
         w[r] = ld_stream<NT>(wp + ub + o);
         m[r] = ld_stream<NT>(mp + ub + o);
         v[r] = ld_stream<NT>(vp + ub + o);
@@ -379,14 +378,14 @@ k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_
 }
 
 typedef void (*adamw_kernel_t)(const uint64_t*, const PtDevState*, uint32_t, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t,
-                               int, int, const uint32_t*, const uint64_t*);
-typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*);
+                               int, int, const uint32_t*, const uint64_t*, uint64_t);
+typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*, uint64_t);
 
 // The instantiation for a launch shape: the library's own (64 lanes, one unit each), and what the options adamw_threads and
 // adamw_unroll ask for.  The latter lose to the former at every size measured; they stay for the options.
-template <int DT, int HINT, bool MASKED, bool GF32>
+template <int DT, bool NT, bool MASKED, bool GF32>
 struct Kernels {
-  template <int TH, int U> static adamw_kernel_t adamw() { return k_adamw<TH, DT, U, HINT, MASKED, GF32>; }
+  template <int TH, int U> static adamw_kernel_t adamw() { return k_adamw<TH, DT, U, NT, MASKED, GF32>; }
   template <int TH> static adamw_kernel_t by_unroll(uint32_t u) {
     return u == 1 ? adamw<TH, 1>() : u == 2 ? adamw<TH, 2>() : u == 8 ? adamw<TH, 8>() : adamw<TH, 4>();
   }
@@ -395,37 +394,32 @@ struct Kernels {
   }
 };
 
-template <int DT, int HINT>
+template <int DT, bool NT>
 adamw_kernel_t pick_flags(const PtAdamwShape& s, bool masked, bool gf32) {
-  if constexpr (HINT != PT_HINT_STATE)          // fp32 gradient chunks never leave their hints out alone (pt_adamw_hints)
-    if (gf32) return masked ? Kernels<DT, HINT, true, true>::pick(s) : Kernels<DT, HINT, false, true>::pick(s);
-  return masked ? Kernels<DT, HINT, true, false>::pick(s) : Kernels<DT, HINT, false, false>::pick(s);
+  if (gf32) return masked ? Kernels<DT, NT, true, true>::pick(s) : Kernels<DT, NT, false, true>::pick(s);
+  return masked ? Kernels<DT, NT, true, false>::pick(s) : Kernels<DT, NT, false, false>::pick(s);
 }
 
 template <int DT>
-adamw_kernel_t pick_kernel(const PtAdamwShape& s, PtHints h, bool masked, bool gf32) {
-  return h == PT_HINT_NONE    ? pick_flags<DT, PT_HINT_NONE>(s, masked, gf32)
-         : h == PT_HINT_STATE ? pick_flags<DT, PT_HINT_STATE>(s, masked, gf32)
-                              : pick_flags<DT, PT_HINT_ALL>(s, masked, gf32);
+adamw_kernel_t pick_kernel(const PtAdamwShape& s, bool nt, bool masked, bool gf32) {
+  return nt ? pick_flags<DT, true>(s, masked, gf32) : pick_flags<DT, false>(s, masked, gf32);
 }
 
-template <int TH, int DT, int HINT>
+template <int TH, int DT, bool NT>
 pattern_kernel_t pattern_by_unroll(uint32_t u) {
-  return u == 1 ? k_adamw_pattern<TH, DT, 1, HINT> : u == 2 ? k_adamw_pattern<TH, DT, 2, HINT>
-       : u == 8 ? k_adamw_pattern<TH, DT, 8, HINT> : k_adamw_pattern<TH, DT, 4, HINT>;
+  return u == 1 ? k_adamw_pattern<TH, DT, 1, NT> : u == 2 ? k_adamw_pattern<TH, DT, 2, NT>
+       : u == 8 ? k_adamw_pattern<TH, DT, 8, NT> : k_adamw_pattern<TH, DT, 4, NT>;
 }
 
-template <int DT, int HINT>
+template <int DT, bool NT>
 pattern_kernel_t pattern_by_shape(const PtAdamwShape& s) {
-  return s.threads == 64 ? k_adamw_pattern<64, DT, 1, HINT>
-                         : s.threads == 256 ? pattern_by_unroll<256, DT, HINT>(s.unroll) : pattern_by_unroll<512, DT, HINT>(s.unroll);
+  return s.threads == 64 ? k_adamw_pattern<64, DT, 1, NT>
+                         : s.threads == 256 ? pattern_by_unroll<256, DT, NT>(s.unroll) : pattern_by_unroll<512, DT, NT>(s.unroll);
 }
 
 template <int DT>
-pattern_kernel_t pick_pattern(const PtAdamwShape& s, PtHints h) {
-  return h == PT_HINT_NONE    ? pattern_by_shape<DT, PT_HINT_NONE>(s)
-         : h == PT_HINT_STATE ? pattern_by_shape<DT, PT_HINT_STATE>(s)
-                              : pattern_by_shape<DT, PT_HINT_ALL>(s);
+pattern_kernel_t pick_pattern(const PtAdamwShape& s, bool nt) {
+  return nt ? pattern_by_shape<DT, true>(s) : pattern_by_shape<DT, false>(s);
 }
 
 // Tiles per chunk and grid of an update launch over n_cols chunks.
@@ -457,13 +451,13 @@ int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_
     return pt_fail(ctx, PT_ERR_UNSUPPORTED, "update launch of %u chunks exceeds 2^31 tiles", n_cols);
   const PtAdamwShape shape = pt_adamw_shape(ctx, n_cols);
   const Geometry geo = geometry(ctx, shape, n_cols);
-  const PtHints hints = pt_adamw_hints(ctx);
+  const bool hints = pt_adamw_hints(ctx);
   const bool masked = ctx->d_nd_begin != nullptr;
   adamw_kernel_t kern = ctx->dtype == PT_BF16 ? pick_kernel<PT_BF16>(shape, hints, masked, ctx->grad_f32)
                                               : pick_kernel<PT_FP16>(shape, hints, masked, ctx->grad_f32);
   hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, ctx->d_table, ctx->d_state, ctx->table_cols,
                      first_col, n_cols, mask_chunk0, ctx->S / 4, geo.tiles, recast_on_skip ? 1 : 0, zero_grads ? 1 : 0,
-                     ctx->d_nd_begin, ctx->d_nd_ranges);
+                     ctx->d_nd_begin, ctx->d_nd_ranges, pt_cached_elems(ctx) / 4);
   PT_LAUNCH_CHECK(ctx, "k_adamw");
   return PT_OK;
 }
@@ -526,10 +520,10 @@ extern "C" int pt_calib_adamw_pattern(pt_ctx* ctx, uint32_t first_chunk, uint32_
   if (too_many_tiles(ctx, n_chunks)) return pt_fail(ctx, PT_ERR_UNSUPPORTED, "pt_calib_adamw_pattern: more than 2^31 tiles");
   const PtAdamwShape shape = pt_adamw_shape(ctx, n_chunks);
   const Geometry geo = geometry(ctx, shape, n_chunks);
-  const PtHints hints = pt_adamw_hints(ctx);
+  const bool hints = pt_adamw_hints(ctx);
   pattern_kernel_t kern = ctx->dtype == PT_BF16 ? pick_pattern<PT_BF16>(shape, hints) : pick_pattern<PT_FP16>(shape, hints);
   hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, (hipStream_t)stream, ctx->d_table, ctx->table_cols,
-                     first_chunk, n_chunks, ctx->S / 4, geo.tiles, (uint32_t*)nullptr);
+                     first_chunk, n_chunks, ctx->S / 4, geo.tiles, (uint32_t*)nullptr, pt_cached_elems(ctx) / 4);
   PT_LAUNCH_CHECK(ctx, "k_adamw_pattern");
   return PT_OK;
 }

@@ -330,16 +330,19 @@ inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
 // Non-temporal hints of an update launch.  On unless switched off: in the library's shape they gain 4-15 % at every size,
 // whether the state was last touched a step ago or 512 MB of other traffic earlier (update with and without hints: 16 MB
 // of state 16.0 / 17.8 us, 108 MB 45.3 / 51.8, 108 MB touched just before 44.6 / 48.2, 733 MB 217 / 237).
-// The gradient words are the exception: pack has just written them, and where the context's gradient chunks fit the 256 MB
-// Infinity Cache together, pack's stores and the update's gradient loads go without hints, so that the update finds them
-// there (step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615; beyond it the cache holds too little: 667 M 3261 ->
-// 3325).  fp32 gradient chunks keep the hints.
-enum PtHints : int { PT_HINT_NONE = 0, PT_HINT_STATE = 1, PT_HINT_ALL = 2 };     // STATE: all but the gradient loads
-inline bool pt_grads_cached(const pt_ctx* ctx) { return !ctx->grad_f32 && 2 * ctx->S * uint64_t(ctx->C) <= (uint64_t(256) << 20); }
-inline PtHints pt_adamw_hints(const pt_ctx* ctx) {
-  if (ctx->opt_adamw_nt == 0) return PT_HINT_NONE;
-  return pt_grads_cached(ctx) ? PT_HINT_STATE : PT_HINT_ALL;
-}
+// The gradient chunks are the exception: what pack or accumulate has written, the next accumulation or the update reads.  Their
+// first PT_CACHED_BYTES are loaded there - and stored by pack - without hints and stay in the 256 MB Infinity Cache from call to call;
+// traffic with hints does not take it from them, but words without hints beyond its size push each other out.  fp32 sums, four
+// micro-batches and the update, with hints and without: 2e6 elements 46.5 -> 44.4 us, 7e6 113 -> 103, 3e7 375 -> 352, 6e7
+// 743 -> 696, 1.24e8 1422 -> 1364, 3.3e8 3715 -> 3635 (without hints on all of them 3800); 192 to 240 MB differ by less than 1 %,
+// 300 MB costs 1.24e8 elements 5 %.  Where 1 GB of other traffic comes between the calls they take 23.8 -> 25.3 us (1.1e7
+// elements), 52.8 -> 52.7 (3e7), 88 -> 86 (5.3e7).  The accumulate kernel's stores make no difference.  16-bit words, a
+// step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615, 200 M 1075 -> 1067, 667 M within its spread.
+inline bool pt_adamw_hints(const pt_ctx* ctx) { return ctx->opt_adamw_nt != 0; }
+constexpr uint64_t PT_CACHED_BYTES = 240ull << 20;
+inline uint64_t pt_cached_elems(const pt_ctx* ctx) { return PT_CACHED_BYTES / (ctx->grad_f32 ? 4 : 2); }
+// Whether element `off` of chunk `chunk` (of S elements each) is one of the first `cached`.
+__device__ __forceinline__ bool pt_in_cache(uint32_t chunk, uint64_t S, uint64_t off, uint64_t cached) { return chunk * S + off < cached; }
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
                     uint32_t mask_chunk0, bool zero_grads);
 // The update of n chunks in pinned host memory, in place (at[i]: gradient, master, m, v, param16 of chunk i as device

@@ -84,7 +84,7 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
-// NTS: non-temporal stores; without them the gradient words stay in the Infinity Cache for the update (pt_grads_cached).
+// Stores with non-temporal hints, but for gradient words that stay in the Infinity Cache for the update (pt_in_cache).
 //
 // Few bytes in flight, in address order, are moved fastest (as in the update).  One wave moves 4 KiB, two vectors a lane at a
 // time, and unused LDS keeps few waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of
@@ -102,10 +102,10 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 inline uint32_t pack_lds(uint64_t elems) { return elems < (1ull << 26) ? 9000 : 12000; }
 inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : elems < (1ull << 28) ? 9000 : 11500; }
 
-template <int DT, int DIR, bool NTS>
+template <int DT, int DIR>
 __global__ void __launch_bounds__(PK_THREADS)
 k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row, uint32_t subs, uint32_t sub_elems,
-       const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag) {
+       const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag, uint64_t S, uint64_t cached) {
   const uint32_t tile = blockIdx.x / subs;
   const PtTile t = tiles[tile];
   uint32_t lo, hi;
@@ -128,8 +128,14 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
 
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL u32x4* db = (PT_GLOBAL u32x4*)(dst + head);
-  if (((uintptr_t)sb & 15u) == 0) move_vecs<DT, DIR, NTS, true>(sb, db, nvec, a0, a1);
-  else move_vecs<DT, DIR, NTS, false>(sb, db, nvec, a0, a1);
+  const bool aligned = ((uintptr_t)sb & 15u) == 0;
+  if (DIR == 0 && pt_in_cache(t.chunk, S, t.chunk_off, cached)) {
+    if (aligned) move_vecs<DT, DIR, false, true>(sb, db, nvec, a0, a1);
+    else move_vecs<DT, DIR, false, false>(sb, db, nvec, a0, a1);
+  } else {
+    if (aligned) move_vecs<DT, DIR, true, true>(sb, db, nvec, a0, a1);
+    else move_vecs<DT, DIR, true, false>(sb, db, nvec, a0, a1);
+  }
 
   // head and tail: at most 7 elements each, one lane per element
   if (threadIdx.x < head) {
@@ -321,11 +327,9 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
   }
   dim3 grid(plan->n_tiles * plan->subs);
   const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : pack_lds(plan->total_elems);
-  const bool bf16 = ctx->dtype == PT_BF16, nts = DIR == 1 || !pt_grads_cached(ctx);
-  auto kern = nts ? (bf16 ? k_pack<PT_BF16, DIR, true> : k_pack<PT_FP16, DIR, true>)
-                  : (bf16 ? k_pack<PT_BF16, DIR, DIR == 1> : k_pack<PT_FP16, DIR, DIR == 1>);
+  auto kern = ctx->dtype == PT_BF16 ? k_pack<PT_BF16, DIR> : k_pack<PT_FP16, DIR>;
   hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), plan->subs, plan->sub_elems,
-                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag);
+                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
     rc = pt_reduce_plan(ctx, plan, st);
