@@ -163,10 +163,10 @@ __device__ __forceinline__ ChunkPtrs<GF32> chunk_ptrs(uint64_t g, uint64_t w, ui
           uint32_t(w >> 4) & (LINE_UNITS - 1)};
 }
 
-// Tile `tile` of a chunk.  gcached: its gradients are kept in the cache (pt_in_cache).  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
-template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
+// Tile `tile` of a chunk.  NT: hints on the state; NTG: and on the gradient loads (host memory only: pt_adamw_hints).  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+template <int TH, int DT, int UNROLL, bool NT, bool NTG, bool MASKED, bool GF32>
 __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
-                                            bool gcached, uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
+                                            uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
                                             const uint64_t* __restrict__ nd_ranges) {
   typedef typename GradUnit<GF32>::vec gvec;
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
@@ -179,7 +179,7 @@ __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const
 #pragma unroll
     for (int r = 0; r < UNROLL; ++r) {
       const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-      g[r] = !NT || gcached ? ld_stream<false>(x.g + ub + o) : ld_stream<true>(x.g + ub + o);
+      g[r] = ld_stream<NTG>(x.g + ub + o);
       w[r] = ld_stream<NT>(x.w + ub + o);
       m[r] = ld_stream<NT>(x.m + ub + o);
       v[r] = ld_stream<NT>(x.v + ub + o);
@@ -264,7 +264,7 @@ template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32>
 __global__ void __launch_bounds__(TH)
 k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, uint32_t table_cols, uint32_t first_col,
         uint32_t n_cols, uint32_t mask_chunk0, uint64_t units, uint64_t tiles, int recast_on_skip, int zero_grads,
-        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges, uint64_t cached) {
+        const uint32_t* __restrict__ nd_begin, const uint64_t* __restrict__ nd_ranges) {
   const int32_t skip = st->skip;
   const Consts k = load_consts(st);
   for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
@@ -273,8 +273,8 @@ k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, u
                                                t[size_t(ROW_M) * table_cols], t[size_t(ROW_V) * table_cols],
                                                t[size_t(ROW_P16) * table_cols]);
     for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-      update_tile<TH, DT, UNROLL, NT, MASKED, GF32>(k, skip, x, tile, units, pt_in_cache(first_col + ci, units, tile * (TH * UNROLL), cached),
-                                                  mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin, nd_ranges);
+      update_tile<TH, DT, UNROLL, NT, false, MASKED, GF32>(k, skip, x, tile, units, mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin,
+                                                  nd_ranges);
   }
 }
 
@@ -309,7 +309,7 @@ k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_
     const ChunkPtrs<GF32> x = chunk_ptrs<GF32>(a[0], a[1], a[2], a[3], a[4]);
     for (; tile < tiles; tile += groups) {
       if (!skip) {
-        update_tile<HOST_TH, DT, 1, true, MASKED, GF32>(k, 0, x, tile, units, false, mask_chunk0 + ci, 0, 0, nd_begin, nd_ranges);
+        update_tile<HOST_TH, DT, 1, true, true, MASKED, GF32>(k, 0, x, tile, units, mask_chunk0 + ci, 0, 0, nd_begin, nd_ranges);
         continue;
       }
       // a skipped step leaves param16 as the recast of the master weights, as the chunk buffers do
@@ -333,7 +333,7 @@ k_adamw_host(const HostChunks chunks, const PtDevState* __restrict__ st, uint32_
 template <int TH, int DT, int UNROLL, bool NT>
 __global__ void __launch_bounds__(TH)
 k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_t first_col, uint32_t n_cols,
-                uint64_t units, uint64_t tiles, uint32_t* __restrict__ sink, uint64_t cached) {
+                uint64_t units, uint64_t tiles, uint32_t* __restrict__ sink) {
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
   uint32_t keep = 0;
   for (uint32_t ci = blockIdx.y; ci < n_cols; ci += gridDim.y) {
@@ -347,13 +347,12 @@ k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_
     const uint32_t back = uint32_t(wa >> 4) & (LINE_UNITS - 1);
     for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
       const uint64_t ub = tile * TILE_UNITS - back;
-      const bool gcached = pt_in_cache(col, units, tile * TILE_UNITS, cached);
       if (!(ub < units && units - ub >= TILE_UNITS)) continue;      // first and last tiles are left out (a few KiB per chunk)
       u32x2 g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
 #pragma unroll
       for (int r = 0; r < UNROLL; ++r) {
         const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-        g[r] = gcached ? ld_stream<false>(gp + ub + o) : ld_stream<NT>(gp + ub + o);
+        g[r] = gp[ub + o];
         w[r] = ld_stream<NT>(wp + ub + o);
         m[r] = ld_stream<NT>(mp + ub + o);
         v[r] = ld_stream<NT>(vp + ub + o);
@@ -378,8 +377,8 @@ k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_
 }
 
 typedef void (*adamw_kernel_t)(const uint64_t*, const PtDevState*, uint32_t, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t,
-                               int, int, const uint32_t*, const uint64_t*, uint64_t);
-typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*, uint64_t);
+                               int, int, const uint32_t*, const uint64_t*);
+typedef void (*pattern_kernel_t)(const uint64_t*, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t*);
 
 // The instantiation for a launch shape: the library's own (64 lanes, one unit each), and what the options adamw_threads and
 // adamw_unroll ask for.  The latter lose to the former at every size measured; they stay for the options.
@@ -457,7 +456,7 @@ int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_
                                               : pick_kernel<PT_FP16>(shape, hints, masked, ctx->grad_f32);
   hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, ctx->d_table, ctx->d_state, ctx->table_cols,
                      first_col, n_cols, mask_chunk0, ctx->S / 4, geo.tiles, recast_on_skip ? 1 : 0, zero_grads ? 1 : 0,
-                     ctx->d_nd_begin, ctx->d_nd_ranges, pt_cached_elems(ctx) / 4);
+                     ctx->d_nd_begin, ctx->d_nd_ranges);
   PT_LAUNCH_CHECK(ctx, "k_adamw");
   return PT_OK;
 }
@@ -523,7 +522,7 @@ extern "C" int pt_calib_adamw_pattern(pt_ctx* ctx, uint32_t first_chunk, uint32_
   const bool hints = pt_adamw_hints(ctx);
   pattern_kernel_t kern = ctx->dtype == PT_BF16 ? pick_pattern<PT_BF16>(shape, hints) : pick_pattern<PT_FP16>(shape, hints);
   hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, (hipStream_t)stream, ctx->d_table, ctx->table_cols,
-                     first_chunk, n_chunks, ctx->S / 4, geo.tiles, (uint32_t*)nullptr, pt_cached_elems(ctx) / 4);
+                     first_chunk, n_chunks, ctx->S / 4, geo.tiles, (uint32_t*)nullptr);
   PT_LAUNCH_CHECK(ctx, "k_adamw_pattern");
   return PT_OK;
 }

@@ -1,5 +1,5 @@
-"""The first 240 MB of a context's gradient chunks are loaded without non-temporal hints.  The hint changes no bit: chunks that end
-before, on and behind that line, tensors that are cut by it, aligned and not."""
+"""The first 240 MB of a context's gradient chunks are stored by pack and loaded by accumulate without non-temporal hints.  That
+changes no bit: tensors that are cut by that line, aligned and not, and chunks before, on and behind it."""
 import pytest
 import torch
 
