@@ -25,6 +25,7 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 
 namespace {
@@ -38,7 +39,8 @@ inline NormShape norm_shape(uint64_t elems, bool fp32) {
   return elems < (fp32 ? 4096ull : 1792ull) * PT_NORM_BLOCK_ELEMS ? NormShape{4, 0} : NormShape{2, 36000};
 }
 typedef void (*norm_kernel_t)(const uint64_t*, uint32_t, uint64_t, const PtDevState*, double*, uint32_t*);
-typedef void (*norm_arena_kernel_t)(const void*, uint64_t, double, double*, uint32_t*, uint32_t*);
+struct OneTicket;
+typedef void (*norm_arena_kernel_t)(const void*, uint64_t, double, double*, uint32_t*, OneTicket*, OneTicket*, double*, int32_t*);
 
 template <int DT>
 __device__ __forceinline__ double word_to_f64(uint32_t w16) {
@@ -519,6 +521,11 @@ constexpr uint32_t PT_STATIC_MAX_PARTIALS = 1u << 19;   // blocks of PT_NORM_BLO
 constexpr uint32_t PT_STATIC_MAX_CHUNKS = 4096;
 constexpr int PT_STATIC_MAX_DEVICES = 64;
 
+constexpr uint32_t PT_ONE_MAX_BLOCKS = 1024, PT_ONE_MAX_WAVES = 16, PT_ONE_TICKETS = 16, ONE_COUNTERS = 16;
+// Workgroups count themselves in on 16 counters, a line of memory each, and the last of each on one more: 256 of them on a single
+// one waited for each other for 2 us.
+struct OneTicket { struct alignas(128) Line { uint32_t n; } line[ONE_COUNTERS + 1]; };
+
 // workgroups of the reduction: n * ceil(per_chunk / PT_REDUCE_SEG) <= n + partials / PT_REDUCE_SEG
 constexpr uint32_t PT_STATIC_MAX_SEGS = PT_STATIC_MAX_CHUNKS + PT_STATIC_MAX_PARTIALS / PT_REDUCE_SEG;
 
@@ -529,7 +536,10 @@ struct PtStaticScratch {
   uint32_t flag[PT_STATIC_MAX_PARTIALS];
   uint32_t chunk_flag[PT_STATIC_MAX_CHUNKS];
   uint32_t seg_flag[PT_STATIC_MAX_SEGS];
-  uint32_t ticket;
+  OneTicket ticket;
+  // Of calls in one launch: a counter each, in turn, which its last workgroup leaves at 0.  A call also clears the one half way
+  // round, so that what calls that overlapped in time have left in one does not stay.
+  OneTicket tickets[PT_ONE_TICKETS];
 };
 
 }  // namespace
@@ -541,25 +551,102 @@ static __device__ __align__(256) unsigned char scratch[sizeof(PtStaticScratch)];
 namespace {
 
 // As k_sqnorm, for chunks that lie back to back in one arena; the loss scale comes by value.
-template <int DT, int U>
+//
+// ONE: the workgroup that finishes last adds the partial sums up, in the order k_scalars has, and writes the results: one launch
+// instead of two, which is what a call costs the host (8.8 -> 5.3 us).  No workgroup waits for another one.  Two launches and one:
+// 2.6e5 words 8.8 -> 5.3 us, 4.2e6 8.8 -> 6.1, 8.4e6 8.8 -> 7.0 (with one counter 9.1), 1.7e7 10.2 -> 9.4 (13.5), 200 chunks of two
+// workgroups 13.0 -> 8.8.
+template <int DT, int U, bool ONE>
 __global__ void __launch_bounds__(NB_THREADS)
-k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, double* __restrict__ part,
-               uint32_t* __restrict__ flagout, uint32_t* __restrict__ ticket) {
+k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, double* __restrict__ part, uint32_t* __restrict__ flagout,
+               OneTicket* __restrict__ ticket, OneTicket* __restrict__ other_ticket, double* __restrict__ out_sq_norm,
+               int32_t* __restrict__ out_found_inf) {
   const uint32_t b = blockIdx.x, i = blockIdx.y;
   const PT_GLOBAL u32x4* base = (const PT_GLOBAL u32x4*)((uint64_t)(uintptr_t)arena + 2ull * S * i);
   double acc;
   uint32_t flag;
   sqnorm_block<DT, U>(base, S, b, 1.0 / loss_scale, acc, flag);
-  if (threadIdx.x == 0) {
-    if (b == 0 && i == 0) *ticket = 0;       // whatever calls that overlapped in time have left there
-    size_t slot = size_t(i) * gridDim.x + b;
-    part[slot] = acc;
-    flagout[slot] = flag;
+  const size_t slot = size_t(i) * gridDim.x + b;
+  if constexpr (!ONE) {
+    if (threadIdx.x == 0) {
+      if (b == 0 && i == 0) ticket->line[0].n = 0;       // whatever calls that overlapped in time have left there
+      part[slot] = acc;
+      flagout[slot] = flag;
+    }
+  } else {
+    __shared__ double s_tree[PT_ONE_MAX_BLOCKS];
+    __shared__ uint32_t s_last;
+    const uint32_t total = gridDim.x * gridDim.y;
+    if (threadIdx.x == 0) {
+      if (slot == 0) for (uint32_t k = 0; k <= ONE_COUNTERS; ++k) st_agent(&other_ticket->line[k].n, 0u);
+      st_agent(part + slot, acc);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const uint32_t k = uint32_t(slot) % ONE_COUNTERS, mine = (total - k + ONE_COUNTERS - 1) / ONE_COUNTERS;
+      uint32_t last = __hip_atomic_fetch_add(&ticket->line[k].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mine - 1;
+      if (last) last = __hip_atomic_fetch_add(&ticket->line[ONE_COUNTERS].n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                       == min(total, ONE_COUNTERS) - 1;
+      s_last = last;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x <= ONE_COUNTERS) st_agent(&ticket->line[threadIdx.x].n, 0u);
+    // As many lanes as a chunk has partial sums; `w` of them, a power of two, add theirs up in a tree, one lane the trees of a chunk
+    // one after the other.
+    const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, per = gridDim.x, n = gridDim.y;
+    uint32_t lg = 0;
+    while (lg < 6 && (1u << lg) < per) ++lg;
+    const uint32_t w = 1u << lg, trees = (per + w - 1) / w, all = n * trees;
+    constexpr uint32_t WAVES = NB_THREADS / 64, R = PT_ONE_MAX_WAVES / WAVES;
+    double x[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t v = ((wid + r * WAVES) << (6 - lg)) + (lane >> lg), c = v / trees, k = (v - c * trees) * w + (lane & (w - 1));
+      x[r] = v < all && k < per ? ld_agent(part + size_t(c) * per + k) : 0.0;
+    }
+    for (uint32_t off = w >> 1; off > 0; off >>= 1)
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) x[r] += __shfl_down(x[r], off, 64);
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t v = ((wid + r * WAVES) << (6 - lg)) + (lane >> lg);
+      if ((lane & (w - 1)) == 0 && v < all) s_tree[v] = x[r];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double sq = 0.0;
+    if (trees == 1) {
+#pragma unroll 8
+      for (uint32_t c = 0; c < n; ++c) sq += s_tree[c];
+    } else {
+      for (uint32_t c = 0; c < n; ++c) {
+        double t = s_tree[c * trees];
+        for (uint32_t k = 1; k < trees; ++k) t += s_tree[c * trees + k];
+        sq += t;
+      }
+    }
+    out_sq_norm[0] = sq;
+    out_sq_norm[1] = sqrt(sq);
+    // a sum of squares is finite if and only if every number is (pt_close_sum)
+    *out_found_inf = (uint32_t(__double2hiint(sq)) & 0x7ff00000u) == 0x7ff00000u ? 1 : 0;
   }
 }
 
-template <int DT> norm_arena_kernel_t pick_norm_arena(int u) {
-  return u == 16 ? k_sqnorm_arena<DT, 16> : u == 4 ? k_sqnorm_arena<DT, 4> : k_sqnorm_arena<DT, 2>;
+// Waves that take the partial sums of n chunks with `per` each in one launch.
+inline uint64_t one_waves(uint64_t per, uint64_t n) {
+  uint64_t w = 1;
+  while (w < 64 && w < per) w *= 2;
+  return (n * ((per + w - 1) / w) * w + 63) / 64;
+}
+// One launch where all workgroups run at once (norm_shape), the last one's four waves have at most four loads a lane (eight cost 0.7 us,
+// more than the rest of what a larger call gains: 960 workgroups 16.8 -> 16.1) and no lane has two partial sums of a chunk (one
+// chunk of 1024: 15.0 -> 15.5).
+inline bool norm_in_one(uint64_t per_chunk, uint64_t n_chunks) {
+  return per_chunk <= SC_SUM && per_chunk * n_chunks <= PT_ONE_MAX_BLOCKS && one_waves(per_chunk, n_chunks) <= PT_ONE_MAX_WAVES;
+}
+
+template <int DT> norm_arena_kernel_t pick_norm_arena(int u, bool one) {
+  return one ? k_sqnorm_arena<DT, 16, true>
+         : u == 16 ? k_sqnorm_arena<DT, 16, false> : u == 4 ? k_sqnorm_arena<DT, 4, false> : k_sqnorm_arena<DT, 2, false>;
 }
 
 std::mutex g_scratch_mutex;
@@ -621,13 +708,19 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   // Nothing here has to start at zero: each launch writes every partial and per-chunk slot that the
   // next one reads (n_chunks * blocks_per_chunk partials, n_chunks sums), so stale contents of an
   // earlier, larger call are never read.
-  norm_arena_kernel_t kern = dtype == PT_BF16 ? pick_norm_arena<PT_BF16>(shape.unroll) : pick_norm_arena<PT_FP16>(shape.unroll);
-  hipLaunchKernelGGL(kern, grid, dim3(NB_THREADS), shape.lds, st, grad_arena, chunk_elems, loss_scale, sc->part, sc->flag, &sc->ticket);
+  const bool one = norm_in_one(blocks_per_chunk, n_chunks);
+  static std::atomic<uint32_t> calls{0};
+  const uint32_t call = one ? calls.fetch_add(1, std::memory_order_relaxed) : 0;
+  norm_arena_kernel_t kern = dtype == PT_BF16 ? pick_norm_arena<PT_BF16>(shape.unroll, one) : pick_norm_arena<PT_FP16>(shape.unroll, one);
+  hipLaunchKernelGGL(kern, grid, dim3(NB_THREADS), shape.lds, st, grad_arena, chunk_elems, loss_scale, sc->part, sc->flag,
+                     one ? sc->tickets + call % PT_ONE_TICKETS : &sc->ticket, sc->tickets + (call + PT_ONE_TICKETS / 2) % PT_ONE_TICKETS,
+                     out_sqnorm_norm, out_found_inf);
   if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_sqnorm_arena failed");
+  if (one) return PT_OK;
   ScalarArgs a{};
   a.r.part = sc->part; a.r.flag = sc->flag; a.r.n = n_chunks; a.r.per_chunk = (uint32_t)blocks_per_chunk;
   a.r.segs = pt_segs(blocks_per_chunk); a.r.seg_sum = sc->seg_sum; a.r.seg_flag = sc->seg_flag;
-  a.chunk_sq = sc->chunk_sq; a.chunk_flag = sc->chunk_flag; a.C = n_chunks; a.ticket = &sc->ticket;
+  a.chunk_sq = sc->chunk_sq; a.chunk_flag = sc->chunk_flag; a.C = n_chunks; a.ticket = &sc->ticket.line[0].n;
   a.out_sq_norm = out_sqnorm_norm; a.out_found_inf = out_found_inf;
   a.do_finalize = 1;
   hipLaunchKernelGGL(k_scalars, dim3(a.r.segs, n_chunks), dim3(SC_THREADS), 0, st, a);
