@@ -19,6 +19,10 @@
 #include <thread>
 #include <vector>
 
+#if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
+#include <emmintrin.h>
+#endif
+
 #if defined(__clang__)
 #pragma clang fp contract(off)
 #endif
@@ -56,20 +60,52 @@ static inline uint16_t f32_to_fp16(float x) {
 
 static inline float f32_identity(float x) { return x; }
 
+// The 16-bit parameters are written and not read: a plain store would fetch each of their lines from memory first, 2 of 30 bytes
+// an element.  They are put together in the first-level cache, a block at a time, and leave it past the caches:
+// seven chunks of 2^23 elements 4.63 -> 4.2 ms a step with 16 threads, 5.05 -> 4.54 with 8, fp16 4.51 -> 4.2.
+constexpr uint64_t PARAM_BLOCK = 2048;
+
+static inline void store_params(uint16_t* __restrict__ p, const uint16_t* __restrict__ from, uint64_t n) {
+#if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
+  uint64_t i = 0;
+  for (; i < n && (reinterpret_cast<uintptr_t>(p + i) & 15u); ++i) p[i] = from[i];
+  for (; i + 8 <= n; i += 8)
+    _mm_stream_si128(reinterpret_cast<__m128i*>(p + i), _mm_loadu_si128(reinterpret_cast<const __m128i*>(from + i)));
+  for (; i < n; ++i) p[i] = from[i];
+#else
+  std::memcpy(p, from, n * sizeof *p);
+#endif
+}
+// Before another thread is told that the parameters are there.
+static inline void params_stored() {
+#if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
+  _mm_sfence();
+#endif
+}
+
 #define PT_HOST_UPDATE_BODY(DECODE, ENCODE)                                         \
-  for (uint64_t i = 0; i < n; ++i) {                                               \
-    float gg = DECODE(g[i]) * k.gm;                                                \
-    float t1 = k.omb1 * gg;                                                        \
-    float mn = std::fmaf(k.b1, m[i], t1);                                          \
-    float t2 = k.omb2 * gg;                                                        \
-    t2 = t2 * gg;                                                                  \
-    float vn = std::fmaf(k.b2, v[i], t2);                                          \
-    float d = std::fmaf(std::sqrt(vn), k.rsb2, k.eps);                             \
-    float u = mn / d;                                                              \
-    float t3 = w[i] * k.decay;                                                     \
-    float wn = std::fmaf(-k.step_size, u, t3);                                     \
-    m[i] = mn; v[i] = vn; w[i] = wn;                                               \
-    p[i] = ENCODE(wn);                                                             \
+  alignas(64) uint16_t block[PARAM_BLOCK];                                         \
+  for (uint64_t b = 0; b < n; b += PARAM_BLOCK) {                                  \
+    const uint64_t cnt = n - b < PARAM_BLOCK ? n - b : PARAM_BLOCK;                \
+    const auto* __restrict__ gb = g + b;                                           \
+    float* __restrict__ wb = w + b;                                                \
+    float* __restrict__ mb = m + b;                                                \
+    float* __restrict__ vb = v + b;                                                \
+    for (uint64_t i = 0; i < cnt; ++i) {                                           \
+      float gg = DECODE(gb[i]) * k.gm;                                             \
+      float t1 = k.omb1 * gg;                                                      \
+      float mn = std::fmaf(k.b1, mb[i], t1);                                       \
+      float t2 = k.omb2 * gg;                                                      \
+      t2 = t2 * gg;                                                                \
+      float vn = std::fmaf(k.b2, vb[i], t2);                                       \
+      float d = std::fmaf(std::sqrt(vn), k.rsb2, k.eps);                           \
+      float u = mn / d;                                                            \
+      float t3 = wb[i] * k.decay;                                                  \
+      float wn = std::fmaf(-k.step_size, u, t3);                                   \
+      mb[i] = mn; vb[i] = vn; wb[i] = wn;                                          \
+      block[i] = ENCODE(wn);                                                       \
+    }                                                                              \
+    store_params(p + b, block, cnt);                                               \
   }
 
 // x86 clones picked at load time; a device pass of a HIP compiler only parses this host code
@@ -141,7 +177,7 @@ static inline void run_grains(Job& job) {
   const uint64_t S = job.S;
   for (;;) {
     const uint64_t gidx = job.next.fetch_add(1, std::memory_order_relaxed);
-    if (gidx >= job.total_grains) return;
+    if (gidx >= job.total_grains) { params_stored(); return; }
     const uint64_t c = gidx / job.grains_per_chunk, lo = (gidx % job.grains_per_chunk) * GRAIN;
     const uint64_t n = (lo + GRAIN <= S) ? GRAIN : S - lo;
     const uint16_t* g = static_cast<const uint16_t*>(job.h_grad[c]) + lo;       // 16-bit gradient chunks
