@@ -99,9 +99,9 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // 12 waves suit large sums; small ones, which lie in the cache (pt_in_cache), and a first micro-batch that only writes its
 // sums (6 bytes an element instead of 10), want 17.  With 12 and 17, four added and the update: 7e6 words 108.5 and 104.1 us, 1.5e7
 // 199 and 189, 3e7 364 and 352, 6e7 696 and 683, 8.5e7 966 and 954, 1.24e8 1365 and 1360, 2.0e8 2302 and 2360, 3.3e8 3630 and 3720
-// (four units a lane in flight with 12: 6e7 690, 2e6 44.4 -> 46.9); writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298; writing with the norm: 3e7 39.7 and
-// 34.3, 3.3e8 401 and 326.  Four launches over 6.7e9 elements whose halves lie in
-// different 96 GiB regions of the memory: 37.5 to 41.5 ms from process to process before, 38.6-38.9 now.
+// (four units a lane in flight with 12: 6e7 690, 2e6 44.4 -> 46.9); writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298;
+// writing with the norm: 3e7 39.7 and 34.3, 3.3e8 401 and 326.  Four launches over 6.7e9 elements whose halves lie in different
+// 96 GiB regions of the memory: 37.5 to 41.5 ms from process to process before, 38.6-38.9 now.
 inline uint32_t accum_lds(bool overwrite, uint64_t elems) { return overwrite || elems < (1ull << 25) ? 9000 : 13000; }
 
 template <int DT, bool OVERWRITE, bool NORM>

@@ -11,7 +11,8 @@
 //
 // Three shapes by the size of the call (norm_shape), all with the same order of additions.  Up to 1024 workgroups (four a
 // compute unit, all of them running at once) a lane has all of its loads in flight: what such a call costs is how often it
-// waits.  8.4e6 words 9.3 us with four loads, 8.8 with sixteen (from there on down the host's two launches are the limit), 3.3e7
+// waits.  8.4e6 words 9.3 us with four loads, 8.8 with sixteen (from there on down the host's two launches were the limit; without a
+// context it is one launch now, 6.9 us), 3.3e7
 // 15.9 and 15.3; 1e8 34.8 and 41.7.  Large arenas are read fastest with few bytes in flight: two loads a lane, and unused LDS that
 // leaves four workgroups on a compute unit instead of eight.  8.1e8 words 233 us (7.2 TB/s with the scalar kernel's 5 us), with
 // four loads 239, one load 291, two loads and no limit 241, six workgroups 237, three 245; 2.5e8 77.0 / 78.5 / 96.3 / 79.2 / 77.9 /
