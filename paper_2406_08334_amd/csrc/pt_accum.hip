@@ -191,7 +191,8 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   accum_kernel_t kern = ctx->dtype == PT_BF16 ? pick<PT_BF16>(overwrite != 0, take_norm != 0)
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
   hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st,
-                     plan->d_tiles, pt_row(ctx, ROW_PACK), plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
+                     plan->d_tiles, pt_row(ctx, ROW_PACK), plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq,
+                     plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {
     rc = pt_reduce_plan(ctx, plan, st);

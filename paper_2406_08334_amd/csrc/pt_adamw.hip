@@ -163,7 +163,8 @@ __device__ __forceinline__ ChunkPtrs<GF32> chunk_ptrs(uint64_t g, uint64_t w, ui
           uint32_t(w >> 4) & (LINE_UNITS - 1)};
 }
 
-// Tile `tile` of a chunk.  NT: hints on the state; NTG: and on the gradient loads (host memory only: pt_adamw_hints).  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+// Tile `tile` of a chunk.  NT: hints on the state; NTG: and on the gradient loads (host memory only: pt_adamw_hints).  c: the chunk's
+// index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
 template <int TH, int DT, int UNROLL, bool NT, bool NTG, bool MASKED, bool GF32>
 __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
                                             uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,

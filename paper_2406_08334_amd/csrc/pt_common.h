@@ -333,9 +333,9 @@ inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
 // The gradient chunks are the exception: what pack or accumulate has written, the next accumulation or the update reads.  Pack
 // stores and accumulate loads the first PT_CACHED_BYTES of them without a hint (the update all of them: it is their last
 // reader), and they stay in the 256 MB Infinity Cache from call to call; traffic with hints does not take it from them, but words
-// without hints beyond its size push each other out.  fp32 sums, four micro-batches and the update, with hints and without: 2e6 elements 46.5 -> 44.4 us, 7e6 113 -> 103, 3e7 375 -> 352, 6e7
-// 743 -> 696, 1.24e8 1422 -> 1364, 3.3e8 3715 -> 3635 (without hints on all of them 3800); 192 to 240 MB differ by less than 1 %,
-// 300 MB costs 1.24e8 elements 5 %.  Where 1 GB of other traffic comes between the calls they take 23.8 -> 25.3 us (1.1e7
+// without hints beyond its size push each other out.  fp32 sums, four micro-batches and the update, with hints and
+// without: 2e6 elements 46.5 -> 44.4 us, 7e6 113 -> 103, 3e7 375 -> 352, 6e7 743 -> 696, 1.24e8 1422 -> 1364, 3.3e8 3715 -> 3635
+// (without hints on all of them 3800); 192 to 240 MB differ by less than 1 %, 300 MB costs 1.24e8 elements 5 %.  Where 1 GB of other traffic comes between the calls they take 23.8 -> 25.3 us (1.1e7
 // elements), 52.8 -> 52.7 (3e7), 88 -> 86 (5.3e7).  The accumulate kernel's stores make no difference.  16-bit words, a
 // step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615, 200 M 1075 -> 1067, 667 M within its spread.
 inline bool pt_adamw_hints(const pt_ctx* ctx) { return ctx->opt_adamw_nt != 0; }
