@@ -13,59 +13,11 @@
 #include <vector>
 
 #include "ptchunk.h"
+#include "pt_step.h"
 
 // Device (global) address space qualifier for pointers rebuilt from integer addresses: the
 // compiler then emits global_* memory instructions instead of flat_* ones.
 #define PT_GLOBAL __attribute__((address_space(1)))
-
-// ---- device-resident scalars of a context ---------------------------------------
-// One instance per context, in device memory.  Written only by the single-thread
-// scalar kernels; read (uniformly) by the bulk kernels.
-struct PtDevState {
-  double sqnorm;
-  double norm;
-  double clip_coef;
-  double loss_scale;
-  double growth;
-  double backoff;
-  int32_t found_inf;
-  int32_t step;          // applied updates so far
-  int32_t good_steps;
-  int32_t growth_interval;
-  int32_t scaler_enabled;
-  int32_t override_active;
-  float override_grad_mult;
-  // constants of the update in flight (see pt_update_consts)
-  float c[9];
-  int32_t skip;
-  uint32_t ticket;       // workgroups of the scalar kernel that have finished (0 between launches)
-  // a step that was ended together with its constants (pt_end_early): its number, and what the end has changed
-  uint32_t ended;
-  int32_t old_step, old_good_steps, old_override;
-  double old_loss_scale;
-};
-
-// The end of a step - loss-scale machine and step counter (dynamic loss scaling with skip on non-finite gradients; the counter
-// does not move on a skipped step) - from the step's found_inf; a forced multiplier lasts one step.
-__device__ __forceinline__ void pt_advance(PtDevState& s, bool found_inf) {
-  if (found_inf) {
-    if (s.scaler_enabled) {
-      const double b = s.loss_scale * s.backoff;
-      s.loss_scale = b > 1.0 ? b : 1.0;
-      s.good_steps = 0;
-    }
-  } else {
-    s.step += 1;
-    if (s.scaler_enabled) {
-      s.good_steps += 1;
-      if (s.good_steps >= s.growth_interval) {
-        s.loss_scale = s.loss_scale * s.growth;
-        s.good_steps = 0;
-      }
-    }
-  }
-  s.override_active = 0;
-}
 
 // Rows of the per-context device pointer table.  Each row has n_chunks + n_slots
 // entries; entries [n_chunks, n_chunks + n_slots) are the device chunk buffers
@@ -115,19 +67,6 @@ struct pt_pack_plan {
 
 namespace pt_host { class Pool; }
 
-// A per-chunk reduction of partial sums, to be launched or put off (see pt_norm.hip).  tile_begin == NULL: chunk first+i owns
-// partials [i*per_chunk, (i+1)*per_chunk), else [tile_begin[c], tile_begin[c+1]) * per_tile.  seg_sum / seg_flag: room for n * segs
-// sums where a chunk has more partials than one workgroup takes (segs > 1).
-struct PtPendingReduce {
-  const double* part = nullptr;
-  const uint32_t* flag = nullptr;
-  const uint32_t* tile_begin = nullptr;
-  uint32_t first = 0, n = 0, per_chunk = 0, segs = 1;
-  uint32_t per_tile = 1;                 // partial sums per entry of tile_begin
-  double* seg_sum = nullptr;
-  uint32_t* seg_flag = nullptr;
-  const pt_pack_plan* plan = nullptr;    // owner of part / flag / tile_begin (NULL: the context)
-};
 constexpr uint32_t PT_REDUCE_SEG = 4096;         // partial sums one workgroup adds up, eight per lane
 inline uint32_t pt_segs(uint64_t partials) { return uint32_t(partials ? (partials + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG : 1); }
 

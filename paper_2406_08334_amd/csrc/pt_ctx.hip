@@ -47,21 +47,12 @@ __global__ void k_override(PtDevState* st, float grad_mult, int32_t found_inf) {
   st->sqnorm = 0.0; st->norm = 0.0;
 }
 
-// The end of step `step_no`, unless the launch that derived its constants has been its end too.
 __global__ void k_step_end(PtDevState* st, uint32_t step_no) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (st->ended == step_no) { st->ended = 0; return; }
-  PtDevState s = *st;
-  pt_advance(s, s.found_inf != 0);
-  st->step = s.step; st->loss_scale = s.loss_scale; st->good_steps = s.good_steps; st->override_active = s.override_active;
+  if (threadIdx.x == 0 && blockIdx.x == 0) pt_end_step(st, step_no);
 }
 
-// Takes the early end of step `step_no` back.
 __global__ void k_reopen(PtDevState* st, uint32_t step_no) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || st->ended != step_no) return;
-  st->step = st->old_step; st->loss_scale = st->old_loss_scale; st->good_steps = st->old_good_steps;
-  st->override_active = st->old_override;
-  st->ended = 0;
+  if (threadIdx.x == 0 && blockIdx.x == 0) pt_take_back(st, step_no);
 }
 
 // ---- public: misc -------------------------------------------------------------------------

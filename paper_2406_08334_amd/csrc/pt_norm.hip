@@ -167,21 +167,6 @@ inline norm_kernel_t pick_norm_f32(int u) { return u == 16 ? k_sqnorm_f32<16> : 
 // chunks 6.5 -> 4.4 us.  With fences for the whole L2 instead: 9.5, 17 and 7.6 us.
 constexpr int SC_SUM = PT_REDUCE_SEG / 8, SC_THREADS = SC_SUM + 128;     // two more waves for the powers
 
-struct ScalarArgs {
-  PtPendingReduce r;             // r.n == 0: nothing to reduce (grid 1 x 1)
-  double* chunk_sq;
-  uint32_t* chunk_flag;
-  uint32_t C;
-  uint32_t* ticket;
-  PtDevState* st;                // NULL: the norm for a caller without a context, into out_*
-  double* out_sq_norm;
-  int32_t* out_found_inf;
-  int do_finalize, do_prepare;
-  uint32_t end_step;             // do_prepare: number of the step that ends with it, or 0
-  pt_hparams hp;
-  PtDevState* mirror;            // pinned host memory that receives the constants, or NULL
-};
-
 // Values other workgroups of the same launch have written (or will read): past this XCD's caches.
 template <class T> __device__ __forceinline__ T ld_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <class T> __device__ __forceinline__ void st_agent(T* p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -225,16 +210,6 @@ __device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& h
   }
 }
 
-// The update reads nothing but the constants and `skip`, so the step can end here, without a launch of its own behind the update
-// (4.8 us; pt_step_end then launches nothing).  What changes is kept: a call of the same step that depends on it takes the
-// end back first (pt_reopen_step).  s: the state this step began with.
-__device__ __forceinline__ void pt_end_early(PtDevState* st, PtDevState s, bool found_inf, uint32_t step_no) {
-  st->old_step = s.step; st->old_good_steps = s.good_steps; st->old_override = s.override_active; st->old_loss_scale = s.loss_scale;
-  pt_advance(s, found_inf);
-  st->step = s.step; st->good_steps = s.good_steps; st->override_active = s.override_active; st->loss_scale = s.loss_scale;
-  st->ended = step_no;
-}
-
 // Partial sums of chunk first + i.
 __device__ __forceinline__ uint32_t partials_of(const PtPendingReduce& r, uint32_t i, uint32_t& lo) {
   if (!r.tile_begin) { lo = i * r.per_chunk; return r.per_chunk; }
@@ -242,7 +217,7 @@ __device__ __forceinline__ uint32_t partials_of(const PtPendingReduce& r, uint32
   return r.tile_begin[r.first + i + 1] * r.per_tile - lo;
 }
 
-__global__ void __launch_bounds__(SC_THREADS) k_scalars(const ScalarArgs a) {
+__global__ void __launch_bounds__(SC_THREADS) k_scalars(const PtScalarArgs a) {
   __shared__ double s_sum[SC_SUM / 64], s_val[SC_SUM], s_bc[2];
   __shared__ uint32_t s_flag[SC_SUM / 64], s_f[SC_SUM], s_last;
   const PtPendingReduce& r = a.r;
@@ -367,7 +342,7 @@ constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 
 static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror,
                           hipStream_t stream) {
-  ScalarArgs a{};
+  PtScalarArgs a{};
   if (r) a.r = *r;
   a.chunk_sq = ctx->d_chunk_sq; a.chunk_flag = ctx->d_chunk_flag; a.C = ctx->C; a.ticket = &ctx->d_state->ticket; a.st = ctx->d_state;
   a.do_finalize = finalize ? 1 : 0;
@@ -718,7 +693,7 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
                      out_sqnorm_norm, out_found_inf);
   if (hipGetLastError() != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "pt_chunk_grad_sqnorm_noalloc: launch of k_sqnorm_arena failed");
   if (one) return PT_OK;
-  ScalarArgs a{};
+  PtScalarArgs a{};
   a.r.part = sc->part; a.r.flag = sc->flag; a.r.n = n_chunks; a.r.per_chunk = (uint32_t)blocks_per_chunk;
   a.r.segs = pt_segs(blocks_per_chunk); a.r.seg_sum = sc->seg_sum; a.r.seg_flag = sc->seg_flag;
   a.chunk_sq = sc->chunk_sq; a.chunk_flag = sc->chunk_flag; a.C = n_chunks; a.ticket = &sc->ticket.line[0].n;
