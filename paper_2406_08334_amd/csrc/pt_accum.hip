@@ -181,6 +181,7 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
   if (plan->ctx != ctx) return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_accum_grads: plan belongs to another context");
   if (!ctx->grad_f32)
     return pt_fail(ctx, PT_ERR_STATE, "pt_chunk_accum_grads: the context holds 16-bit gradient chunks (set option grad_fp32)");
+  if (take_norm) pt_capturing(ctx, st);
   int rc = pt_table_bind(ctx, ROW_PACK, 0, ctx->C, (const void* const*)acc_chunks, true, st);
   if (rc != PT_OK) return rc;
   if (plan->n_tiles == 0) return PT_OK;

@@ -495,6 +495,7 @@ extern "C" int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t f
   if (!ctx->norm_finalized)
     return pt_fail(ctx, PT_ERR_STATE, "pt_chunk_adamw_step: no finalized gradient norm in this step");
   if (n_chunks == 0) return PT_OK;
+  pt_capturing(ctx, st);
   int rc;
   const PtBind binds[5] = {{ROW_GRAD, grad}, {ROW_MASTER, (const void* const*)master}, {ROW_M, (const void* const*)m},
                            {ROW_V, (const void* const*)v}, {ROW_P16, (const void* const*)param16}};

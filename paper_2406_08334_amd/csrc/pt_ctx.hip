@@ -183,6 +183,7 @@ extern "C" int pt_ctx_set_state(pt_ctx* ctx, int32_t step, double loss_scale, in
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_ctx_set_state: step, good_steps >= 0 and loss_scale >= 1 required");
   if (!ctx->scaler && loss_scale != 1.0)
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_ctx_set_state: context has no scaler, loss_scale must be 1");
+  pt_capturing(ctx, (hipStream_t)stream);
   if (int rc = pt_reopen_step(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   if (int rc = pt_flush_pending(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   hipLaunchKernelGGL(k_set_state, dim3(1), dim3(1), 0, (hipStream_t)stream, ctx->d_state, step,
@@ -302,6 +303,7 @@ extern "C" int pt_step_override(pt_ctx* ctx, float grad_mult, int32_t found_inf,
   if (ctx->stream_pending)
     return pt_fail(ctx, PT_ERR_STATE, "pt_step_override: a streamed update is still open (its kernels read the step's "
                    "scalars); close the step with pt_step_end first");
+  pt_capturing(ctx, (hipStream_t)stream);
   if (int rc = pt_reopen_step(ctx, (hipStream_t)stream); rc != PT_OK) return rc;
   if (int rc = pt_flush_pending(ctx, (hipStream_t)stream); rc != PT_OK) return rc;   // a computed norm, if any, comes first
   hipLaunchKernelGGL(k_override, dim3(1), dim3(1), 0, (hipStream_t)stream, ctx->d_state, grad_mult,
@@ -321,10 +323,11 @@ extern "C" int pt_step_end(pt_ctx* ctx, void* stream) {
     if (ctx->direct_pending) PT_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_direct, 0));
     ctx->stream_pending = ctx->slots_pending = ctx->direct_pending = false;
   }
+  const bool capturing = pt_capturing(ctx, st);
   if (int rc = pt_flush_pending(ctx, st); rc != PT_OK) return rc;     // a step without an update still needs its found_inf
   // Nothing to launch where the step has ended with its constants.  Under capture the kernel goes into the graph either way:
   // it looks whether the step it is replayed in has ended.
-  if (!ctx->ended_early || pt_capturing(ctx, st)) {
+  if (!ctx->ended_early || capturing) {
     hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state, ctx->step_no);
     PT_LAUNCH_CHECK(ctx, "k_step_end");
   }

@@ -38,6 +38,7 @@ extern "C" int pt_chunk_host_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint3
     if (!h_grad[i] || !h_master[i] || !h_m[i] || !h_v[i] || !h_param16[i])
       return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_host_adamw_step: NULL host pointer for chunk %u", first_chunk + i);
   if (n_chunks == 0) return PT_OK;
+  pt_capturing(ctx, st);
 
   // The step's constants come from the device, so that host and device updates use the same
   // bits.  Only the scalar kernels are waited for, not the bulk work queued behind them.

@@ -403,7 +403,7 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
   if (rc != PT_OK) return rc;
   // The launch is the step's end too (pt_end_early), but not in a graph, whose replays may be followed by a step end outside it, nor
   // in a context that has graphs.
-  const bool end = !pt_capturing(ctx, stream) && !ctx->captured;
+  const bool end = !ctx->captured;
   rc = launch_pending(ctx, hp, end ? ctx->step_no : 0, mirror ? ctx->h_state_dev : nullptr, stream);
   if (rc != PT_OK) return rc;
   ctx->ended_early = end;
@@ -434,6 +434,7 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
                    first_chunk, first_chunk + n_chunks, ctx->C);
   if (finalize < 0 || finalize > PT_FINALIZE_CARRY)
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_grad_sqnorm: finalize must be 0, PT_FINALIZE_STRICT or PT_FINALIZE_CARRY");
+  pt_capturing(ctx, st);
   PtPendingReduce r;                             // of a recompute
   if (grad_chunks && n_chunks) {
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);

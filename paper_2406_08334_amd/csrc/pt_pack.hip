@@ -308,6 +308,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
                     const char* who) {
   if (!plan || !chunks) return pt_fail(ctx, PT_ERR_INVALID_ARG, "%s: NULL argument", who);
   if (plan->ctx != ctx) return pt_fail(ctx, PT_ERR_INVALID_ARG, "%s: plan belongs to another context", who);
+  if (DIR == 0) pt_capturing(ctx, st);
   int rc = pt_table_bind(ctx, row, 0, ctx->C, chunks, true, st);
   if (rc != PT_OK) return rc;
   if (plan->n_tiles == 0) return PT_OK;

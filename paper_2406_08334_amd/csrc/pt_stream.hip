@@ -311,6 +311,7 @@ extern "C" int pt_chunk_stream_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t 
     if (!h_grad[i] || !h_master[i] || !h_m[i] || !h_v[i] || !h_param16[i])
       return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_stream_step: NULL host pointer for chunk %u", first_chunk + i);
   if (n_chunks == 0) return PT_OK;
+  pt_capturing(ctx, st);
 
   std::vector<uint64_t> at;
   bool direct = false;

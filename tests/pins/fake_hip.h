@@ -70,6 +70,7 @@ inline std::vector<Op> launches(const char* kernel, size_t from = 0) {
   return v;
 }
 inline hipStream_t stream(uintptr_t id) { return (hipStream_t)id; }
+inline void (*on_launch)(const Op&, void** args) = nullptr;      // looks at a launch's arguments
 
 struct Call { dim3 grid, block; size_t lds; hipStream_t stream; };
 inline std::vector<Call> calls;
@@ -96,11 +97,12 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
   *g = c.grid; *b = c.block; *lds = c.lds; *s = c.stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t lds, hipStream_t s) {
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t s) {
   fake::Op o;
   o.what = "launch"; o.kernel = fake::kernels()[f]; o.stream = (uintptr_t)s; o.grid = g; o.block = b; o.lds = lds;
   if (o.kernel == fake::fail_kernel && fake::fail_after >= 0 && fake::fail_after-- == 0) { fake::fail_after = 0; return fake::last = hipErrorLaunchFailure; }
   fake::ops.push_back(o);
+  if (fake::on_launch) fake::on_launch(o, args);
   return hipSuccess;
 }
 hipError_t hipGetLastError(void) { const hipError_t e = fake::last; fake::last = hipSuccess; return e; }

@@ -4,6 +4,7 @@
 
 #include <tuple>
 
+#include "pt_step.h"
 #include "ptchunk.h"
 
 #define EXPECT(cond)                                                                                     \
@@ -28,8 +29,8 @@ struct State {
   std::vector<float*> w, m, v;
   std::vector<pt_pack_plan*> plans;
 
-  State(uint32_t n, uint64_t elems, bool fp32 = false) : S(elems), C(n) {
-    if (pt_ctx_create(&ctx, PT_BF16, S, C, nullptr) != PT_OK || (fp32 && pt_ctx_set_option(ctx, "grad_fp32", 1) != PT_OK)) die(nullptr);
+  State(uint32_t n, uint64_t elems, bool fp32 = false, const pt_scaler_cfg* scaler = nullptr) : S(elems), C(n) {
+    if (pt_ctx_create(&ctx, PT_BF16, S, C, scaler) != PT_OK || (fp32 && pt_ctx_set_option(ctx, "grad_fp32", 1) != PT_OK)) die(nullptr);
     for (uint32_t c = 0; c < C; ++c) {
       g.push_back(device(4 * S)); p.push_back(device(2 * S));
       w.push_back((float*)device(4 * S)); m.push_back((float*)device(4 * S)); v.push_back((float*)device(4 * S));
@@ -440,7 +441,187 @@ int step_ends_with_its_constants() {
   return 0;
 }
 
+// ---- steps that end with their constants, and graphs ----------------------------------------------
+//
+// A stand-in for the device that runs the step's scalar kernels: at once, or when the graph is replayed they were captured into.  A
+// call sequence has to give the same values whether steps end with their constants or in a kernel of their own (which is
+// what a context does that has been captured into a graph; here into one that is never replayed).
+struct Launch { std::string kernel; PtDevState* st; PtScalarArgs a; uint32_t no; float mult; int32_t inf, step, good; double scale; bool reads_scale; };
+std::vector<Launch>* graph = nullptr;              // what is captured now
+bool reads_scale = false, inf_now = false;         // of the call in flight: its kernel reads the loss scale; gradients hold an infinity
+std::vector<double> seen;
+
+void run(const Launch& l) {
+  PtDevState* st = l.st;
+  if (l.kernel == "k_step_end") pt_end_step(st, l.no);
+  else if (l.kernel == "k_reopen") pt_take_back(st, l.no);
+  else if (l.kernel == "k_override") { st->override_active = 1; st->override_grad_mult = l.mult; st->found_inf = l.inf; }
+  else if (l.kernel == "k_set_state") { st->step = l.step; st->loss_scale = l.scale; st->good_steps = l.good; }
+  else if (l.kernel == "k_adamw") seen.insert(seen.end(), {1.0, st->c[0], st->c[8], double(st->skip)});
+  else if (l.kernel == "k_scalars" && st) {
+    PtDevState s = *st;
+    if (l.a.do_finalize) { st->found_inf = s.found_inf = inf_now; st->override_active = s.override_active = 0; }
+    if (l.a.do_prepare) {
+      st->c[0] = float(s.step + 1);                // the number of the update
+      st->c[8] = s.override_active ? s.override_grad_mult : float(1.0 / s.loss_scale);
+      st->skip = s.found_inf;
+      if (l.a.end_step) pt_end_early(st, s, s.found_inf != 0, l.a.end_step);
+    }
+  } else if (l.reads_scale) seen.insert(seen.end(), {2.0, st->loss_scale});
+}
+
+void on_launch(const fake::Op& op, void** args) {
+  Launch l{};
+  l.kernel = op.kernel;
+  if (op.kernel == "k_step_end" || op.kernel == "k_reopen") { l.st = *(PtDevState**)args[0]; l.no = *(uint32_t*)args[1]; }
+  else if (op.kernel == "k_override") { l.st = *(PtDevState**)args[0]; l.mult = *(float*)args[1]; l.inf = *(int32_t*)args[2]; }
+  else if (op.kernel == "k_set_state") { l.st = *(PtDevState**)args[0]; l.step = *(int32_t*)args[1]; l.scale = *(double*)args[2]; l.good = *(int32_t*)args[3]; }
+  else if (op.kernel == "k_scalars") { l.a = *(PtScalarArgs*)args[0]; l.st = l.a.st; }
+  else if (op.kernel == "k_adamw") l.st = *(PtDevState**)args[1];
+  else if (op.kernel == "k_pack" || op.kernel == "k_accum") { l.st = *(PtDevState**)args[4]; l.reads_scale = reads_scale; }
+  else if (op.kernel == "k_sqnorm" || op.kernel == "k_sqnorm_f32") { l.st = *(PtDevState**)args[3]; l.reads_scale = true; }
+  else if (op.kernel == "k_init_state") {
+    PtDevState* st = *(PtDevState**)args[0];
+    memset(st, 0, sizeof *st);
+    st->loss_scale = *(double*)args[1]; st->growth = *(double*)args[2]; st->backoff = *(double*)args[3];
+    st->growth_interval = *(int32_t*)args[4]; st->scaler_enabled = *(int32_t*)args[5];
+    return;
+  } else return;
+  if (fake::capturing[op.stream]) graph->push_back(l);
+  else run(l);
+}
+
+enum Do { PACK, ACCUM, UNPACK, FINALIZE, RECOMPUTE, UPDATE, UPDATE_PART, UPDATE_OTHER, OVERRIDE, SET_STATE, END, N_CALLS, REPORT = N_CALLS, CAPTURE, CAPTURED, REPLAY };
+struct Act { int what; uint32_t arg; };            // CAPTURE: the next `arg` acts go into a new graph; REPLAY: graph number `arg`
+const pt_scaler_cfg SCALER = {1024.0, 2.0, 0.5, 2, 0};
+
+// The values that `acts` lead to (`seen`) and how many kernels end a step in it.
+std::vector<double> play(const std::vector<Act>& acts, bool fp32, bool kernel_ends, size_t* ends = nullptr, size_t* reopened = nullptr) {
+  fake::ops.clear();
+  fake::on_launch = on_launch;
+  seen.clear();
+  std::vector<std::vector<Launch>> graphs(1);
+  const hipStream_t cap = fake::stream(0xc0);
+  State s(2, 64, fp32, &SCALER);
+  pt_pack_plan* q = s.plan();
+  if (kernel_ends) {
+    graph = &graphs[0];
+    fake::capturing[0xc0] = true;
+    (void)pt_step_end(s.ctx, cap);
+    fake::capturing[0xc0] = false;
+  }
+  size_t left = 0;
+  auto act = [&](const Act& a, hipStream_t st) {
+    int rc = PT_OK;
+    reads_scale = false;
+    pt_hparams hp = HP;
+    pt_step_report r{};
+    switch (a.what) {
+      case PACK:
+        reads_scale = true;
+        rc = fp32 ? s.accum(q, st) : s.pack(q, st);
+        break;
+      case ACCUM: if (fp32) rc = pt_chunk_accum_grads(s.ctx, q, (float* const*)s.g.data(), 0, 0, st); break;
+      case UNPACK: rc = pt_chunk_unpack(s.ctx, q, s.p.data(), st); break;
+      case FINALIZE: rc = s.finalize(1 + a.arg % 2, st); break;
+      case RECOMPUTE: rc = pt_chunk_grad_sqnorm(s.ctx, s.g.data(), a.arg % 2, 1, 2 * (a.arg / 2 % 2), st); break;
+      case UPDATE: rc = s.update(st); break;
+      case UPDATE_PART: rc = s.update(a.arg % 2, 1, st); break;
+      case UPDATE_OTHER:
+        hp.lr = 1.0 + a.arg;
+        rc = pt_chunk_adamw_step(s.ctx, &hp, 0, 2, s.g.data(), s.w.data(), s.m.data(), s.v.data(), s.p.data(), st);
+        break;
+      case OVERRIDE: rc = pt_step_override(s.ctx, 0.25f * a.arg, a.arg % 3 == 0, st); break;
+      case SET_STATE: rc = pt_ctx_set_state(s.ctx, 10 + a.arg, 64.0, a.arg % 2, st); break;
+      case END: rc = pt_step_end(s.ctx, st); break;
+      case REPORT:
+        rc = pt_step_report_read(s.ctx, &r, st);
+        seen.insert(seen.end(), {3.0, r.loss_scale, r.grad_mult, double(r.found_inf), double(r.step), double(r.good_steps)});
+    }
+    if (rc != PT_OK) seen.insert(seen.end(), {4.0, double(rc)});
+  };
+  auto step = [&](bool inf) {
+    inf_now = inf;
+    for (const int what : {PACK, UNPACK, FINALIZE, UPDATE, END, REPORT}) act({what, 0}, nullptr);
+  };
+  // the pointers a graph may use are bound by an eager call, as a program has to
+  if (pt_chunk_unpack(s.ctx, q, s.p.data(), nullptr) != PT_OK) State::die(s.ctx);
+  for (size_t i = 0; i < acts.size(); ++i) {
+    inf_now = acts[i].arg % 5 == 4;
+    if (acts[i].what == CAPTURE) {
+      graphs.emplace_back();
+      graph = &graphs.back();
+      left = acts[i].arg;
+      fake::capturing[0xc0] = left != 0;
+    } else if (acts[i].what == REPLAY) {
+      if (acts[i].arg < graphs.size())
+        for (const Launch& l : std::vector<Launch>(graphs[acts[i].arg])) run(l);
+    } else if (left) {
+      if (acts[i].what < N_CALLS) act(acts[i], cap);
+      fake::capturing[0xc0] = --left != 0;
+    } else act(acts[i], nullptr);
+  }
+  fake::capturing[0xc0] = false;
+  for (int t = 0; t < 3; ++t) step(t == 1);
+  if (ends) *ends = fake::launches("k_step_end").size();
+  if (reopened) *reopened = fake::launches("k_reopen").size();
+  fake::on_launch = nullptr;
+  return seen;
+}
+
+std::string text(const std::vector<Act>& acts) {
+  static const char* names[] = {"pack", "accum", "unpack", "finalize", "recompute", "update", "update_part", "update_other", "override", "set_state",
+                                "end", "report", "capture", "captured", "replay"};
+  std::string t;
+  for (const Act& a : acts) t += std::string(names[a.what]) + " " + std::to_string(a.arg) + "; ";
+  return t;
+}
+
+int same(const std::vector<Act>& acts, bool fp32 = false) {
+  size_t ends = 0;
+  const std::vector<double> apart = play(acts, fp32, true, &ends), now = play(acts, fp32, false);
+  size_t calls = 1 + 3;                            // the first one, and the three steps behind `acts`
+  for (const Act& a : acts) calls += a.what == END;
+  if (ends != calls) { fprintf(stderr, "%zu calls ended a step with %zu kernels: %s\n", calls, ends, text(acts).c_str()); return 1; }
+  if (apart == now) return 0;
+  fprintf(stderr, "differ (fp32 %d): %s\n", fp32, text(acts).c_str());
+  for (const auto* v : {&apart, &now}) {
+    for (double x : *v) fprintf(stderr, "%g ", x);
+    fprintf(stderr, "\n");
+  }
+  return 1;
+}
+
+// A step end captured alone, in a context whose packs, norms and updates are eager: every replay ends a step.
+int step_end_in_a_graph() {
+  std::vector<Act> acts = {{CAPTURE, 1}, {END, 0}};
+  for (int t = 0; t < 4; ++t) for (const Act& a : {Act{PACK, 0}, Act{FINALIZE, 0}, Act{UPDATE, 0}, Act{REPLAY, 1}, Act{REPORT, 0}}) acts.push_back(a);
+  const std::vector<double> v = play(acts, false, false);
+  std::vector<double> t;
+  for (size_t i = 0; i < v.size(); i += v[i] == 1.0 ? 4 : v[i] == 3.0 ? 6 : 2)
+    if (v[i] == 1.0) t.push_back(v[i + 1]);
+  EXPECT((t == std::vector<double>{1, 2, 3, 4, 5, 6, 6}));       // the sixth is skipped
+  return same(acts);
+}
+
+// Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
+// kernel of their own; what does not, does not.
+int captured_alone() {
+  for (int fp32 = 0; fp32 < 2; ++fp32)
+    for (int what = 0; what < N_CALLS; ++what) {
+      const bool plain = what == UNPACK || what == ACCUM;
+      const std::vector<Act> acts = {{PACK, 0}, {FINALIZE, 0}, {UPDATE, 0}, {END, 0}, {PACK, 0}, {FINALIZE, 0}, {CAPTURE, 1}, {what, 1}, {END, 0}};
+      size_t ends = 0;
+      (void)play(acts, fp32, false, &ends);
+      EXPECT(ends == (what == END ? 5u : plain ? 1u : 4u));
+      if (same(acts, fp32)) return 1;
+    }
+  return 0;
+}
+
 const std::map<std::string, int (*)()> checks = {
+    {"step_end_in_a_graph", step_end_in_a_graph},
+    {"captured_alone", captured_alone},
     {"step_ends_with_its_constants", step_ends_with_its_constants},
     {"captured_without_the_pack", captured_without_the_pack},
     {"put_off_at_most_once", put_off_at_most_once},

@@ -18,7 +18,7 @@ def exe(tmp_path_factory):
         build.build()
     out = str(tmp_path_factory.mktemp("host_calls") / "host_calls")
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-rdynamic", "-Wno-unused-result", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I",
-           os.path.join(ROOT, "include"), os.path.join(PINS, "host_calls.cpp"), "-o", out, "-L", PKG, "-lptchunk",
+           os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"), os.path.join(PINS, "host_calls.cpp"), "-o", out, "-L", PKG, "-lptchunk",
            "-Wl,-rpath," + PKG, "-Wl,--allow-shlib-undefined"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-4000:]
@@ -40,6 +40,8 @@ def exe(tmp_path_factory):
     "side_streams_are_judged_by_their_own_steps",
     "recompute_and_norm_in_one_launch",
     "step_ends_with_its_constants",
+    "step_end_in_a_graph",
+    "captured_alone",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
