@@ -106,7 +106,10 @@ struct pt_ctx {
   bool norm_finalized = false;
   bool prepared = false;
   uint32_t step_no = 1;                 // steps opened so far; never 0
-  bool ended_early = false;             // the launch that derived this step's constants has advanced the step counter and loss scale too
+  // Number of the step whose constants' launch has advanced the step counter and loss scale too, as long as no kernel that took that
+  // into account has been launched and the step is open; 0: none.  A call under capture launches nothing, so it leaves this
+  // as it is: then the device's own `ended` says whether a replay has closed the step or taken its end back.
+  uint32_t ended_early = 0;
   bool captured = false;                // a call of this context has been captured into a graph
   PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;

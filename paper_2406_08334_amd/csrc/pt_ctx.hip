@@ -47,12 +47,12 @@ __global__ void k_override(PtDevState* st, float grad_mult, int32_t found_inf) {
   st->sqnorm = 0.0; st->norm = 0.0;
 }
 
-__global__ void k_step_end(PtDevState* st, uint32_t step_no) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) pt_end_step(st, step_no);
+__global__ void k_step_end(PtDevState* st, uint32_t early) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) pt_end_step(st, early);
 }
 
-__global__ void k_reopen(PtDevState* st, uint32_t step_no) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) pt_take_back(st, step_no);
+__global__ void k_reopen(PtDevState* st, uint32_t early) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) pt_take_back(st, early);
 }
 
 // ---- public: misc -------------------------------------------------------------------------
@@ -325,15 +325,15 @@ extern "C" int pt_step_end(pt_ctx* ctx, void* stream) {
   }
   const bool capturing = pt_capturing(ctx, st);
   if (int rc = pt_flush_pending(ctx, st); rc != PT_OK) return rc;     // a step without an update still needs its found_inf
-  // Nothing to launch where the step has ended with its constants.  Under capture the kernel goes into the graph either way:
-  // it looks whether the step it is replayed in has ended.
-  if (!ctx->ended_early || capturing) {
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state, ctx->step_no);
+  // Nothing to launch where the step has ended with its constants - unless a graph may have closed it already, or is to close it:
+  // then the kernel looks for itself.
+  if (!ctx->ended_early || ctx->captured) {
+    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, st, ctx->d_state, ctx->ended_early);
     PT_LAUNCH_CHECK(ctx, "k_step_end");
   }
   ctx->norm_finalized = false;
   ctx->prepared = false;
-  ctx->ended_early = false;
+  if (!capturing) ctx->ended_early = 0;
   if (++ctx->step_no == 0) ctx->step_no = 1;
   std::fill(ctx->chunk_fresh.begin(), ctx->chunk_fresh.end(), uint8_t(0));   // the next step needs new partial sums
   std::fill(ctx->chunk_packed_by.begin(), ctx->chunk_packed_by.end(), uint64_t(0));
@@ -350,9 +350,9 @@ bool pt_capturing(pt_ctx* ctx, hipStream_t stream) {
 
 int pt_reopen_step(pt_ctx* ctx, hipStream_t stream) {
   if (!ctx->ended_early) return PT_OK;
-  hipLaunchKernelGGL(k_reopen, dim3(1), dim3(1), 0, stream, ctx->d_state, ctx->step_no);
+  hipLaunchKernelGGL(k_reopen, dim3(1), dim3(1), 0, stream, ctx->d_state, ctx->ended_early);
   PT_LAUNCH_CHECK(ctx, "k_reopen");
-  ctx->ended_early = false;
+  if (!pt_capturing(ctx, stream)) ctx->ended_early = 0;
   return PT_OK;
 }
 
@@ -362,7 +362,7 @@ extern "C" int pt_step_report_read(pt_ctx* ctx, pt_step_report* out, void* strea
   PtDevState h;
   PT_HIP(ctx, hipMemcpyAsync(&h, ctx->d_state, sizeof h, hipMemcpyDeviceToHost, (hipStream_t)stream));
   PT_HIP(ctx, hipStreamSynchronize((hipStream_t)stream));
-  if (ctx->ended_early) { h.loss_scale = h.old_loss_scale; h.step = h.old_step; h.good_steps = h.old_good_steps; }   // still open for the caller
+  if (ctx->ended_early && h.ended == ctx->ended_early) { h.loss_scale = h.old_loss_scale; h.step = h.old_step; h.good_steps = h.old_good_steps; }   // still open for the caller
   out->sqnorm = h.sqnorm; out->norm = h.norm; out->clip_coef = h.clip_coef;
   out->loss_scale = h.loss_scale; out->grad_mult = h.c[8]; out->found_inf = h.found_inf;
   out->step = h.step; out->good_steps = h.good_steps;

@@ -366,6 +366,9 @@ static int launch_pending(pt_ctx* ctx, const pt_hparams* hp, uint32_t end_step, 
 
 int pt_flush_pending(pt_ctx* ctx, hipStream_t stream) {
   if (!ctx->pend_reduce.n && !ctx->pend_finalize) return PT_OK;
+  // one that was asked for under capture, in a step that had ended early: the end follows its found_inf
+  if (ctx->pend_finalize)
+    if (const int rc = pt_reopen_step(ctx, stream); rc != PT_OK) return rc;
   return launch_pending(ctx, nullptr, 0, nullptr, stream);
 }
 
@@ -406,7 +409,7 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
   const bool end = !ctx->captured;
   rc = launch_pending(ctx, hp, end ? ctx->step_no : 0, mirror ? ctx->h_state_dev : nullptr, stream);
   if (rc != PT_OK) return rc;
-  ctx->ended_early = end;
+  if (end) ctx->ended_early = ctx->step_no;
   if (mirror) {
     PT_HIP(ctx, hipEventRecord(ctx->ev_scalar, stream));
     ctx->mirrored = true;

@@ -71,17 +71,18 @@ PT_STEP_FN void pt_end_early(PtDevState* st, PtDevState s, bool found_inf, uint3
   st->ended = step_no;
 }
 
-// The end of step `step_no`, unless the launch that derived its constants has been its end too.
-PT_STEP_FN void pt_end_step(PtDevState* st, uint32_t step_no) {
-  if (st->ended == step_no) { st->ended = 0; return; }
+// The end of a step, unless that has come with its constants: `early` is the number of the step that is known to have ended so, or
+// 0.  (What `ended` still holds of a step closed without a launch is never asked for again.)
+PT_STEP_FN void pt_end_step(PtDevState* st, uint32_t early) {
+  if (early && st->ended == early) { st->ended = 0; return; }
   PtDevState s = *st;
   pt_advance(s, s.found_inf != 0);
   st->step = s.step; st->loss_scale = s.loss_scale; st->good_steps = s.good_steps; st->override_active = s.override_active;
 }
 
-// Takes the early end of step `step_no` back.
-PT_STEP_FN void pt_take_back(PtDevState* st, uint32_t step_no) {
-  if (st->ended != step_no) return;
+// Takes the early end of that step back, unless that has happened or the step is closed.
+PT_STEP_FN void pt_take_back(PtDevState* st, uint32_t early) {
+  if (st->ended != early) return;
   st->step = st->old_step; st->loss_scale = st->old_loss_scale; st->good_steps = st->old_good_steps;
   st->override_active = st->old_override;
   st->ended = 0;

@@ -42,6 +42,7 @@ def exe(tmp_path_factory):
     "step_ends_with_its_constants",
     "step_end_in_a_graph",
     "captured_alone",
+    "sequences_at_random",
 ])
 def test_calls(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
