@@ -111,6 +111,7 @@ struct pt_ctx {
   // as it is: then the device's own `ended` says whether a replay has closed the step or taken its end back.
   uint32_t ended_early = 0;
   bool captured = false;                // a call of this context has been captured into a graph
+  bool goes_on = false;                 // an early end has been taken back: this context's steps do more behind their first update
   PtPendingReduce pend_reduce;                // scalar work put off to be fused into one launch (pt_norm.hip); n == 0: none
   bool pend_finalize = false;
   bool mirrored = false;                // the prepared constants are in h_state, with ev_scalar behind them

@@ -353,6 +353,9 @@ int pt_reopen_step(pt_ctx* ctx, hipStream_t stream) {
   hipLaunchKernelGGL(k_reopen, dim3(1), dim3(1), 0, stream, ctx->d_state, ctx->ended_early);
   PT_LAUNCH_CHECK(ctx, "k_reopen");
   if (!pt_capturing(ctx, stream)) ctx->ended_early = 0;
+  // Taking it back is a launch, as the step end is one.  Updates with different hyper-parameters for different chunks, or a norm and an
+  // update a layer, would pay it once a call: such steps end in a kernel of their own from here on.
+  ctx->goes_on = true;
   return PT_OK;
 }
 

@@ -405,8 +405,8 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
   int rc = pt_reopen_step(ctx, stream);              // other hyper-parameters: the constants are derived anew
   if (rc != PT_OK) return rc;
   // The launch is the step's end too (pt_end_early), but not in a graph, whose replays may be followed by a step end outside it, nor
-  // in a context that has graphs.
-  const bool end = !ctx->captured;
+  // in a context that has graphs, nor where a step of the context has gone on behind it.
+  const bool end = !ctx->captured && !ctx->goes_on;
   rc = launch_pending(ctx, hp, end ? ctx->step_no : 0, mirror ? ctx->h_state_dev : nullptr, stream);
   if (rc != PT_OK) return rc;
   if (end) ctx->ended_early = ctx->step_no;

@@ -2,6 +2,7 @@
 // Usage: host_calls <check>.  Exit code 0 = the check held.
 #include "fake_hip.h"
 
+#include <memory>
 #include <random>
 #include <tuple>
 
@@ -44,11 +45,11 @@ struct State {
   static void die(const pt_ctx* c) { fprintf(stderr, "setup failed: %s\n", pt_last_error(c)); exit(3); }
   static void* device(size_t n) { void* q = nullptr; (void)hipMalloc(&q, n); return q; }
   static void* pinned(size_t n) { void* q = nullptr; (void)hipHostMalloc(&q, n, 0); return q; }
-  pt_pack_plan* plan() {
+  pt_pack_plan* plan(int only = -1) {
     std::vector<pt_segment> segs;
-    for (uint32_t c = 0; c < C; ++c) segs.push_back({device(2 * S), 0, S, 0, c, c});
+    for (uint32_t c = 0; c < C; ++c) if (only < 0 || uint32_t(only) == c) segs.push_back({device(2 * S), 0, S, 0, c, c});
     pt_pack_plan* q = nullptr;
-    if (pt_pack_plan_create(ctx, segs.data(), C, &q) != PT_OK) die(ctx);
+    if (pt_pack_plan_create(ctx, segs.data(), uint32_t(segs.size()), &q) != PT_OK) die(ctx);
     plans.push_back(q);
     return q;
   }
@@ -410,12 +411,14 @@ int recompute_and_norm_in_one_launch() {
 // The launch that derives a step's constants is its end too: pt_step_end launches nothing, unless a call of the same step that
 // depends on the step counter or loss scale came in between (which takes the end back), or the context has graphs.
 int step_ends_with_its_constants() {
-  State s(2, 4096);
-  pt_pack_plan* q = s.plan();
+  std::unique_ptr<State> own;                      // a context each: taking an end back and a capture change its later steps
+  pt_pack_plan* q = nullptr;
   pt_step_report rep;
   const hipStream_t cap = fake::stream(0xc0);
   enum { NOTHING, REPORT, AGAIN, PACK, FINALIZE, RECOMPUTE, OVERRIDE, STATE, OTHER, NO_UPDATE, CAPTURED, AFTERWARDS, N };
   for (int how = 0; how < N; ++how) {
+    if (how != AFTERWARDS) { own.reset(new State(2, 4096)); q = own->plan(); }
+    State& s = *own;
     OK(s.pack(q));
     OK(s.finalize(PT_FINALIZE_STRICT));
     size_t at = fake::ops.size();
@@ -436,7 +439,7 @@ int step_ends_with_its_constants() {
     if (how == CAPTURED) fake::capturing[0xc0] = true;
     OK(pt_step_end(s.ctx, how == CAPTURED ? cap : nullptr));
     fake::capturing[0xc0] = false;
-    const bool of_its_own = (taken_back && how != OTHER) || how >= NO_UPDATE;      // other constants: ended by their launch again
+    const bool of_its_own = taken_back || how >= NO_UPDATE;
     EXPECT(fake::launches("k_step_end", at).size() == (of_its_own ? 1u : 0u));
   }
   return 0;
@@ -604,6 +607,47 @@ int step_end_in_a_graph() {
   return same(acts);
 }
 
+// Updates with hyper-parameters of their own for each of three groups of chunks, and a norm and an update a layer: from the second step on
+// no more launches than with a step end of its own.
+int steps_that_go_on_behind_an_update() {
+  for (int layers = 0; layers < 2; ++layers) {
+    State s(3, 4096);
+    std::vector<pt_pack_plan*> q;
+    for (uint32_t c = 0; c < 3; ++c) q.push_back(s.plan(c));
+    for (int t = 0; t < 4; ++t) {
+      const size_t at = fake::ops.size();
+      if (!layers) {
+        for (uint32_t c = 0; c < 3; ++c) OK(s.pack(q[c]));
+        OK(s.finalize(PT_FINALIZE_STRICT));
+      }
+      for (uint32_t c = 0; c < 3; ++c) {
+        pt_hparams hp = HP;
+        hp.lr *= layers ? 1.0 : c + 1.0;
+        if (layers) {
+          OK(s.pack(q[c]));
+          OK(s.finalize(PT_FINALIZE_CARRY));
+        }
+        OK(pt_chunk_adamw_step(s.ctx, &hp, c, 1, &s.g[c], &s.w[c], &s.m[c], &s.v[c], &s.p[c], nullptr));
+      }
+      OK(pt_step_end(s.ctx, nullptr));
+      if (t == 0) continue;                        // the one that finds out
+      EXPECT(fake::launches("k_reopen", at).empty());
+      EXPECT(fake::launches("k_step_end", at).size() == 1);
+    }
+  }
+  State s(3, 4096);                                // updates in parts with the same hyper-parameters go on ending early
+  pt_pack_plan* q = s.plan();
+  for (int t = 0; t < 3; ++t) {
+    OK(s.pack(q));
+    OK(s.finalize(PT_FINALIZE_STRICT));
+    for (uint32_t c = 0; c < 3; ++c) OK(s.update(c, 1));
+    const size_t at = fake::ops.size();
+    OK(pt_step_end(s.ctx, nullptr));
+    EXPECT(fake::ops.size() == at);
+  }
+  return 0;
+}
+
 // Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
 // kernel of their own; what does not, does not.
 int captured_alone() {
@@ -641,6 +685,7 @@ int sequences_at_random() {
 const std::map<std::string, int (*)()> checks = {
     {"step_end_in_a_graph", step_end_in_a_graph},
     {"captured_alone", captured_alone},
+    {"steps_that_go_on_behind_an_update", steps_that_go_on_behind_an_update},
     {"sequences_at_random", sequences_at_random},
     {"step_ends_with_its_constants", step_ends_with_its_constants},
     {"captured_without_the_pack", captured_without_the_pack},
