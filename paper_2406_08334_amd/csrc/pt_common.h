@@ -308,9 +308,14 @@ int pt_static_scratch_setup(void** out);
 // The reduction of a plan's tile sums (pack, accumulate) to per-chunk values: launched on `stream`, a small plan's put off until the
 // norm is read or another call's sums come.
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);
-// True if `stream` is being captured; the context remembers that it ever was.  Every call that reads or changes what the end of a
-// step changes asks first of all: a graph holds such a call then, and may be replayed anywhere in a later step, so those end
-// in a kernel of their own.  Unpacking and adding without the norm read none of it, and leave it at that.
+inline bool pt_is_capturing(hipStream_t stream) {      // whether `stream` is being captured into a graph
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
+  return cs != hipStreamCaptureStatusNone;
+}
+// The same; the context remembers that it ever was.  Every call that reads or changes what the end of a step changes asks first of
+// all: a graph holds such a call then, and may be replayed anywhere in a later step, so those end in a kernel of their own.
+// Unpacking and adding without the norm read none of it and do not ask.
 bool pt_capturing(pt_ctx* ctx, hipStream_t stream);
 // Before a call on `stream` that reads or changes what the end of a step changes: takes an early end of this step back.
 int pt_reopen_step(pt_ctx* ctx, hipStream_t stream);

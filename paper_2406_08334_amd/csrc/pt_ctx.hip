@@ -341,9 +341,7 @@ extern "C" int pt_step_end(pt_ctx* ctx, void* stream) {
 }
 
 bool pt_capturing(pt_ctx* ctx, hipStream_t stream) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) (void)hipGetLastError();
-  const bool yes = cs != hipStreamCaptureStatusNone;
+  const bool yes = pt_is_capturing(stream);
   ctx->captured = ctx->captured || yes;
   return yes;
 }

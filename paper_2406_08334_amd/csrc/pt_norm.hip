@@ -688,7 +688,9 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   // Nothing here has to start at zero: each launch writes every partial and per-chunk slot that the
   // next one reads (n_chunks * blocks_per_chunk partials, n_chunks sums), so stale contents of an
   // earlier, larger call are never read.
-  const bool one = norm_in_one(blocks_per_chunk, n_chunks);
+  // Not under capture: a replay would use the same counter every time, and clear another one.  A count that calls which overlapped
+  // have left in it would stay, and no workgroup of a later replay would be the last.  Two launches clear theirs themselves.
+  const bool one = norm_in_one(blocks_per_chunk, n_chunks) && !pt_is_capturing(st);
   static std::atomic<uint32_t> calls{0};
   const uint32_t call = one ? calls.fetch_add(1, std::memory_order_relaxed) : 0;
   norm_arena_kernel_t kern = dtype == PT_BF16 ? pick_norm_arena<PT_BF16>(shape.unroll, one) : pick_norm_arena<PT_FP16>(shape.unroll, one);

@@ -648,6 +648,23 @@ int steps_that_go_on_behind_an_update() {
   return 0;
 }
 
+// The norm without a context, of an arena that one launch takes: under capture it is two, whose counter every replay clears for itself.
+int norm_without_a_context_captured() {
+  void* arena = State::device(2 * 4096);
+  double* out = (double*)State::device(16);
+  int32_t* inf = (int32_t*)State::device(4);
+  const hipStream_t s = fake::stream(0xc0);
+  for (int n = 0; n < 40; ++n) {
+    const bool capture = n % 3 == 1;
+    const size_t at = fake::ops.size();
+    fake::capturing[0xc0] = capture;
+    OK(pt_chunk_grad_sqnorm_noalloc(arena, PT_BF16, 4096, 1, 1.0, out, inf, s));
+    fake::capturing[0xc0] = false;
+    EXPECT(fake::launches("k_sqnorm_arena", at).size() == 1 && fake::launches("k_scalars", at).size() == (capture ? 1u : 0u));
+  }
+  return 0;
+}
+
 // Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
 // kernel of their own; what does not, does not.
 int captured_alone() {
@@ -685,6 +702,7 @@ int sequences_at_random() {
 const std::map<std::string, int (*)()> checks = {
     {"step_end_in_a_graph", step_end_in_a_graph},
     {"captured_alone", captured_alone},
+    {"norm_without_a_context_captured", norm_without_a_context_captured},
     {"steps_that_go_on_behind_an_update", steps_that_go_on_behind_an_update},
     {"sequences_at_random", sequences_at_random},
     {"step_ends_with_its_constants", step_ends_with_its_constants},
