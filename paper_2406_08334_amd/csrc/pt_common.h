@@ -302,9 +302,9 @@ void pt_host_pool_destroy(pt_ctx* ctx);
 
 // ---- implemented in pt_norm.hip ---------------------------------------------------------
 // Looks up (once per device) the device address of the file-scope scratch array that
-// pt_chunk_grad_sqnorm_noalloc works in; out may be NULL.  Called by pt_ctx_create, so that a process
+// pt_chunk_grad_sqnorm_noalloc works in; out and device may be NULL.  Called by pt_ctx_create, so that a process
 // with a context never pays the lookup inside a hot call.
-int pt_static_scratch_setup(void** out);
+int pt_static_scratch_setup(void** out, int* device = nullptr);
 // The reduction of a plan's tile sums (pack, accumulate) to per-chunk values: launched on `stream`, a small plan's put off until the
 // norm is read or another call's sums come.
 int pt_reduce_plan(pt_ctx* ctx, const pt_pack_plan* plan, hipStream_t stream);

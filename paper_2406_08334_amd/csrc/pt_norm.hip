@@ -636,7 +636,7 @@ void* g_scratch_addr[PT_STATIC_MAX_DEVICES] = {};
 
 // Device address of `scratch` on the current device, looked up once per device (every GPU holds its
 // own copy of the array at its own address).
-int pt_static_scratch_setup(void** out) {
+int pt_static_scratch_setup(void** out, int* device) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return pt_fail(nullptr, PT_ERR_HIP, "hipGetDevice failed: %s", hipGetErrorString(e));
@@ -651,6 +651,7 @@ int pt_static_scratch_setup(void** out) {
     g_scratch_addr[dev] = p;
   }
   if (out) *out = g_scratch_addr[dev];
+  if (device) *device = dev;
   return PT_OK;
 }
 
@@ -678,7 +679,8 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
                    n_chunks, (unsigned long long)chunk_elems, PT_STATIC_MAX_CHUNKS, PT_STATIC_MAX_PARTIALS,
                    PT_NORM_BLOCK_ELEMS);
   void* base = nullptr;
-  int rc = pt_static_scratch_setup(&base);
+  int dev = 0;
+  int rc = pt_static_scratch_setup(&base, &dev);
   if (rc != PT_OK) return rc;
   // every address below derives from the looked-up device address, never from the array's name
   PtStaticScratch* sc = static_cast<PtStaticScratch*>(base);
@@ -691,8 +693,8 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   // Not under capture: a replay would use the same counter every time, and clear another one.  A count that calls which overlapped
   // have left in it would stay, and no workgroup of a later replay would be the last.  Two launches clear theirs themselves.
   const bool one = norm_in_one(blocks_per_chunk, n_chunks) && !pt_is_capturing(st);
-  static std::atomic<uint32_t> calls{0};
-  const uint32_t call = one ? calls.fetch_add(1, std::memory_order_relaxed) : 0;
+  static std::atomic<uint32_t> calls[PT_STATIC_MAX_DEVICES];       // so far, a number each: every device has its own counters
+  const uint32_t call = one ? calls[dev].fetch_add(1, std::memory_order_relaxed) : 0;
   norm_arena_kernel_t kern = dtype == PT_BF16 ? pick_norm_arena<PT_BF16>(shape.unroll, one) : pick_norm_arena<PT_FP16>(shape.unroll, one);
   hipLaunchKernelGGL(kern, grid, dim3(NB_THREADS), shape.lds, st, grad_arena, chunk_elems, loss_scale, sc->part, sc->flag,
                      one ? sc->tickets + call % PT_ONE_TICKETS : &sc->ticket, sc->tickets + (call + PT_ONE_TICKETS / 2) % PT_ONE_TICKETS,

@@ -32,6 +32,7 @@ inline uintptr_t next_handle = 0x1000;
 inline std::string fail_kernel;                   // launches of this kernel fail once `fail_after` of them have passed
 inline int fail_after = -1;
 inline hipError_t last = hipSuccess;
+inline int device = 0;
 
 inline void note(const char* what, hipStream_t s = nullptr, hipEvent_t e = nullptr) {
   Op o;
@@ -107,9 +108,14 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t ld
 }
 hipError_t hipGetLastError(void) { const hipError_t e = fake::last; fake::last = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t) { return "fake error"; }
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = fake::device; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { fake::note("sync device"); return hipSuccess; }
-hipError_t hipGetSymbolAddress(void** p, const void*) { static void* mem = calloc(1, 8 << 20); *p = mem; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  static std::map<int, void*> mem;
+  if (!mem[fake::device]) mem[fake::device] = calloc(1, 8 << 20);
+  *p = mem[fake::device];
+  return hipSuccess;
+}
 hipError_t hipMalloc(void** p, size_t n) { return fake::alloc(p, n, hipMemoryTypeDevice); }
 hipError_t hipFree(void* p) { fake::memory.erase((uintptr_t)p); free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return fake::alloc(p, n, hipMemoryTypeHost); }

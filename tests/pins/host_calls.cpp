@@ -665,6 +665,31 @@ int norm_without_a_context_captured() {
   return 0;
 }
 
+// The same on two devices in turn, eight calls each: a counter is cleared by another call on its device before it is used again.
+std::vector<uintptr_t> counters;                   // used, cleared
+void note_counters(const fake::Op& op, void** args) {
+  if (op.kernel == "k_sqnorm_arena") for (int k : {5, 6}) counters.push_back(*(uintptr_t*)args[k]);
+}
+int norm_counters_of_two_devices() {
+  void* arena = State::device(2 * 4096);
+  double* out = (double*)State::device(16);
+  int32_t* inf = (int32_t*)State::device(4);
+  fake::on_launch = note_counters;
+  std::map<uintptr_t, bool> spoilt;
+  for (int n = 0; n < 200; ++n) {
+    fake::device = n / 8 % 2;
+    counters.clear();
+    OK(pt_chunk_grad_sqnorm_noalloc(arena, PT_BF16, 4096, 1, 1.0, out, inf, nullptr));
+    EXPECT(counters.size() == 2 && counters[0] != counters[1]);
+    if (spoilt.count(counters[0])) EXPECT(!spoilt[counters[0]]);
+    spoilt[counters[0]] = true;
+    spoilt[counters[1]] = false;
+  }
+  fake::on_launch = nullptr;
+  fake::device = 0;
+  return 0;
+}
+
 // Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
 // kernel of their own; what does not, does not.
 int captured_alone() {
@@ -702,6 +727,7 @@ int sequences_at_random() {
 const std::map<std::string, int (*)()> checks = {
     {"step_end_in_a_graph", step_end_in_a_graph},
     {"captured_alone", captured_alone},
+    {"norm_counters_of_two_devices", norm_counters_of_two_devices},
     {"norm_without_a_context_captured", norm_without_a_context_captured},
     {"steps_that_go_on_behind_an_update", steps_that_go_on_behind_an_update},
     {"sequences_at_random", sequences_at_random},
