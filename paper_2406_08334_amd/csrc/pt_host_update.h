@@ -63,7 +63,12 @@ static inline float f32_identity(float x) { return x; }
 // The 16-bit parameters are written and not read: a plain store would fetch each of their lines from memory first, 2 of 30 bytes
 // an element.  They are put together in the first-level cache, a block at a time, and leave it past the caches:
 // seven chunks of 2^23 elements 4.63 -> 4.2 ms a step with 16 threads, 5.05 -> 4.54 with 8, fp16 4.51 -> 4.2.
+// Not in calls whose state stays in the processor's caches from step to step (30 bytes an element against 32 MB of last-level
+// cache), which store them plainly.  Plain and past the caches: 2^17 elements 41.9 and 47.5 us (one thread), 2^20 206 and 251
+// (one), 84 and 90 (four), 3 * 2^19 296 and 367 (one); 2^21 510 and 490 (one), 132 and 163 (eight), 294 and 227 (sixteen); 3 * 2^20 1022
+// and 905 (one), 366 and 268 (four), 293 and 249 (eight).
 constexpr uint64_t PARAM_BLOCK = 2048;
+constexpr uint64_t STREAM_ELEMS = 1u << 21;
 
 static inline void store_params(uint16_t* __restrict__ p, const uint16_t* __restrict__ from, uint64_t n) {
 #if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
@@ -85,8 +90,10 @@ static inline void params_stored() {
 
 #define PT_HOST_UPDATE_BODY(DECODE, ENCODE)                                         \
   alignas(64) uint16_t block[PARAM_BLOCK];                                         \
-  for (uint64_t b = 0; b < n; b += PARAM_BLOCK) {                                  \
-    const uint64_t cnt = n - b < PARAM_BLOCK ? n - b : PARAM_BLOCK;                \
+  const uint64_t step = stream ? PARAM_BLOCK : n;                                  \
+  for (uint64_t b = 0; b < n; b += step) {                                         \
+    const uint64_t cnt = n - b < step ? n - b : step;                              \
+    uint16_t* __restrict__ out = stream ? block : p;                               \
     const auto* __restrict__ gb = g + b;                                           \
     float* __restrict__ wb = w + b;                                                \
     float* __restrict__ mb = m + b;                                                \
@@ -103,9 +110,9 @@ static inline void params_stored() {
       float t3 = wb[i] * k.decay;                                                  \
       float wn = std::fmaf(-k.step_size, u, t3);                                   \
       mb[i] = mn; vb[i] = vn; wb[i] = wn;                                          \
-      block[i] = ENCODE(wn);                                                       \
+      out[i] = ENCODE(wn);                                                         \
     }                                                                              \
-    store_params(p + b, block, cnt);                                               \
+    if (stream) store_params(p + b, block, cnt);                                   \
   }
 
 // x86 clones picked at load time; a device pass of a HIP compiler only parses this host code
@@ -118,26 +125,30 @@ static inline void params_stored() {
 
 PT_HOST_CLONES
 static void update_bf16(const Consts k, const uint16_t* __restrict__ g, float* __restrict__ w,
-                        float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n) {
+                        float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n,
+                        bool stream = true) {
   PT_HOST_UPDATE_BODY(bf16_to_f32, f32_to_bf16)
 }
 
 PT_HOST_CLONES
 static void update_fp16(const Consts k, const uint16_t* __restrict__ g, float* __restrict__ w,
-                        float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n) {
+                        float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n,
+                        bool stream = true) {
   PT_HOST_UPDATE_BODY(fp16_to_f32, f32_to_fp16)
 }
 
 // fp32 gradient chunks (accumulated micro-batches): the gradient is read as it is
 PT_HOST_CLONES
 static void update_bf16_g32(const Consts k, const float* __restrict__ g, float* __restrict__ w,
-                            float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n) {
+                            float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n,
+                            bool stream = true) {
   PT_HOST_UPDATE_BODY(f32_identity, f32_to_bf16)
 }
 
 PT_HOST_CLONES
 static void update_fp16_g32(const Consts k, const float* __restrict__ g, float* __restrict__ w,
-                            float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n) {
+                            float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ p, uint64_t n,
+                            bool stream = true) {
   PT_HOST_UPDATE_BODY(f32_identity, f32_to_fp16)
 }
 
@@ -163,8 +174,10 @@ struct Job {
   const uint64_t* nd_ranges = nullptr;
   std::atomic<uint64_t> next{0};
   uint64_t grains_per_chunk = 0, total_grains = 0;
+  bool stream = true;                   // the parameters go past the caches
 
   void prepare() {
+    stream = S * n_chunks >= STREAM_ELEMS;
     grains_per_chunk = (S + GRAIN - 1) / GRAIN;
     total_grains = grains_per_chunk * n_chunks;
     next.store(0, std::memory_order_relaxed);
@@ -201,11 +214,11 @@ static inline void run_grains(Job& job) {
       const uint64_t off = pos - lo, cnt = stop - pos;
       float* w_ = job.h_master[c] + pos; float* m_ = job.h_m[c] + pos; float* v_ = job.h_v[c] + pos;
       if (job.grad_f32) {
-        if (!job.dtype_fp16) update_bf16_g32(kk, g32 + off, w_, m_, v_, p + off, cnt);
-        else update_fp16_g32(kk, g32 + off, w_, m_, v_, p + off, cnt);
+        if (!job.dtype_fp16) update_bf16_g32(kk, g32 + off, w_, m_, v_, p + off, cnt, job.stream);
+        else update_fp16_g32(kk, g32 + off, w_, m_, v_, p + off, cnt, job.stream);
       } else {
-        if (!job.dtype_fp16) update_bf16(kk, g + off, w_, m_, v_, p + off, cnt);
-        else update_fp16(kk, g + off, w_, m_, v_, p + off, cnt);
+        if (!job.dtype_fp16) update_bf16(kk, g + off, w_, m_, v_, p + off, cnt, job.stream);
+        else update_fp16(kk, g + off, w_, m_, v_, p + off, cnt, job.stream);
       }
       pos = stop;
     }
