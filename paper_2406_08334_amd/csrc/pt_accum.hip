@@ -96,7 +96,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // compute unit.  Adding 3.3e8 words: 521 us with workgroups of four waves and tiles of 4096
 // taken from two ends of the list, 510 with three of those on a unit, 493 now (6.6 TB/s) - 507 with four units per lane in
 // flight, 513 without the limit, 535-550 with 2048 elements per wave.
-// 12 waves suit large sums; small ones, which lie in the cache (pt_in_cache), and a first micro-batch that only writes its
+// 12 waves suit large sums; small ones, which the cache serves in part, and a first micro-batch that only writes its
 // sums (6 bytes an element instead of 10), want 17.  With 12 and 17, four added and the update: 7e6 words 108.5 and 104.1 us, 1.5e7
 // 199 and 189, 3e7 364 and 352, 6e7 696 and 683, 8.5e7 966 and 954, 1.24e8 1365 and 1360, 2.0e8 2302 and 2360, 3.3e8 3630 and 3720
 // (four units a lane in flight with 12: 6e7 690, 2e6 44.4 -> 46.9); writing: 8e6 11.5 and 10.5, 3e7 33.9 and 30.5, 3.3e8 339 and 298;

@@ -276,14 +276,20 @@ inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
 // The gradient chunks are the exception: what pack or accumulate has written, the next accumulation or the update reads.  Pack
 // stores and accumulate loads the first PT_CACHED_BYTES of them without a hint (the update all of them: it is their last
 // reader), and they stay in the 256 MB Infinity Cache from call to call; traffic with hints does not take it from them, but words
-// without hints beyond its size push each other out.  fp32 sums, four micro-batches and the update, with hints and
-// without: 2e6 elements 46.5 -> 44.4 us, 7e6 113 -> 103, 3e7 375 -> 352, 6e7 743 -> 696, 1.24e8 1422 -> 1364, 3.3e8 3715 -> 3635
-// (without hints on all of them 3800); 192 to 240 MB differ by less than 1 %, 300 MB costs 1.24e8 elements 5 %.  Where 1 GB of other traffic comes between the calls they take 23.8 -> 25.3 us (1.1e7
-// elements), 52.8 -> 52.7 (3e7), 88 -> 86 (5.3e7).  The accumulate kernel's stores make no difference.  16-bit words, a
-// step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615, 200 M 1075 -> 1067, 667 M within its spread.
+// without hints beyond its size push each other out.  16-bit words, a step of 68 M parameters 370 -> 357 us, 124 M 631 -> 615,
+// 200 M 1075 -> 1067, 667 M within its spread.
+// fp32 sums, four micro-batches and the update, with hints and without: 3e7 elements 363 and 353 us, 5.3e7 612 and 589, 1.24e8
+// 1422 and 1364, 3.3e8 3715 and 3635 (without hints on all of them 3800); 192 to 240 MB differ by less than 1 %, 300 MB costs
+// 1.24e8 elements 5 %.  In training a forward and a backward pass come in between, which take the cache for themselves; then
+// smaller sums are better off with the hints.  One call behind 2 GB of other traffic, with and without: 4.2e6 elements
+// 13.0 and 14.1 us, 7.3e6 18.0 and 19.1, 1.6e7 30.2 and 32.1, 2.3e7 40.8 and 41.6, 3e7 51.5 and 51.3, 5.3e7 86.8 and 87.7, 1.0e8 155.4
+// and 154.9.  Hence the line (below it, call behind call: 4.2e6 11.3 and 11.5, 7.3e6 16.9 and 14.8, 1.6e7 29.0 and 29.4, 2.3e7 39.4 and 38.7).
 inline bool pt_adamw_hints(const pt_ctx* ctx) { return ctx->opt_adamw_nt != 0; }
-constexpr uint64_t PT_CACHED_BYTES = 240ull << 20;
-inline uint64_t pt_cached_elems(const pt_ctx* ctx) { return PT_CACHED_BYTES / (ctx->grad_f32 ? 4 : 2); }
+constexpr uint64_t PT_CACHED_BYTES = 240ull << 20, PT_CACHED_SUMS = 3ull << 23;
+inline uint64_t pt_cached_elems(const pt_ctx* ctx) {
+  if (!ctx->grad_f32) return PT_CACHED_BYTES / 2;
+  return ctx->S * ctx->C < PT_CACHED_SUMS ? 0 : PT_CACHED_BYTES / 4;
+}
 // Whether element `off` of chunk `chunk` (of S elements each) is one of the first `cached`.
 __device__ __forceinline__ bool pt_in_cache(uint32_t chunk, uint64_t S, uint64_t off, uint64_t cached) { return chunk * S + off < cached; }
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,

@@ -690,6 +690,33 @@ int norm_counters_of_two_devices() {
   return 0;
 }
 
+// Sums of less than 100 MB are added to with hints (what comes between two micro-batches takes the cache from them), the first 240 MB
+// of larger ones without; packed words of any size are kept.
+uint64_t kept = 0;                                 // elements, of the last launch
+void note_kept(const fake::Op& op, void** args) {
+  if (op.kernel == "k_accum" || op.kernel == "k_pack") kept = *(uint64_t*)args[8];
+}
+int kept_in_the_cache_by_size() {
+  fake::on_launch = note_kept;
+  for (int fp32 = 0; fp32 < 2; ++fp32)
+    for (uint32_t C : {1u, 6143u, 6144u, 60000u}) {
+      pt_ctx* ctx = nullptr;
+      pt_pack_plan* q = nullptr;
+      OK(pt_ctx_create(&ctx, PT_BF16, 4096, C, nullptr));
+      OK(pt_ctx_set_option(ctx, "grad_fp32", fp32));
+      const pt_segment seg = {State::device(2 * 4096), 0, 4096, 0, 0, 0};
+      OK(pt_pack_plan_create(ctx, &seg, 1, &q));
+      std::vector<void*> g(C, nullptr);
+      g[0] = State::device(4 * 4096);
+      OK(fp32 ? pt_chunk_accum_grads(ctx, q, (float* const*)g.data(), 0, 0, nullptr) : pt_chunk_pack_grads(ctx, q, g.data(), nullptr));
+      EXPECT(kept == (!fp32 ? 240u << 19 : C < 6144 ? 0u : 240u << 18));
+      OK(pt_pack_plan_destroy(q));
+      OK(pt_ctx_destroy(ctx));
+    }
+  fake::on_launch = nullptr;
+  return 0;
+}
+
 // Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
 // kernel of their own; what does not, does not.
 int captured_alone() {
@@ -727,6 +754,7 @@ int sequences_at_random() {
 const std::map<std::string, int (*)()> checks = {
     {"step_end_in_a_graph", step_end_in_a_graph},
     {"captured_alone", captured_alone},
+    {"kept_in_the_cache_by_size", kept_in_the_cache_by_size},
     {"norm_counters_of_two_devices", norm_counters_of_two_devices},
     {"norm_without_a_context_captured", norm_without_a_context_captured},
     {"steps_that_go_on_behind_an_update", steps_that_go_on_behind_an_update},
