@@ -437,9 +437,9 @@ extern "C" int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks,
                    first_chunk, first_chunk + n_chunks, ctx->C);
   if (finalize < 0 || finalize > PT_FINALIZE_CARRY)
     return pt_fail(ctx, PT_ERR_INVALID_ARG, "pt_chunk_grad_sqnorm: finalize must be 0, PT_FINALIZE_STRICT or PT_FINALIZE_CARRY");
-  pt_capturing(ctx, st);
   PtPendingReduce r;                             // of a recompute
   if (grad_chunks && n_chunks) {
+    pt_capturing(ctx, st);                       // without chunks the call launches nothing
     int rc = pt_table_bind(ctx, ROW_PACK, first_chunk, n_chunks, grad_chunks + first_chunk, false, st);
     if (rc != PT_OK || (rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
     const NormShape shape = norm_shape(ctx->S * n_chunks, ctx->grad_f32);
