@@ -90,16 +90,15 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // time, and unused LDS keeps few waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of
 // 1.56e9 elements 1012 -> 955 us (6.5 TB/s), 6.7e8 fp16 words 438 -> 414; unpack of 6.7e8 425 -> 404 us (6.6 TB/s).  2 KiB per wave cost
 // pack 20 % (too little work behind the look-up of a tile), 8 KiB 6-8 %.
-// Pack: about 17 waves a unit below 2^26 elements, 13 from there on.  With four vectors in flight and 17 waves, two and 17,
-// two and 13, two and 10: pack of 7.1e6 words 7.8 / 7.1 / 8.1 / 8.0 us, 2.8e7 20.7 / 20.6 / 21.7 / 22.6, 3.4e8 209 / 207 / 210 / 223,
-// 1.56e9 974 / 959 / 956 / 1021; with what follows (the words stay in the cache for the update, which starts sooner the fewer
-// stores are under way), a whole step of 7.1e6 52.1 / 50.8 / 52.2 / 51.9, 2.8e7 149 / 149 / 151 / 151, 4.5e7 233 / 231 / 233 / 234, 6.8e7
-// off the alignment 356 / 354 / 352 / 355, 1.2e8 613 / 610 / 605 / 615, 1.56e9 7759 / 7673 / 7650 / 7784.  Four in flight suited
-// pack as long as every word cost it two to three times the instructions.
+// Pack: two vectors a lane in flight and about 17 waves a unit.  With four and 17, two and 17, two and 13, two and 10, the kernel by
+// itself: 7.1e6 words 7.8 / 7.1 / 8.1 / 8.0 us, 2.8e7 20.7 / 20.6 / 21.7 / 22.6, 3.4e8 209 / 207 / 210 / 223, 1.56e9 974 / 959 / 956 /
+// 1021.  Whole steps, four and two in turn: 7.1e6 51.5-52.0 and 50.9-51.1 us, larger ones within 0.5 %, which is their spread; with 13
+// waves no step from 6.8e7 to 1.56e9 is faster (1.24e8 617 with 17 waves, 619 with 13).  Four in flight suited pack as long as every
+// word cost it two to three times the instructions.
 // Unpack: the limit gives 2-5 %: 1e7 words 8.1 -> 7.9 us, 3.7e7 24.7 -> 23.7, 1.25e8 79.8 -> 77.0, 6.3e8 404 -> 386.  About 14 waves are
 // better still from 2^28 words on (4.1e8 262.5 and 259.2 us, 1.4e9 858 and 849) and worse below (2.0e7 13.7 and
 // 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6); below 2^24 words it runs without a limit (1.5e7 11.6, with one 11.8).
-inline uint32_t pack_lds(uint64_t elems) { return elems < (1ull << 26) ? 9000 : 12000; }
+constexpr uint32_t PACK_LDS = 9000;
 inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : elems < (1ull << 28) ? 9000 : 11500; }
 
 template <int DT, int DIR>
@@ -327,7 +326,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
     if ((rc = pt_reopen_step(ctx, st)) != PT_OK || (rc = pt_before_partials(ctx, st)) != PT_OK) return rc;
   }
   dim3 grid(plan->n_tiles * plan->subs);
-  const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : pack_lds(plan->total_elems);
+  const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : PACK_LDS;
   auto kern = ctx->dtype == PT_BF16 ? k_pack<PT_BF16, DIR> : k_pack<PT_FP16, DIR>;
   hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), plan->subs, plan->sub_elems,
                      ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
