@@ -21,7 +21,7 @@
  *     pt_chunk_stream_step     host-resident chunks: updated over the link on side streams, in place or
  *                              H2D -> update -> D2H  (optional)
  *     pt_chunk_adamw_step      GPU-resident chunks, one launch
- *     pt_step_end              joins the side streams, advances the step counter / loss scale
+ *     pt_step_end              joins the side streams, advances the step counter / loss scale (if the update has not)
  * Everything is enqueued asynchronously; nothing in these five calls allocates or
  * synchronises with the host (one exception, stated at pt_chunk_adamw_step).
  *
@@ -148,8 +148,8 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
  *   "adamw_threads" workgroup size of the update kernel: 256, 512, or 0 (default).  With both this and adamw_unroll 0
  *                   the library takes its own shape: workgroups of one wave, few of them per compute unit
  *   "adamw_unroll"  4-element units a lane loads before it computes: 1, 2, 4, 8, or 0 (default)
- *   "adamw_nt"      non-temporal hints on the update's loads and stores: 0 = none, 1 or 2 (default) = on all of them,
- *                   but on the gradient loads only where the context's gradient chunks exceed the 256 MB Infinity Cache
+ *   "adamw_nt"      non-temporal hints on the update's loads and stores: 0 = none, 1 or 2 (default) = on all but the
+ *                   gradient loads, which never have one (chunks updated in place in host memory: on all of them)
  *   "pack_tile_elems"  elements of a tile of pack/unpack, which up to four workgroups share; read by pt_pack_plan_create
  *   "stream_test_reject"  for tests of pt_stream_reserve: its trial of the copy streams rejects that many
  *                   stream pairs (0..5) whatever it measures, so that the replacement runs
@@ -284,10 +284,11 @@ int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks, uint32_t f
 
 /* The global gradient norm for callers that cannot allocate: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Computes what pt_chunk_grad_sqnorm(grad_chunks, 0,
- * n_chunks, finalize) computes - same kernels, same fixed reduction order, the same bits - without a
+ * n_chunks, finalize) computes - the same fixed reduction order, the same bits - without a
  * context: the block partials and per-chunk sums live in a file-scope device array of the library
  * (6.1 MiB per GPU, held until the process ends) instead of memory a context allocated.  Calls no
- * hipMalloc / hipFree and no allocating routine; enqueues two kernels on `stream` and returns.
+ * hipMalloc / hipFree and no allocating routine; enqueues one kernel on `stream` (up to 1024 blocks of 32768
+ * elements, at most 512 of them in a chunk; not while `stream` is captured into a graph) or two, and returns.
  *   grad_arena       device: n_chunks gradient chunks of chunk_elems 16-bit words each, back to back
  *                    (chunk c starts at element c * chunk_elems); 16-byte aligned; read only
  *   dtype            PT_BF16 or PT_FP16 (how the words decode)
@@ -299,8 +300,10 @@ int pt_chunk_grad_sqnorm(pt_ctx* ctx, const void* const* grad_chunks, uint32_t f
  * are multiples of 32768: the LLaMA-7B and -13B states fit); beyond that PT_ERR_UNSUPPORTED, nothing is
  * launched.  Errors have no context: their text is pt_last_error(NULL) of the calling thread.
  * All calls on one GPU share the one scratch array: calls that overlap in time on one GPU (two
- * streams, two threads) race; order them.  The array keeps the last call's contents; every launch
- * overwrites all the entries the next launch reads, so nothing needs clearing.  The array's device
+ * streams, two threads, a graph's replay) race; order them.  The array keeps the last call's contents; every
+ * launch overwrites all the sums the next launch reads.  The counters that blocks count themselves in on are left
+ * at zero; calls that raced may leave something else, which two kernels clear before they use it and one kernel does
+ * not: of the sixteen sets it uses in turn, every call clears the one that comes eight calls later.  The array's device
  * address is looked up once per device (hipGetSymbolAddress), by pt_ctx_create or by the first call
  * of this function on that device - make that first call outside a graph capture. */
 int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, uint64_t chunk_elems, uint32_t n_chunks,
@@ -397,7 +400,13 @@ int pt_chunk_host_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t first_c
 /* Closes the step: makes `stream` wait for the side streams of a streamed update,
  * then on the device: found_inf ? (loss_scale = max(loss_scale*backoff, 1),
  * good_steps = 0) : (step += 1, good_steps += 1, and loss_scale *= growth when
- * good_steps reaches growth_interval).  Without a scaler only the counter moves. */
+ * good_steps reaches growth_interval).  Without a scaler only the counter moves.
+ * Where nothing stands against it this has happened already, in the launch that derived the constants for the
+ * step's first update, and the call launches nothing: the read-backs below show the step as open until this call,
+ * and a call of the same step that depends on the counter, the loss scale or found_inf (pack, accumulate with
+ * take_norm, norm, override, set_state, an update with other hyper-parameters) takes it back first.  A context in
+ * which that has happened, or in which a call that uses these scalars has been captured into a graph, ends its later
+ * steps in a kernel that this call launches.  A capture may begin at any point of a step. */
 int pt_step_end(pt_ctx* ctx, void* stream);
 
 /* ---- read-back (these synchronise `stream`) ----------------------------------------- */

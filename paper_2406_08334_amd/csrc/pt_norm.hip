@@ -14,8 +14,8 @@
 // waits.  8.4e6 words 9.3 us with four loads, 8.8 with sixteen (from there on down the host's two launches were the limit; without a
 // context it is one launch now, 6.9 us), 3.3e7
 // 15.9 and 15.3; 1e8 34.8 and 41.7.  Large arenas are read fastest with few bytes in flight: two loads a lane, and unused LDS that
-// leaves four workgroups on a compute unit instead of eight.  8.1e8 words 233 us (7.2 TB/s with the scalar kernel's 5 us), with
-// four loads 239, one load 291, two loads and no limit 241, six workgroups 237, three 245; 2.5e8 77.0 / 78.5 / 96.3 / 79.2 / 77.9 /
+// leaves four workgroups on a compute unit instead of eight.  8.1e8 words 233 us (6.9 TB/s; 7.05 without the scalar kernel's 5 us),
+// with four loads 239, one load 291, two loads and no limit 241, six workgroups 237, three 245; 2.5e8 77.0 / 78.5 / 96.3 / 79.2 / 77.9 /
 // 81.4.  The line is where a second set of 1024 workgroups is three quarters full: below it eight at once are faster or
 // it makes no difference (4.5e7 fp16 words 19.7 us either way, 6e7 23.7 with the limit and 25.3 without).  In between four loads
 // are as good as two or better (6e7 23.65, 1e8 34.8 against 35.1).  fp32 chunks are twice the bytes for as many
@@ -690,7 +690,7 @@ extern "C" int pt_chunk_grad_sqnorm_noalloc(const void* grad_arena, int dtype, u
   // Nothing here has to start at zero: each launch writes every partial and per-chunk slot that the
   // next one reads (n_chunks * blocks_per_chunk partials, n_chunks sums), so stale contents of an
   // earlier, larger call are never read.
-  // Not under capture: a replay would use the same counter every time, and clear another one.  A count that calls which overlapped
+  // Never under capture: a replay would use the same counter every time, and clear another one.  A count that calls which overlapped
   // have left in it would stay, and no workgroup of a later replay would be the last.  Two launches clear theirs themselves.
   const bool one = norm_in_one(blocks_per_chunk, n_chunks) && !pt_is_capturing(st);
   static std::atomic<uint32_t> calls[PT_STATIC_MAX_DEVICES];       // so far, a number each: every device has its own counters

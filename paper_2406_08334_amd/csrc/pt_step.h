@@ -62,8 +62,9 @@ PT_STEP_FN void pt_advance(PtDevState& s, bool found_inf) {
 }
 
 // The update reads nothing but the constants and `skip`, so the step can end here, without a launch of its own behind the update
-// (4.8 us; pt_step_end then launches nothing).  What changes is kept: a call of the same step that depends on it takes the
-// end back first (pt_reopen_step).  s: the state this step began with.
+// (4.8 us; pt_step_end then launches nothing; a step of 0.8 M parameters 22.3 -> 18.7 us, of 7 M 54.0 -> 52.5).  What changes is kept: a call
+// of the same step that depends on it takes the end back first (pt_reopen_step).  Contexts with graphs, and those whose steps
+// go on behind an update, end in the kernel (pt_prepare_consts).  s: the state this step began with.
 PT_STEP_FN void pt_end_early(PtDevState* st, PtDevState s, bool found_inf, uint32_t step_no) {
   st->old_step = s.step; st->old_good_steps = s.good_steps; st->old_override = s.override_active; st->old_loss_scale = s.loss_scale;
   pt_advance(s, found_inf);

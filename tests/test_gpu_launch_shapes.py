@@ -46,8 +46,8 @@ def test_update_in_its_default_shape(orc, dtype, S, C, grid, masked):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("masked", [False, True])
 def test_hints_by_the_size_of_the_gradient_chunks_change_no_bit(orc, dtype, masked):
-    """A context whose 16-bit gradient chunks exceed the 256 MB Infinity Cache packs and updates with non-temporal hints on
-    the gradients too.  Only three of its chunks exist here: their bits are the oracle's."""
+    """A context whose 16-bit gradient chunks exceed the 256 MB Infinity Cache, of which pack stores the first 240 MB without
+    non-temporal hints.  Only three of its chunks exist here: their bits are the oracle's."""
     S, n = 4096 * 3 + 40, 3
     C = (256 << 20) // (2 * S) + 1
     small = ChunkedState([S * n - 5], S, dtype=dtype)
