@@ -1,5 +1,5 @@
-"""The first 240 MB of a context's gradient chunks are stored by pack and loaded by accumulate without non-temporal hints.  That
-changes no bit: tensors that are cut by that line, aligned and not, and chunks before, on and behind it."""
+"""The first 240 MB of a context's gradient chunks are stored by pack and, from 100 MB of sums on, loaded by accumulate without
+non-temporal hints.  That changes no bit: tensors that are cut by that line, aligned and not, and chunks before, on and behind it."""
 import pytest
 import torch
 

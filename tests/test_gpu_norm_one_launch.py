@@ -47,7 +47,8 @@ def test_same_bits_as_two_launches(per, chunks):
 
 
 def test_call_after_call_of_other_sizes():
-    """More calls than there are counters, sizes of one and of two launches in turn, on the current and on another stream, and replayed."""
+    """More calls than there are counters, sizes of one and of two launches in turn, on the current and on another stream; and a call captured
+    (two launches) and replayed among them."""
     gen = torch.Generator(device="cuda").manual_seed(1)
     sizes = [(8, 1), (BLOCK * 3, 5), (BLOCK * 600, 1), (BLOCK * 100 + 8, 2)]
     gs = [torch.empty(C, S, device="cuda").normal_(0.0, 1.0, generator=gen).bfloat16() for S, C in sizes]
