@@ -48,6 +48,8 @@
  *    All other per-chunk sums are enqueued by the call that packs, accumulates or recomputes, so that
  *    a graph of norm, update and step end may be captured without it and replayed behind it.
  *    With a small plan the graph holds the pack too, and the plan outlives the graph.
+ *    An update of all chunks takes what is left of that along in its own launch, where nothing but it depends on the
+ *    result (contexts that have never been captured, of 2^16 elements or more and 256 chunks at most).
  *  - A context is not thread-safe; use one per optimizer instance.
  */
 #ifndef PTCHUNK_H
@@ -155,6 +157,8 @@ int pt_ctx_set_no_decay(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs);
  *                   stream pairs (0..5) whatever it measures, so that the replacement runs
  *   "stream_test_unhealthy"  for tests: 1 = the next look at a finished streamed step through the chunk buffers finds
  *                   it serialised whatever it measured, so that the replacement of the side streams runs
+ *   "update_test_tries"  for tests: looks (0..8192, the default) that the workgroups of an update that derives its constants
+ *                   itself take for what others of them publish, before each does that work alone
  *   "stream_in_place"  pt_chunk_stream_step updates host arrays in place over the link: 1 = where it can (default),
  *                   0 = never, 2 = PT_ERR_UNSUPPORTED where it cannot
  * Gradient storage (variants of the path; the paper's gradients are the 16-bit array):

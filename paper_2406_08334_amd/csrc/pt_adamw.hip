@@ -10,6 +10,7 @@
 // Arithmetic: the fp32 operation sequence below with correctly rounded *, fma,
 // sqrt and / (this file is compiled with contraction off and without fast-math).
 #include "pt_common.h"
+#include "pt_scalars.h"
 
 #include <hip/hip_fp16.h>
 
@@ -163,30 +164,42 @@ __device__ __forceinline__ ChunkPtrs<GF32> chunk_ptrs(uint64_t g, uint64_t w, ui
           uint32_t(w >> 4) & (LINE_UNITS - 1)};
 }
 
-// Tile `tile` of a chunk.  NT: hints on the state; NTG: and on the gradient loads (host memory only: pt_adamw_hints).  c: the chunk's
-// index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
-template <int TH, int DT, int UNROLL, bool NT, bool NTG, bool MASKED, bool GF32>
-__device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
-                                            uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
-                                            const uint64_t* __restrict__ nd_ranges) {
-  typedef typename GradUnit<GF32>::vec gvec;
+// The units of a tile in a lane's registers, if the tile is a whole one.
+template <int UNROLL, bool GF32>
+struct Tile {
+  uint64_t ub;              // first unit; "negative" (wrapped around, above the chunk's units) for the idle lanes of the first tile
+  bool full;
+  typename GradUnit<GF32>::vec g[UNROLL];
+  f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
+};
+
+// Loads tile `tile` of a chunk.  NT: hints on the state; NTG: and on the gradient loads (host memory only: pt_adamw_hints).
+template <int TH, int UNROLL, bool NT, bool NTG, bool GF32>
+__device__ __forceinline__ void load_tile(Tile<UNROLL, GF32>& t, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units) {
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
-  const gvec gzero = {};
-  // first unit of the tile; "negative" (wrapped around, above `units`) for the idle lanes of the first tile
-  const uint64_t ub = tile * TILE_UNITS - x.back;
-  const bool full = ub < units && units - ub >= TILE_UNITS;
-  gvec g[UNROLL]; f32x4 w[UNROLL], m[UNROLL], v[UNROLL];
-  if (full) {
+  t.ub = tile * TILE_UNITS - x.back;
+  t.full = t.ub < units && units - t.ub >= TILE_UNITS;
+  if (t.full) {
 #pragma unroll
     for (int r = 0; r < UNROLL; ++r) {
       const uint32_t o = threadIdx.x + uint32_t(r) * TH;
-      g[r] = ld_stream<NTG>(x.g + ub + o);
-      w[r] = ld_stream<NT>(x.w + ub + o);
-      m[r] = ld_stream<NT>(x.m + ub + o);
-      v[r] = ld_stream<NT>(x.v + ub + o);
+      t.g[r] = ld_stream<NTG>(x.g + t.ub + o);
+      t.w[r] = ld_stream<NT>(x.w + t.ub + o);
+      t.m[r] = ld_stream<NT>(x.m + t.ub + o);
+      t.v[r] = ld_stream<NT>(x.v + t.ub + o);
     }
   }
-  asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind the branch
+  asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind a branch on the step's scalars
+}
+
+// Updates a tile that has been loaded.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32, class P32, class P64>
+__device__ __forceinline__ void finish_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, Tile<UNROLL, GF32>& t, uint64_t units,
+                                            uint32_t c, int recast_on_skip, int zero_grads, P32 nd_begin, P64 nd_ranges) {
+  typedef typename GradUnit<GF32>::vec gvec;
+  constexpr uint32_t TILE_UNITS = TH * UNROLL;
+  const gvec gzero = {};
+  const uint64_t ub = t.ub;
   if (skip) {
     for (int r = 0; r < UNROLL; ++r) {
       const uint64_t u = ub + (threadIdx.x + uint32_t(r) * TH);
@@ -219,16 +232,16 @@ __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const
       else cut = true;
     }
   }
-  if (full && !(MASKED && cut)) {
+  if (t.full && !(MASKED && cut)) {
     const float dk[4] = {dtile, dtile, dtile, dtile};
 #pragma unroll
     for (int r = 0; r < UNROLL; ++r) {
       const uint32_t o = threadIdx.x + uint32_t(r) * TH;
       u32x2 p;
-      update_unit<DT, GF32>(k, dk, g[r], w[r], m[r], v[r], p);
-      st_stream<NT>(w[r], x.w + ub + o);
-      st_stream<NT>(m[r], x.m + ub + o);
-      st_stream<NT>(v[r], x.v + ub + o);
+      update_unit<DT, GF32>(k, dk, t.g[r], t.w[r], t.m[r], t.v[r], p);
+      st_stream<NT>(t.w[r], x.w + ub + o);
+      st_stream<NT>(t.m[r], x.m + ub + o);
+      st_stream<NT>(t.v[r], x.v + ub + o);
       st_stream<NT>(p, x.p + ub + o);
       if (zero_grads) st_stream<NT>(gzero, x.g + ub + o);
     }
@@ -254,6 +267,15 @@ __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const
   }
 }
 
+template <int TH, int DT, int UNROLL, bool NT, bool NTG, bool MASKED, bool GF32>
+__device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, uint64_t tile, uint64_t units,
+                                            uint32_t c, int recast_on_skip, int zero_grads, const uint32_t* __restrict__ nd_begin,
+                                            const uint64_t* __restrict__ nd_ranges) {
+  Tile<UNROLL, GF32> t;
+  load_tile<TH, UNROLL, NT, NTG, GF32>(t, x, tile, units);
+  finish_tile<TH, DT, UNROLL, NT, MASKED, GF32>(k, skip, x, t, units, c, recast_on_skip, zero_grads, nd_begin, nd_ranges);
+}
+
 __device__ __forceinline__ Consts load_consts(const PtDevState* __restrict__ st) {
   Consts k;
   k.b1 = st->c[0]; k.b2 = st->c[1]; k.omb1 = st->c[2]; k.omb2 = st->c[3]; k.decay = st->c[4];
@@ -277,6 +299,271 @@ k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, u
       update_tile<TH, DT, UNROLL, NT, false, MASKED, GF32>(k, skip, x, tile, units, mask_chunk0 + ci, recast_on_skip, zero_grads, nd_begin,
                                                   nd_ranges);
   }
+}
+
+// ---- the update that derives its own constants ---------------------------------------------------
+//
+// The update of every chunk of a context, with the step's scalar work (the sums of a small plan, the norm, the constants, the end of
+// the step) done by its first workgroups while the others have their first loads under way: one launch instead of two.
+//
+// What workgroups hand each other goes past the caches word by word, each next to the number of the launch in one 8-byte store: whoever
+// reads the number has the word, without an order between stores.  The first workgroup publishes the constants, FUSED_COPIES times, so
+// that the 2800 waves that run by then do not all ask one line.  Those ask until they have all words; the workgroups behind the first FUSED_EARLY
+// start after others have finished, hence after the words were published, and read them through the scalar cache (were they to find
+// older ones, they would ask like the others).
+//
+// What it costs is latency, from the start of the kernel: state and constants that need no norm 1.3 us (the powers of beta 0.9 of it, while the
+// sums are on their way), trees published 1.8 to 2.6, all sums 3.8, the words published 4.7 and seen 4.8 to 5.1; with sums that are there already
+// seen at 3.5.  The first tiles have arrived at 0.7 to 1.5, so 2 to 3.5 us of the launch of 4.7 that it replaces stay, but the memory is
+// busy from the first microsecond.  One wave that takes all trees of 3500 sums by itself is slower (the 7 M step 51.0 us instead of 48.2): that
+// code runs once, so what counts is how much of it has to be fetched.  A step, with the scalar kernel in front and without: 0.8 M
+// parameters 19.6 and 16.0 us, 3 M 31.6 and 29.9, 7 M 50.2 and 48.2, 1e7 81.3 and 79.1, 2.8e7 149 and 147, 4.5e7 231 and 225, 6.8e7
+// 362 and 354, 1.24e8 615 and 605, 2e8 1062 and 1053.
+//
+// No wait is without an end and none depends on the order in which workgroups start: after `tries` looks, some milliseconds, a wave
+// derives the constants by itself.  The state it needs is written by the first workgroup only when the published words have arrived; so if they
+// are still not there when the state has been read, what was read is the state before the step's end.
+constexpr uint32_t FUSED_EARLY = 4096;
+
+__device__ __forceinline__ double readlane_f64(double x, uint32_t lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+#define PT_SCALAR __attribute__((address_space(4)))      // loaded through the scalar cache
+
+// What the kernel is called with.  The first workgroup alone reads `work`, from where the arguments lie (fused_work): as an ordinary argument it
+// would be loaded by every wave.
+struct FusedArgs {
+  const PT_SCALAR uint64_t* table;
+  uint32_t table_cols, no;
+  uint64_t units;
+  const PT_SCALAR uint32_t* nd_begin;
+  const PT_SCALAR uint64_t* nd_ranges;
+  const uint64_t* pub;
+  int zero_grads;
+  uint32_t summers;
+  PtFused work;
+};
+
+__device__ __forceinline__ const PT_SCALAR PtFused& fused_work() {
+  const PT_SCALAR FusedArgs* a = (const PT_SCALAR FusedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));                    // loads are not moved in front of this
+  return a->work;
+}
+
+// What the scalar work of a step leaves: the word of the lane (0-8: the constants, 9: skip), and what goes into the state.
+struct Derived { uint32_t word; double sq, norm, clip, chunk; bool inf, has; };
+
+// The tree `tree` of units 2 * pair and 2 * pair + 1, in lanes 0 to 31 and 32 to 63: in the order of the scalar kernel a lane's partial sums 512
+// apart, then the tree over the 64 lanes.
+struct Pair { double x[2][PT_REDUCE_SEG / PT_FUSED_ROW]; };
+__device__ __forceinline__ void load_pair(Pair& p, const PT_SCALAR PtFused& a, uint32_t pair, uint32_t tree) {
+#pragma unroll
+  for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+    for (uint32_t j = 0; j < PT_REDUCE_SEG / PT_FUSED_ROW; ++j) {
+      // in bounds: no row begins behind the unit's sums, and a plan's have PT_FUSED_ROW more behind them
+      const uint32_t row = a.lo[2 * pair + u] + j * PT_FUSED_ROW;
+      p.x[u][j] = ((const PT_GLOBAL double*)a.part + (row < a.hi[2 * pair + u] ? row : 0))[tree * 64 + threadIdx.x];
+    }
+}
+__device__ __forceinline__ double sum_pair(const Pair& p, const PT_SCALAR PtFused& a, uint32_t pair, uint32_t tree) {
+  const uint32_t lane = threadIdx.x;
+  double y[2] = {};
+#pragma unroll
+  for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+    for (uint32_t j = 0; j < PT_REDUCE_SEG / PT_FUSED_ROW; ++j)
+      y[u] += a.lo[2 * pair + u] + j * PT_FUSED_ROW + tree * 64 + lane < a.hi[2 * pair + u] ? p.x[u][j] : 0.0;
+  const double keep = lane < 32 ? y[0] : y[1], send = lane < 32 ? y[1] : y[0];
+  double t = keep + __shfl_xor(send, 32, 64);
+#pragma unroll
+  for (uint32_t off = 16; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  return t;
+}
+
+// A tree's sum as it is published: two words.
+__device__ __forceinline__ uint64_t* tree_words(const PT_SCALAR PtFused& a, uint32_t unit, uint32_t tree) {
+  return a.pub + FUSED_COPIES * FUSED_LINE + (size_t(unit) * FUSED_TREES + tree) * 2;
+}
+__device__ __forceinline__ void publish_pair(const PT_SCALAR PtFused& a, uint32_t pair, uint32_t tree, double t) {
+  const uint32_t half = threadIdx.x & 31;
+  if (half < 2) st_agent(tree_words(a, 2 * pair + (threadIdx.x >> 5), tree) + half,
+                         uint64_t(a.no) << 32 | uint32_t(half ? __double2hiint(t) : __double2loint(t)));
+}
+
+// ALONE: takes every tree itself instead of waiting for the workgroups that do.  Lane u has the sum of unit u.
+template <bool ALONE>
+__device__ __forceinline__ Derived derive(const PT_SCALAR PtFused& a) {
+  const uint32_t lane = threadIdx.x;
+  const int32_t step = ld_agent(&a.st->step);
+  const double loss_scale = ld_agent(&a.st->loss_scale);
+  double t = 0.0, acc = 0.0;
+  uint32_t g = 0;
+  if (lane < a.C) { t = ld_agent(a.chunk_sq + lane); g = ld_agent(a.chunk_flag + lane); }
+  // what depends on the step counter alone, while the sums are on their way
+  const double bc = 1.0 - pow(lane == 1 ? a.hp.beta2 : a.hp.beta1, double(step + 1));
+  const pt_hparams hp = {a.hp.lr, a.hp.beta1, a.hp.beta2, a.hp.eps, a.hp.weight_decay, a.hp.max_norm};
+  float c[9];
+  pt_step_consts(c, hp, readlane_f64(bc, 0), readlane_f64(bc, 1));
+  Derived d{};
+  if (a.units) {
+    // the units of chunk first + i, if that is the lane's
+    uint32_t at = 0, begin = 0, count = 0, most = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < FUSED_CHUNKS; ++i) {
+      const uint32_t n = a.chunk_units[i];
+      if (lane == a.first + i && i < a.n) { begin = at; count = n; }
+      at += n;
+      most = max(most, n);
+    }
+    const uint32_t unit = min(lane, a.units - 1);
+    uint64_t lo[FUSED_TREES], hi[FUSED_TREES];
+    bool alone = ALONE;
+    for (uint32_t tries = ALONE ? 0 : a.tries;; --tries) {
+      if (tries == 0) { alone = true; break; }
+      bool all = true;
+#pragma unroll
+      for (uint32_t k = 0; k < FUSED_TREES; ++k) { lo[k] = ld_agent(tree_words(a, unit, k)); hi[k] = ld_agent(tree_words(a, unit, k) + 1); }
+#pragma unroll
+      for (uint32_t k = 0; k < FUSED_TREES; ++k)
+        all = all && (k >= a.trees || (uint32_t(lo[k] >> 32) == a.no && uint32_t(hi[k] >> 32) == a.no));
+      if (__all(all)) break;
+    }
+    if (!alone) {
+#pragma unroll
+      for (uint32_t k = 0; k < FUSED_TREES; ++k)
+        acc = k < a.trees ? acc + __hiloint2double(uint32_t(hi[k]), uint32_t(lo[k])) : acc;
+    } else {
+      for (uint32_t p = 0; 2 * p < a.units; ++p) {
+        double s = 0.0;
+        for (uint32_t k = 0; k < a.trees; ++k) {
+          Pair x;
+          load_pair(x, a, p, k);
+          s += sum_pair(x, a, p, k);
+        }
+        const double s0 = readlane_f64(s, 0), s1 = readlane_f64(s, 32);
+        acc = lane == 2 * p ? s0 : lane == 2 * p + 1 ? s1 : acc;
+      }
+    }
+    double mine = 0.0;
+    for (uint32_t k = 0; k < most; ++k) {
+      const double x = __shfl(acc, (begin + k) & 63, 64);
+      if (k < count) mine += x;
+    }
+    d.has = count != 0;
+    if (d.has) { t = mine; g = pt_not_finite(mine); }
+  }
+  d.chunk = t;
+  bool inf = __any(g != 0);
+  for (uint32_t k = 0; k < min(a.C, 64u); ++k) d.sq += readlane_f64(t, k);
+  for (uint32_t base = 64; base < a.C; base += 64) {
+    t = 0.0; g = 0;
+    if (base + lane < a.C) { t = ld_agent(a.chunk_sq + base + lane); g = ld_agent(a.chunk_flag + base + lane); }
+    inf = inf || __any(g != 0);
+    for (uint32_t k = 0; k < min(a.C - base, 64u); ++k) d.sq += readlane_f64(t, k);
+  }
+  d.inf = inf;
+  d.norm = sqrt(d.sq);
+  c[8] = pt_grad_mult(d.clip, hp.max_norm, d.norm, loss_scale);
+  const uint32_t w = lane & 15;
+  d.word = inf ? 1u : 0u;
+#pragma unroll
+  for (uint32_t k = 0; k < 9; ++k) d.word = w == k ? __float_as_uint(c[k]) : d.word;
+  return d;
+}
+
+__device__ __forceinline__ void publish(const PT_SCALAR PtFused& a, uint32_t word) {
+  const uint32_t lane = threadIdx.x;
+  if ((lane & 15) > 9) return;
+#pragma unroll
+  for (uint32_t k = 0; k < FUSED_COPIES; k += 4)
+    st_agent(a.pub + size_t(k + (lane >> 4)) * FUSED_LINE + (lane & 15), uint64_t(a.no) << 32 | word);
+}
+
+// The published word of each lane, if all of them are there within `tries` looks.
+__device__ __forceinline__ bool published(const uint64_t* pub, uint32_t no, uint32_t copy, uint32_t tries, uint32_t& word) {
+  const uint64_t* p = pub + size_t(copy) * FUSED_LINE + min(threadIdx.x & 15, 9u);
+  for (; tries > 0; --tries) {
+    const uint64_t x = ld_agent(p);
+    if (__all(uint32_t(x >> 32) == no)) { word = uint32_t(x); return true; }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return false;
+}
+
+// What the scalar kernel writes besides the constants, with the published words arrived (see above).
+__device__ __forceinline__ void write_state(const PT_SCALAR PtFused& a, const Derived& d) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const uint32_t lane = threadIdx.x;
+  if (d.has) { a.chunk_sq[lane] = d.chunk; a.chunk_flag[lane] = pt_not_finite(d.chunk); }
+  if (lane < 9) a.st->c[lane] = __uint_as_float(d.word);
+  if (lane != 0) return;
+  PtDevState s = *a.st;
+  s.override_active = 0;
+  a.st->sqnorm = d.sq; a.st->norm = d.norm; a.st->clip_coef = d.clip;
+  a.st->found_inf = d.inf; a.st->skip = d.inf; a.st->override_active = 0;
+  pt_end_early(a.st, s, d.inf, a.end_step);
+}
+
+template <bool GF32>
+__device__ __forceinline__ ChunkPtrs<GF32> fused_ptrs(const PT_SCALAR uint64_t* table, uint32_t table_cols) {
+  asm volatile("" : "+s"(table));                // not moved in front of what comes before
+  const PT_SCALAR uint64_t* t = table + blockIdx.y;
+  return chunk_ptrs<GF32>(t[size_t(ROW_GRAD) * table_cols], t[size_t(ROW_MASTER) * table_cols], t[size_t(ROW_M) * table_cols],
+                          t[size_t(ROW_V) * table_cols], t[size_t(ROW_P16) * table_cols]);
+}
+
+template <int DT, bool MASKED, bool GF32>
+__global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
+  const bool first = (blockIdx.x | blockIdx.y) == 0;
+  const uint32_t copy = blockIdx.x % FUSED_COPIES;
+  Derived d;
+  uint32_t mine = 0, word[10];                   // word: the same in every lane
+  if (__builtin_expect(blockIdx.y == 0 && blockIdx.x <= a.summers, 0)) {
+    const PT_SCALAR PtFused& work = fused_work();
+    if (first) {
+      d = derive<false>(work);
+      mine = d.word;
+      publish(work, mine);
+    } else {
+      const uint32_t pair = (blockIdx.x - 1) / work.trees, tree = (blockIdx.x - 1) % work.trees;
+      Pair p;
+      load_pair(p, work, pair, tree);
+      publish_pair(work, pair, tree, sum_pair(p, work, pair, tree));
+    }
+  }
+  Tile<1, GF32> tile;
+  ChunkPtrs<GF32> x = fused_ptrs<GF32>(a.table, a.table_cols);
+  load_tile<64, 1, true, false, GF32>(tile, x, blockIdx.x, a.units);
+  bool known = false;
+  if (!(blockIdx.y == 0 && blockIdx.x < FUSED_EARLY)) {
+    const PT_SCALAR uint64_t* w = (const PT_SCALAR uint64_t*)a.pub + copy * FUSED_LINE;
+    asm volatile("" : "+s"(w));                  // behind the tile's loads, whose latency hides this one's
+    known = true;
+#pragma unroll
+    for (uint32_t k = 0; k < 10; ++k) {
+      const uint64_t q = w[k];
+      word[k] = uint32_t(q);
+      known = known && uint32_t(q >> 32) == a.no;
+    }
+  }
+  if (!known) {
+    if (!first && __builtin_expect(!published(a.pub, a.no, copy, fused_work().tries, mine), 0)) {
+      mine = derive<true>(fused_work()).word;
+      published(a.pub, a.no, copy, 1, mine);
+      x = fused_ptrs<GF32>(a.table, a.table_cols);         // again: nothing is held meanwhile
+      load_tile<64, 1, true, false, GF32>(tile, x, blockIdx.x, a.units);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 10; ++k) word[k] = __builtin_amdgcn_readlane(mine, k);
+  }
+  float c[9];
+#pragma unroll
+  for (uint32_t k = 0; k < 9; ++k) c[k] = __uint_as_float(word[k]);
+  const Consts k = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8]};
+  finish_tile<64, DT, 1, true, MASKED, GF32>(k, int32_t(word[9]), x, tile, a.units, blockIdx.y, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
+  if (__builtin_expect(first, 0)) write_state(fused_work(), d);
 }
 
 // The update of chunks in pinned host memory, in place over the link: the kernel itself reads gradient, master, momentum
@@ -405,6 +692,13 @@ adamw_kernel_t pick_kernel(const PtAdamwShape& s, bool nt, bool masked, bool gf3
   return nt ? pick_flags<DT, true>(s, masked, gf32) : pick_flags<DT, false>(s, masked, gf32);
 }
 
+typedef void (*fused_kernel_t)(FusedArgs);
+template <int DT>
+fused_kernel_t pick_fused(bool masked, bool gf32) {
+  if (gf32) return masked ? k_adamw_fused<DT, true, true> : k_adamw_fused<DT, false, true>;
+  return masked ? k_adamw_fused<DT, true, false> : k_adamw_fused<DT, false, false>;
+}
+
 template <int TH, int DT, bool NT>
 pattern_kernel_t pattern_by_unroll(uint32_t u) {
   return u == 1 ? k_adamw_pattern<TH, DT, 1, NT> : u == 2 ? k_adamw_pattern<TH, DT, 2, NT>
@@ -439,13 +733,19 @@ Geometry geometry(const pt_ctx* ctx, const PtAdamwShape& s, uint32_t n_cols) {
   return g;
 }
 
+// Whether an update of all chunks in the library's shape has a workgroup for every tile.
+bool one_tile_each(const pt_ctx* ctx) {
+  const Geometry g = geometry(ctx, pt_adamw_shape(ctx, ctx->C), ctx->C);
+  return g.grid.x == g.tiles && g.grid.y == ctx->C;
+}
+
 // Launches of more than 2^31 tiles of 8192 elements are refused (no memory holds them).
 bool too_many_tiles(const pt_ctx* ctx, uint32_t n_cols) { return (ctx->S / 8192 + 1) * n_cols > 0x7fffffffull; }
 
 }  // namespace
 
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
-                    uint32_t mask_chunk0, bool zero_grads) {
+                    uint32_t mask_chunk0, bool zero_grads, const PtFused* fused) {
   if (n_cols == 0) return PT_OK;
   if (too_many_tiles(ctx, n_cols))
     return pt_fail(ctx, PT_ERR_UNSUPPORTED, "update launch of %u chunks exceeds 2^31 tiles", n_cols);
@@ -453,6 +753,14 @@ int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_
   const Geometry geo = geometry(ctx, shape, n_cols);
   const bool hints = pt_adamw_hints(ctx);
   const bool masked = ctx->d_nd_begin != nullptr;
+  if (fused) {
+    fused_kernel_t kern = ctx->dtype == PT_BF16 ? pick_fused<PT_BF16>(masked, ctx->grad_f32) : pick_fused<PT_FP16>(masked, ctx->grad_f32);
+    const FusedArgs args{(const PT_SCALAR uint64_t*)ctx->d_table, ctx->table_cols, fused->no, ctx->S / 4, (const PT_SCALAR uint32_t*)ctx->d_nd_begin,
+                         (const PT_SCALAR uint64_t*)ctx->d_nd_ranges, fused->pub, zero_grads ? 1 : 0, pt_fused_summers(*fused), *fused};
+    hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, args);
+    PT_LAUNCH_CHECK(ctx, "k_adamw_fused");
+    return PT_OK;
+  }
   adamw_kernel_t kern = ctx->dtype == PT_BF16 ? pick_kernel<PT_BF16>(shape, hints, masked, ctx->grad_f32)
                                               : pick_kernel<PT_FP16>(shape, hints, masked, ctx->grad_f32);
   hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, ctx->d_table, ctx->d_state, ctx->table_cols,
@@ -500,6 +808,11 @@ extern "C" int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t f
   const PtBind binds[5] = {{ROW_GRAD, grad}, {ROW_MASTER, (const void* const*)master}, {ROW_M, (const void* const*)m},
                            {ROW_V, (const void* const*)v}, {ROW_P16, (const void* const*)param16}};
   if ((rc = pt_table_bind(ctx, binds, 5, first_chunk, n_chunks, false, st)) != PT_OK) return rc;
+  PtFused fused;
+  if (n_chunks == ctx->C && one_tile_each(ctx) && pt_fuse_scalars(ctx, hp, &fused)) {
+    if ((rc = pt_launch_adamw(ctx, 0, n_chunks, st, false, 0, ctx->opt_zero_grads != 0, &fused)) == PT_OK) pt_fused_launched(ctx, fused);
+    return rc;
+  }
   if ((rc = pt_prepare_consts(ctx, hp, n_chunks < ctx->C, st)) != PT_OK) return rc;
   return pt_launch_adamw(ctx, first_chunk, n_chunks, st, false, first_chunk, ctx->opt_zero_grads != 0);
 }

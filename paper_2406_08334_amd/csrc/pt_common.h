@@ -63,10 +63,12 @@ struct pt_pack_plan {
   uint64_t total_elems = 0;
   uint64_t id = 0;                         // never reused within a context (a destroyed plan's address may be)
   std::vector<uint32_t> touched;           // chunks that own at least one tile
+  std::vector<uint32_t> tile_begin;        // d_chunk_tile_begin from the first to behind the last touched chunk
 };
 
 namespace pt_host { class Pool; }
 
+constexpr uint32_t PT_FUSED_ROW = 512;            // partial sums an update that derives its constants loads from a row's start on
 constexpr uint32_t PT_REDUCE_SEG = 4096;         // partial sums one workgroup adds up, eight per lane
 inline uint32_t pt_segs(uint64_t partials) { return uint32_t(partials ? (partials + PT_REDUCE_SEG - 1) / PT_REDUCE_SEG : 1); }
 
@@ -86,6 +88,7 @@ struct pt_ctx {
   uint32_t opt_in_place = 1;        // streamed update in place: 0 never, 1 where it can be, 2 or not at all
   bool scaler = false;
   bool grad_f32 = false;            // gradient chunks hold fp32 (accumulated micro-batches), option "grad_fp32"
+  uint32_t opt_fused_tries = 1u << 13;  // looks of an update's waves for the constants that its first workgroup publishes
   uint32_t opt_zero_grads = 0;      // pt_chunk_adamw_step zeroes the gradient chunks it has read
 
   PtDevState* d_state = nullptr;
@@ -98,6 +101,9 @@ struct pt_ctx {
   uint32_t norm_segs = 1;               // reduction workgroups per chunk of a recompute
   double* d_norm_seg_sum = nullptr;     // [C * norm_segs], if norm_segs > 1
   uint32_t* d_norm_seg_flag = nullptr;
+
+  uint64_t* d_pub = nullptr;            // constants published by an update that derives them itself (pt_scalars.h)
+  uint32_t pub_no = 0;                  // such launches so far; never 0 once there was one
 
   // host-side step bookkeeping
   std::vector<uint64_t> chunk_packed_by;   // [C] id of the pack plan whose partial sum is the chunk's value in this step, 0 = none
@@ -292,8 +298,10 @@ inline uint64_t pt_cached_elems(const pt_ctx* ctx) {
 }
 // Whether element `off` of chunk `chunk` (of S elements each) is one of the first `cached`.
 __device__ __forceinline__ bool pt_in_cache(uint32_t chunk, uint64_t S, uint64_t off, uint64_t cached) { return chunk * S + off < cached; }
+struct PtFused;
+// fused: the step's scalar work that the update of all chunks takes along (pt_fuse_scalars), or NULL.
 int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_t stream, bool recast_on_skip,
-                    uint32_t mask_chunk0, bool zero_grads);
+                    uint32_t mask_chunk0, bool zero_grads, const PtFused* fused = nullptr);
 // The update of n chunks in pinned host memory, in place (at[i]: gradient, master, m, v, param16 of chunk i as device
 // addresses; fp32 arrays 16-byte, 16-bit ones 8-byte aligned).  A skipped step recasts param16.
 int pt_launch_adamw_host(pt_ctx* ctx, const uint64_t (*at)[5], uint32_t n, hipStream_t stream, uint32_t mask_chunk0);
@@ -333,5 +341,9 @@ int pt_before_partials(pt_ctx* ctx, hipStream_t stream);
 // Derives this step's update constants from `hp` if that has not happened yet - in one launch together
 // with any pending reduction and finalize.  host_part: chunks the calling update leaves out may be updated on the host.
 int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStream_t stream);
+// Whether an update of all chunks can take this step's scalar work along in its own launch instead (then *fused holds the work), and what
+// follows once that has been launched.
+bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* fused);
+void pt_fused_launched(pt_ctx* ctx, const PtFused& fused);
 // Makes sure the prepared constants are on their way to h_state, with ev_scalar behind them.
 int pt_mirror_consts(pt_ctx* ctx, hipStream_t stream);

@@ -1,6 +1,6 @@
 // Context, error plumbing, pointer tables, host-side layout builder and the
 // single-thread scalar kernels (state set / override / step end).
-#include "pt_common.h"
+#include "pt_scalars.h"
 
 #include <algorithm>
 
@@ -87,6 +87,7 @@ static void ctx_free_all(pt_ctx* ctx) {
   if (ctx->d_nd_ranges) (void)hipFree(ctx->d_nd_ranges);
   if (ctx->d_state) (void)hipFree(ctx->d_state);
   if (ctx->d_table) (void)hipFree(ctx->d_table);
+  if (ctx->d_pub) (void)hipFree(ctx->d_pub);
   if (ctx->d_chunk_sq) (void)hipFree(ctx->d_chunk_sq);
   if (ctx->d_chunk_flag) (void)hipFree(ctx->d_chunk_flag);
   if (ctx->d_norm_part) (void)hipFree(ctx->d_norm_part);
@@ -105,6 +106,9 @@ static int ctx_alloc(pt_ctx* ctx, const pt_scaler_cfg* sc) {
   ctx->h_table.assign(size_t(N_ROWS) * ctx->table_cols, 0);
   ctx->chunk_fresh.assign(ctx->C, 0);
   ctx->chunk_packed_by.assign(ctx->C, 0);
+  constexpr size_t pub_bytes = FUSED_PUB_WORDS * sizeof(uint64_t);
+  PT_HIP(ctx, hipMalloc(&ctx->d_pub, pub_bytes));
+  PT_HIP(ctx, hipMemset(ctx->d_pub, 0, pub_bytes));
   PT_HIP(ctx, hipMalloc(&ctx->d_chunk_sq, ctx->C * sizeof(double)));
   PT_HIP(ctx, hipMemset(ctx->d_chunk_sq, 0, ctx->C * sizeof(double)));
   PT_HIP(ctx, hipMalloc(&ctx->d_chunk_flag, ctx->C * sizeof(uint32_t)));
@@ -213,6 +217,11 @@ extern "C" int pt_ctx_set_option(pt_ctx* ctx, const char* name, int64_t value) {
   }
   if (std::strcmp(name, "stream_test_unhealthy") == 0) {
     ctx->opt_force_unhealthy = value != 0;
+    return PT_OK;
+  }
+  if (std::strcmp(name, "update_test_tries") == 0) {
+    if (value < 0 || value > (1 << 13)) return pt_fail(ctx, PT_ERR_INVALID_ARG, "update_test_tries must be in [0, 2^13]");
+    ctx->opt_fused_tries = uint32_t(value);
     return PT_OK;
   }
   if (std::strcmp(name, "stream_test_reject") == 0) {

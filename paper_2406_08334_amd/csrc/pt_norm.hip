@@ -22,6 +22,7 @@
 // workgroups and gain from the limit from four full sets on: 6.7e7 words 50.8 us with it and two loads, 47.3 with four loads and
 // without it, 1.3e8 88.6 and 86.7, 4e8 239 and 241.
 #include "pt_common.h"
+#include "pt_scalars.h"
 
 #include <hip/hip_fp16.h>
 
@@ -165,36 +166,16 @@ inline norm_kernel_t pick_norm_f32(int u) { return u == 16 ? k_sqnorm_f32<16> : 
 // finalize and constants: 15 chunks, 1.2e8 elements: 8.8 us in two launches and 5.5 us of a gap behind an event before, 6.8 us
 // in one launch now (a kernel that does nothing takes 4.7 there); 47 chunks, 1.56e9 elements: 14.0 -> 8.8 us; one block's two
 // chunks 6.5 -> 4.4 us.  With fences for the whole L2 instead: 9.5, 17 and 7.6 us.
+static_assert(PT_FUSED_ROW == PT_REDUCE_SEG / 8, "the same order of additions");
 constexpr int SC_SUM = PT_REDUCE_SEG / 8, SC_THREADS = SC_SUM + 128;     // two more waves for the powers
 
-// Values other workgroups of the same launch have written (or will read): past this XCD's caches.
-template <class T> __device__ __forceinline__ T ld_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <class T> __device__ __forceinline__ void st_agent(T* p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// The nine fp32 constants of this update from the fp64 hyper-parameters and the step's device scalars (Adam bias
-// correction with t = applied updates + 1; clip coefficient min(1, c/(norm+1e-6)); unscale by the loss scale).
-// bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
+// Leaves the constants of this update, and whether it is skipped, where the update reads them.
 __device__ __forceinline__ void prepare_body(PtDevState* st, const pt_hparams& hp, double bc1, double bc2, double norm, double loss_scale,
                                              bool override_active, float override_grad_mult, int32_t found_inf, PtDevState* mirror) {
-  double clip = 1.0;
   float c[9];
-  if (override_active) {
-    c[8] = override_grad_mult;
-  } else {
-    if (hp.max_norm > 0.0) {
-      const double q = hp.max_norm / (norm + 1e-6);
-      clip = q < 1.0 ? q : 1.0;
-    }
-    c[8] = float(clip / loss_scale);
-  }
-  c[0] = float(hp.beta1);
-  c[1] = float(hp.beta2);
-  c[2] = float(1.0 - hp.beta1);
-  c[3] = float(1.0 - hp.beta2);
-  c[4] = float(1.0 - hp.lr * hp.weight_decay);
-  c[5] = float(hp.lr / bc1);
-  c[6] = float(1.0 / sqrt(bc2));
-  c[7] = float(hp.eps);
+  double clip = 1.0;
+  pt_step_consts(c, hp, bc1, bc2);
+  c[8] = override_active ? override_grad_mult : pt_grad_mult(clip, hp.max_norm, norm, loss_scale);
   st->clip_coef = clip;
   const int32_t skip = found_inf ? 1 : 0;
 #pragma unroll
@@ -339,6 +320,12 @@ __global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
 
 constexpr uint32_t PT_FUSE_MAX_CHUNKS = 8;
 constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
+// Where an update takes all of this along in its own launch (k_adamw_fused).  More than 256 chunks, which one wave adds up one after the other,
+// would take longer than a launch.  Below 2^16 elements the scalar kernel stays by itself, though a launch less would gain there too (12 700
+// elements 18.4 and 15.0 us a step): nobody trains states of that size, and it is at those that the sequences of a step's launches are played
+// through on the host with that kernel among them.
+constexpr uint32_t PT_FUSED_MAX_CHUNKS = 256;
+constexpr uint64_t PT_FUSED_MIN_ELEMS = 1u << 16;
 
 static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror,
                           hipStream_t stream) {
@@ -417,6 +404,50 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
   ctx->prepared = true;
   ctx->prepared_hp = *hp;
   return PT_OK;
+}
+
+// The update takes the scalar work along where it covers all chunks, a finalize waits, nothing but the update depends on the constants
+// (no host-side update: its event would be behind the whole update), and the step can end with them (pt_prepare_consts).
+bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
+  if (ctx->prepared || !ctx->pend_finalize || ctx->host_pool || ctx->captured || ctx->goes_on || ctx->ended_early) return false;
+  if (ctx->opt_adamw_grid || ctx->opt_adamw_unroll || ctx->opt_adamw_threads || !pt_adamw_hints(ctx)) return false;
+  if (ctx->C > PT_FUSED_MAX_CHUNKS || ctx->S * ctx->C < PT_FUSED_MIN_ELEMS) return false;
+  const PtPendingReduce& r = ctx->pend_reduce;
+  if (r.n > FUSED_CHUNKS || (r.n && ctx->C > 64)) return false;
+  if (r.n) {
+    uint32_t most = 0;
+    for (uint32_t i = 0; i < r.n; ++i) {
+      uint32_t lo = r.plan->tile_begin[i] * r.per_tile;
+      const uint32_t hi = r.plan->tile_begin[i + 1] * r.per_tile;
+      for (; lo < hi; lo += PT_REDUCE_SEG) {
+        if (f->units == FUSED_UNITS) return false;
+        f->lo[f->units] = lo;
+        f->hi[f->units] = std::min(hi, lo + PT_REDUCE_SEG);
+        most = std::max(most, f->hi[f->units] - lo);
+        ++f->units;
+        ++f->chunk_units[i];
+      }
+    }
+    f->trees = (std::min(most, PT_FUSED_ROW) + 63) / 64;
+    if (ctx->S / 256 <= pt_fused_summers(*f)) return false;        // they are workgroups of the first chunk
+    f->part = r.part; f->first = r.first; f->n = r.n;
+  }
+  f->C = ctx->C; f->chunk_sq = ctx->d_chunk_sq; f->chunk_flag = ctx->d_chunk_flag; f->st = ctx->d_state; f->pub = ctx->d_pub;
+  f->no = ctx->pub_no + 1 ? ctx->pub_no + 1 : 1;
+  f->end_step = ctx->step_no;
+  f->tries = ctx->opt_fused_tries;
+  f->hp = *hp;
+  return true;
+}
+
+void pt_fused_launched(pt_ctx* ctx, const PtFused& f) {
+  ctx->pub_no = f.no;
+  ctx->pend_reduce = PtPendingReduce{};
+  ctx->pend_finalize = false;
+  ctx->mirrored = false;
+  ctx->ended_early = ctx->step_no;
+  ctx->prepared = true;
+  ctx->prepared_hp = f.hp;
 }
 
 int pt_mirror_consts(pt_ctx* ctx, hipStream_t stream) {
@@ -607,7 +638,7 @@ k_sqnorm_arena(const void* __restrict__ arena, uint64_t S, double loss_scale, do
     out_sq_norm[0] = sq;
     out_sq_norm[1] = sqrt(sq);
     // a sum of squares is finite if and only if every number is (pt_close_sum)
-    *out_found_inf = (uint32_t(__double2hiint(sq)) & 0x7ff00000u) == 0x7ff00000u ? 1 : 0;
+    *out_found_inf = pt_not_finite(sq) ? 1 : 0;
   }
 }
 

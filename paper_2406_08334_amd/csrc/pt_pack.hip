@@ -249,6 +249,7 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   uint32_t most = 0;
   for (uint32_t c = 0; c < ctx->C; ++c)
     if (begin[c + 1] > begin[c]) { p->touched.push_back(c); most = std::max(most, begin[c + 1] - begin[c]); }
+  if (!p->touched.empty()) p->tile_begin.assign(begin.begin() + p->touched.front(), begin.begin() + p->touched.back() + 2);
   p->subs = subs; p->sub_elems = sub_elems;
   p->segs = pt_segs(uint64_t(most) * subs);
   auto bail = [&](hipError_t e, const char* what) {
@@ -261,7 +262,7 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   size_t nt = std::max<size_t>(tiles.size(), 1);
   if ((e = hipMalloc(&p->d_tiles, nt * sizeof(PtTile))) != hipSuccess) return bail(e, "hipMalloc(tiles)");
   if ((e = hipMalloc(&p->d_chunk_tile_begin, begin.size() * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(begin)");
-  if ((e = hipMalloc(&p->d_tile_sq, nt * subs * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(tile_sq)");
+  if ((e = hipMalloc(&p->d_tile_sq, (nt * subs + PT_FUSED_ROW) * sizeof(double))) != hipSuccess) return bail(e, "hipMalloc(tile_sq)");
   if ((e = hipMalloc(&p->d_tile_flag, nt * subs * sizeof(uint32_t))) != hipSuccess) return bail(e, "hipMalloc(tile_flag)");
   if (p->segs > 1) {
     const size_t ns = size_t(p->touched.back() - p->touched.front() + 1) * p->segs;
