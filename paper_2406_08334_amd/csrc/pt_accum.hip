@@ -57,16 +57,17 @@ __device__ __forceinline__ u32x2 load4(const PT_GLOBAL uint16_t* s) {
   return __builtin_nontemporal_load((const PT_GLOBAL u32x2_a2*)s);
 }
 
-// KEEP: sums that stay in the Infinity Cache (pt_in_cache) are loaded without the hint; stores need none of that.
+// KEEP: sums that stay in the Infinity Cache (pt_in_cache) are loaded without the hint.
 template <bool KEEP> __device__ __forceinline__ f32x4 load_sums(const PT_GLOBAL f32x4* p) {
   if constexpr (KEEP) return *p;
   else return __builtin_nontemporal_load(p);
 }
 
-// nvec units of four elements from sb onto db: two per lane in flight.
-template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED, bool KEEP>
+// nvec units of four elements from sb onto db: two per lane in flight.  NEAR: the sums are among the first that the cache can hold, and are
+// stored so that they stay there (pt_store), also where they are not loaded so.
+template <int DT, bool OVERWRITE, bool NORM, bool ALIGNED, bool KEEP, bool NEAR>
 __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBAL f32x4* db, uint32_t nvec, double& a0, double& a1) {
-  constexpr int U = 2;
+  constexpr int U = 2, POLICY = NEAR ? PT_THROUGH : PT_NT;
   uint32_t i = threadIdx.x;
   for (; i + (U - 1) * AC_THREADS < nvec; i += U * AC_THREADS) {
     u32x2 q[U];
@@ -80,7 +81,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 #pragma unroll
     for (int r = 0; r < U; ++r) {
       add4<DT, OVERWRITE, NORM>(q[r], a[r], a0, a1);
-      __builtin_nontemporal_store(a[r], db + i + r * AC_THREADS);
+      pt_store<POLICY>(a[r], db, (i + r * AC_THREADS) * 16);
     }
   }
   for (; i < nvec; i += AC_THREADS) {
@@ -88,7 +89,7 @@ __device__ __forceinline__ void add_units(const PT_GLOBAL uint16_t* sb, PT_GLOBA
     f32x4 a = {};
     if (!OVERWRITE) a = load_sums<KEEP>(db + i);
     add4<DT, OVERWRITE, NORM>(q, a, a0, a1);
-    __builtin_nontemporal_store(a, db + i);
+    pt_store<POLICY>(a, db, i * 16);
   }
 }
 
@@ -107,7 +108,7 @@ inline uint32_t accum_lds(bool overwrite, uint64_t elems) { return overwrite || 
 template <int DT, bool OVERWRITE, bool NORM>
 __global__ void __launch_bounds__(AC_THREADS)
 k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row, uint32_t subs, uint32_t sub_elems,
-        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag, uint64_t S, uint64_t cached) {
+        const PtDevState* __restrict__ st, double* __restrict__ tile_sq, uint32_t* __restrict__ tile_flag, uint64_t S, uint64_t cached, uint64_t near) {
   const uint32_t tile = blockIdx.x / subs;
   const PtTile t = tiles[tile];
   uint32_t lo, hi;
@@ -129,11 +130,14 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
   PT_GLOBAL f32x4* db = (PT_GLOBAL f32x4*)(dst + head);
   const bool aligned = ((uintptr_t)sb & 7u) == 0;
   if (!OVERWRITE && pt_in_cache(t.chunk, S, t.chunk_off, cached)) {
-    if (aligned) add_units<DT, OVERWRITE, NORM, true, true>(sb, db, nvec, a0, a1);
-    else add_units<DT, OVERWRITE, NORM, false, true>(sb, db, nvec, a0, a1);
+    if (aligned) add_units<DT, OVERWRITE, NORM, true, true, true>(sb, db, nvec, a0, a1);
+    else add_units<DT, OVERWRITE, NORM, false, true, true>(sb, db, nvec, a0, a1);
+  } else if (pt_in_cache(t.chunk, S, t.chunk_off, near)) {
+    if (aligned) add_units<DT, OVERWRITE, NORM, true, false, true>(sb, db, nvec, a0, a1);
+    else add_units<DT, OVERWRITE, NORM, false, false, true>(sb, db, nvec, a0, a1);
   } else {
-    if (aligned) add_units<DT, OVERWRITE, NORM, true, false>(sb, db, nvec, a0, a1);
-    else add_units<DT, OVERWRITE, NORM, false, false>(sb, db, nvec, a0, a1);
+    if (aligned) add_units<DT, OVERWRITE, NORM, true, false, false>(sb, db, nvec, a0, a1);
+    else add_units<DT, OVERWRITE, NORM, false, false, false>(sb, db, nvec, a0, a1);
   }
 
   // head and tail: at most 3 elements each, one lane per element
@@ -163,7 +167,7 @@ k_accum(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row
   }
 }
 
-typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, uint32_t, uint32_t, const PtDevState*, double*, uint32_t*, uint64_t, uint64_t);
+typedef void (*accum_kernel_t)(const PtTile*, const uint64_t*, uint32_t, uint32_t, const PtDevState*, double*, uint32_t*, uint64_t, uint64_t, uint64_t);
 
 template <int DT>
 accum_kernel_t pick(bool overwrite, bool norm) {
@@ -193,7 +197,7 @@ extern "C" int pt_chunk_accum_grads(pt_ctx* ctx, const pt_pack_plan* plan, float
                                               : pick<PT_FP16>(overwrite != 0, take_norm != 0);
   hipLaunchKernelGGL(kern, dim3(plan->n_tiles * plan->subs), dim3(AC_THREADS), accum_lds(overwrite != 0, plan->total_elems), st,
                      plan->d_tiles, pt_row(ctx, ROW_PACK), plan->subs, plan->sub_elems, ctx->d_state, plan->d_tile_sq,
-                     plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
+                     plan->d_tile_flag, ctx->S, pt_cached_loads(ctx), pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, "k_accum");
   if (take_norm) {
     rc = pt_reduce_plan(ctx, plan, st);

@@ -192,12 +192,13 @@ __device__ __forceinline__ void load_tile(Tile<UNROLL, GF32>& t, const ChunkPtrs
   asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind a branch on the step's scalars
 }
 
-// Updates a tile that has been loaded.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
-template <int TH, int DT, int UNROLL, bool NT, bool MASKED, bool GF32, class P32, class P64>
+// Updates a tile that has been loaded.  HOST: of chunks in host memory.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+template <int TH, int DT, int UNROLL, bool NT, bool HOST, bool MASKED, bool GF32, class P32, class P64>
 __device__ __forceinline__ void finish_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, Tile<UNROLL, GF32>& t, uint64_t units,
                                             uint32_t c, int recast_on_skip, int zero_grads, P32 nd_begin, P64 nd_ranges) {
   typedef typename GradUnit<GF32>::vec gvec;
   constexpr uint32_t TILE_UNITS = TH * UNROLL;
+  constexpr int POLICY = !NT ? PT_PLAIN : HOST ? PT_NT : PT_NT_THROUGH;
   const gvec gzero = {};
   const uint64_t ub = t.ub;
   if (skip) {
@@ -239,11 +240,11 @@ __device__ __forceinline__ void finish_tile(const Consts& k, int32_t skip, const
       const uint32_t o = threadIdx.x + uint32_t(r) * TH;
       u32x2 p;
       update_unit<DT, GF32>(k, dk, t.g[r], t.w[r], t.m[r], t.v[r], p);
-      st_stream<NT>(t.w[r], x.w + ub + o);
-      st_stream<NT>(t.m[r], x.m + ub + o);
-      st_stream<NT>(t.v[r], x.v + ub + o);
-      st_stream<NT>(p, x.p + ub + o);
-      if (zero_grads) st_stream<NT>(gzero, x.g + ub + o);
+      pt_store<POLICY>(t.w[r], x.w + ub, 16 * o);
+      pt_store<POLICY>(t.m[r], x.m + ub, 16 * o);
+      pt_store<POLICY>(t.v[r], x.v + ub, 16 * o);
+      pt_store<POLICY>(p, x.p + ub, 8 * o);
+      if (zero_grads) pt_store<NT ? PT_THROUGH : PT_PLAIN>(gzero, x.g + ub, uint32_t(sizeof gzero) * o);
     }
     return;
   }
@@ -273,7 +274,7 @@ __device__ __forceinline__ void update_tile(const Consts& k, int32_t skip, const
                                             const uint64_t* __restrict__ nd_ranges) {
   Tile<UNROLL, GF32> t;
   load_tile<TH, UNROLL, NT, NTG, GF32>(t, x, tile, units);
-  finish_tile<TH, DT, UNROLL, NT, MASKED, GF32>(k, skip, x, t, units, c, recast_on_skip, zero_grads, nd_begin, nd_ranges);
+  finish_tile<TH, DT, UNROLL, NT, NTG, MASKED, GF32>(k, skip, x, t, units, c, recast_on_skip, zero_grads, nd_begin, nd_ranges);
 }
 
 __device__ __forceinline__ Consts load_consts(const PtDevState* __restrict__ st) {
@@ -562,7 +563,7 @@ __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
 #pragma unroll
   for (uint32_t k = 0; k < 9; ++k) c[k] = __uint_as_float(word[k]);
   const Consts k = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8]};
-  finish_tile<64, DT, 1, true, MASKED, GF32>(k, int32_t(word[9]), x, tile, a.units, blockIdx.y, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
+  finish_tile<64, DT, 1, true, false, MASKED, GF32>(k, int32_t(word[9]), x, tile, a.units, blockIdx.y, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
   if (__builtin_expect(first, 0)) write_state(fused_work(), d);
 }
 
@@ -654,10 +655,10 @@ k_adamw_pattern(const uint64_t* __restrict__ table, uint32_t table_cols, uint32_
         p.x = encode16<DT>(w[r][0]) | (encode16<DT>(w[r][1]) << 16);
         p.y = encode16<DT>(w[r][2]) | (encode16<DT>(w[r][3]) << 16);
         keep ^= g[r].x ^ g[r].y;
-        st_stream<NT>(w[r], wp + ub + o);
-        st_stream<NT>(m[r], mp + ub + o);
-        st_stream<NT>(v[r], vp + ub + o);
-        st_stream<NT>(p, pp + ub + o);
+        pt_store<NT ? PT_NT_THROUGH : PT_PLAIN>(w[r], wp + ub, 16 * o);
+        pt_store<NT ? PT_NT_THROUGH : PT_PLAIN>(m[r], mp + ub, 16 * o);
+        pt_store<NT ? PT_NT_THROUGH : PT_PLAIN>(v[r], vp + ub, 16 * o);
+        pt_store<NT ? PT_NT_THROUGH : PT_PLAIN>(p, pp + ub, 8 * o);
       }
     }
   }

@@ -248,6 +248,27 @@ __device__ __forceinline__ void pt_sub_range(const PtTile& t, uint32_t sub, uint
   hi = h > l ? uint32_t(h - t.phase) : lo;
 }
 
+// Stores 8 or 16 bytes at byte `off` of `base`, which is the same in every lane, with a cache policy: none, the non-temporal hint, through the
+// L2 at once instead of when its line is evicted (agent scope, sc1), or both.
+//
+// Stores that go through at once are the faster ones wherever the traffic is a mix of reads and writes, at every size, warm or cold: an
+// evicted line is written at another time than its neighbours.  The update (all of its stores with the hint and through): 6.8e7
+// parameters 355 -> 347 us a step, 6.67e8 3235 -> 3182, 1.4e7 88.4 -> 86.2; through without the hint 367, 3257, 90.0; neither 397,
+// 3578, 96.8.  Words and sums that are to stay in the Infinity Cache (pt_in_cache) go through without the hint: packed words plainly and
+// so 6.8e7 343.3 -> 340.3, 1.24e8 596.7 -> 591.7, 1.4e7 86.4 -> 85.2 (with the hint 353, 612, 89); sums added to with the hint and so, one
+// call behind 2 GB of other traffic: 7.3e6 18.5 -> 17.3, 1.6e7 31.6 -> 29.2, 3e7 53.1 -> 50.0, 5.3e7 89.2 -> 84.3; sums the update zeroes
+// likewise: four micro-batches and update 7e6 108.3 -> 104.3, 3e7 337 -> 335, 1.24e8 1350 -> 1334, 3.3e8 3603 -> 3585.  Sums and words
+// beyond it have the hint alone (through: 3.3e8 3655; packed words the same).
+constexpr int PT_PLAIN = 0, PT_NT = 2, PT_THROUGH = 16, PT_NT_THROUGH = 18;
+typedef int pt_i32x4 __attribute__((ext_vector_type(4)));
+typedef int pt_i32x2 __attribute__((ext_vector_type(2)));
+template <int POLICY, class T>
+__device__ __forceinline__ void pt_store(T v, PT_GLOBAL void* base, uint32_t off) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)base, 0, 0xffffffffu, 0x27000);
+  if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(pt_i32x4, v), r, off, 0, POLICY);
+  else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(pt_i32x2, v), r, off, 0, POLICY);
+}
+
 // ---- helpers implemented in pt_ctx.hip ---------------------------------------------
 // Makes rows[r][first .. first+n) of the device pointer table equal to ptrs[0..n), for each of n_binds rows; uploads (on
 // `stream`, which it synchronises) only when something changed.
@@ -292,9 +313,9 @@ inline PtAdamwShape pt_adamw_shape(const pt_ctx* ctx, uint32_t n_cols) {
 // and 154.9.  Hence the line (below it, call behind call: 4.2e6 11.3 and 11.5, 7.3e6 16.9 and 14.8, 1.6e7 29.0 and 29.4, 2.3e7 39.4 and 38.7).
 inline bool pt_adamw_hints(const pt_ctx* ctx) { return ctx->opt_adamw_nt != 0; }
 constexpr uint64_t PT_CACHED_BYTES = 240ull << 20, PT_CACHED_SUMS = 3ull << 23;
-inline uint64_t pt_cached_elems(const pt_ctx* ctx) {
-  if (!ctx->grad_f32) return PT_CACHED_BYTES / 2;
-  return ctx->S * ctx->C < PT_CACHED_SUMS ? 0 : PT_CACHED_BYTES / 4;
+inline uint64_t pt_cached_elems(const pt_ctx* ctx) { return PT_CACHED_BYTES / (ctx->grad_f32 ? 4 : 2); }
+inline uint64_t pt_cached_loads(const pt_ctx* ctx) {
+  return ctx->grad_f32 && ctx->S * ctx->C < PT_CACHED_SUMS ? 0 : pt_cached_elems(ctx);
 }
 // Whether element `off` of chunk `chunk` (of S elements each) is one of the first `cached`.
 __device__ __forceinline__ bool pt_in_cache(uint32_t chunk, uint64_t S, uint64_t off, uint64_t cached) { return chunk * S + off < cached; }

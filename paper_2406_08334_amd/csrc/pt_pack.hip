@@ -43,10 +43,6 @@ __device__ __forceinline__ void take_vec(const u32x4& q, double& a0, double& a1)
   }
 }
 
-template <bool NT>
-__device__ __forceinline__ void store_vec(const u32x4& q, PT_GLOBAL u32x4* p) {
-  if (NT) __builtin_nontemporal_store(q, p); else *p = q;
-}
 
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));   // global memory takes a 16-byte load at any address
 
@@ -63,28 +59,29 @@ __device__ __forceinline__ u32x4 load_vec(const PT_GLOBAL uint16_t* s) {
 // nvec vectors from sb to db: two per lane in flight.
 template <int DT, int DIR, bool NTS, bool ALIGNED>
 __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBAL u32x4* db, uint32_t nvec, double& a0, double& a1) {
-  constexpr int U = 2;
+  constexpr int U = 2, POLICY = NTS ? PT_NT : PT_THROUGH;
   uint32_t i = threadIdx.x;
   for (; i + (U - 1) * PK_THREADS < nvec; i += U * PK_THREADS) {
     u32x4 q[U];
 #pragma unroll
     for (int r = 0; r < U; ++r) q[r] = load_vec<DIR, ALIGNED>(sb + size_t(i + r * PK_THREADS) * 8);
 #pragma unroll
-    for (int r = 0; r < U; ++r) store_vec<NTS>(q[r], db + i + r * PK_THREADS);
+    for (int r = 0; r < U; ++r) pt_store<POLICY>(q[r], db, (i + r * PK_THREADS) * 16);
     if (DIR == 0)
 #pragma unroll
       for (int r = 0; r < U; ++r) take_vec<DT>(q[r], a0, a1);
   }
   for (; i < nvec; i += PK_THREADS) {
     const u32x4 q = load_vec<DIR, ALIGNED>(sb + size_t(i) * 8);
-    store_vec<NTS>(q, db + i);
+    pt_store<POLICY>(q, db, i * 16);
     if (DIR == 0) take_vec<DT>(q, a0, a1);
   }
 }
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
-// Stores with non-temporal hints, but for gradient words that stay in the Infinity Cache for the update (pt_in_cache).
+// Stores with non-temporal hints, but for gradient words that stay in the Infinity Cache for the update (pt_in_cache): those go through the L2 at
+// once (pt_store).
 //
 // Few bytes in flight, in address order, are moved fastest (as in the update).  One wave moves 4 KiB, two vectors a lane at a
 // time, and unused LDS keeps few waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of
