@@ -57,9 +57,9 @@ __device__ __forceinline__ u32x4 load_vec(const PT_GLOBAL uint16_t* s) {
 }
 
 // nvec vectors from sb to db: two per lane in flight.
-template <int DT, int DIR, bool NTS, bool ALIGNED>
+template <int DT, int DIR, bool KEEP, bool ALIGNED>
 __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBAL u32x4* db, uint32_t nvec, double& a0, double& a1) {
-  constexpr int U = 2, POLICY = NTS ? PT_NT : PT_THROUGH;
+  constexpr int U = 2, POLICY = KEEP ? PT_THROUGH : PT_NT_THROUGH;
   uint32_t i = threadIdx.x;
   for (; i + (U - 1) * PK_THREADS < nvec; i += U * PK_THREADS) {
     u32x4 q[U];
@@ -80,8 +80,7 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
-// Stores with non-temporal hints, but for gradient words that stay in the Infinity Cache for the update (pt_in_cache): those go through the L2 at
-// once (pt_store).
+// KEEP: words that stay in the Infinity Cache: packed ones for the update (pt_in_cache), unpacked ones for whoever reads the tensors (unpack_kept).
 //
 // Few bytes in flight, in address order, are moved fastest (as in the update).  One wave moves 4 KiB, two vectors a lane at a
 // time, and unused LDS keeps few waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of
@@ -97,6 +96,13 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6); below 2^24 words it runs without a limit (1.5e7 11.6, with one 11.8).
 constexpr uint32_t PACK_LDS = 9000;
 inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : elems < (1ull << 28) ? 9000 : 11500; }
+// Stores (pt_store).  Unpack: through the L2 without the hint, so that they stay in the Infinity Cache for the forward pass, but from 3 * 2^24 to
+// 2^28 words, where the cache is about as large as the words of a call or two.  With the hint alone, through without it, through with it: 7.1e6
+// words 6.76 / 6.32 / 6.72 us, 2.2e7 15.4 / 14.9 / 16.1, 4.2e7 28.0 / 26.2 / 28.4, 6e7 38.9 / 39.7 / 38.9, 2.0e8 124.0 / 124.7 / 123.2, 2.8e8 168.4 /
+// 165.9 / 167, 6.7e8 400.9 / 391.3 / 400.3, 1.4e9 867 / 848 / 867; one call behind 2 GB of other traffic and a pass that reads the tensors, 7.1e6
+// 10.6 + 13.2 / 10.2 + 9.7 / 10.9 + 13.1, 6.1e7 43.0 + 43.8 / 39.1 + 37.8 / 42.1 + 43.4.
+// Packed words that don't fit the cache: through with the hint, a step of 2e8 parameters 1024 us with the hint alone and 1010 so, 6.7e8 3214 and 3169.
+inline bool unpack_kept(uint64_t elems) { return elems < (3ull << 24) || elems >= (1ull << 28); }
 
 template <int DT, int DIR>
 __global__ void __launch_bounds__(PK_THREADS)
@@ -125,12 +131,12 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL u32x4* db = (PT_GLOBAL u32x4*)(dst + head);
   const bool aligned = ((uintptr_t)sb & 15u) == 0;
-  if (DIR == 0 && pt_in_cache(t.chunk, S, t.chunk_off, cached)) {
-    if (aligned) move_vecs<DT, DIR, false, true>(sb, db, nvec, a0, a1);
-    else move_vecs<DT, DIR, false, false>(sb, db, nvec, a0, a1);
-  } else {
+  if (DIR == 0 ? pt_in_cache(t.chunk, S, t.chunk_off, cached) : cached != 0) {
     if (aligned) move_vecs<DT, DIR, true, true>(sb, db, nvec, a0, a1);
     else move_vecs<DT, DIR, true, false>(sb, db, nvec, a0, a1);
+  } else {
+    if (aligned) move_vecs<DT, DIR, false, true>(sb, db, nvec, a0, a1);
+    else move_vecs<DT, DIR, false, false>(sb, db, nvec, a0, a1);
   }
 
   // head and tail: at most 7 elements each, one lane per element
@@ -327,7 +333,8 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
   const size_t lds = DIR == 1 ? unpack_lds(plan->total_elems) : PACK_LDS;
   auto kern = ctx->dtype == PT_BF16 ? k_pack<PT_BF16, DIR> : k_pack<PT_FP16, DIR>;
   hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), plan->subs, plan->sub_elems,
-                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S, pt_cached_elems(ctx));
+                     ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S,
+                     DIR == 1 ? uint64_t(unpack_kept(plan->total_elems)) : pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
     rc = pt_reduce_plan(ctx, plan, st);
