@@ -75,6 +75,7 @@ class PtError(RuntimeError):
 
 _lib = None
 _raw_stream = None      # torch's look-up of the current stream's handle, if this torch has it
+_native = None          # the step's calls in native code (csrc/pt_call.cpp), bound to the library by lib()
 
 
 def lib():
@@ -136,6 +137,16 @@ def lib():
         for name in EXPORTS:
             if name not in ("pt_version", "pt_status_string", "pt_last_error"):
                 getattr(L, name).restype = C.c_int
+        global _native
+        try:
+            from . import _ptcall
+        except ImportError as e:
+            raise RuntimeError("_ptcall.so is missing: build it with __graft_entry__.build() (python -m paper_2406_08334_amd.build)") from e
+        entries = ("pt_chunk_pack_grads", "pt_chunk_unpack", "pt_chunk_accum_grads", "pt_chunk_grad_sqnorm", "pt_chunk_adamw_step",
+                   "pt_step_end", "pt_chunk_grad_sqnorm_noalloc")
+        _ptcall.bind([C.cast(getattr(L, name), C.c_void_p).value for name in entries], C.c_void_p, pt_hparams, torch.cuda.is_initialized,
+                     torch._C._cuda_getDevice if _raw_stream is not None else None, _raw_stream)
+        _native = _ptcall
         _lib = L
     return _lib
 
@@ -239,35 +250,60 @@ def pt_pack_plan_destroy(plan):
     _check(lib().pt_pack_plan_destroy(plan), "pt_pack_plan_destroy")
 
 
+# The calls of a step go through native code first, which says None, having done nothing, where an argument has another form than the usual
+# one (lists of tensors, handles of this module, plain numbers): then ctypes takes them.  Four calls of a small step: 17.4 -> 10.2 us of
+# host time.
+
 def pt_chunk_pack_grads(ctx, plan, grad_chunks, stream=None):
-    _check(lib().pt_chunk_pack_grads(ctx, plan, _ptr_array(grad_chunks), _stream(stream)),
-           "pt_chunk_pack_grads", ctx)
+    L = lib()
+    rc = _native.pack(ctx, plan, grad_chunks, stream)
+    if rc is None:
+        rc = L.pt_chunk_pack_grads(ctx, plan, _ptr_array(grad_chunks), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_pack_grads", ctx)
 
 
 def pt_chunk_unpack(ctx, plan, chunks, stream=None):
-    _check(lib().pt_chunk_unpack(ctx, plan, _ptr_array(chunks), _stream(stream)), "pt_chunk_unpack", ctx)
+    L = lib()
+    rc = _native.unpack(ctx, plan, chunks, stream)
+    if rc is None:
+        rc = L.pt_chunk_unpack(ctx, plan, _ptr_array(chunks), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_unpack", ctx)
 
 
 def pt_chunk_grad_sqnorm(ctx, grad_chunks, first_chunk: int, n_chunks: int, finalize, stream=None):
     """finalize: False / 0, True / PT_FINALIZE_STRICT, or PT_FINALIZE_CARRY"""
-    _check(lib().pt_chunk_grad_sqnorm(ctx, _ptr_array(grad_chunks), int(first_chunk), int(n_chunks),
-                                      int(finalize), _stream(stream)), "pt_chunk_grad_sqnorm", ctx)
+    L = lib()
+    rc = _native.sqnorm(ctx, grad_chunks, first_chunk, n_chunks, finalize, stream)
+    if rc is None:
+        rc = L.pt_chunk_grad_sqnorm(ctx, _ptr_array(grad_chunks), int(first_chunk), int(n_chunks), int(finalize), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_grad_sqnorm", ctx)
 
 
 def pt_chunk_grad_sqnorm_noalloc(grad_arena, dtype: int, chunk_elems: int, n_chunks: int, loss_scale: float,
                                  out_sqnorm_norm, out_found_inf, stream=None):
     """grad_arena: device tensor holding the chunks back to back; out_sqnorm_norm: device float64[2];
     out_found_inf: device int32[1].  Allocates nothing."""
-    _check(lib().pt_chunk_grad_sqnorm_noalloc(_addr(grad_arena), int(dtype), int(chunk_elems), int(n_chunks),
-                                              float(loss_scale), _addr(out_sqnorm_norm), _addr(out_found_inf),
-                                              _stream(stream)), "pt_chunk_grad_sqnorm_noalloc")
+    L = lib()
+    rc = _native.noalloc(grad_arena, dtype, chunk_elems, n_chunks, loss_scale, out_sqnorm_norm, out_found_inf, stream)
+    if rc is None:
+        rc = L.pt_chunk_grad_sqnorm_noalloc(_addr(grad_arena), int(dtype), int(chunk_elems), int(n_chunks), float(loss_scale),
+                                            _addr(out_sqnorm_norm), _addr(out_found_inf), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_grad_sqnorm_noalloc")
 
 
 def pt_chunk_adamw_step(ctx, hp: pt_hparams, first_chunk: int, n_chunks: int, grad, master, m, v, param16,
                         stream=None):
-    _check(lib().pt_chunk_adamw_step(ctx, C.byref(hp), int(first_chunk), int(n_chunks), _ptr_array(grad),
-                                     _ptr_array(master), _ptr_array(m), _ptr_array(v), _ptr_array(param16),
-                                     _stream(stream)), "pt_chunk_adamw_step", ctx)
+    L = lib()
+    rc = _native.update(ctx, hp, first_chunk, n_chunks, grad, master, m, v, param16, stream)
+    if rc is None:
+        rc = L.pt_chunk_adamw_step(ctx, C.byref(hp), int(first_chunk), int(n_chunks), _ptr_array(grad), _ptr_array(master), _ptr_array(m),
+                                   _ptr_array(v), _ptr_array(param16), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_adamw_step", ctx)
 
 
 def pt_stream_reserve(ctx, n_slots: int):
@@ -291,7 +327,12 @@ def pt_chunk_stream_step(ctx, hp: pt_hparams, first_chunk: int, n_chunks: int, h
 
 
 def pt_step_end(ctx, stream=None):
-    _check(lib().pt_step_end(ctx, _stream(stream)), "pt_step_end", ctx)
+    L = lib()
+    rc = _native.step_end(ctx, stream)
+    if rc is None:
+        rc = L.pt_step_end(ctx, _stream(stream))
+    if rc:
+        _check(rc, "pt_step_end", ctx)
 
 
 def pt_step_report_read(ctx, stream=None) -> pt_step_report:
@@ -402,5 +443,9 @@ def pt_ctx_set_no_decay(ctx, segments):
 
 
 def pt_chunk_accum_grads(ctx, plan, acc_chunks, overwrite, take_norm, stream=None):
-    _check(lib().pt_chunk_accum_grads(ctx, plan, _ptr_array(acc_chunks), int(bool(overwrite)), int(bool(take_norm)),
-                                      _stream(stream)), "pt_chunk_accum_grads", ctx)
+    L = lib()
+    rc = _native.accum(ctx, plan, acc_chunks, bool(overwrite), bool(take_norm), stream)
+    if rc is None:
+        rc = L.pt_chunk_accum_grads(ctx, plan, _ptr_array(acc_chunks), int(bool(overwrite)), int(bool(take_norm)), _stream(stream))
+    if rc:
+        _check(rc, "pt_chunk_accum_grads", ctx)

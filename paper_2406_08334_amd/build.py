@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libptchunk.so")
 PROBE = os.path.join(HERE, "ptchunk_probe")
+CALL = os.path.join(HERE, "_ptcall.so")
 SOURCES = ["pt_ctx.hip", "pt_norm.hip", "pt_pack.hip", "pt_accum.hip", "pt_adamw.hip", "pt_stream.hip", "pt_host.hip", "pt_model.hip"]
 
 FLAGS = [
@@ -54,6 +56,15 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed on pt_probe.cpp")
+    # the step's calls from Python (host code only; the library's entry points are handed to it when it is loaded)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pt_call.cpp"), "-o", CALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed on pt_call.cpp")
     return LIB
 
 
