@@ -324,7 +324,12 @@ k_adamw(const uint64_t* __restrict__ table, const PtDevState* __restrict__ st, u
 // No wait is without an end and none depends on the order in which workgroups start: after `tries` looks, some milliseconds, a wave
 // derives the constants by itself.  The state it needs is written by the first workgroup only when the published words have arrived; so if they
 // are still not there when the state has been read, what was read is the state before the step's end.
-constexpr uint32_t FUSED_EARLY = 4096;
+// The workgroups that run by then take a tile more each, from the far end, and load it with their own: twice the bytes are under way while
+// they wait.  3 M parameters 29.8 -> 29.0 us a step, 2.5 M 23.3 -> 21.7, 3.2 M 26.2 -> 24.7, 4.3 M 31.0 -> 29.3, 7 M 47.8 -> 46.9, 1.4e7 84.5 -> 83.8,
+// from 6e7 on the same (a third one 0.5 to 1 % more up to there).  Below 6144 tiles, 1.57 M elements, the state of a few such steps
+// lies in the Infinity Cache and little waits for it: 1.1 M 17.1 -> 17.3, 0.8 M in chunks of 2^18 13.9 -> 14.3, 1.4 M 18.3 -> 18.2, 1.9 M 20.7
+// -> 19.7.  All tiles are counted through in one dimension of the grid for that.
+constexpr uint32_t FUSED_EARLY = 4096, FUSED_RESIDENT = 256 * 11, FUSED_DOUBLED_FROM = 6144;
 
 __device__ __forceinline__ double readlane_f64(double x, uint32_t lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
@@ -343,6 +348,8 @@ struct FusedArgs {
   const uint64_t* pub;
   int zero_grads;
   uint32_t summers;
+  uint32_t tiles, total, doubled;                // of a chunk, of all chunks; workgroups that take two
+  uint32_t inv_lo, inv_hi;                       // 2^58 / tiles, rounded up
   PtFused work;
 };
 
@@ -507,38 +514,51 @@ __device__ __forceinline__ void write_state(const PT_SCALAR PtFused& a, const De
   pt_end_early(a.st, s, d.inf, a.end_step);
 }
 
+// Tile `at` of all chunks: its chunk, the tile within it, and the chunk's arrays.
 template <bool GF32>
-__device__ __forceinline__ ChunkPtrs<GF32> fused_ptrs(const PT_SCALAR uint64_t* table, uint32_t table_cols) {
-  asm volatile("" : "+s"(table));                // not moved in front of what comes before
-  const PT_SCALAR uint64_t* t = table + blockIdx.y;
-  return chunk_ptrs<GF32>(t[size_t(ROW_GRAD) * table_cols], t[size_t(ROW_MASTER) * table_cols], t[size_t(ROW_M) * table_cols],
-                          t[size_t(ROW_V) * table_cols], t[size_t(ROW_P16) * table_cols]);
+struct Place { uint32_t c, tile; ChunkPtrs<GF32> x; };
+template <bool GF32>
+__device__ __forceinline__ Place<GF32> place(const FusedArgs& a, uint32_t at) {
+  Place<GF32> p;
+  p.c = uint32_t((uint64_t(at) * a.inv_hi + (uint64_t(at) * a.inv_lo >> 32)) >> 26);      // at / tiles
+  p.tile = at - p.c * a.tiles;
+  const PT_SCALAR uint64_t* t = a.table;
+  asm volatile("" : "+s"(t));                    // not moved in front of what comes before
+  t += p.c;
+  const uint32_t cols = a.table_cols;
+  p.x = chunk_ptrs<GF32>(t[size_t(ROW_GRAD) * cols], t[size_t(ROW_MASTER) * cols], t[size_t(ROW_M) * cols], t[size_t(ROW_V) * cols],
+                         t[size_t(ROW_P16) * cols]);
+  return p;
 }
 
 template <int DT, bool MASKED, bool GF32>
 __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
-  const bool first = (blockIdx.x | blockIdx.y) == 0;
-  const uint32_t copy = blockIdx.x % FUSED_COPIES;
+  const uint32_t at = blockIdx.x, copy = at % FUSED_COPIES;
+  const bool first = at == 0, two = at < a.doubled;
   Derived d;
   uint32_t mine = 0, word[10];                   // word: the same in every lane
-  if (__builtin_expect(blockIdx.y == 0 && blockIdx.x <= a.summers, 0)) {
+  if (__builtin_expect(at <= a.summers, 0)) {
     const PT_SCALAR PtFused& work = fused_work();
     if (first) {
       d = derive<false>(work);
       mine = d.word;
       publish(work, mine);
     } else {
-      const uint32_t pair = (blockIdx.x - 1) / work.trees, tree = (blockIdx.x - 1) % work.trees;
+      const uint32_t pair = (at - 1) / work.trees, tree = (at - 1) % work.trees;
       Pair p;
       load_pair(p, work, pair, tree);
       publish_pair(work, pair, tree, sum_pair(p, work, pair, tree));
     }
   }
-  Tile<1, GF32> tile;
-  ChunkPtrs<GF32> x = fused_ptrs<GF32>(a.table, a.table_cols);
-  load_tile<64, 1, true, false, GF32>(tile, x, blockIdx.x, a.units);
+  Tile<1, GF32> tile, tile2;
+  Place<GF32> p = place<GF32>(a, at), p2;
+  load_tile<64, 1, true, false, GF32>(tile, p.x, p.tile, a.units);
+  if (two) {
+    p2 = place<GF32>(a, a.total - 1 - at);
+    load_tile<64, 1, true, false, GF32>(tile2, p2.x, p2.tile, a.units);
+  }
   bool known = false;
-  if (!(blockIdx.y == 0 && blockIdx.x < FUSED_EARLY)) {
+  if (at >= FUSED_EARLY) {
     const PT_SCALAR uint64_t* w = (const PT_SCALAR uint64_t*)a.pub + copy * FUSED_LINE;
     asm volatile("" : "+s"(w));                  // behind the tile's loads, whose latency hides this one's
     known = true;
@@ -553,8 +573,12 @@ __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
     if (!first && __builtin_expect(!published(a.pub, a.no, copy, fused_work().tries, mine), 0)) {
       mine = derive<true>(fused_work()).word;
       published(a.pub, a.no, copy, 1, mine);
-      x = fused_ptrs<GF32>(a.table, a.table_cols);         // again: nothing is held meanwhile
-      load_tile<64, 1, true, false, GF32>(tile, x, blockIdx.x, a.units);
+      p = place<GF32>(a, at);                    // again: nothing is held meanwhile
+      load_tile<64, 1, true, false, GF32>(tile, p.x, p.tile, a.units);
+      if (two) {
+        p2 = place<GF32>(a, a.total - 1 - at);
+        load_tile<64, 1, true, false, GF32>(tile2, p2.x, p2.tile, a.units);
+      }
     }
 #pragma unroll
     for (uint32_t k = 0; k < 10; ++k) word[k] = __builtin_amdgcn_readlane(mine, k);
@@ -563,7 +587,9 @@ __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
 #pragma unroll
   for (uint32_t k = 0; k < 9; ++k) c[k] = __uint_as_float(word[k]);
   const Consts k = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8]};
-  finish_tile<64, DT, 1, true, false, MASKED, GF32>(k, int32_t(word[9]), x, tile, a.units, blockIdx.y, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
+  finish_tile<64, DT, 1, true, false, MASKED, GF32>(k, int32_t(word[9]), p.x, tile, a.units, p.c, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
+  if (__builtin_expect(two, 0))
+    finish_tile<64, DT, 1, true, false, MASKED, GF32>(k, int32_t(word[9]), p2.x, tile2, a.units, p2.c, 0, a.zero_grads, a.nd_begin, a.nd_ranges);
   if (__builtin_expect(first, 0)) write_state(fused_work(), d);
 }
 
@@ -734,11 +760,8 @@ Geometry geometry(const pt_ctx* ctx, const PtAdamwShape& s, uint32_t n_cols) {
   return g;
 }
 
-// Whether an update of all chunks in the library's shape has a workgroup for every tile.
-bool one_tile_each(const pt_ctx* ctx) {
-  const Geometry g = geometry(ctx, pt_adamw_shape(ctx, ctx->C), ctx->C);
-  return g.grid.x == g.tiles && g.grid.y == ctx->C;
-}
+// Whether the tiles of an update of all chunks in the library's shape can be counted through in one dimension of a grid (and `place`).
+bool tiles_in_one_row(const pt_ctx* ctx) { return (ctx->S / 256 + 2) * ctx->C < (uint64_t(1) << 26); }
 
 // Launches of more than 2^31 tiles of 8192 elements are refused (no memory holds them).
 bool too_many_tiles(const pt_ctx* ctx, uint32_t n_cols) { return (ctx->S / 8192 + 1) * n_cols > 0x7fffffffull; }
@@ -756,9 +779,12 @@ int pt_launch_adamw(pt_ctx* ctx, uint32_t first_col, uint32_t n_cols, hipStream_
   const bool masked = ctx->d_nd_begin != nullptr;
   if (fused) {
     fused_kernel_t kern = ctx->dtype == PT_BF16 ? pick_fused<PT_BF16>(masked, ctx->grad_f32) : pick_fused<PT_FP16>(masked, ctx->grad_f32);
+    const uint32_t total = uint32_t(geo.tiles * n_cols), doubled = total < FUSED_DOUBLED_FROM ? 0 : FUSED_RESIDENT;
+    const uint64_t inv = (uint64_t(1) << 58) / geo.tiles + 1;
     const FusedArgs args{(const PT_SCALAR uint64_t*)ctx->d_table, ctx->table_cols, fused->no, ctx->S / 4, (const PT_SCALAR uint32_t*)ctx->d_nd_begin,
-                         (const PT_SCALAR uint64_t*)ctx->d_nd_ranges, fused->pub, zero_grads ? 1 : 0, pt_fused_summers(*fused), *fused};
-    hipLaunchKernelGGL(kern, geo.grid, dim3(shape.threads), shape.lds, stream, args);
+                         (const PT_SCALAR uint64_t*)ctx->d_nd_ranges, fused->pub, zero_grads ? 1 : 0, pt_fused_summers(*fused), uint32_t(geo.tiles),
+                         total, doubled, uint32_t(inv), uint32_t(inv >> 32), *fused};
+    hipLaunchKernelGGL(kern, dim3(total - doubled), dim3(shape.threads), shape.lds, stream, args);
     PT_LAUNCH_CHECK(ctx, "k_adamw_fused");
     return PT_OK;
   }
@@ -810,7 +836,7 @@ extern "C" int pt_chunk_adamw_step(pt_ctx* ctx, const pt_hparams* hp, uint32_t f
                            {ROW_V, (const void* const*)v}, {ROW_P16, (const void* const*)param16}};
   if ((rc = pt_table_bind(ctx, binds, 5, first_chunk, n_chunks, false, st)) != PT_OK) return rc;
   PtFused fused;
-  if (n_chunks == ctx->C && one_tile_each(ctx) && pt_fuse_scalars(ctx, hp, &fused)) {
+  if (n_chunks == ctx->C && tiles_in_one_row(ctx) && pt_fuse_scalars(ctx, hp, &fused)) {
     if ((rc = pt_launch_adamw(ctx, 0, n_chunks, st, false, 0, ctx->opt_zero_grads != 0, &fused)) == PT_OK) pt_fused_launched(ctx, fused);
     return rc;
   }

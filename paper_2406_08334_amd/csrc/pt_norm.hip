@@ -429,7 +429,7 @@ bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
       }
     }
     f->trees = (std::min(most, PT_FUSED_ROW) + 63) / 64;
-    if (ctx->S / 256 <= pt_fused_summers(*f)) return false;        // they are workgroups of the first chunk
+    if (ctx->S / 256 * ctx->C <= 2 * pt_fused_summers(*f)) return false;       // they are among the workgroups of the update
     f->part = r.part; f->first = r.first; f->n = r.n;
   }
   f->C = ctx->C; f->chunk_sq = ctx->d_chunk_sq; f->chunk_flag = ctx->d_chunk_flag; f->st = ctx->d_state; f->pub = ctx->d_pub;

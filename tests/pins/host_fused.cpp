@@ -56,7 +56,10 @@ int by_size() {
       EXPECT(count("k_adamw_fused", at) == (fused ? 1u : 0u) && count("k_adamw", at) == (fused ? 0u : 1u));
       EXPECT(count("k_scalars", at) == (fused ? 0u : 1u));
       const fake::Op run = fake::ops.back();
-      EXPECT(run.grid.y == C && run.grid.x == (S / 4 + 7 + 63) / 64 && run.block.x == 64);
+      const uint64_t tiles = (S / 4 + 7 + 63) / 64, all = C * tiles;      // 2816 run at once: so many take two
+      if (fused) EXPECT(run.grid.y == 1 && run.grid.x == (all < 6144 ? all : all - 2816));
+      else EXPECT(run.grid.y == C && run.grid.x == tiles);
+      EXPECT(run.block.x == 64);
       OK(pt_step_end(s.ctx, nullptr));
       EXPECT(count("k_step_end", at) == 0);        // the step has ended with its constants
     }
