@@ -39,8 +39,8 @@ PACK_BYTES_PER_ELEM = 4            # read 2 + write 2
 # HBM traffic of one AdamW launch from rocprofv3 --pmc (FETCH_SIZE / WRITE_SIZE, scaled by the
 # same counters on pt_calib_copy); filled from the summaries under profiles/.  bytes per launch.
 MEASURED_TRAFFIC = {
-    # profiles/k_adamw_llama7b_hbm_traffic.md: (46 334 778.72 x 1.999761 + 92 667 997.31 x 0.999988) KiB
-    "llama_7b": 189_773_212_215,
+    # profiles/k_adamw_llama7b_hbm_traffic.md: (46 334 800.44 x 1.999761 + 92 667 905.66 x 0.999989) KiB
+    "llama_7b": 189_773_246_101,
 }
 
 
@@ -231,7 +231,7 @@ def run_resident(workload, steps, warmup, fp16=False, grad_sets=3, layout="dense
     adamw_bytes = adamw_per_elem * N_pad
     achieved = adamw_bytes / (mean(adamw_ms) * 1e-3) / 1e9
     value = step_bytes / (ms_step * 1e-3) / 1e9
-    kname = "k_adamw<%s, one wave per workgroup, non-temporal%s%s%s>" % ("fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "",
+    kname = "k_adamw_fused<%s, one wave per workgroup, non-temporal, through the L2%s%s%s>" % ("fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "",
                                                           ", fp32 gradients" if A else "", ", zeroing gradients" if zero_grads else "")
     out = {
         "workload": f"{workload}: {N} elements in {C} chunks of {S}, {layout_note}; arenas spread over physical memory, all "

@@ -572,6 +572,7 @@ __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
   if (!known) {
     if (!first && __builtin_expect(!published(a.pub, a.no, copy, fused_work().tries, mine), 0)) {
       mine = derive<true>(fused_work()).word;
+      asm volatile("" ::: "memory");           // looked for behind the loads of the state
       published(a.pub, a.no, copy, 1, mine);
       p = place<GF32>(a, at);                    // again: nothing is held meanwhile
       load_tile<64, 1, true, false, GF32>(tile, p.x, p.tile, a.units);

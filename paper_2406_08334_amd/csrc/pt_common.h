@@ -103,7 +103,7 @@ struct pt_ctx {
   uint32_t* d_norm_seg_flag = nullptr;
 
   uint64_t* d_pub = nullptr;            // constants published by an update that derives them itself (pt_scalars.h)
-  uint32_t pub_no = 0;                  // such launches so far; never 0 once there was one
+  uint32_t pub_no = 0;                  // such launches so far
 
   // host-side step bookkeeping
   std::vector<uint64_t> chunk_packed_by;   // [C] id of the pack plan whose partial sum is the chunk's value in this step, 0 = none

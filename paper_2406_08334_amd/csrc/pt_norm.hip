@@ -409,6 +409,7 @@ int pt_prepare_consts(pt_ctx* ctx, const pt_hparams* hp, bool host_part, hipStre
 // The update takes the scalar work along where it covers all chunks, a finalize waits, nothing but the update depends on the constants
 // (no host-side update: its event would be behind the whole update), and the step can end with them (pt_prepare_consts).
 bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
+  if (ctx->pub_no == UINT32_MAX) return false;         // the numbers of launches don't come round again
   if (ctx->prepared || !ctx->pend_finalize || ctx->host_pool || ctx->captured || ctx->goes_on || ctx->ended_early) return false;
   if (ctx->opt_adamw_grid || ctx->opt_adamw_unroll || ctx->opt_adamw_threads || !pt_adamw_hints(ctx)) return false;
   if (ctx->C > PT_FUSED_MAX_CHUNKS || ctx->S * ctx->C < PT_FUSED_MIN_ELEMS) return false;
@@ -433,7 +434,7 @@ bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
     f->part = r.part; f->first = r.first; f->n = r.n;
   }
   f->C = ctx->C; f->chunk_sq = ctx->d_chunk_sq; f->chunk_flag = ctx->d_chunk_flag; f->st = ctx->d_state; f->pub = ctx->d_pub;
-  f->no = ctx->pub_no + 1 ? ctx->pub_no + 1 : 1;
+  f->no = ++ctx->pub_no;                              // also if the launch fails: no two have the same
   f->end_step = ctx->step_no;
   f->tries = ctx->opt_fused_tries;
   f->hp = *hp;
@@ -441,7 +442,6 @@ bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
 }
 
 void pt_fused_launched(pt_ctx* ctx, const PtFused& f) {
-  ctx->pub_no = f.no;
   ctx->pend_reduce = PtPendingReduce{};
   ctx->pend_finalize = false;
   ctx->mirrored = false;

@@ -51,7 +51,7 @@ struct PtFused {
   uint32_t* chunk_flag = nullptr;
   PtDevState* st = nullptr;
   uint64_t* pub = nullptr;
-  uint32_t no = 0;                 // of this launch, never 0 and never the one before
+  uint32_t no = 0;                 // of this launch in its context, from 1 on
   uint32_t end_step = 0;           // number of the step that ends with it
   uint32_t tries = 0;              // looks for what another workgroup publishes, before a wave does the work itself
   pt_hparams hp{};
