@@ -231,8 +231,9 @@ def run_resident(workload, steps, warmup, fp16=False, grad_sets=3, layout="dense
     adamw_bytes = adamw_per_elem * N_pad
     achieved = adamw_bytes / (mean(adamw_ms) * 1e-3) / 1e9
     value = step_bytes / (ms_step * 1e-3) / 1e9
-    kname = "k_adamw_fused<%s, one wave per workgroup, non-temporal, through the L2%s%s%s>" % ("fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "",
-                                                          ", fp32 gradients" if A else "", ", zeroing gradients" if zero_grads else "")
+    kname = "k_adamw_fused<%s, one wave per workgroup, non-temporal, through the L2%s%s%s>" % (
+        "fp16" if fp16 else "bf16", ", no-decay runs" if no_decay_1d else "", ", fp32 gradients" if A else "",
+        ", zeroing gradients" if zero_grads else "")
     out = {
         "workload": f"{workload}: {N} elements in {C} chunks of {S}, {layout_note}; arenas spread over physical memory, all "
                     f"GPU-resident, {'fp16, loss scale 2^16' if fp16 else 'bf16'} params/grads N(0,0.02)/N(0,1e-3)"
