@@ -500,7 +500,8 @@ __device__ __forceinline__ bool published(const uint64_t* pub, uint32_t no, uint
   return false;
 }
 
-// What the scalar kernel writes besides the constants, with the published words arrived (see above).
+// What the scalar kernel writes besides the constants, with the published words arrived.  A wave that has given up reads the state, waits for
+// what it reads, and looks for the words once more: if it has read anything from here, it finds them.
 __device__ __forceinline__ void write_state(const PT_SCALAR PtFused& a, const Derived& d) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   const uint32_t lane = threadIdx.x;
@@ -572,7 +573,7 @@ __global__ void __launch_bounds__(64, 3) k_adamw_fused(const FusedArgs a) {
   if (!known) {
     if (!first && __builtin_expect(!published(a.pub, a.no, copy, fused_work().tries, mine), 0)) {
       mine = derive<true>(fused_work()).word;
-      asm volatile("" ::: "memory");           // looked for behind the loads of the state
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // looked for when the state has been read: see write_state
       published(a.pub, a.no, copy, 1, mine);
       p = place<GF32>(a, at);                    // again: nothing is held meanwhile
       load_tile<64, 1, true, false, GF32>(tile, p.x, p.tile, a.units);
