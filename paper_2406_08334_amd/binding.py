@@ -251,7 +251,7 @@ def pt_pack_plan_destroy(plan):
 
 
 # The calls of a step go through native code first, which says None, having done nothing, where an argument has another form than the usual
-# one (lists of tensors, handles of this module, plain numbers): then ctypes takes them.  Four calls of a small step: 17.4 -> 10.2 us of
+# one (lists of tensors, handles of this module, plain numbers, streams): then ctypes takes them.  Four calls of a small step: 17.4 -> 10.2 us of
 # host time.
 
 def pt_chunk_pack_grads(ctx, plan, grad_chunks, stream=None):

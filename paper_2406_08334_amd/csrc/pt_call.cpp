@@ -3,7 +3,8 @@
 // ctypes builds an array object for every list and converts every argument by its type: a step's four calls took 17.4 us of host time where the
 // library itself takes 10, more than the kernels of a small state run.  Here they take 10.2 with the one launch less of an update that derives its
 // constants: a step of 0.8 M parameters 16.1 -> 13.9 us, of 0.1 M 14.5 -> 9.9.  What a call is handed in another form than the
-// usual one (an argument type not named below) is left to ctypes: the function returns None and has done nothing.
+// usual one (an argument type not named below) is left to ctypes: the function returns None and has done nothing.  The lists come last, since
+// their addresses are what a call takes time for: 100 tensors by ctypes 45 us, here 16; both, one behind the other, 58.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -31,7 +32,7 @@ struct Entry {
 constexpr size_t N_ENTRIES = sizeof(Entry) / sizeof(void*);
 PyTypeObject *handle_type = nullptr, *hparams_type = nullptr;      // ctypes.c_void_p, binding.pt_hparams
 PyObject *initialized = nullptr, *get_device = nullptr, *raw_stream = nullptr;     // torch's, for the current stream; raw_stream may be None
-PyObject *s_data_ptr = nullptr, *s_value = nullptr;
+PyObject *s_data_ptr = nullptr, *s_value = nullptr, *s_cuda_stream = nullptr;
 
 // Each returns false, with no Python error set or with the one a callee has raised, where it does not know the form.
 bool as_address(PyObject* x, void** out) {
@@ -61,8 +62,9 @@ bool tensor_address(PyObject* x, void** out) {
 }
 
 // A list of tensors, addresses and None into `out`, which holds one NULL for an empty one.
+bool is_array(PyObject* list) { return PyList_CheckExact(list); }
 bool as_array(PyObject* list, std::vector<void*>& out) try {
-  if (!PyList_CheckExact(list)) return false;
+  if (!is_array(list)) return false;
   out.reserve(size_t(PyList_GET_SIZE(list)) + 1);
   for (Py_ssize_t i = 0; i < PyList_GET_SIZE(list); ++i) {
     PyObject* x = PyList_GET_ITEM(list, i);
@@ -92,9 +94,19 @@ bool as_number(PyObject* x, T* out) {
   return true;
 }
 
-// None: torch's current stream.
+// None: torch's current stream; a stream object: its handle.
 bool as_stream(PyObject* x, void** out) {
-  if (x != Py_None) return as_address(x, out);
+  if (PyLong_Check(x)) return as_address(x, out);
+  if (x != Py_None) {
+    PyObject* v = PyObject_GetAttr(x, s_cuda_stream);
+    if (!v) {
+      if (PyErr_ExceptionMatches(PyExc_AttributeError)) PyErr_Clear();      // no stream: ctypes' route says so
+      return false;
+    }
+    const bool ok = as_address(v, out);
+    Py_DECREF(v);
+    return ok;
+  }
   if (raw_stream == Py_None) return false;
   PyObject* is = PyObject_CallNoArgs(initialized);
   if (!is) return false;
@@ -127,14 +139,14 @@ PyObject* run(F&& f) {
 PyObject* pack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void *ctx, *plan, *st;
   std::vector<void*> p;
-  if (n != 4 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_array(a[2], p) || !as_stream(a[3], &st)) return not_here();
+  if (n != 4 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_stream(a[3], &st) || !as_array(a[2], p)) return not_here();
   return run([&] { return entry.pack((pt_ctx*)ctx, (const pt_pack_plan*)plan, p.data(), st); });
 }
 
 PyObject* unpack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void *ctx, *plan, *st;
   std::vector<void*> p;
-  if (n != 4 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_array(a[2], p) || !as_stream(a[3], &st)) return not_here();
+  if (n != 4 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_stream(a[3], &st) || !as_array(a[2], p)) return not_here();
   return run([&] { return entry.unpack((pt_ctx*)ctx, (const pt_pack_plan*)plan, p.data(), st); });
 }
 
@@ -142,8 +154,8 @@ PyObject* accum(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void *ctx, *plan, *st;
   std::vector<void*> p;
   int over, norm;
-  if (n != 6 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_array(a[2], p) || !as_number(a[3], &over) ||
-      !as_number(a[4], &norm) || !as_stream(a[5], &st))
+  if (n != 6 || !as_handle(a[0], &ctx) || !as_handle(a[1], &plan) || !as_number(a[3], &over) || !as_number(a[4], &norm) ||
+      !as_stream(a[5], &st) || !as_array(a[2], p))
     return not_here();
   return run([&] { return entry.accum((pt_ctx*)ctx, (const pt_pack_plan*)plan, (float* const*)p.data(), over != 0, norm != 0, st); });
 }
@@ -153,8 +165,8 @@ PyObject* sqnorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
   std::vector<void*> p;
   uint32_t first, count;
   int how;
-  if (n != 6 || !as_handle(a[0], &ctx) || (a[1] != Py_None && !as_array(a[1], p)) || !as_number(a[2], &first) ||
-      !as_number(a[3], &count) || !as_number(a[4], &how) || !as_stream(a[5], &st))
+  if (n != 6 || !as_handle(a[0], &ctx) || !as_number(a[2], &first) || !as_number(a[3], &count) || !as_number(a[4], &how) ||
+      !as_stream(a[5], &st) || (a[1] != Py_None && !as_array(a[1], p)))
     return not_here();
   return run([&] { return entry.sqnorm((pt_ctx*)ctx, p.empty() ? nullptr : p.data(), first, count, how, st); });
 }
@@ -166,12 +178,14 @@ PyObject* update(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 10 || !as_handle(a[0], &ctx) || Py_TYPE(a[1]) != hparams_type || !as_number(a[2], &first) || !as_number(a[3], &count))
     return not_here();
   for (int k = 0; k < 5; ++k)
-    if (!as_array(a[4 + k], p[k])) return not_here();
+    if (!is_array(a[4 + k])) return not_here();
   pt_hparams hp;
   Py_buffer b;
   if (!as_stream(a[9], &st) || PyObject_GetBuffer(a[1], &b, PyBUF_SIMPLE) != 0) return not_here();
   std::memcpy(&hp, b.buf, sizeof hp);                      // hparams_type has its size (bind)
   PyBuffer_Release(&b);
+  for (int k = 0; k < 5; ++k)
+    if (!as_array(a[4 + k], p[k])) return not_here();
   return run([&] {
     return entry.update((pt_ctx*)ctx, &hp, first, count, p[0].data(), (float* const*)p[1].data(), (float* const*)p[2].data(),
                         (float* const*)p[3].data(), p[4].data(), st);
@@ -192,7 +206,7 @@ PyObject* noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 8 || !as_number(a[1], &dtype) || !as_number(a[2], &elems) || !as_number(a[3], &chunks) || !PyFloat_CheckExact(a[4])) return not_here();
   const double scale = PyFloat_AS_DOUBLE(a[4]);
   if (PyLong_Check(a[0]) || PyLong_Check(a[5]) || PyLong_Check(a[6]) || a[0] == Py_None || a[5] == Py_None || a[6] == Py_None) return not_here();
-  if (!tensor_address(a[0], &g) || !tensor_address(a[5], &out) || !tensor_address(a[6], &inf) || !as_stream(a[7], &st)) return not_here();
+  if (!as_stream(a[7], &st) || !tensor_address(a[0], &g) || !tensor_address(a[5], &out) || !tensor_address(a[6], &inf)) return not_here();
   return run([&] { return entry.noalloc(g, dtype, elems, chunks, scale, (double*)out, (int32_t*)inf, st); });
 }
 
@@ -221,5 +235,6 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ptcall", nullptr, -1, methods, nu
 PyMODINIT_FUNC PyInit__ptcall(void) {
   s_data_ptr = PyUnicode_InternFromString("data_ptr");
   s_value = PyUnicode_InternFromString("value");
-  return s_data_ptr && s_value ? PyModule_Create(&module) : nullptr;
+  s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+  return s_data_ptr && s_value && s_cuda_stream ? PyModule_Create(&module) : nullptr;
 }

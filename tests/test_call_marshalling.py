@@ -96,3 +96,51 @@ def test_refused_forms_are_refused_as_before(calls, monkeypatch):
                     call()
                 raised.append(type(e.value))
         assert raised[0] is raised[1] and not calls
+
+
+class Stream:                                                # torch.cuda.Stream as the binding looks at it
+    cuda_stream = 0x7770
+
+
+class Counted:
+    """A tensor as the binding looks at it, which counts how often its address is taken."""
+
+    def __init__(self, at):
+        self.at, self.asked = at, 0
+
+    def data_ptr(self):
+        self.asked += 1
+        return self.at
+
+
+STEP_CALLS = {
+    "pack": lambda hp, x, st: B.pt_chunk_pack_grads(CTX, PLAN, x, st), "unpack": lambda hp, x, st: B.pt_chunk_unpack(CTX, PLAN, x, st),
+    "accum": lambda hp, x, st: B.pt_chunk_accum_grads(CTX, PLAN, x, 0, 1, st), "norm": lambda hp, x, st: B.pt_chunk_grad_sqnorm(CTX, x, 0, N, 1, st),
+    "update": lambda hp, x, st: B.pt_chunk_adamw_step(CTX, hp, 0, N, x, x, x, x, x, st), "end": lambda hp, x, st: B.pt_step_end(CTX, st),
+    "noalloc": lambda hp, x, st: B.pt_chunk_grad_sqnorm_noalloc(x[0], B.PT_FP16, 8, 3, 1.0, x[1], x[2], st)}
+
+
+@pytest.mark.parametrize("name", STEP_CALLS)
+def test_stream_objects(calls, monkeypatch, name):
+    hp = B.hparams(1e-4, 0.9, 0.95, 1e-8, 0.1, 1.0)
+    both(calls, monkeypatch, lambda: STEP_CALLS[name](hp, T, Stream()))
+
+
+@pytest.mark.parametrize("name,how", [(name, how) for name in STEP_CALLS for how in ("object", "handle", "large")])
+def test_an_address_is_taken_once(calls, monkeypatch, name, how):
+    """With a stream object in native code; a call that is left to ctypes because of its handle or stream has not been through its lists before."""
+    hp = B.hparams(1e-4, 0.9, 0.95, 1e-8, 0.1, 1.0)
+    x = [Counted(0x1000 * (k + 1)) for k in range(N)]
+    stream = {"object": Stream(), "handle": 0x10, "large": 2 ** 64 + 16}[how]      # ctypes cuts the last one off
+    if how == "handle":
+        monkeypatch.setitem(globals(), "CTX", 0x1230)        # a form that ctypes takes
+    STEP_CALLS[name](hp, x, stream)
+    times = {"update": 5, "end": 0}.get(name, 1)
+    assert len(calls) == 1 and [t.asked for t in x] == [times] * N, [t.asked for t in x]
+
+
+def test_lists_of_other_forms_are_found_first(calls, monkeypatch):
+    hp = B.hparams(1e-4, 0.9, 0.95, 1e-8, 0.1, 1.0)
+    x = [Counted(0x1000 * (k + 1)) for k in range(N)]
+    B.pt_chunk_adamw_step(CTX, hp, 0, N, x, x, x, x, tuple(x), 0)
+    assert [t.asked for t in x] == [5] * N
