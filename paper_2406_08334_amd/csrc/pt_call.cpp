@@ -218,6 +218,13 @@ PyObject* bind(PyObject*, PyObject* args) {
   void* at[N_ENTRIES];
   for (size_t i = 0; i < N_ENTRIES; ++i)
     if (!(at[i] = PyLong_AsVoidPtr(PyList_GET_ITEM(list, Py_ssize_t(i))))) return PyErr_Occurred() ? nullptr : PyErr_Format(PyExc_ValueError, "bind: NULL");
+  PyObject* one = PyObject_CallNoArgs(hp);
+  Py_buffer b;
+  if (!one || PyObject_GetBuffer(one, &b, PyBUF_SIMPLE) != 0) { Py_XDECREF(one); return nullptr; }
+  const Py_ssize_t size = b.len;
+  PyBuffer_Release(&b);
+  Py_DECREF(one);
+  if (size != Py_ssize_t(sizeof(pt_hparams))) return PyErr_Format(PyExc_ValueError, "bind: pt_hparams of %zd bytes, built with %zu", size, sizeof(pt_hparams));
   std::memcpy(&entry, at, sizeof entry);
   for (PyObject* o : {ht, hp, is, dev, raw}) Py_INCREF(o);      // kept as long as the process
   handle_type = (PyTypeObject*)ht; hparams_type = (PyTypeObject*)hp;

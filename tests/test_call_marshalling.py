@@ -98,6 +98,17 @@ def test_refused_forms_are_refused_as_before(calls, monkeypatch):
         assert raised[0] is raised[1] and not calls
 
 
+def test_hyper_parameters_of_another_layout_are_refused(calls):
+    class Short(C.Structure):                                # as an extension module would see that another header was built with
+        _fields_ = B.pt_hparams._fields_[:-1]
+
+    entries = [C.cast(C.CDLL(None).abs, VP).value] * 7
+    with pytest.raises(ValueError):
+        B._native.bind(entries, VP, Short, torch.cuda.is_initialized, None, None)
+    B.pt_step_end(CTX, 8)                                    # still bound to the stand-ins
+    assert len(calls) == 1
+
+
 class Stream:                                                # torch.cuda.Stream as the binding looks at it
     cuda_stream = 0x7770
 
