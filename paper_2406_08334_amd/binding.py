@@ -8,6 +8,7 @@ this module raises on first use - there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -75,7 +76,7 @@ class PtError(RuntimeError):
 
 _lib = None
 _raw_stream = None      # torch's look-up of the current stream's handle, if this torch has it
-_native = None          # the step's calls in native code (csrc/pt_call.cpp), bound to the library by lib()
+_native = None          # the step's calls in native code (csrc/pt_call.cpp), bound to the library by lib(), or _Ctypes
 
 
 def lib():
@@ -138,17 +139,27 @@ def lib():
             if name not in ("pt_version", "pt_status_string", "pt_last_error"):
                 getattr(L, name).restype = C.c_int
         global _native
-        try:
-            from . import _ptcall
-        except ImportError as e:
-            raise RuntimeError("_ptcall.so is missing: build it with __graft_entry__.build() (python -m paper_2406_08334_amd.build)") from e
-        entries = ("pt_chunk_pack_grads", "pt_chunk_unpack", "pt_chunk_accum_grads", "pt_chunk_grad_sqnorm", "pt_chunk_adamw_step",
-                   "pt_step_end", "pt_chunk_grad_sqnorm_noalloc")
-        _ptcall.bind([C.cast(getattr(L, name), C.c_void_p).value for name in entries], C.c_void_p, pt_hparams, torch.cuda.is_initialized,
-                     torch._C._cuda_getDevice if _raw_stream is not None else None, _raw_stream)
-        _native = _ptcall
+        _native = _load_native(L, torch)
         _lib = L
     return _lib
+
+
+class _Ctypes:
+    """In the place of the extension module where there is none for this interpreter: every call is left to ctypes."""
+
+    pack = unpack = accum = sqnorm = update = step_end = noalloc = staticmethod(lambda *args: None)
+
+
+def _load_native(L, torch):
+    try:
+        _ptcall = importlib.import_module("._ptcall", __package__)
+    except ModuleNotFoundError:
+        return _Ctypes
+    entries = ("pt_chunk_pack_grads", "pt_chunk_unpack", "pt_chunk_accum_grads", "pt_chunk_grad_sqnorm", "pt_chunk_adamw_step",
+               "pt_step_end", "pt_chunk_grad_sqnorm_noalloc")
+    _ptcall.bind([C.cast(getattr(L, name), C.c_void_p).value for name in entries], C.c_void_p, pt_hparams, torch.cuda.is_initialized,
+                 torch._C._cuda_getDevice if _raw_stream is not None else None, _raw_stream)
+    return _ptcall
 
 
 # ---- marshalling helpers ----------------------------------------------------------------

@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -11,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libptchunk.so")
 PROBE = os.path.join(HERE, "ptchunk_probe")
-CALL = os.path.join(HERE, "_ptcall.so")
+CALL = os.path.join(HERE, "_ptcall" + sysconfig.get_config_var("EXT_SUFFIX"))      # of this interpreter: no other loads it
 SOURCES = ["pt_ctx.hip", "pt_norm.hip", "pt_pack.hip", "pt_accum.hip", "pt_adamw.hip", "pt_stream.hip", "pt_host.hip", "pt_model.hip"]
 
 FLAGS = [
@@ -56,16 +57,29 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed on pt_probe.cpp")
-    # the step's calls from Python (host code only; the library's entry points are handed to it when it is loaded)
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "include"),
-           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pt_call.cpp"), "-o", CALL]
+    build_call(verbose)
+    return LIB
+
+
+def build_call(verbose: bool = False):
+    """Compiles the step's calls from Python (host code only; the library's entry points are handed to it when it is loaded).  Without a C++
+    compiler or CPython's headers there is none, and ctypes takes those calls."""
+    include = sysconfig.get_paths()["include"]
+    cxx = shutil.which("g++") or shutil.which("/opt/rocm/llvm/bin/clang++")
+    if os.path.exists(CALL):
+        os.remove(CALL)                      # none rather than an old one
+    if cxx is None or not os.path.exists(os.path.join(include, "Python.h")):
+        sys.stderr.write("no C++ compiler or no Python.h: without native marshalling\n")
+        return None
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "include"),
+           "-I", include, os.path.join(CSRC, "pt_call.cpp"), "-o", CALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("g++ failed on pt_call.cpp")
-    return LIB
+        raise RuntimeError("the C++ compiler failed on pt_call.cpp")
+    return CALL
 
 
 if __name__ == "__main__":

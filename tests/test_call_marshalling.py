@@ -1,6 +1,9 @@
 """The step's calls reach the library with the same arguments through native code (csrc/pt_call.cpp) as through ctypes, in every form that
 either takes.  The entry points are stand-ins that write their arguments down; no GPU."""
 import ctypes as C
+import importlib.machinery
+import os
+import sys
 
 import pytest
 import torch
@@ -155,3 +158,30 @@ def test_lists_of_other_forms_are_found_first(calls, monkeypatch):
     x = [Counted(0x1000 * (k + 1)) for k in range(N)]
     B.pt_chunk_adamw_step(CTX, hp, 0, N, x, x, x, x, tuple(x), 0)
     assert [t.asked for t in x] == [5] * N
+
+
+def test_without_the_extension_module(monkeypatch):
+    """The library serves a Python that the module was not built for: its calls go by ctypes."""
+    with monkeypatch.context() as m:
+        m.setitem(sys.modules, B.__package__ + "._ptcall", None)        # as if it were not there
+        m.setattr(B, "_lib", None)
+        segs, chunks = B.pt_layout_dense([5, 11], 8)
+        assert chunks == 2 and len(segs) == 3
+        with pytest.raises(B.PtError) as e:                  # reaches the library, which refuses it
+            B.pt_chunk_pack_grads(None, None, T, 0)
+        assert e.value.status == B.PT_ERR_INVALID_ARG
+    B._lib = None
+    B.lib()
+    if B._native is not B._Ctypes:                           # a module of this interpreter alone
+        assert os.path.basename(B._native.__file__) == "_ptcall" + importlib.machinery.EXTENSION_SUFFIXES[0]
+
+
+def test_a_module_that_does_not_load_says_why(monkeypatch):
+    def broken(*args):
+        raise ImportError("undefined symbol")
+
+    with monkeypatch.context() as m:
+        m.setattr(B, "_lib", None)
+        m.setattr(B.importlib, "import_module", broken)
+        with pytest.raises(ImportError, match="undefined symbol"):
+            B.lib()
