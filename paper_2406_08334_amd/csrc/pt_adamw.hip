@@ -335,24 +335,6 @@ __device__ __forceinline__ double readlane_f64(double x, uint32_t lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
 
-#define PT_SCALAR __attribute__((address_space(4)))      // loaded through the scalar cache
-
-// What the kernel is called with.  The first workgroup alone reads `work`, from where the arguments lie (fused_work): as an ordinary argument it
-// would be loaded by every wave.
-struct FusedArgs {
-  const PT_SCALAR uint64_t* table;
-  uint32_t table_cols, no;
-  uint64_t units;
-  const PT_SCALAR uint32_t* nd_begin;
-  const PT_SCALAR uint64_t* nd_ranges;
-  const uint64_t* pub;
-  int zero_grads;
-  uint32_t summers;
-  uint32_t tiles, total, doubled;                // of a chunk, of all chunks; workgroups that take two
-  uint32_t inv_lo, inv_hi;                       // 2^58 / tiles, rounded up
-  PtFused work;
-};
-
 __device__ __forceinline__ const PT_SCALAR PtFused& fused_work() {
   const PT_SCALAR FusedArgs* a = (const PT_SCALAR FusedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(a));                    // loads are not moved in front of this

@@ -1,6 +1,6 @@
 // Context, error plumbing, pointer tables, host-side layout builder and the
 // single-thread scalar kernels (state set / override / step end).
-#include "pt_scalars.h"
+#include "pt_common.h"
 
 #include <algorithm>
 

@@ -321,11 +321,9 @@ __global__ void k_mirror(const PtDevState* st, PtDevState* mirror) {
 constexpr uint32_t PT_FUSE_MAX_CHUNKS = 8;
 constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 // Where an update takes all of this along in its own launch (k_adamw_fused).  More than 256 chunks, which one wave adds up one after the other,
-// would take longer than a launch.  Below 2^16 elements the scalar kernel stays by itself, though a launch less would gain there too (12 700
-// elements 18.4 and 15.0 us a step): nobody trains states of that size, and it is at those that the sequences of a step's launches are played
-// through on the host with that kernel among them.
+// would take longer than a launch.  There is no lower line: k_scalars in front and not, one chunk of 768 elements 13.5 and 9.5 us a step, of 12 700
+// 13.6 and 9.6, eight of 512 15.1 and 11.4, nine of 4096 18.6 and 15.3, 64 of 256 30.3 and 27.6.
 constexpr uint32_t PT_FUSED_MAX_CHUNKS = 256;
-constexpr uint64_t PT_FUSED_MIN_ELEMS = 1u << 16;
 
 static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror,
                           hipStream_t stream) {
@@ -412,7 +410,7 @@ bool pt_fuse_scalars(pt_ctx* ctx, const pt_hparams* hp, PtFused* f) {
   if (ctx->pub_no == UINT32_MAX) return false;         // the numbers of launches don't come round again
   if (ctx->prepared || !ctx->pend_finalize || ctx->host_pool || ctx->captured || ctx->goes_on || ctx->ended_early) return false;
   if (ctx->opt_adamw_grid || ctx->opt_adamw_unroll || ctx->opt_adamw_threads || !pt_adamw_hints(ctx)) return false;
-  if (ctx->C > PT_FUSED_MAX_CHUNKS || ctx->S * ctx->C < PT_FUSED_MIN_ELEMS) return false;
+  if (ctx->C > PT_FUSED_MAX_CHUNKS) return false;
   const PtPendingReduce& r = ctx->pend_reduce;
   if (r.n > FUSED_CHUNKS || (r.n && ctx->C > 64)) return false;
   if (r.n) {

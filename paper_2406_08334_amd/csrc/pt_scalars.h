@@ -1,5 +1,5 @@
-// What the scalar kernel and an update that takes the scalar work along share: the constants of an update, values that pass between
-// workgroups of one launch, and the arguments of such an update.
+// What the scalar kernel and an update that takes the scalar work along share: the constants of an update, and values that pass between
+// workgroups of one launch.
 #pragma once
 
 #include "pt_common.h"
@@ -33,28 +33,3 @@ __device__ __forceinline__ float pt_grad_mult(double& clip, double max_norm, dou
   }
   return float(clip / loss_scale);
 }
-
-// ---- an update that derives its own constants (k_adamw_fused) --------------------------------------
-//
-// The sums it takes first, if a plan's wait: units of PT_REDUCE_SEG partial sums at most, [lo, hi) of unit u, chunk by chunk; chunk first + i
-// has chunk_units[i] of them, possibly none.  `trees`: of 64 lanes, in the longest unit.
-constexpr uint32_t FUSED_UNITS = 24, FUSED_TREES = 8, FUSED_CHUNKS = 8;
-// What its workgroups publish: FUSED_COPIES copies of the words of the update (FUSED_LINE words apart), then the trees' sums.
-constexpr uint32_t FUSED_COPIES = 16, FUSED_LINE = 32, FUSED_PUB_WORDS = FUSED_COPIES * FUSED_LINE + FUSED_UNITS * FUSED_TREES * 2;
-struct PtFused {
-  const double* part = nullptr;
-  uint32_t lo[FUSED_UNITS] = {}, hi[FUSED_UNITS] = {};
-  uint32_t units = 0, trees = 0, first = 0, n = 0;
-  uint8_t chunk_units[FUSED_CHUNKS] = {};
-  uint32_t C = 0;
-  double* chunk_sq = nullptr;
-  uint32_t* chunk_flag = nullptr;
-  PtDevState* st = nullptr;
-  uint64_t* pub = nullptr;
-  uint32_t no = 0;                 // of this launch in its context, from 1 on
-  uint32_t end_step = 0;           // number of the step that ends with it
-  uint32_t tries = 0;              // looks for what another workgroup publishes, before a wave does the work itself
-  pt_hparams hp{};
-};
-// Its workgroups that take sums: workgroup 1 + k the tree k % trees of the units 2 * (k / trees) and 2 * (k / trees) + 1.
-inline uint32_t pt_fused_summers(const PtFused& f) { return (f.units + 1) / 2 * f.trees; }

@@ -1,4 +1,5 @@
-// The step's scalars in device memory and what is done to them: loss-scale machine, step counter, the end of a step and its taking back.
+// The step's scalars in device memory and what is done to them: loss-scale machine, step counter, the end of a step and its taking back;
+// what the kernels that derive them are called with.
 // Without a HIP compiler these are ordinary functions, so that the sequences of launches can be played through on the host.
 #pragma once
 
@@ -8,8 +9,10 @@
 
 #ifdef __HIPCC__
 #define PT_STEP_FN __device__ __forceinline__
+#define PT_SCALAR __attribute__((address_space(4)))      // loaded through the scalar cache
 #else
 #define PT_STEP_FN inline
+#define PT_SCALAR
 #endif
 
 // ---- device-resident scalars of a context ---------------------------------------
@@ -119,4 +122,45 @@ struct PtScalarArgs {
   uint32_t end_step;             // do_prepare: number of the step that ends with it, or 0
   pt_hparams hp;
   PtDevState* mirror;            // pinned host memory that receives the constants, or NULL
+};
+
+// ---- an update that derives its own constants (k_adamw_fused) --------------------------------------
+//
+// The sums it takes first, if a plan's wait: units of PT_REDUCE_SEG partial sums at most, [lo, hi) of unit u, chunk by chunk; chunk first + i
+// has chunk_units[i] of them, possibly none.  `trees`: of 64 lanes, in the longest unit.
+constexpr uint32_t FUSED_UNITS = 24, FUSED_TREES = 8, FUSED_CHUNKS = 8;
+// What its workgroups publish: FUSED_COPIES copies of the words of the update (FUSED_LINE words apart), then the trees' sums.
+constexpr uint32_t FUSED_COPIES = 16, FUSED_LINE = 32, FUSED_PUB_WORDS = FUSED_COPIES * FUSED_LINE + FUSED_UNITS * FUSED_TREES * 2;
+struct PtFused {
+  const double* part = nullptr;
+  uint32_t lo[FUSED_UNITS] = {}, hi[FUSED_UNITS] = {};
+  uint32_t units = 0, trees = 0, first = 0, n = 0;
+  uint8_t chunk_units[FUSED_CHUNKS] = {};
+  uint32_t C = 0;
+  double* chunk_sq = nullptr;
+  uint32_t* chunk_flag = nullptr;
+  PtDevState* st = nullptr;
+  uint64_t* pub = nullptr;
+  uint32_t no = 0;                 // of this launch in its context, from 1 on
+  uint32_t end_step = 0;           // number of the step that ends with it
+  uint32_t tries = 0;              // looks for what another workgroup publishes, before a wave does the work itself
+  pt_hparams hp{};
+};
+// Its workgroups that take sums: workgroup 1 + k the tree k % trees of the units 2 * (k / trees) and 2 * (k / trees) + 1.
+inline uint32_t pt_fused_summers(const PtFused& f) { return (f.units + 1) / 2 * f.trees; }
+
+// What the kernel is called with.  The first workgroup alone reads `work`, from where the arguments lie (fused_work): as an ordinary argument it
+// would be loaded by every wave.
+struct FusedArgs {
+  const PT_SCALAR uint64_t* table;
+  uint32_t table_cols, no;
+  uint64_t units;
+  const PT_SCALAR uint32_t* nd_begin;
+  const PT_SCALAR uint64_t* nd_ranges;
+  const uint64_t* pub;
+  int zero_grads;
+  uint32_t summers;
+  uint32_t tiles, total, doubled;                // of a chunk, of all chunks; workgroups that take two
+  uint32_t inv_lo, inv_hi;                       // 2^58 / tiles, rounded up
+  PtFused work;
 };

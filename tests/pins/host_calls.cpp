@@ -22,6 +22,13 @@ namespace {
 
 const pt_hparams HP = {1e-4, 0.9, 0.95, 1e-8, 0.1, 1.0};
 
+// Launches that take scalar work: of the scalar kernel, and of an update that does it itself.
+std::vector<fake::Op> scalars(size_t from) {
+  std::vector<fake::Op> v = fake::launches("k_scalars", from);
+  for (const fake::Op& o : fake::launches("k_adamw_fused", from)) v.push_back(o);
+  return v;
+}
+
 // C chunks of S elements in device memory and a context for them; the plan's tensors are the chunks themselves, one each.
 struct State {
   uint64_t S;
@@ -117,7 +124,7 @@ int put_off_at_most_once() {
   const size_t at = fake::ops.size();
   OK(s.finalize(PT_FINALIZE_STRICT));
   OK(s.update());
-  EXPECT(fake::launches("k_scalars", at).size() == 1);
+  EXPECT(scalars(at).size() == 1);
   return 0;
 }
 
@@ -134,10 +141,10 @@ int finalize_on_a_stream_that_is_gone() {
     if (how == 0) OK(s.pack(q, fake::stream(0xb0)));
     if (how == 1) OK(pt_chunk_grad_sqnorm(s.ctx, s.g.data(), 0, 2, 0, fake::stream(0xb0)));
     if (how == 2) OK(s.update(fake::stream(0xb0)));
-    EXPECT(fake::ops.size() > at && fake::launches("k_scalars", at).size() >= 1);
+    EXPECT(fake::ops.size() > at && scalars(at).size() >= 1);
     for (size_t i = at; i < fake::ops.size(); ++i) EXPECT(fake::ops[i].stream != 0xa0);
     // the waiting norm comes first
-    EXPECT(fake::ops[at].what == "launch" && fake::ops[at].kernel == "k_scalars");
+    EXPECT(fake::ops[at].what == "launch" && fake::ops[at].kernel == (how == 2 ? "k_adamw_fused" : "k_scalars"));
     OK(pt_step_end(s.ctx, fake::stream(0xb0)));
   }
   return 0;
@@ -316,7 +323,11 @@ int launch_shape_options_and_back() {
   State s(2, 4096);
   pt_pack_plan* q = s.plan();
   OK(s.step(q));
-  const auto shape = [&] { return fake::launches("k_adamw").back(); };
+  const auto shape = [&] {                         // of the last update
+    size_t i = fake::ops.size();
+    while (fake::ops[--i].kernel.rfind("k_adamw", 0) != 0) {}
+    return fake::ops[i];
+  };
   const fake::Op own = shape();
   for (const char* name : {"adamw_unroll", "adamw_threads", "adamw_grid"}) {
     OK(pt_ctx_set_option(s.ctx, name, strcmp(name, "adamw_unroll") == 0 ? 4 : strcmp(name, "adamw_threads") == 0 ? 256 : 1));
@@ -450,7 +461,7 @@ int step_ends_with_its_constants() {
 // A stand-in for the device that runs the step's scalar kernels: at once, or when the graph is replayed they were captured into.  A
 // call sequence has to give the same values whether steps end with their constants or in a kernel of their own (which is
 // what a context does that has been captured into a graph; here into one that is never replayed).
-struct Launch { std::string kernel; PtDevState* st; PtScalarArgs a; uint32_t no; float mult; int32_t inf, step, good; double scale; bool reads_scale; };
+struct Launch { std::string kernel; PtDevState* st; PtScalarArgs a; uint32_t no; float mult; int32_t inf, step, good; double scale; bool reads_scale; PtFused f; };
 std::vector<Launch>* graph = nullptr;              // what is captured now
 bool reads_scale = false, inf_now = false;         // of the call in flight: its kernel reads the loss scale; gradients hold an infinity
 std::vector<double> seen;
@@ -462,6 +473,13 @@ void run(const Launch& l) {
   else if (l.kernel == "k_override") { st->override_active = 1; st->override_grad_mult = l.mult; st->found_inf = l.inf; }
   else if (l.kernel == "k_set_state") { st->step = l.step; st->loss_scale = l.scale; st->good_steps = l.good; }
   else if (l.kernel == "k_adamw") seen.insert(seen.end(), {1.0, st->c[0], st->c[8], double(st->skip)});
+  else if (l.kernel == "k_adamw_fused") {          // norm, constants and end of the step, and the update with them
+    PtDevState s = *st;
+    st->found_inf = st->skip = inf_now; st->override_active = s.override_active = 0;
+    st->c[0] = float(s.step + 1); st->c[8] = float(1.0 / s.loss_scale);
+    pt_end_early(st, s, inf_now, l.f.end_step);
+    seen.insert(seen.end(), {1.0, st->c[0], st->c[8], double(st->skip)});
+  }
   else if (l.kernel == "k_scalars" && st) {
     PtDevState s = *st;
     if (l.a.do_finalize) { st->found_inf = s.found_inf = inf_now; st->override_active = s.override_active = 0; }
@@ -482,6 +500,7 @@ void on_launch(const fake::Op& op, void** args) {
   else if (op.kernel == "k_set_state") { l.st = *(PtDevState**)args[0]; l.step = *(int32_t*)args[1]; l.scale = *(double*)args[2]; l.good = *(int32_t*)args[3]; }
   else if (op.kernel == "k_scalars") { l.a = *(PtScalarArgs*)args[0]; l.st = l.a.st; }
   else if (op.kernel == "k_adamw") l.st = *(PtDevState**)args[1];
+  else if (op.kernel == "k_adamw_fused") { l.f = ((FusedArgs*)args[0])->work; l.st = l.f.st; }
   else if (op.kernel == "k_pack" || op.kernel == "k_accum") { l.st = *(PtDevState**)args[4]; l.reads_scale = reads_scale; }
   else if (op.kernel == "k_sqnorm" || op.kernel == "k_sqnorm_f32") { l.st = *(PtDevState**)args[3]; l.reads_scale = true; }
   else if (op.kernel == "k_init_state") {
@@ -500,13 +519,13 @@ struct Act { int what; uint32_t arg; };            // CAPTURE: the next `arg` ac
 const pt_scaler_cfg SCALER = {1024.0, 2.0, 0.5, 2, 0};
 
 // The values that `acts` lead to (`seen`) and how many kernels end a step in it.
-std::vector<double> play(const std::vector<Act>& acts, bool fp32, bool kernel_ends, size_t* ends = nullptr, size_t* reopened = nullptr) {
+std::vector<double> play(const std::vector<Act>& acts, bool fp32, bool kernel_ends, uint64_t elems, size_t* ends = nullptr) {
   fake::ops.clear();
   fake::on_launch = on_launch;
   seen.clear();
   std::vector<std::vector<Launch>> graphs(1);
   const hipStream_t cap = fake::stream(0xc0);
-  State s(2, 64, fp32, &SCALER);
+  State s(2, elems, fp32, &SCALER);
   pt_pack_plan* q = s.plan();
   if (kernel_ends) {
     graph = &graphs[0];
@@ -567,7 +586,6 @@ std::vector<double> play(const std::vector<Act>& acts, bool fp32, bool kernel_en
   fake::capturing[0xc0] = false;
   for (int t = 0; t < 3; ++t) step(t == 1);
   if (ends) *ends = fake::launches("k_step_end").size();
-  if (reopened) *reopened = fake::launches("k_reopen").size();
   fake::on_launch = nullptr;
   return seen;
 }
@@ -580,14 +598,20 @@ std::string text(const std::vector<Act>& acts) {
   return t;
 }
 
-int same(const std::vector<Act>& acts, bool fp32 = false) {
+// Chunks of so few elements that an update takes a norm alone along, its plan's sums not; of so many that it takes both.
+constexpr uint64_t FEW = 64, MANY = 4096;
+
+int same(const std::vector<Act>& acts, bool fp32 = false, uint64_t elems = FEW) {
   size_t ends = 0;
-  const std::vector<double> apart = play(acts, fp32, true, &ends), now = play(acts, fp32, false);
+  const std::vector<double> apart = play(acts, fp32, true, elems, &ends);
+  const size_t fused = fake::launches("k_adamw_fused").size();
+  if (fused) { fprintf(stderr, "%zu fused updates in a captured context: %s\n", fused, text(acts).c_str()); return 1; }
+  const std::vector<double> now = play(acts, fp32, false, elems);
   size_t calls = 2 + 3;                            // before and behind `acts`
   for (const Act& a : acts) calls += a.what == END;
   if (ends != calls) { fprintf(stderr, "%zu calls ended a step with %zu kernels: %s\n", calls, ends, text(acts).c_str()); return 1; }
   if (apart == now) return 0;
-  fprintf(stderr, "differ (fp32 %d): %s\n", fp32, text(acts).c_str());
+  fprintf(stderr, "differ (fp32 %d, %zu elements): %s\n", fp32, size_t(elems), text(acts).c_str());
   for (const auto* v : {&apart, &now}) {
     for (double x : *v) fprintf(stderr, "%g ", x);
     fprintf(stderr, "\n");
@@ -599,12 +623,13 @@ int same(const std::vector<Act>& acts, bool fp32 = false) {
 int step_end_in_a_graph() {
   std::vector<Act> acts = {{CAPTURE, 1}, {END, 0}};
   for (int t = 0; t < 4; ++t) for (const Act& a : {Act{PACK, 0}, Act{FINALIZE, 0}, Act{UPDATE, 0}, Act{REPLAY, 1}, Act{REPORT, 0}}) acts.push_back(a);
-  const std::vector<double> v = play(acts, false, false);
+  const std::vector<double> v = play(acts, false, false, FEW);
+  EXPECT(play(acts, false, false, MANY) == v);
   std::vector<double> t;
   for (size_t i = 0; i < v.size(); i += v[i] == 1.0 ? 4 : v[i] == 3.0 ? 6 : 2)
     if (v[i] == 1.0) t.push_back(v[i + 1]);
   EXPECT((t == std::vector<double>{1, 2, 3, 4, 5, 6, 7, 7}));    // the last but one is skipped
-  return same(acts);
+  return same(acts) || same(acts, false, MANY);
 }
 
 // Updates with hyper-parameters of their own for each of three groups of chunks, and a norm and an update a layer: from the second step on
@@ -724,10 +749,14 @@ int captured_alone() {
     for (int what = 0; what < N_CALLS; ++what) {
       const bool plain = what == UNPACK || what == ACCUM || what == FINALIZE;      // the last launches nothing
       const std::vector<Act> acts = {{PACK, 0}, {FINALIZE, 0}, {UPDATE, 0}, {END, 0}, {PACK, 0}, {FINALIZE, 0}, {CAPTURE, 1}, {what, 1}, {END, 0}};
-      size_t ends = 0;
-      (void)play(acts, fp32, false, &ends);
-      EXPECT(ends == (what == END ? 5u : plain ? 1u : 4u));
-      if (same(acts, fp32)) return 1;
+      for (uint64_t elems : {FEW, MANY}) {
+        size_t ends = 0;
+        (void)play(acts, fp32, false, elems, &ends);
+        EXPECT(ends == (what == END ? 5u : plain ? 1u : 4u));
+        // with its plan's sums: before the capture, and behind it where it did not count
+        EXPECT(fake::launches("k_adamw_fused").size() == (elems == FEW ? 0u : plain ? 5u : 2u));
+        if (same(acts, fp32, elems)) return 1;
+      }
     }
   return 0;
 }
@@ -746,7 +775,7 @@ int sequences_at_random() {
       else if (x < 27 && n % 3) acts.push_back({CAPTURE, 1 + uint32_t(r() % 5)});
       else if (x < 31 && n % 3) acts.push_back({REPLAY, 1 + uint32_t(r() % 3)});
     }
-    if (same(acts, n & 1)) return 1;
+    if (same(acts, n & 1, n / 2 % 2 ? MANY : FEW)) return 1;
   }
   return 0;
 }

@@ -1,6 +1,6 @@
-"""A step ends in the launch that derives its constants, without a launch of its own behind the update - unless something of
-the same step still depends on the step counter or the loss scale, or the context has been captured into a graph.  Either way
-leads to the values of the machine written out here; every sequence runs in a context of each kind."""
+"""A step ends in the launch that derives its constants - here the update itself - without a launch of its own behind it, unless
+something of the same step still depends on the step counter or the loss scale, or the context has been captured into a graph.
+Either way leads to the values of the machine written out here; every sequence runs in a context of each kind."""
 import pytest
 import torch
 
@@ -10,7 +10,8 @@ from gpu_harness import ChunkedState, assert_same_bits, hp_pair
 
 pytestmark = pytest.mark.gpu
 
-S, C = 4096, 3
+C = 3
+SIZES = [4096, (1 << 19) + 8]       # elements of a chunk: below 6144 tiles of the update altogether, and above
 GROWTH_INTERVAL = 2
 INF_STEPS = (3, 6)
 
@@ -41,7 +42,7 @@ class Machine:
         return r.sqnorm, r.norm, r.clip_coef, r.grad_mult
 
 
-def make(captured):
+def make(captured, S):
     st = ChunkedState([S * C - 5], S, dtype=torch.float16, scaler=B.pt_scaler_cfg(1024.0, 2.0, 0.5, GROWTH_INTERVAL, 0))
     if captured:                            # from here on its steps end in a kernel of their own (tests/pins/host_calls.cpp counts them)
         with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=torch.cuda.Stream()):
@@ -97,10 +98,11 @@ def between(st, kind, hp, hp2, model):
     return False, hp
 
 
+@pytest.mark.parametrize("S", SIZES)
 @pytest.mark.parametrize("kind", ["nothing", "pack", "recompute", "finalize", "override", "skip", "state", "hyper-parameters",
                                   "in parts", "graph"])
-def test_the_step_ends_with_its_constants_or_behind_the_update(kind):
-    states = [make(captured) for captured in (False, True)]
+def test_the_step_ends_with_its_constants_or_behind_the_update(kind, S):
+    states = [make(captured, S) for captured in (False, True)]
     hp, _, _ = hp_pair()
     hp2, _, _ = hp_pair(lr=3e-3, beta1=0.5, beta2=0.7, max_norm=0.1)
     models = [Machine() for _ in states]
@@ -131,9 +133,10 @@ def test_the_step_ends_with_its_constants_or_behind_the_update(kind):
             st.close()
 
 
-def test_step_end_in_a_graph_behind_eager_updates():
+@pytest.mark.parametrize("S", SIZES)
+def test_step_end_in_a_graph_behind_eager_updates(S):
     """The step end alone, captured on a fresh context and replayed in every step: Adam's t and the loss scale move."""
-    st, model = make(False), Machine()
+    st, model = make(False, S), Machine()
     hp, _, _ = hp_pair()
     try:
         g = torch.cuda.CUDAGraph()
@@ -155,10 +158,11 @@ def test_step_end_in_a_graph_behind_eager_updates():
         st.close()
 
 
+@pytest.mark.parametrize("S", SIZES)
 @pytest.mark.parametrize("first", ["eager step", "replay"])
-def test_graph_captured_in_a_step_that_has_ended_early(first):
+def test_graph_captured_in_a_step_that_has_ended_early(first, S):
     """Norm, update and step end are captured between an update and its step end, then replayed with eager steps in between."""
-    st, model = make(False), Machine()
+    st, model = make(False, S), Machine()
     hp, _, _ = hp_pair()
 
     def gradients(t):
