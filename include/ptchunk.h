@@ -49,7 +49,7 @@
  *    a graph of norm, update and step end may be captured without it and replayed behind it.
  *    With a small plan the graph holds the pack too, and the plan outlives the graph.
  *    An update of all chunks takes what is left of that along in its own launch, where nothing but it depends on the
- *    result (contexts that have never been captured, of 256 chunks at most).
+ *    result (contexts that have never been captured, of 208 chunks at most).
  *  - A context is not thread-safe; use one per optimizer instance.
  */
 #ifndef PTCHUNK_H
