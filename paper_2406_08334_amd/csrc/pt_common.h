@@ -61,6 +61,7 @@ struct pt_pack_plan {
   double* d_seg_sum = nullptr;             // [chunks from the first to the last touched one * segs], if segs > 1
   uint32_t* d_seg_flag = nullptr;
   uint64_t total_elems = 0;
+  uint32_t kept_tiles = 0;                 // the first ones, whose unpacked words are to stay in the Infinity Cache
   uint64_t id = 0;                         // never reused within a context (a destroyed plan's address may be)
   std::vector<uint32_t> touched;           // chunks that own at least one tile
   std::vector<uint32_t> tile_begin;        // d_chunk_tile_begin from the first to behind the last touched chunk

@@ -80,7 +80,8 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 
 // DIR 0: tensor -> chunk with sum of squares and non-finite scan (pack).
 // DIR 1: chunk -> tensor (unpack), no reduction.
-// KEEP: words that stay in the Infinity Cache: packed ones for the update (pt_in_cache), unpacked ones for whoever reads the tensors (unpack_kept).
+// cached: of packed words as many, of unpacked ones those of as many tiles.
+// KEEP: words that stay in the Infinity Cache: packed ones for the update (pt_in_cache), unpacked ones for whoever reads the tensors (UNPACK_KEPT).
 //
 // Few bytes in flight, in address order, are moved fastest (as in the update).  One wave moves 4 KiB, two vectors a lane at a
 // time, and unused LDS keeps few waves on a compute unit.  Against workgroups of four waves with 16 KiB, eight on a unit: pack of
@@ -96,13 +97,15 @@ __device__ __forceinline__ void move_vecs(const PT_GLOBAL uint16_t* sb, PT_GLOBA
 // 14.2 us, 5.5e7 34.5 and 35.0, 1.25e8 77.0 and 77.6); below 2^24 words it runs without a limit (1.5e7 11.6, with one 11.8).
 constexpr uint32_t PACK_LDS = 9000;
 inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : elems < (1ull << 28) ? 9000 : 11500; }
-// Stores (pt_store).  Unpack: through the L2 without the hint, so that they stay in the Infinity Cache for the forward pass, but from 3 * 2^24 to
-// 2^28 words, where the cache is about as large as the words of a call or two.  With the hint alone, through without it, through with it: 7.1e6
-// words 6.76 / 6.32 / 6.72 us, 2.2e7 15.4 / 14.9 / 16.1, 4.2e7 28.0 / 26.2 / 28.4, 6e7 38.9 / 39.7 / 38.9, 2.0e8 124.0 / 124.7 / 123.2, 2.8e8 168.4 /
-// 165.9 / 167, 6.7e8 400.9 / 391.3 / 400.3, 1.4e9 867 / 848 / 867; one call behind 2 GB of other traffic and a pass that reads the tensors, 7.1e6
-// 10.6 + 13.2 / 10.2 + 9.7 / 10.9 + 13.1, 6.1e7 43.0 + 43.8 / 39.1 + 37.8 / 42.1 + 43.4.
+// Stores (pt_store).  Unpacked words go through the L2 without the hint, so that the forward pass finds them in the Infinity Cache: the plan's first
+// 240 MB (as of packed ones, whose place in the context counts), the rest with it.  All with the hint, the first 240 MB without, one call behind 2 GB of
+// other traffic and a pass that reads the tensors from the first on: 6.1e7 words 42 + 51 and 39 + 34 us, 1.0e8 65 + 75 and 60 + 47, 1.35e8 86 + 96
+// and 78 + 63, 2.0e8 124 + 131 and 116 + 105, 2.6e8 160 + 162 and 152 + 143, 6.7e8 391 + 375 and 391 + 357, 1.4e9 823 + 774 and 825 + 757; the call repeated
+// 38.6 and 35.7, 61.6 and 56.2, 82.0 and 75.0, 120.7 and 113.4, 156.3 and 149.1, 395.8 and 389.4, 841 and 833.  None with the hint is as fast up to 1.3e8
+// words; from there on the reading pass finds nothing and waits for what is still to be written: 1.45e8 83 + 114, 2.0e8 114 + 145, 6.7e8 389 + 391,
+// 1.4e9 825 + 792.  The first 120 MB: 1.0e8 61 + 59, 2.0e8 120 + 120, 6.7e8 396 + 367; 200 MB: 2.0e8 118 + 108, 6.7e8 392 + 361; 256 MB: 2.0e8 116 + 134.
 // Packed words that don't fit the cache: through with the hint, a step of 2e8 parameters 1024 us with the hint alone and 1010 so, 6.7e8 3214 and 3169.
-inline bool unpack_kept(uint64_t elems) { return elems < (3ull << 24) || elems >= (1ull << 28); }
+constexpr uint64_t UNPACK_KEPT = PT_CACHED_BYTES / 2;
 
 template <int DT, int DIR>
 __global__ void __launch_bounds__(PK_THREADS)
@@ -131,7 +134,7 @@ k_pack(const PtTile* __restrict__ tiles, const uint64_t* __restrict__ chunk_row,
   const PT_GLOBAL uint16_t* sb = src + head;
   PT_GLOBAL u32x4* db = (PT_GLOBAL u32x4*)(dst + head);
   const bool aligned = ((uintptr_t)sb & 15u) == 0;
-  if (DIR == 0 ? pt_in_cache(t.chunk, S, t.chunk_off, cached) : cached != 0) {
+  if (DIR == 0 ? pt_in_cache(t.chunk, S, t.chunk_off, cached) : tile < cached) {
     if (aligned) move_vecs<DT, DIR, true, true>(sb, db, nvec, a0, a1);
     else move_vecs<DT, DIR, true, false>(sb, db, nvec, a0, a1);
   } else {
@@ -221,6 +224,7 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   tiles.reserve(room_for);
   std::vector<uint32_t> begin(size_t(ctx->C) + 1, 0);
   uint64_t total = 0;
+  uint32_t kept = 0;
   for (uint32_t k = 0; k < n_segs; ++k) {
     const pt_segment& s = segs[order[k]];
     uint64_t done = 0;
@@ -234,8 +238,9 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
       tiles.push_back(t);
       begin[s.chunk + 1] += 1;
       done += run;
+      total += run;
+      if (total <= UNPACK_KEPT) kept = uint32_t(tiles.size());
     }
-    total += s.len;
   }
   // a tile of the default size goes to four waves; one of another size to as many, if it has 2048 (1024) elements for each
   const uint64_t least = ctx->grad_f32 ? 1024 : 2048;
@@ -247,7 +252,7 @@ static int plan_create(pt_ctx* ctx, const pt_segment* segs, uint32_t n_segs, pt_
   pt_pack_plan* p = new (std::nothrow) pt_pack_plan();
   if (!p) return pt_fail(ctx, PT_ERR_NOMEM, "pt_pack_plan_create: out of host memory");
   std::unique_ptr<pt_pack_plan> hold(p);            // freed on every early return and on an exception
-  p->ctx = ctx; p->n_tiles = uint32_t(tiles.size()); p->total_elems = total;
+  p->ctx = ctx; p->n_tiles = uint32_t(tiles.size()); p->total_elems = total; p->kept_tiles = kept;
   p->id = ++ctx->plan_ids;
   uint32_t most = 0;
   for (uint32_t c = 0; c < ctx->C; ++c)
@@ -334,7 +339,7 @@ static int run_pack(pt_ctx* ctx, const pt_pack_plan* plan, const void* const* ch
   auto kern = ctx->dtype == PT_BF16 ? k_pack<PT_BF16, DIR> : k_pack<PT_FP16, DIR>;
   hipLaunchKernelGGL(kern, grid, dim3(PK_THREADS), lds, st, plan->d_tiles, pt_row(ctx, row), plan->subs, plan->sub_elems,
                      ctx->d_state, plan->d_tile_sq, plan->d_tile_flag, ctx->S,
-                     DIR == 1 ? uint64_t(unpack_kept(plan->total_elems)) : pt_cached_elems(ctx));
+                     DIR == 1 ? uint64_t(plan->kept_tiles) : pt_cached_elems(ctx));
   PT_LAUNCH_CHECK(ctx, who);
   if (DIR == 0) {
     rc = pt_reduce_plan(ctx, plan, st);

@@ -742,6 +742,28 @@ int kept_in_the_cache_by_size() {
   return 0;
 }
 
+// Unpacked words are kept as far as the plan's first 240 MB go, wherever in the context they lie.
+int unpack_kept_by_size() {
+  constexpr uint64_t TILE = 1 << 16, FIT = 240u << 19;
+  fake::on_launch = note_kept;
+  for (const auto& [n, tiles] : {std::tuple<uint64_t, uint64_t>{3, 1}, {TILE + 1, 2}, {FIT, FIT / TILE}, {FIT + 1, FIT / TILE}, {1ull << 28, FIT / TILE}})
+    for (uint32_t chunk = 0; chunk < 2; ++chunk) {
+      pt_ctx* ctx = nullptr;
+      pt_pack_plan* q = nullptr;
+      OK(pt_ctx_create(&ctx, PT_BF16, 1 << 28, 2, nullptr));
+      OK(pt_ctx_set_option(ctx, "pack_tile_elems", TILE));
+      void* at[2] = {State::device(16), State::device(16)};
+      const pt_segment seg = {State::device(16), 0, n, 0, chunk, 0};
+      OK(pt_pack_plan_create(ctx, &seg, 1, &q));
+      OK(pt_chunk_unpack(ctx, q, at, nullptr));
+      EXPECT(kept == tiles);
+      OK(pt_pack_plan_destroy(q));
+      OK(pt_ctx_destroy(ctx));
+    }
+  fake::on_launch = nullptr;
+  return 0;
+}
+
 // Every call alone, captured on a fresh context: what reads or changes what the end of a step changes makes later steps end in a
 // kernel of their own; what does not, does not.
 int captured_alone() {
@@ -784,6 +806,7 @@ const std::map<std::string, int (*)()> checks = {
     {"step_end_in_a_graph", step_end_in_a_graph},
     {"captured_alone", captured_alone},
     {"kept_in_the_cache_by_size", kept_in_the_cache_by_size},
+    {"unpack_kept_by_size", unpack_kept_by_size},
     {"norm_counters_of_two_devices", norm_counters_of_two_devices},
     {"norm_without_a_context_captured", norm_without_a_context_captured},
     {"steps_that_go_on_behind_an_update", steps_that_go_on_behind_an_update},

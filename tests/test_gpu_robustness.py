@@ -472,6 +472,29 @@ def test_pack_unpack_and_accumulate_at_the_edges_of_a_tile(dtype, n):
             B.pt_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("n", [(240 << 19) - 5, (240 << 19) + 3, (240 << 19) + 5 * 8192 + 1])
+def test_unpack_around_what_the_cache_keeps(n):
+    """The first 240 MB of unpacked words are stored in another way than what follows; the tensor lies off the chunks' alignment."""
+    S = 1 << 25
+    C = -(-n // S)
+    chunks = torch.randint(-2 ** 15, 2 ** 15, (C, S), dtype=torch.int16, device="cuda")
+    flat = torch.zeros(n + 2, dtype=torch.int16, device="cuda")
+    segs, _ = B.pt_layout_dense([n], S)
+    for s in segs:
+        s.src = flat.data_ptr() + 2
+    ctx = B.pt_ctx_create(B.PT_BF16, S, C, None)
+    plan = B.pt_pack_plan_create(ctx, segs)
+    try:
+        for _ in range(2):
+            flat.zero_()
+            B.pt_chunk_unpack(ctx, plan, [chunks[c] for c in range(C)])
+            assert torch.equal(flat[1:n + 1], chunks.view(-1)[:n]) and int(flat[0]) == int(flat[-1]) == 0
+    finally:
+        torch.cuda.synchronize()
+        B.pt_pack_plan_destroy(plan)
+        B.pt_ctx_destroy(ctx)
+
+
 @pytest.mark.parametrize("C", [1, 48, 49, 192, 193])        # 5 pointers a chunk: one launch of 240, two, four, a copy
 def test_chunk_pointers_of_any_number_reach_the_device(C):
     """Many small chunks give what one large chunk gives, also after every chunk has moved."""

@@ -43,6 +43,7 @@ def exe(tmp_path_factory):
     "step_end_in_a_graph",
     "captured_alone",
     "kept_in_the_cache_by_size",
+    "unpack_kept_by_size",
     "norm_counters_of_two_devices",
     "norm_without_a_context_captured",
     "steps_that_go_on_behind_an_update",
