@@ -23,7 +23,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["by_size", "not_otherwise", "failed_launch"])
+@pytest.mark.parametrize("check", ["by_size", "not_otherwise", "not_with_host_threads", "sums_it_does_not_take", "failed_launch"])
 def test_fused_updates(exe, check):
     res = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, (res.stdout + res.stderr)[-6000:]
