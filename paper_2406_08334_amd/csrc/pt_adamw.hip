@@ -192,7 +192,8 @@ __device__ __forceinline__ void load_tile(Tile<UNROLL, GF32>& t, const ChunkPtrs
   asm volatile("" ::: "memory");        // keeps the compiler from moving the loads behind a branch on the step's scalars
 }
 
-// Updates a tile that has been loaded.  HOST: of chunks in host memory.  c: the chunk's index in the no-decay ranges.  skip, recast_on_skip, zero_grads as above.
+// Updates a tile that has been loaded.  HOST: of chunks in host memory.  c: the chunk's index in the no-decay ranges.  skip,
+// recast_on_skip, zero_grads as above.
 template <int TH, int DT, int UNROLL, bool NT, bool HOST, bool MASKED, bool GF32, class P32, class P64>
 __device__ __forceinline__ void finish_tile(const Consts& k, int32_t skip, const ChunkPtrs<GF32>& x, Tile<UNROLL, GF32>& t, uint64_t units,
                                             uint32_t c, int recast_on_skip, int zero_grads, P32 nd_begin, P64 nd_ranges) {

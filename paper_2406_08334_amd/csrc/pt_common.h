@@ -259,7 +259,8 @@ __device__ __forceinline__ void pt_sub_range(const PtTile& t, uint32_t sub, uint
 // so 6.8e7 343.3 -> 340.3, 1.24e8 596.7 -> 591.7, 1.4e7 86.4 -> 85.2 (with the hint 353, 612, 89); sums added to with the hint and so, one
 // call behind 2 GB of other traffic: 7.3e6 18.5 -> 17.3, 1.6e7 31.6 -> 29.2, 3e7 53.1 -> 50.0, 5.3e7 89.2 -> 84.3; sums the update zeroes
 // likewise: four micro-batches and update 7e6 108.3 -> 104.3, 3e7 337 -> 335, 1.24e8 1350 -> 1334, 3.3e8 3603 -> 3585.  Sums
-// beyond it have the hint alone (through: 3.3e8 3655).
+// beyond it have the hint alone (through: 3.3e8 3655).  All figures of arrays that both sides share: where a process's arrays lie moves its steps by
+// 1 % either way.
 constexpr int PT_PLAIN = 0, PT_NT = 2, PT_THROUGH = 16, PT_NT_THROUGH = 18;
 typedef int pt_i32x4 __attribute__((ext_vector_type(4)));
 typedef int pt_i32x2 __attribute__((ext_vector_type(2)));

@@ -323,8 +323,8 @@ constexpr uint32_t PT_FUSE_MAX_PARTIALS = 16384;
 // Where an update takes all of this along in its own launch (k_adamw_fused).  One wave adds the chunks up one after the other, which takes longer
 // than a launch if there are many: chunks of 2^18, k_scalars in front and not, 128 of them 169.1 and 166.0 us a step, 160 211.4 and 208.7, 208
 // 268.8 and 266.6, 224 295.5 and 296.1, 256 331.5 and 334.1.  (Chunks of 256 elements, where nothing hides it: call behind call, which the host
-// decides, 192 63.7 and 60.6, a step alone 128 56.4 and 57.8, 192 72.4 and 77.7.)  There is no lower line: k_scalars in front and not, one chunk of 768 elements 13.5 and 9.5 us a step, of 12 700
-// 13.6 and 9.6, eight of 512 15.1 and 11.4, nine of 4096 18.6 and 15.3, 64 of 256 30.3 and 27.6.
+// decides, 192 63.7 and 60.6, a step alone 128 56.4 and 57.8, 192 72.4 and 77.7.)  There is no lower line: one chunk of 768 elements 13.5 and 9.5,
+// of 12 700 13.6 and 9.6, eight of 512 15.1 and 11.4, nine of 4096 18.6 and 15.3, 64 of 256 30.3 and 27.6.
 constexpr uint32_t PT_FUSED_MAX_CHUNKS = 208;
 
 static int launch_scalars(pt_ctx* ctx, const PtPendingReduce* r, bool finalize, const pt_hparams* hp, uint32_t end_step, PtDevState* mirror,

@@ -43,7 +43,6 @@ __device__ __forceinline__ void take_vec(const u32x4& q, double& a0, double& a1)
   }
 }
 
-
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));   // global memory takes a 16-byte load at any address
 
 // Off the alignment every line at a lane's or a wave's end is read twice, and unpack takes it without the hint: with and
@@ -104,7 +103,8 @@ inline uint32_t unpack_lds(uint64_t elems) { return elems < (1ull << 24) ? 0 : e
 // 38.6 and 35.7, 61.6 and 56.2, 82.0 and 75.0, 120.7 and 113.4, 156.3 and 149.1, 395.8 and 389.4, 841 and 833.  None with the hint is as fast up to 1.3e8
 // words; from there on the reading pass finds nothing and waits for what is still to be written: 1.45e8 83 + 114, 2.0e8 114 + 145, 6.7e8 389 + 391,
 // 1.4e9 825 + 792.  The first 120 MB: 1.0e8 61 + 59, 2.0e8 120 + 120, 6.7e8 396 + 367; 200 MB: 2.0e8 118 + 108, 6.7e8 392 + 361; 256 MB: 2.0e8 116 + 134.
-// Packed words that don't fit the cache: through with the hint, a step of 2e8 parameters 1024 us with the hint alone and 1010 so, 6.7e8 3214 and 3169.
+// Packed words that don't fit the cache: through with the hint; with the hint alone a step, on the same arrays, takes the same within 0.3 %, 1.8e8
+// parameters 865 and 865 us, 6.7e8 3185 and 3180, 1.56e9 7486 and 7462.
 constexpr uint64_t UNPACK_KEPT = PT_CACHED_BYTES / 2;
 
 template <int DT, int DIR>

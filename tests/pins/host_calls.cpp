@@ -461,7 +461,17 @@ int step_ends_with_its_constants() {
 // A stand-in for the device that runs the step's scalar kernels: at once, or when the graph is replayed they were captured into.  A
 // call sequence has to give the same values whether steps end with their constants or in a kernel of their own (which is
 // what a context does that has been captured into a graph; here into one that is never replayed).
-struct Launch { std::string kernel; PtDevState* st; PtScalarArgs a; uint32_t no; float mult; int32_t inf, step, good; double scale; bool reads_scale; PtFused f; };
+struct Launch {
+  std::string kernel;
+  PtDevState* st;
+  PtScalarArgs a;
+  PtFused f;
+  uint32_t no;
+  float mult;
+  int32_t inf, step, good;
+  double scale;
+  bool reads_scale;
+};
 std::vector<Launch>* graph = nullptr;              // what is captured now
 bool reads_scale = false, inf_now = false;         // of the call in flight: its kernel reads the loss scale; gradients hold an infinity
 std::vector<double> seen;

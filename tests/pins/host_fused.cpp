@@ -46,8 +46,9 @@ size_t count(const char* kernel, size_t from) { return fake::launches(kernel, fr
 
 // Up to 208 chunks, if a waiting plan's sums have workgroups to take them; a launch of the scalar kernel less then.
 int by_size() {
-  for (const auto& [C, S, fused] : {std::tuple{1u, 760ull, false}, {1u, 768ull, true}, {8u, 504ull, false}, {8u, 512ull, true}, {9u, 8ull, true}, {1u, 1ull << 16, true},
-                                    {8u, 1ull << 13, true}, {64u, 1ull << 20, true}, {208u, 4096ull, true}, {209u, 4096ull, false}}) {
+  for (const auto& [C, S, fused] : {std::tuple{1u, 760ull, false}, {1u, 768ull, true}, {8u, 504ull, false}, {8u, 512ull, true}, {9u, 8ull, true},
+                                    {1u, 1ull << 16, true}, {8u, 1ull << 13, true}, {64u, 1ull << 20, true}, {208u, 4096ull, true},
+                                    {209u, 4096ull, false}}) {
     State s(C, S);
     for (int step = 0; step < 3; ++step) {
       OK(s.pack());
